@@ -11,7 +11,7 @@
 //             the same elements for all rows, so LDS is a per-lane indexable store - no lane ever
 //             reads what another lane wrote, one barrier separates staging from use.  All sources
 //             of the tile are read before anything is written, so updating in place is legal.
-//   k_direct  one workgroup updates one tile of one row and streams the row's sources from global
+//   k_direct  one wavefront updates one vector per lane of one row and streams the row's sources from global
 //             memory (a node's own parameters plus receive buffers: no source is shared by two rows).
 //   k_acc     accumulate / fold only (Algorithm 3 lines 9-13).
 //
@@ -34,9 +34,9 @@ namespace dadam {
 namespace {
 
 
-// distance (in elements) between the two groups of four that an 8-element lane vector consists of
-constexpr int kHalfWave = 4 * kWave;             // tile kernel: the lanes of a wavefront work side by side
-constexpr int kHalfGroup = 4 * kDirectThreads;   // direct and accumulate kernels: the whole workgroup does
+// distance (in elements) between the two groups of four that an 8-element lane vector consists of: the lanes
+// of a wavefront work side by side
+constexpr int kHalfWave = 4 * kWave;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
@@ -112,8 +112,7 @@ __device__ __forceinline__ void store_elem(void* base, uint64_t e, float v) {
 
 // The VEC elements of one lane and vector, of type T, widened to float.  VEC = 4: elements
 // [e, e + 4).  VEC = 8: two groups of four, [e, e + 4) and [e + H, e + H + 4), where H is four times
-// the number of lanes that work side by side (a wavefront in the tile kernel, a workgroup in the
-// others): every access instruction of the group then covers one contiguous run of memory, 16
+// the number of lanes that work side by side (a wavefront): every access instruction of the group then covers one contiguous run of memory, 16
 // bytes per lane for float32 and 8 for bfloat16, and every 128-byte line it touches is touched
 // whole.  (Giving a lane 8 consecutive elements instead makes each float32 state access two
 // instructions that each touch half of every line: measured 5-13 % slower once stores are involved.)
@@ -670,44 +669,62 @@ __global__ __launch_bounds__(kWave* W) void k_tile(const StepArgs a) {
 // ---------------------------------------------------------------------------------------------
 // direct mode
 // ---------------------------------------------------------------------------------------------
-constexpr int kUD = 2;  // 16-byte parameter vectors per thread (1 and 4 measured slower)
+// A work item is kDirectItem parameter vectors of 16 bytes per lane of a wavefront (2048 float32 or 4096
+// bfloat16 elements of one row); kPieces workgroups of ONE wavefront take it, one vector per lane each.
+// The kernel is bound by HBM.  Why one small workgroup per vector: what the memory sustains depends on how
+// much of a stream one workgroup covers, because consecutive workgroups go to the eight dies in turn.  7 reads
+// and 2 writes of 1.4 GB arrays in place (one node's share), fraction of 8 TB/s by bytes of a stream per workgroup
+// (ordinary allocations): 8 KB 0.73 (256 threads, two vectors: what this kernel used to be), 4 KB 0.74, 2 KB 0.78,
+// 1 KB 0.795; the same with the hints off 0.68.  On the step itself: one row with three sources 0.72 -> 0.76.
+constexpr int kPieces = kDirectItem;
+
+// Where workgroup `b` of a launch over one-wavefront pieces works: `tile` counts pieces of the launch.
+struct PieceAt {
+  uint64_t tbase, lo, hi;
+  float wd;
+  bool any, full;  // some / all elements of the piece lie in [lo, hi)
+};
+template <int VEC>
+__device__ __forceinline__ PieceAt locate_piece(const StepArgs& a, uint32_t tile) {
+  constexpr uint64_t PIECE = (uint64_t)kWave * VEC;
+  PieceAt p;
+  uint64_t tile_index;
+  locate(a, a.work_begin + tile / kPieces, tile_index, p.lo, p.hi, p.wd);
+  p.tbase = (tile_index * kPieces + tile % kPieces) * PIECE;
+  p.any = p.tbase < p.hi && p.tbase + PIECE > p.lo;
+  p.full = p.tbase >= p.lo && p.tbase + PIECE <= p.hi;
+  return p;
+}
 
 // Neighbour sum with all loads of DEG sources issued before the first use.  DEG == 0: any degree.
 template <typename XT, int DEG, bool MASKED, bool NT, bool EXT>  // NT: hint on the source loads
-__device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int lane,
-                                           const uint64_t (&e)[kUD], uint64_t lo, uint64_t hi,
-                                           float (&mix)[kUD][XT::vec]) {
+__device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int lane, uint64_t e, uint64_t lo,
+                                           uint64_t hi, float (&mix)[XT::vec]) {
   constexpr int VEC = XT::vec;
   if constexpr (DEG > 0) {
-    u4 r[DEG][kUD];
+    u4 r[DEG];
     float wk[DEG];
 #pragma unroll
     for (int k = 0; k < DEG; ++k) {
       const void* src = src_of<EXT>(a, list_col(rl, k));
       wk[k] = list_w(rl, k);
-#pragma unroll
-      for (int u = 0; u < kUD; ++u) r[k][u] = load_raw<XT, kHalfGroup, MASKED, NT>(src, e[u], lo, hi);
+      r[k] = load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi);
     }
 #pragma unroll
-    for (int k = 0; k < DEG; ++k)
+    for (int k = 0; k < DEG; ++k) {
+      float xs[VEC];
+      unpack_raw<XT>(r[k], xs);
 #pragma unroll
-      for (int u = 0; u < kUD; ++u) {
-        float xs[VEC];
-        unpack_raw<XT>(r[k][u], xs);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) mix[u][j] = (k == 0) ? wk[0] * xs[j] : fmaf(wk[k], xs[j], mix[u][j]);
-      }
+      for (int j = 0; j < VEC; ++j) mix[j] = (k == 0) ? wk[0] * xs[j] : fmaf(wk[k], xs[j], mix[j]);
+    }
   } else {
     {
       const void* src = src_of<EXT>(a, list_col(rl, 0));
       const float w0 = list_w(rl, 0);
+      float xs[VEC];
+      unpack_raw<XT>(load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi), xs);
 #pragma unroll
-      for (int u = 0; u < kUD; ++u) {
-        float xs[VEC];
-        unpack_raw<XT>(load_raw<XT, kHalfGroup, MASKED, NT>(src, e[u], lo, hi), xs);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) mix[u][j] = w0 * xs[j];
-      }
+      for (int j = 0; j < VEC; ++j) mix[j] = w0 * xs[j];
     }
     for (int k = 1, first = 0; k < rl.deg; ++k) {
       if constexpr (EXT) {
@@ -718,13 +735,10 @@ __device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int la
       }
       const void* src = src_of<EXT>(a, list_col(rl, k - first));
       const float wk = list_w(rl, k - first);
+      float xs[VEC];
+      unpack_raw<XT>(load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi), xs);
 #pragma unroll
-      for (int u = 0; u < kUD; ++u) {
-        float xs[VEC];
-        unpack_raw<XT>(load_raw<XT, kHalfGroup, MASKED, NT>(src, e[u], lo, hi), xs);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) mix[u][j] = fmaf(wk, xs[j], mix[u][j]);
-      }
+      for (int j = 0; j < VEC; ++j) mix[j] = fmaf(wk, xs[j], mix[j]);
     }
   }
 }
@@ -735,10 +749,8 @@ template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT>
 __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t tbase, uint64_t lo,
                                             uint64_t hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
-  constexpr int VEC = XT::vec;
-  uint64_t e[kUD];
-#pragma unroll
-  for (int u = 0; u < kUD; ++u) e[u] = tbase + (uint64_t)u * (kDirectThreads * VEC) + 4u * threadIdx.x;
+  constexpr int VEC = XT::vec, H = kHalfWave;
+  const uint64_t e = tbase + 4u * (uint32_t)lane;
   // The neighbour list sits one entry per lane and is handed out with readlane, which must find a
   // loaded value in whichever lane it asks.  So no lane may leave before the last readlane: a
   // thread of a clipped tile whose vectors all lie outside the range runs through the body with
@@ -746,26 +758,14 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t
   // free to sink the list's load below it, into the lanes that stay - and a row whose leading
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_row_list(a, row, lane);
-  float g[kUD][VEC], mh[kUD][VEC], vh[kUD][VEC], b[kUD][VEC];
-  if constexpr (Needs<PHASE>::grad) {
-    const void* gp = a.grad[row];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<GT, VEC, kHalfGroup, MASKED, NT>(gp, e[u], lo, hi, g[u]);
-  }
+  float g[VEC], mh[VEC], vh[VEC], b[VEC];
+  if constexpr (Needs<PHASE>::grad) load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e, lo, hi, g);
   if constexpr (Needs<PHASE>::moments_in) {
-    const float* mp = m_hat_of<EXT>(a, row);
-    const float* vp = v_hat_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(mp, e[u], lo, hi, mh[u]);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(vp, e[u], lo, hi, vh[u]);
+    load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
-  if constexpr (Needs<PHASE>::acc_in) {
-    const float* bp = acc_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(bp, e[u], lo, hi, b[u]);
-  }
-  float mix[kUD][VEC];
+  if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  float mix[VEC];
   switch (rl.deg) {
     case 1: mix_direct<XT, 1, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
     case 2: mix_direct<XT, 2, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
@@ -776,52 +776,31 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t
   }
   // decoupled weight decay acts on the row's own previous parameters: source buffer `row` (the
   // load repeats one the mixing sum has just made, so it is served by the cache)
-  float decay[kUD][VEC];
+  float decay[VEC];
 #pragma unroll
-  for (int u = 0; u < kUD; ++u)
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) decay[u][j] = 0.0f;
+  for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
   if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
-    const void* own = src_of<EXT>(a, row);
+    float xs[VEC];
+    unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e, lo, hi), xs);
 #pragma unroll
-    for (int u = 0; u < kUD; ++u) {
-      float xs[VEC];
-      unpack_raw<XT>(load_raw<XT, kHalfGroup, MASKED, false>(own, e[u], lo, hi), xs);
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) decay[u][j] = wd * xs[j];
-    }
+    for (int j = 0; j < VEC; ++j) decay[j] = wd * xs[j];
   }
-  float xo[kUD][VEC];
+  float xo[VEC];
 #pragma unroll
-  for (int u = 0; u < kUD; ++u)
-#pragma unroll
-    for (int j = 0; j < VEC; ++j)
-      xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[u][j]);
-  void* xd = dst_of<EXT>(a, row);
-#pragma unroll
-  for (int u = 0; u < kUD; ++u) store_vals<XT, VEC, kHalfGroup, MASKED, NT>(xd, e[u], lo, hi, xo[u]);
-  if constexpr (Needs<PHASE>::acc_out) {
-    float* bp = acc_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(bp, e[u], lo, hi, b[u]);
-  }
+  for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[j], mh[j], vh[j], b[j], decay[j]);
+  store_vals<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    float* mp = m_hat_of<EXT>(a, row);
-    float* vp = v_hat_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(mp, e[u], lo, hi, mh[u]);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(vp, e[u], lo, hi, vh[u]);
+    store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
-// Work items are numbered tile-major, row-minor, so that workgroups running at the same time work
+// Pieces are numbered element-major, row-minor, so that workgroups running at the same time work
 // on the same elements of different rows.
 template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
-__global__ __launch_bounds__(kDirectThreads) void k_direct(const StepArgs a) {
-  constexpr int VEC = XT::vec;
-  constexpr uint64_t TILE = (uint64_t)kDirectThreads * VEC * kUD;
-  const int lane = threadIdx.x & (kWave - 1);
+__global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
+  const int lane = threadIdx.x;
   const uint32_t n_rows = a.n_rows;
   uint32_t t;
   int row;
@@ -837,25 +816,21 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(const StepArgs a) {
     active = die_group_order(blockIdx.x, n_rows, a.n_xcd, a.order_group, t, position);
     row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
   } else {
-    // Nothing is shared: workgroups in launch order.  (Tile mode's orders were measured here too: one contiguous
-    // X-th of the tiles per die costs 1 % on one row with three sources and 4 % bucket by bucket, blocks of 2 to
-    // 256 workgroups per die 0.1-1.3 %.)
+    // Nothing is shared: workgroups in launch order.  (Tile mode's orders were measured here too, on one row with
+    // three sources: runs of 2, 4, 8 pieces per die 0.79, 0.77, 0.77 against 0.795, one contiguous X-th of the
+    // pieces per die 0.73.)
     t = blockIdx.x / n_rows;
     row = (int)(blockIdx.x - t * n_rows);
   }
-  uint64_t tile_index, lo, hi;
-  float wd;
-  locate(a, a.work_begin + t, tile_index, lo, hi, wd);
-  const uint64_t tbase = tile_index * TILE;
-  const bool full = tbase >= lo && tbase + TILE <= hi;
-  if (active) {  // uniform over the workgroup
-    if (full) direct_body<XT, GT, PHASE, false, HINT, EXT>(a, row, tbase, lo, hi, wd, lane);
-    else direct_body<XT, GT, PHASE, true, HINT, EXT>(a, row, tbase, lo, hi, wd, lane);
+  const PieceAt p = locate_piece<XT::vec>(a, t);
+  if (active && p.any) {  // uniform over the workgroup
+    if (p.full) direct_body<XT, GT, PHASE, false, HINT, EXT>(a, row, p.tbase, p.lo, p.hi, p.wd, lane);
+    else direct_body<XT, GT, PHASE, true, HINT, EXT>(a, row, p.tbase, p.lo, p.hi, p.wd, lane);
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// accumulate / fold only (Algorithm 3 lines 9-13).  Walks the direct kernel's tile grid, so a lane
+// accumulate / fold only (Algorithm 3 lines 9-13).  Walks the direct kernel's grid in the same pieces, so a lane
 // vector has as many elements as a parameter vector of the handle (4 or 8).
 // ---------------------------------------------------------------------------------------------
 template <int PHASE>
@@ -872,60 +847,36 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
 template <typename GT, int VEC, int PHASE, bool MASKED, bool NT, bool EXT>
 __device__ __forceinline__ void acc_body(const StepArgs& a, int row, uint64_t tbase, uint64_t lo,
                                          uint64_t hi) {
-  uint64_t e[kUD];
-#pragma unroll
-  for (int u = 0; u < kUD; ++u) e[u] = tbase + (uint64_t)u * (kDirectThreads * VEC) + 4u * threadIdx.x;
-  float g[kUD][VEC], mh[kUD][VEC], vh[kUD][VEC], b[kUD][VEC];
-  const void* gp = a.grad[row];
-#pragma unroll
-  for (int u = 0; u < kUD; ++u) load_vals<GT, VEC, kHalfGroup, MASKED, NT>(gp, e[u], lo, hi, g[u]);
+  constexpr int H = kHalfWave;
+  const uint64_t e = tbase + 4u * threadIdx.x;
+  float g[VEC], mh[VEC], vh[VEC], b[VEC];
+  load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e, lo, hi, g);
   if constexpr (Needs<PHASE>::moments_out) {
-    const float* mp = m_hat_of<EXT>(a, row);
-    const float* vp = v_hat_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(mp, e[u], lo, hi, mh[u]);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(vp, e[u], lo, hi, vh[u]);
+    load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
-  if constexpr (Needs<PHASE>::acc_in) {
-    const float* bp = acc_of<EXT>(a, row);
+  if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
 #pragma unroll
-    for (int u = 0; u < kUD; ++u) load_vals<TF32, VEC, kHalfGroup, MASKED, NT>(bp, e[u], lo, hi, b[u]);
-  }
-#pragma unroll
-  for (int u = 0; u < kUD; ++u)
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
-  if constexpr (Needs<PHASE>::acc_out) {
-    float* bp = acc_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(bp, e[u], lo, hi, b[u]);
-  }
+  for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[j], mh[j], vh[j], b[j]);
+  if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    float* mp = m_hat_of<EXT>(a, row);
-    float* vp = v_hat_of<EXT>(a, row);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(mp, e[u], lo, hi, mh[u]);
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) store_vals<TF32, VEC, kHalfGroup, MASKED, NT>(vp, e[u], lo, hi, vh[u]);
+    store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
-// VEC is the element count of a direct-mode parameter vector of this handle, so that the
-// accumulate kernel walks the same tile grid as the direct kernel.
+// VEC is the element count of a parameter vector of this handle, so that the accumulate kernel walks the
+// same grid as the direct kernel.
 template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
-__global__ __launch_bounds__(kDirectThreads) void k_acc(const StepArgs a) {
-  constexpr uint64_t TILE = (uint64_t)kDirectThreads * VEC * kUD;
+__global__ __launch_bounds__(kWave) void k_acc(const StepArgs a) {
   const uint32_t n_rows = a.n_rows;
   const uint32_t t = blockIdx.x / n_rows;
   const int row = (int)(blockIdx.x - t * n_rows);
-  uint64_t tile_index, lo, hi;
-  float wd_unused;
-  locate(a, a.work_begin + t, tile_index, lo, hi, wd_unused);
-  const uint64_t tbase = tile_index * TILE;
-  const bool full = tbase >= lo && tbase + TILE <= hi;
-  if (full) acc_body<GT, VEC, PHASE, false, NT, EXT>(a, row, tbase, lo, hi);
-  else acc_body<GT, VEC, PHASE, true, NT, EXT>(a, row, tbase, lo, hi);
+  const PieceAt p = locate_piece<VEC>(a, t);
+  if (p.any) {
+    if (p.full) acc_body<GT, VEC, PHASE, false, NT, EXT>(a, row, p.tbase, p.lo, p.hi);
+    else acc_body<GT, VEC, PHASE, true, NT, EXT>(a, row, p.tbase, p.lo, p.hi);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------

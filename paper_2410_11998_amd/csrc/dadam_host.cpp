@@ -571,7 +571,7 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   }
   h->shape = shape;
   h->tile_elems = (uint32_t)(kWave * h->vec * shape.ut);
-  h->direct_elems = (uint32_t)(kDirectThreads * h->vec * direct_unroll());
+  h->direct_elems = (uint32_t)(kWave * h->vec * kDirectItem);
   h->lds_bytes = cfg->n_cols * (uint32_t)shape.ut * kWave * 16u;
   h->tile_possible = h->lds_bytes <= h->lds_limit;
   // The mixing-only launch moves few bytes per row, so it wants more of them in flight per

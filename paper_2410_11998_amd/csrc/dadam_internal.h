@@ -12,7 +12,7 @@ namespace dadam {
 constexpr int kMaxRows = DADAM_MAX_ROWS;  // rows / source buffers a handle may have
 constexpr int kInlineRows = 64;           // up to this many, every pointer table travels in the kernel arguments
 constexpr int kWave = 64;            // gfx950 wavefront
-constexpr int kDirectThreads = 256;  // workgroup of the direct and accumulate kernels
+constexpr int kDirectItem = 8;  // direct and accumulate kernels: wavefronts (16-byte vectors per lane) per work item
 
 // A maximal run of contiguous tensors with the same hyper-parameters: elements [lo, hi) of every buffer.  Work items are tiles of a
 // fixed grid anchored at element 0, so that vector accesses are 16-byte aligned whenever the
@@ -129,7 +129,6 @@ int static_partials(double** out, uint32_t* capacity);
 
 // Geometry the host planner needs.
 int vec_elems(int xdt);              // elements per 16-byte parameter vector: 4 (f32) or 8 (bf16)
-int direct_unroll();                 // vectors per thread in the direct and accumulate kernels
 bool tile_shape_supported(TileShape s);
 
 }  // namespace dadam

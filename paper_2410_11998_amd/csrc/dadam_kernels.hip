@@ -100,6 +100,22 @@ int launch(KernelFn fn, uint32_t grid, uint32_t block, uint32_t lds, const StepA
   return (int)hipGetLastError();
 }
 
+// Launch of a kernel whose workgroups are one-wavefront pieces of work items, for every row.  A grid holds less
+// than 2^32 threads (17 billion float32 elements), so what is larger goes out in several launches.
+int launch_pieces(KernelFn fn, StepArgs a, uint32_t n_items, void* stream) {
+  // with a sharing order every die gets the same number of workgroups per piece (see k_direct)
+  const uint64_t per_item = (uint64_t)kDirectItem * (a.row_order != nullptr ? a.n_xcd * a.order_group : a.n_rows);
+  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / kWave / per_item);
+  int e = (int)hipSuccess;
+  while (n_items > 0 && e == (int)hipSuccess) {
+    const uint32_t now = n_items < most ? n_items : most;
+    e = launch(fn, (uint32_t)(now * per_item), kWave, 0, a, stream);
+    a.work_begin += now;
+    n_items -= now;
+  }
+  return e;
+}
+
 static_assert(sizeof(StepArgs) <= 4096, "kernel argument block must fit the kernarg segment");
 
 }  // namespace
@@ -138,7 +154,6 @@ int launch_consensus_sum(const double* partials, double* out, void* stream) {
 }
 
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? TBF16::vec : TF32::vec; }
-int direct_unroll() { return kUD; }
 bool tile_shape_supported(TileShape s) {
 #ifdef DADAM_TUNING
   if ((s.waves == 16 && (s.ut == 1 || s.ut == 2)) || ((s.waves == 4 || s.waves == 8) && s.ut == 4)) return true;
@@ -173,9 +188,7 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const Ste
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
-  // with a sharing order every die gets the same number of workgroups per tile (see k_direct)
-  const uint32_t per_tile = a.row_order != nullptr ? a.n_xcd * a.order_group : a.n_rows;
-  return launch(fn, n_work_tiles * per_tile, kDirectThreads, 0, a, stream);
+  return launch_pieces(fn, a, n_work_tiles, stream);
 }
 
 int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t n_work_tiles, void* stream,
@@ -190,9 +203,7 @@ int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t
   if (gdt == DADAM_BF16 && vec == 4) fn = DADAM_PICK(TBF16, 4);
   if (gdt == DADAM_BF16 && vec == 8) fn = DADAM_PICK(TBF16, 8);
 #undef DADAM_PICK
-  // with a sharing order every die gets the same number of workgroups per tile (see k_direct)
-  const uint32_t per_tile = a.row_order != nullptr ? a.n_xcd * a.order_group : a.n_rows;
-  return launch(fn, n_work_tiles * per_tile, kDirectThreads, 0, a, stream);
+  return launch_pieces(fn, a, n_work_tiles, stream);
 }
 
 }  // namespace dadam
