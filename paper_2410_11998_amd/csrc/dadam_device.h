@@ -696,51 +696,67 @@ __device__ __forceinline__ PieceAt locate_piece(const StepArgs& a, uint32_t tile
   return p;
 }
 
-// Neighbour sum with all loads of DEG sources issued before the first use.  DEG == 0: any degree.
-template <typename XT, int DEG, bool MASKED, bool NT, bool EXT>  // NT: hint on the source loads
+// N entries of the neighbour sum, from entry k of the list's chunk on, with all loads issued before the first
+// use.  FIRST: the sum starts with a product, everything after that is a fused multiply-add.
+template <typename XT, int N, bool FIRST, bool MASKED, bool NT, bool EXT>  // NT: hint on the source loads
+__device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl, int k, uint64_t e, uint64_t lo,
+                                            uint64_t hi, float (&mix)[XT::vec]) {
+  constexpr int VEC = XT::vec;
+  u4 r[N];
+  float wk[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const void* src = src_of<EXT>(a, list_col(rl, k + q));
+    wk[q] = list_w(rl, k + q);
+    r[q] = load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi);
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    float xs[VEC];
+    unpack_raw<XT>(r[q], xs);
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) mix[j] = (FIRST && q == 0) ? wk[0] * xs[j] : fmaf(wk[q], xs[j], mix[j]);
+  }
+}
+
+// Neighbour sum of one row, in the order the row lists its entries.
+template <typename XT, bool MASKED, bool NT, bool EXT>
 __device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int lane, uint64_t e, uint64_t lo,
                                            uint64_t hi, float (&mix)[XT::vec]) {
-  constexpr int VEC = XT::vec;
-  if constexpr (DEG > 0) {
-    u4 r[DEG];
-    float wk[DEG];
-#pragma unroll
-    for (int k = 0; k < DEG; ++k) {
-      const void* src = src_of<EXT>(a, list_col(rl, k));
-      wk[k] = list_w(rl, k);
-      r[k] = load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi);
-    }
-#pragma unroll
-    for (int k = 0; k < DEG; ++k) {
-      float xs[VEC];
-      unpack_raw<XT>(r[k], xs);
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) mix[j] = (k == 0) ? wk[0] * xs[j] : fmaf(wk[k], xs[j], mix[j]);
-    }
-  } else {
-    {
-      const void* src = src_of<EXT>(a, list_col(rl, 0));
-      const float w0 = list_w(rl, 0);
-      float xs[VEC];
-      unpack_raw<XT>(load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi), xs);
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) mix[j] = w0 * xs[j];
-    }
-    for (int k = 1, first = 0; k < rl.deg; ++k) {
-      if constexpr (EXT) {
-        if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them
-          first = k;
-          load_list_chunk(a, rl, first, lane);
+#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix)
+  switch (rl.deg) {
+    case 1: DADAM_MIX(1, true, 0); break;
+    case 2: DADAM_MIX(2, true, 0); break;
+    case 3: DADAM_MIX(3, true, 0); break;
+    case 4: DADAM_MIX(4, true, 0); break;
+    case 5: DADAM_MIX(5, true, 0); break;
+    case 6: DADAM_MIX(6, true, 0); break;
+    case 7: DADAM_MIX(7, true, 0); break;
+    default: {
+      DADAM_MIX(8, true, 0);
+      int k = 8, first = 0;
+      for (; k + 4 <= rl.deg; k += 4) {
+        if constexpr (EXT) {
+          if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them (64 = 8 + 14 x 4)
+            first = k;
+            load_list_chunk(a, rl, first, lane);
+          }
         }
+        DADAM_MIX(4, false, k - first);
       }
-      const void* src = src_of<EXT>(a, list_col(rl, k - first));
-      const float wk = list_w(rl, k - first);
-      float xs[VEC];
-      unpack_raw<XT>(load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi), xs);
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) mix[j] = fmaf(wk, xs[j], mix[j]);
+      if (k < rl.deg) {
+        if constexpr (EXT) {
+          if (k - first == kWave) {
+            first = k;
+            load_list_chunk(a, rl, first, lane);
+          }
+        }
+        if ((rl.deg - k) & 2) DADAM_MIX(2, false, k - first);
+        if ((rl.deg - k) & 1) DADAM_MIX(1, false, k - first + ((rl.deg - k) & 2));
+      }
     }
   }
+#undef DADAM_MIX
 }
 
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
@@ -766,14 +782,7 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t
   }
   if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   float mix[VEC];
-  switch (rl.deg) {
-    case 1: mix_direct<XT, 1, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-    case 2: mix_direct<XT, 2, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-    case 3: mix_direct<XT, 3, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-    case 4: mix_direct<XT, 4, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-    case 5: mix_direct<XT, 5, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-    default: mix_direct<XT, 0, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix); break;
-  }
+  mix_direct<XT, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix);
   // decoupled weight decay acts on the row's own previous parameters: source buffer `row` (the
   // load repeats one the mixing sum has just made, so it is served by the cache)
   float decay[VEC];
@@ -805,7 +814,16 @@ __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
   uint32_t t;
   int row;
   bool active = true;
-  if (a.row_order != nullptr) {
+  if (a.order == kOrderDieBlocks) {
+    // Rows share sources: every row of a piece runs on one die, one after the other in the sharing order, so that
+    // a source comes from memory once and from that die's L2 for its other readers.  Runs of B = 32 pieces go to
+    // the dies in turn, as in tile mode.
+    const uint32_t X = a.n_xcd, x = blockIdx.x % X, j = blockIdx.x / X;
+    const uint32_t index = j / n_rows * X + x;
+    active = index < a.n_pieces;
+    t = active ? die_block_order(index, a.n_pieces, X, a.xcd_block) : 0;
+    row = __builtin_amdgcn_readfirstlane(a.row_order[j % n_rows]);
+  } else if (a.order == kOrderDieGroups) {
     // Rows share sources.  Consecutive workgroup ids go to the device's X dies in turn; die x takes the
     // rows at positions [x R / X, (x + 1) R / X) of the sharing order (R = n_rows), tile after tile: the
     // rows that read a source run on one die at about the same time, and the second reader finds the

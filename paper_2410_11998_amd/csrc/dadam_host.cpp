@@ -261,7 +261,7 @@ void fill_args(const dadam_handle* h, const Slot* slot, const void* const* grads
     a->row_ptr = slot->d_row_ptr;
     a->col = slot->d_col;
     a->w = slot->d_w;
-    // the dies take contiguous groups of the sharing order in turn
+    // rows that share sources: the launch walks the sharing order (see step_impl)
     if (slot->d_order && h->n_xcds > 1) {
       a->row_order = slot->d_order;
       a->order_group = (R + h->n_xcds - 1) / h->n_xcds;
@@ -301,19 +301,23 @@ Phase fused_phase(const dadam_handle* h, uint64_t t) {
   return kPlain;
 }
 
+// A row updated in place overwrites every source buffer that shares its memory (two source
+// entries may name one buffer); the direct kernel may do that only if nobody but the row itself
+// reads any of them.
+bool direct_is_legal(const dadam_handle* h, const Slot& slot) {
+  for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
+    for (int32_t c : h->inplace_cols[i]) {
+      const int32_t sr = slot.sole_reader[c];
+      if (!(sr == -1 || sr == (int32_t)i)) return false;
+    }
+  return true;
+}
+
 // Decide tile or direct mode for this slot and these flags; checks in-place legality.
 int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool* tile_mode) {
   if ((flags & DADAM_FORCE_DIRECT) && (flags & DADAM_FORCE_TILE))
     return fail(h, DADAM_EINVAL, "DADAM_FORCE_DIRECT and DADAM_FORCE_TILE are exclusive");
-  bool direct_legal = true;
-  // A row updated in place overwrites every source buffer that shares its memory (two source
-  // entries may name one buffer); the direct kernel may do that only if nobody but the row itself
-  // reads any of them.
-  for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
-    for (int32_t c : h->inplace_cols[i]) {
-      int32_t sr = slot.sole_reader[c];
-      if (!(sr == -1 || sr == (int32_t)i)) direct_legal = false;
-    }
+  const bool direct_legal = direct_is_legal(h, slot);
   if (flags & DADAM_FORCE_TILE) {
     if (!h->tile_possible) return fail(h, DADAM_EINVAL, "tile mode needs the source tile to fit in LDS");
     *tile_mode = true;
@@ -413,10 +417,24 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     return DADAM_OK;
   }
   uint32_t w0 = 0, w1 = 0;
+  work_range(h, kGridTile, s0, s1, lo, hi, &w0, &w1);
+  const uint32_t n_tiles = w1 - w0;
+  // A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: with no more than
+  // one tile per compute unit and more rows than a workgroup has wavefronts, the direct kernel's one wavefront per
+  // row takes the launch instead, with the same sums in the same order.  A loop of four steps, us, tile / direct, by
+  // tiles: 16 rows of 5 sources 98: 27 / 24, 488: 48 / 48; 32 rows of 6 sources 49: 45 / 24, 244: 65 / 48, 977:
+  // 158 / 165; 64 rows of 7 sources 24: 82 / 27, 122: 108 / 48, 488: 173 / 171; 8 rows the same up to 195 tiles.
+  const bool few_tiles = tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
+                         n_tiles <= kFewTiles && direct_is_legal(h, slot);
+  if (few_tiles) tile_mode = false;
   const Grid grid = !tile_mode ? kGridDirect : mix_only ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, &slot, mix_only ? nullptr : grads, &a);
+  // Rows that share sources: in a small launch every row of a piece runs on one die, in a large one each die has a
+  // group of rows.  us, pieces / groups: 64 rows of two sources 244 tiles 83 / 87; 96 rows of 7 sources 81 tiles
+  // 53 / 74, 325 tiles 186 / 215, 1220 tiles 792 / 780; 32 rows of two sources in bfloat16, 18000 tiles, 5160 / 4970.
+  if (a.row_order) a.order = n_tiles < kManyTiles ? kOrderDieBlocks : kOrderDieGroups;
   a.grid = grid;
   a.work_begin = w0;
   a.clip_lo = lo;

@@ -28,6 +28,9 @@ struct Segment {
 // kernels' tiles, or the wider tiles of the mixing-only launch.
 enum Grid : uint32_t { kGridTile = 0, kGridDirect = 1, kGridMix = 2 };
 
+// How the workgroups of a direct-kernel launch walk the (piece, row) pairs.
+enum Order : uint32_t { kOrderLinear = 0, kOrderDieGroups = 1, kOrderDieBlocks = 2 };
+
 // Scalars of one iteration, computed on the host in double and rounded once.
 struct Scalars {
   float beta1, omb1;     // beta1, 1 - beta1
@@ -78,11 +81,12 @@ struct StepArgs {
   const int32_t* row_ptr;  // device CSR of the slot
   const int32_t* col;
   const float* w;
-  // Direct kernels: the rows in an order in which neighbours share sources (device; null: rows as numbered).
-  // The device's dies take contiguous groups of this order, so that the rows which read a source run on the
-  // die whose L2 already holds it.
+  // Direct kernels: the rows in an order in which neighbours share sources (device; null: rows as numbered),
+  // so that the rows which read a source run on the die whose L2 already holds it.
   const int32_t* row_order;
-  uint32_t order_group;  // with row_order: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
+  uint32_t order;        // Order: how a launch of the row kernel walks pieces and rows
+  uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
+  uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
   const Segment* seg;  // device
   uint32_t n_seg;
@@ -99,6 +103,8 @@ struct StepArgs {
 static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 KB");
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
+constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see step_impl
+constexpr uint32_t kManyTiles = 1024;    // measured, see step_impl
 
 typedef void (*KernelFn)(const StepArgs);
 

@@ -103,13 +103,16 @@ int launch(KernelFn fn, uint32_t grid, uint32_t block, uint32_t lds, const StepA
 // Launch of a kernel whose workgroups are one-wavefront pieces of work items, for every row.  A grid holds less
 // than 2^32 threads (17 billion float32 elements), so what is larger goes out in several launches.
 int launch_pieces(KernelFn fn, StepArgs a, uint32_t n_items, void* stream) {
-  // with a sharing order every die gets the same number of workgroups per piece (see k_direct)
-  const uint64_t per_item = (uint64_t)kDirectItem * (a.row_order != nullptr ? a.n_xcd * a.order_group : a.n_rows);
-  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / kWave / per_item);
+  // with a sharing order every die gets the same number of workgroups (see k_direct)
+  const uint32_t X = a.n_xcd;
+  const uint64_t per_piece = a.order == kOrderDieGroups ? X * a.order_group : a.n_rows;
+  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / kWave / per_piece / kDirectItem - X);
   int e = (int)hipSuccess;
   while (n_items > 0 && e == (int)hipSuccess) {
     const uint32_t now = n_items < most ? n_items : most;
-    e = launch(fn, (uint32_t)(now * per_item), kWave, 0, a, stream);
+    a.n_pieces = now * kDirectItem;
+    const uint32_t pieces = a.order == kOrderDieBlocks ? (a.n_pieces + X - 1) / X * X : a.n_pieces;
+    e = launch(fn, (uint32_t)(pieces * per_piece), kWave, 0, a, stream);
     a.work_begin += now;
     n_items -= now;
   }

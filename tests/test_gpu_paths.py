@@ -1,0 +1,55 @@
+"""Which kernel a launch takes, and what it computes, at the sizes where the choice changes: against the CPU
+oracle, and where two kernels do the same sums in the same order, against each other bit for bit."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_11998_amd import binding as B
+from paper_2410_11998_amd import workloads as WL
+
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of_degree(n, deg):
+    """n rows of `deg` sources each, spread over all n, weights summing to 1 in float32."""
+    w = np.float32(1.0) / np.float32(deg)
+    col = [(i + k * (k + 1) // 2) % n if deg <= 7 else (i + k) % n for i in range(n) for k in range(deg)]
+    return np.arange(0, n * deg + 1, deg, dtype=np.int32), np.array(col, np.int32), np.full(n * deg, w, np.float32)
+
+
+@pytest.mark.parametrize("n,deg,tiles,dtype", [
+    (9, 3, 256, "f32"), (9, 3, 257, "f32"), (64, 7, 3, "f32"), (16, 6, 11, "bf16"), (12, 8, 5, "f32"),
+    (13, 9, 2, "bf16"), (20, 12, 2, "f32"), (24, 15, 3, "f32"), (96, 68, 1, "f32"), (160, 71, 1, "bf16"),
+])
+def test_launches_of_few_tiles_give_the_tile_kernels_bits(n, deg, tiles, dtype):
+    """Up to 256 tiles, more than eight rows run one wavefront per row and piece; the sums are those of the tile
+    kernel, in the same order, for every length of the neighbour list (batches of eight, then four, then the rest,
+    and a second chunk of the list beyond 64 entries)."""
+    print("case", n, deg, tiles, dtype, flush=True)
+    elems = 64 * (8 if dtype == "bf16" else 4)
+    layout = WL.pack([("a", ((tiles - 1) * elems + 37,)), ("b", (elems - 60,))] if tiles > 1 else [("a", (elems - 3,))])
+    csr = rows_of_degree(n, deg)
+    hp = H.HyperF32(s=2)
+    worst = H.run_parity(f"few-{n}-{deg}-{tiles}-{dtype}", n, n, layout, hp, [csr], lambda t: 0, 3, seed=77, param_dtype=dtype,
+                         grad_dtype=dtype, flags=B.DADAM_FUSE_ACCUM, pad_fill=None)
+    print("worst error / tolerance:", worst, flush=True)
+    sims = [H.GpuSim(n, n, layout, hp, [csr], dtype, dtype) for _ in range(2)]
+    for c in range(n):
+        x0 = H.to_device(WL.normal_np(500 + c, layout.d, 0.02), dtype, "cuda:0")
+        for sim in sims:
+            sim.x_src[c].copy_(x0)
+    for t in range(1, 4):
+        grads = [H.to_device(WL.normal_np(600 + t * 200 + i, layout.d, 1e-3), dtype, "cuda:0") for i in range(n)]
+        for sim, mode in zip(sims, (0, B.DADAM_FORCE_TILE)):
+            sim.step(grads, t, 0, B.DADAM_FUSE_ACCUM | mode)
+        torch.cuda.synchronize()
+        for i in range(n):
+            assert torch.equal(sims[0].x_dst[i], sims[1].x_dst[i]), (t, i)
+            assert torch.equal(sims[0].m[i], sims[1].m[i]) and torch.equal(sims[0].b[i], sims[1].b[i])
+        for sim in sims:
+            sim.swap()
+    for sim in sims:
+        sim.close()
