@@ -697,10 +697,17 @@ __device__ __forceinline__ PieceAt locate_piece(const StepArgs& a, uint32_t tile
 }
 
 // N entries of the neighbour sum, from entry k of the list's chunk on, with all loads issued before the first
-// use.  FIRST: the sum starts with a product, everything after that is a fused multiply-add.
+// use.  FIRST: the sum starts with a product, everything after that is a fused multiply-add.  Where the list
+// names source own.col, its values are kept in own.x.
+template <int VEC>
+struct OwnSource {
+  int col;  // wave-uniform; -1: not wanted
+  bool found = false;
+  float x[VEC];
+};
 template <typename XT, int N, bool FIRST, bool MASKED, bool NT, bool EXT>  // NT: hint on the source loads
 __device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl, int k, uint64_t e, uint64_t lo,
-                                            uint64_t hi, float (&mix)[XT::vec]) {
+                                            uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
   constexpr int VEC = XT::vec;
   u4 r[N];
   float wk[N];
@@ -714,6 +721,11 @@ __device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl
   for (int q = 0; q < N; ++q) {
     float xs[VEC];
     unpack_raw<XT>(r[q], xs);
+    if (list_col(rl, k + q) == own.col) {
+      own.found = true;
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) own.x[j] = xs[j];
+    }
 #pragma unroll
     for (int j = 0; j < VEC; ++j) mix[j] = (FIRST && q == 0) ? wk[0] * xs[j] : fmaf(wk[q], xs[j], mix[j]);
   }
@@ -722,8 +734,8 @@ __device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl
 // Neighbour sum of one row, in the order the row lists its entries.
 template <typename XT, bool MASKED, bool NT, bool EXT>
 __device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int lane, uint64_t e, uint64_t lo,
-                                           uint64_t hi, float (&mix)[XT::vec]) {
-#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix)
+                                           uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
+#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
   switch (rl.deg) {
     case 1: DADAM_MIX(1, true, 0); break;
     case 2: DADAM_MIX(2, true, 0); break;
@@ -782,17 +794,19 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t
   }
   if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   float mix[VEC];
-  mix_direct<XT, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix);
-  // decoupled weight decay acts on the row's own previous parameters: source buffer `row` (the
-  // load repeats one the mixing sum has just made, so it is served by the cache)
+  // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
+  // sum where the row lists itself (loading them again would be a second trip to memory after the first).
+  const bool decays = !Needs<PHASE>::mixing_only && wd != 0.0f;
+  OwnSource<VEC> own;
+  own.col = decays ? row : -1;
+  mix_direct<XT, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
   float decay[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
-  if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
-    float xs[VEC];
-    unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e, lo, hi), xs);
+  if (decays) {
+    if (!own.found) unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e, lo, hi), own.x);
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) decay[j] = wd * xs[j];
+    for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
   }
   float xo[VEC];
 #pragma unroll

@@ -53,3 +53,22 @@ def test_launches_of_few_tiles_give_the_tile_kernels_bits(n, deg, tiles, dtype):
             sim.swap()
     for sim in sims:
         sim.close()
+
+
+@pytest.mark.parametrize("deg,self_at,dtype", [(3, 2, "f32"), (2, None, "f32"), (9, 8, "bf16"), (9, None, "f32"), (14, 13, "f32")])
+def test_weight_decay_finds_the_rows_own_parameters_wherever_the_list_has_them(deg, self_at, dtype):
+    """The direct kernel keeps the row's own previous parameters from the mixing sum when the row lists itself, in
+    any batch of the list, and loads them when it does not."""
+    print("case", deg, self_at, dtype, flush=True)
+    n = 16
+    col = []
+    for i in range(n):
+        others = [(i + 1 + k) % n for k in range(deg)]
+        if self_at is not None:
+            others = others[:self_at] + [i] + others[self_at:deg - 1]
+        col += others
+    csr = (np.arange(0, n * deg + 1, deg, dtype=np.int32), np.array(col, np.int32), np.full(n * deg, np.float32(1) / np.float32(deg), np.float32))
+    layout = WL.pack([("a", (530,)), ("b", (77,)), ("c", (1200,))])
+    worst = H.run_parity(f"own-{deg}-{self_at}-{dtype}", n, n, layout, H.HyperF32(s=2), [csr], lambda t: 0, 3, seed=91, param_dtype=dtype,
+                         grad_dtype=dtype, flags=B.DADAM_FUSE_ACCUM | B.DADAM_FORCE_DIRECT, weight_decay=[0.1, 0.0, 0.05])
+    print("worst error / tolerance:", worst, flush=True)
