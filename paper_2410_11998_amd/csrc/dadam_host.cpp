@@ -343,6 +343,24 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool* t
   return DADAM_OK;
 }
 
+// LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
+// holds: with all 32 of them the row's 8 or 9 streams are requested over too wide a window of memory.  What counts
+// is the bytes of loads in flight per unit; about 90 KB is best.  Fraction of 8 TB/s, by wavefronts per unit,
+// one row with three sources, 3e8 elements: float32 (7 KB a wavefront) 32: 0.772, 18: 0.791, 14: 0.800, 11: 0.809,
+// 9: 0.780; bfloat16 (10 KB) 32: 0.744, 14: 0.770, 11: 0.787, 9: 0.805; s = 1 0.767 -> 0.809.  Short launches need
+// every wavefront (12000 pieces: 0.725 -> 0.670; 25000 in buckets 0.743 -> 0.713; 117000: 0.755 -> 0.779), and so do
+// the passes that load little (mixing 0.828 -> 0.625, accumulation).
+uint32_t bounded_occupancy_lds(const dadam_handle* h, const Slot& slot, Phase phase, uint32_t n_pieces) {
+  if (h->cfg.n_rows != 1 || phase == kMixOnly || !h->nontemporal || n_pieces < kBoundedPieces) return 0;
+  if (h->lds_limit < kLdsPerUnit) return 0;  // the configuration keeps LDS for other kernels
+  const uint32_t state = kWave * 4 * (uint32_t)h->vec;
+  const uint32_t loads = 16 * kWave * (uint32_t)std::min(slot.max_degree, 8) + kWave * (uint32_t)h->vec * (uint32_t)dtype_bytes(h->cfg.grad_dtype) +
+                         state * (phase == kPlain || phase == kFold ? 3u : 2u);
+  const uint32_t waves = std::max(4u, kInFlightBytes / loads);
+  if (waves >= 20) return 0;
+  return kLdsPerUnit / waves / kLdsGranule * kLdsGranule;
+}
+
 int resolve_range(const dadam_handle* h, uint32_t tb, uint32_t te, bool whole, uint64_t* lo,
                   uint64_t* hi, uint32_t* s0, uint32_t* s1, bool* empty) {
   *empty = false;
@@ -440,6 +458,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   a.clip_lo = lo;
   a.clip_hi = hi;
   a.partials = partials;
+  if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
   fill_scalars(h, mix_only ? 1 : t, &a.s);
   int e = tile_mode
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, mix_only ? h->mix_shape : h->shape, a, w1 - w0,

@@ -88,6 +88,7 @@ struct StepArgs {
   uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
   uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
+  uint32_t reserve_lds;  // direct kernels: LDS a workgroup reserves (see bounded_occupancy_lds)
   const Segment* seg;  // device
   uint32_t n_seg;
   uint32_t n_rows, n_cols;
@@ -105,6 +106,8 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see step_impl
 constexpr uint32_t kManyTiles = 1024;    // measured, see step_impl
+constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
+constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
 
 typedef void (*KernelFn)(const StepArgs);
 

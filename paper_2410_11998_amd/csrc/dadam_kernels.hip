@@ -112,7 +112,7 @@ int launch_pieces(KernelFn fn, StepArgs a, uint32_t n_items, void* stream) {
     const uint32_t now = n_items < most ? n_items : most;
     a.n_pieces = now * kDirectItem;
     const uint32_t pieces = a.order == kOrderDieBlocks ? (a.n_pieces + X - 1) / X * X : a.n_pieces;
-    e = launch(fn, (uint32_t)(pieces * per_piece), kWave, 0, a, stream);
+    e = launch(fn, (uint32_t)(pieces * per_piece), kWave, a.reserve_lds, a, stream);
     a.work_begin += now;
     n_items -= now;
   }
