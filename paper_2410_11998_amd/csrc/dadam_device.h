@@ -3,7 +3,7 @@
 //
 //
 // The work is streaming and elementwise over the packed parameter vector; neighbour mixing couples
-// replicas, never elements.  Three kernels:
+// replicas, never elements.  Four kernels:
 //
 //   k_tile    one workgroup owns a tile of elements for ALL rows: every source buffer's slice of the
 //             tile is read from HBM once and parked in LDS, then the wavefronts of the group deal the
@@ -13,6 +13,8 @@
 //             of the tile are read before anything is written, so updating in place is legal.
 //   k_direct  one wavefront updates one vector per lane of one row and streams the row's sources from global
 //             memory (a node's own parameters plus receive buffers: no source is shared by two rows).
+//   k_loop    one workgroup owns a piece of one loop: rows that list the same sources with the same weights share
+//             one neighbour sum.
 //   k_acc     accumulate / fold only (Algorithm 3 lines 9-13).
 //
 // Every access of a full tile is a 128-bit (float32) or 64-bit (bfloat16) load or store per lane,
@@ -862,6 +864,104 @@ __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// loops: groups of rows that list the same sources with the same weights
+// ---------------------------------------------------------------------------------------------
+// The rows of an All-Reduce loop (the complete graph; the loops of the alternating exponential ring) share one
+// neighbour sum.  A workgroup takes one piece of one loop: its wavefronts share out the loop's sources, each sums
+// its own straight from memory, the partial sums (one vector per lane and wavefront) meet in LDS, and after one
+// barrier the wavefronts deal the loop's rows among themselves.  Every source is read once and summed once, where
+// the tile kernel sums it once per row from a staged copy.  What that costs there: 64 rows of 64 sources read 64 x
+// the tile from LDS, and beyond 80 sources a CU holds one workgroup of the tile, whose phases nothing overlaps.
+// All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM where rows are
+// many; measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
+// of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
+template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT>
+__device__ __forceinline__ void loop_body(const StepArgs& a, f4* lds, int loop, uint64_t tbase, uint64_t lo, uint64_t hi,
+                                          float wd, int lane, int wave, int waves) {
+  constexpr bool NT = HINT != 0;
+  constexpr int VEC = XT::vec, H = kHalfWave;
+  const uint64_t e[1] = {tbase + 4u * (uint32_t)lane};
+  const Loop l = a.loops[loop];
+  // this wavefront's sources and rows: every `waves`-th of the loop's, one per lane (at most 160 / 8 of each)
+  RowList rl;
+  rl.k0 = 0;
+  rl.deg = wave < l.n_entries ? (l.n_entries - wave + waves - 1) / waves : 0;
+  const int my_rows = wave < l.n_rows ? (l.n_rows - wave + waves - 1) / waves : 0;
+  const int entry = l.first_entry + (lane < rl.deg ? wave + lane * waves : 0);
+  rl.col_v = a.loop_col[entry];
+  rl.w_v = a.loop_w[entry];
+  const int row_v = a.loop_rows[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
+  float g[1][VEC], mh[1][VEC], vh[1][VEC], b[1][VEC];
+  int row = __builtin_amdgcn_readlane(row_v, 0);
+  if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+  if (rl.deg > 0) {
+    float part[VEC];
+    OwnSource<VEC> none;
+    none.col = -1;
+    mix_direct<XT, MASKED, HINT == 1, EXT>(a, rl, lane, e[0], lo, hi, part, none);
+#pragma unroll
+    for (int h = 0; h < VEC / 4; ++h) {
+      f4 v = {part[4 * h], part[4 * h + 1], part[4 * h + 2], part[4 * h + 3]};
+      lds[(wave * (VEC / 4) + h) * kWave + lane] = v;
+    }
+  }
+  __syncthreads();
+  float mix[VEC];
+  const int parts = waves < l.n_entries ? waves : l.n_entries;
+  for (int p = 0; p < parts; ++p)
+#pragma unroll
+    for (int h = 0; h < VEC / 4; ++h) {
+      const f4 v = lds[(p * (VEC / 4) + h) * kWave + lane];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mix[4 * h + j] = p == 0 ? v[j] : mix[4 * h + j] + v[j];
+    }
+  for (int r = 0; r < my_rows; ++r) {
+    float decay[VEC], xo[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
+    if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
+      float own[VEC];
+      unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e[0], lo, hi), own);
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) decay[j] = wd * own[j];
+    }
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[0][j], mh[0][j], vh[0][j], b[0][j], decay[j]);
+    store_vals<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e[0], lo, hi, xo);
+    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e[0], lo, hi, b[0]);
+    if constexpr (Needs<PHASE>::moments_out) {
+      store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e[0], lo, hi, mh[0]);
+      store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e[0], lo, hi, vh[0]);
+    }
+    if (r + 1 < my_rows) {
+      row = __builtin_amdgcn_readlane(row_v, r + 1);
+      load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+    }
+  }
+}
+
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a) {
+  constexpr uint64_t TILE = (uint64_t)kWave * XT::vec;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
+  f4* lds = reinterpret_cast<f4*>(lds_bytes);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // the dies take runs of tiles in turn, all loops of a tile one after the other (see k_tile)
+  const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * a.n_loops);
+  const uint32_t tile = b / a.n_loops;
+  const int loop = (int)(b - tile * a.n_loops);
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate(a, a.work_begin + tile, tile_index, lo, hi, wd);
+  const uint64_t tbase = tile_index * TILE;
+  const bool full = tbase >= lo && tbase + TILE <= hi;
+  const int waves = (int)(blockDim.x / kWave);
+  if (full) loop_body<XT, GT, PHASE, false, HINT, EXT>(a, lds, loop, tbase, lo, hi, wd, lane, wave, waves);
+  else loop_body<XT, GT, PHASE, true, HINT, EXT>(a, lds, loop, tbase, lo, hi, wd, lane, wave, waves);
+}
+
+// ---------------------------------------------------------------------------------------------
 // accumulate / fold only (Algorithm 3 lines 9-13).  Walks the direct kernel's grid in the same pieces, so a lane
 // vector has as many elements as a parameter vector of the handle (4 or 8).
 // ---------------------------------------------------------------------------------------------
@@ -943,6 +1043,18 @@ KernelFn tile_kernel_for_shape_nt(int phase, TileShape s) {
     if (s.waves == 8 && s.ut == 4) return tile_kernel_for_phase<XT, GT, 8, 4, NT, EXT>(phase);
   }
 #endif
+  return nullptr;
+}
+template <typename XT, typename GT, int HINT, bool EXT>
+KernelFn loop_kernel_for_phase(int phase) {
+  switch (phase) {
+    case kMixOnly: return k_loop<XT, GT, kMixOnly, HINT, EXT>;
+    case kUpdateOnly: return k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return k_loop<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return k_loop<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return k_loop<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return k_loop<XT, GT, kAlg1, HINT, EXT>;
+  }
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>

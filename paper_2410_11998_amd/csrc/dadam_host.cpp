@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <new>
 #include <string>
 #include <utility>
@@ -34,6 +35,14 @@ struct Slot {
   std::vector<int32_t> order;         // rows ordered so that neighbours share sources (empty: nothing is shared)
   int32_t* d_order = nullptr;
   bool reuse = false;                 // some source is read by two or more rows
+  // Loops: rows that list the same sources with the same weights.  Filled only where the loop kernel may take the
+  // slot (see find_loops).
+  std::vector<Loop> loops;
+  std::vector<int32_t> loop_of_row, loop_of_source;  // the loop a row is in / that reads a source (-1: none)
+  Loop* d_loops = nullptr;
+  int32_t* d_loop_col = nullptr;
+  float* d_loop_w = nullptr;
+  int32_t* d_loop_rows = nullptr;
   std::vector<int32_t> sole_reader;   // per source: the only row reading it, -1 none, -2 several
 };
 
@@ -74,6 +83,7 @@ struct dadam_handle {
   uint32_t mix_tile_elems = 0, mix_lds_bytes = 0;
   uint64_t n_work_m = 0;
   bool nontemporal = false;
+  bool decays = false;  // some tensor carries weight decay
   int vec = 4;
   uint32_t tile_elems = 0, direct_elems = 0, lds_bytes = 0;
   bool tile_possible = false;
@@ -159,6 +169,7 @@ int plan(dadam_handle* h) {
   }
   uint64_t wt = 0, wd = 0, wm = 0;
   for (Segment& s : h->segs) {
+    if (s.weight_decay != 0.f) h->decays = true;
     s.first_tile[kGridTile] = s.lo / h->tile_elems;
     s.first_tile[kGridDirect] = s.lo / h->direct_elems;
     s.first_tile[kGridMix] = s.lo / h->mix_tile_elems;
@@ -343,6 +354,27 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool* t
   return DADAM_OK;
 }
 
+// Wavefronts of a loop kernel's workgroup, 0: another kernel takes the launch.  Depends on the slot and on the whole
+// layout, never on the range of a launch: the order in which a loop is summed follows from it, and a step issued
+// range by range has the bits of the whole one.
+// Legal: a row updated in place overwrites sources that only its own loop may read (the loop reads them all before
+// it writes), and with weight decay a row reads its own parameters again after that.
+// Faster: with 16 rows to a loop on average.  us, other kernels / 4 / 8 / 16 wavefronts, 3e8 elements, mixing:
+// 32 rows in one loop 1349 / 862 / 837 / 900, 64 rows 3163 / 881 / 871 / 865, 96 rows in loops of 48, 24, 24 8486 /
+// 1764 / 1737 / 2091, but 32 rows in loops of 16, 8, 8 1756 / 1667 / 1933 / 3531 and 16 rows in loops of 8, 4, 4
+// 1709 / 1850 / 3098; four steps, 3e7 elements: 32 rows 667 / 655 / 634 / 663, 64 rows 926 / 669 / 623 / 631, 96 rows
+// 1416 / 731 / 706 / 743.  In small launches each wavefront walks its rows in turn, so more of them, from 8 rows a
+// loop on: 64 rows 4e5 elements 85 / 121 / 75 / 52, 4e6 225 / 176 / 118 / 84; 32 rows in loops of 16, 8, 8 4e5 36 /
+// 44 / 32 / 27.
+int loop_kernel_waves(const dadam_handle* h, const Slot& slot) {
+  const uint64_t R = h->cfg.n_rows, G = slot.loops.size();
+  if (G == 0 || (R < 16 * G && (R < 8 * G || h->n_work_t > kFewTiles))) return 0;
+  for (uint32_t i = 0; i < R; ++i)
+    for (int32_t c : h->inplace_cols[i])
+      if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
+  return h->n_work_t * G <= 2 * kFewTiles ? 16 : 8;
+}
+
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
 // holds: with all 32 of them the row's 8 or 9 streams are requested over too wide a window of memory.  What counts
 // is the bytes of loads in flight per unit; about 90 KB is best.  Fraction of 8 TB/s, by wavefronts per unit,
@@ -442,10 +474,13 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   // row takes the launch instead, with the same sums in the same order.  A loop of four steps, us, tile / direct, by
   // tiles: 16 rows of 5 sources 98: 27 / 24, 488: 48 / 48; 32 rows of 6 sources 49: 45 / 24, 244: 65 / 48, 977:
   // 158 / 165; 64 rows of 7 sources 24: 82 / 27, 122: 108 / 48, 488: 173 / 171; 8 rows the same up to 195 tiles.
-  const bool few_tiles = tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
+  const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot);
+  const bool by_loops = loop_waves > 0;
+  const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= kFewTiles && direct_is_legal(h, slot);
   if (few_tiles) tile_mode = false;
-  const Grid grid = !tile_mode ? kGridDirect : mix_only ? kGridMix : kGridTile;
+  if (by_loops) tile_mode = true;
+  const Grid grid = !tile_mode ? kGridDirect : mix_only && !by_loops ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, &slot, mix_only ? nullptr : grads, &a);
@@ -460,9 +495,20 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
   fill_scalars(h, mix_only ? 1 : t, &a.s);
+  TileShape shape = mix_only ? h->mix_shape : h->shape;
+  uint32_t lds = mix_only ? h->mix_lds_bytes : h->lds_bytes;
+  if (by_loops) {
+    a.loops = slot.d_loops;
+    a.loop_col = slot.d_loop_col;
+    a.loop_w = slot.d_loop_w;
+    a.loop_rows = slot.d_loop_rows;
+    a.n_loops = (uint32_t)slot.loops.size();
+    shape.ut = 1;
+    shape.waves = loop_waves;
+    lds = (uint32_t)(shape.waves * kWave * h->vec * 4);
+  }
   int e = tile_mode
-              ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, mix_only ? h->mix_shape : h->shape, a, w1 - w0,
-                            mix_only ? h->mix_lds_bytes : h->lds_bytes, stream)
+              ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
               : launch_direct((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase,
                               // where rows share sources the re-reads must find them in the cache
                               h->nontemporal, slot.reuse, a, w1 - w0, stream);
@@ -505,7 +551,41 @@ std::vector<int32_t> sharing_order(uint32_t R, uint32_t C, const int32_t* row_pt
   return order;
 }
 
+// The loops of a neighbour list, for the loop kernel: at least eight rows to a loop on average, so that a
+// workgroup's wavefronts have rows to share, and no source in two loops, so that each is read once.
+// col / w / rows: the loops' entries, in source order, and their rows.
+void find_loops(uint32_t R, uint32_t C, Slot& s, std::vector<int32_t>& col, std::vector<float>& w, std::vector<int32_t>& rows) {
+  std::map<std::vector<std::pair<int32_t, float>>, std::vector<int32_t>> by_list;
+  for (uint32_t i = 0; i < R; ++i) {
+    std::vector<std::pair<int32_t, float>> list;
+    for (int32_t k = s.row_ptr[i]; k < s.row_ptr[i + 1]; ++k) list.push_back({s.col[k], s.w[k]});
+    std::sort(list.begin(), list.end());
+    by_list[list].push_back((int32_t)i);
+    if (by_list.size() * 8 > R) return;
+  }
+  std::vector<int32_t> of_row(R, -1), of_source(C, -1);
+  std::vector<Loop> loops;
+  for (const auto& it : by_list) {
+    const int32_t id = (int32_t)loops.size();
+    loops.push_back({(int32_t)col.size(), (int32_t)it.first.size(), (int32_t)rows.size(), (int32_t)it.second.size()});
+    for (const auto& e : it.first) {
+      if (of_source[e.first] != -1) return;
+      of_source[e.first] = id;
+      col.push_back(e.first);
+      w.push_back(e.second);
+    }
+    for (int32_t i : it.second) { of_row[i] = id; rows.push_back(i); }
+  }
+  s.loops = loops;
+  s.loop_of_row = of_row;
+  s.loop_of_source = of_source;
+}
+
 void free_slot(Slot& s) {
+  if (s.d_loops) (void)hipFree(s.d_loops);
+  if (s.d_loop_col) (void)hipFree(s.d_loop_col);
+  if (s.d_loop_w) (void)hipFree(s.d_loop_w);
+  if (s.d_loop_rows) (void)hipFree(s.d_loop_rows);
   if (s.d_row_ptr) (void)hipFree(s.d_row_ptr);
   if (s.d_col) (void)hipFree(s.d_col);
   if (s.d_w) (void)hipFree(s.d_w);
@@ -700,6 +780,9 @@ int dadam_set_topology(dadam_handle* h, uint32_t slot_id, const int32_t* row_ptr
   fresh.sole_reader = sole;
   for (uint32_t i = 0; i < R; ++i) fresh.max_degree = std::max(fresh.max_degree, row_ptr[i + 1] - row_ptr[i]);
   if (reuse) fresh.order = sharing_order(R, C, row_ptr, col_idx);
+  std::vector<int32_t> loop_col, loop_rows;
+  std::vector<float> loop_w;
+  find_loops(R, C, fresh, loop_col, loop_w, loop_rows);
   if (h->cfg.device != DADAM_DEVICE_NONE) {
     DeviceGuard guard(h->cfg.device);
     hipError_t e = guard.err;
@@ -712,6 +795,16 @@ int dadam_set_topology(dadam_handle* h, uint32_t slot_id, const int32_t* row_ptr
     if (e == hipSuccess && !fresh.order.empty()) {
       e = hipMalloc((void**)&fresh.d_order, R * sizeof(int32_t));
       if (e == hipSuccess) e = hipMemcpy(fresh.d_order, fresh.order.data(), R * sizeof(int32_t), hipMemcpyHostToDevice);
+    }
+    auto upload = [&e](auto** to, const auto& from) {
+      if (e == hipSuccess) e = hipMalloc((void**)to, from.size() * sizeof(from[0]));
+      if (e == hipSuccess) e = hipMemcpy(*to, from.data(), from.size() * sizeof(from[0]), hipMemcpyHostToDevice);
+    };
+    if (!fresh.loops.empty()) {
+      upload(&fresh.d_loops, fresh.loops);
+      upload(&fresh.d_loop_col, loop_col);
+      upload(&fresh.d_loop_w, loop_w);
+      upload(&fresh.d_loop_rows, loop_rows);
     }
     if (e != hipSuccess) {
       free_slot(fresh);

@@ -55,6 +55,13 @@ enum Phase : int {
 constexpr uint32_t kConsensusPartials = 1024;  // partial sums the tiles scatter their contributions over
 static_assert(kConsensusPartials * sizeof(double) == DADAM_STATIC_SCRATCH_BYTES, "the header states the static scratch size");
 
+// Rows that list the same sources with the same weights.
+struct Loop {
+  int32_t first_entry, n_entries;  // in StepArgs::loop_col / loop_w
+  int32_t first_row, n_rows;       // in StepArgs::loop_rows
+};
+constexpr int kMaxLoopWaves = 16;  // wavefronts of a loop kernel's workgroup
+
 // Pointer tables of the bound buffers of a handle with more than kInlineRows rows or sources: they do not
 // fit the 4 KB kernel-argument segment and live in device memory, one immutable copy per binding and
 // exchange state (see dadam_bind).
@@ -84,6 +91,12 @@ struct StepArgs {
   // Direct kernels: the rows in an order in which neighbours share sources (device; null: rows as numbered),
   // so that the rows which read a source run on the die whose L2 already holds it.
   const int32_t* row_order;
+  // Loop kernel (n_loops > 0, see launch_tile): the slot's loops
+  const Loop* loops;  // device
+  const int32_t* loop_col;
+  const float* loop_w;
+  const int32_t* loop_rows;
+  uint32_t n_loops;
   uint32_t order;        // Order: how a launch of the row kernel walks pieces and rows
   uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
   uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
@@ -119,6 +132,7 @@ struct TileShape {
 
 // Launchers.  All of them enqueue on `stream` and return the hipError_t of the launch as int.
 // xdt / gdt are DADAM_F32 | DADAM_BF16.  n_work is the number of tiles in this launch.
+// launch_tile with a.n_loops > 0 launches the loop kernel, shape.waves wavefronts a workgroup.
 int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& a, uint32_t n_work,
                 uint32_t lds_bytes, void* stream);
 // shared: rows share sources; a streaming launch then keeps the hint off the source loads.

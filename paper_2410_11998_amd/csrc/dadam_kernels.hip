@@ -24,6 +24,8 @@ namespace dadam {
 #define DADAM_PART(name)                                       \
   KernelFn tile_kernel_##name(int phase, TileShape s);         \
   KernelFn direct_kernel_##name(int phase, bool shared);       \
+  KernelFn loop_kernel_##name(int phase);                      \
+  KernelFn loop_kernel_##name##_ext(int phase);                \
   KernelFn tile_kernel_##name##_ext(int phase, TileShape s);   \
   KernelFn direct_kernel_##name##_ext(int phase, bool shared)
 DADAM_PART(f32_f32_nt);
@@ -164,8 +166,33 @@ bool tile_shape_supported(TileShape s) {
   return (s.waves == 4 || s.waves == 8) && (s.ut == 1 || s.ut == 2);
 }
 
+// Loop kernel: one workgroup per tile and loop, in several launches where a grid would reach 2^32 threads.
+static int launch_loops(int xdt, int gdt, Phase phase, TileShape shape, StepArgs a, uint32_t n_tiles, uint32_t lds_bytes,
+                        void* stream) {
+  KernelFn fn = nullptr;
+  const bool nt = shape.nontemporal, ext = a.ext != nullptr;
+#define DADAM_PICK(name) (ext ? (nt ? loop_kernel_##name##_nt_ext(phase) : loop_kernel_##name##_ext(phase)) \
+                              : (nt ? loop_kernel_##name##_nt(phase) : loop_kernel_##name(phase)))
+  if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
+  if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
+  if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
+  if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
+#undef DADAM_PICK
+  const uint32_t threads = (uint32_t)(kWave * shape.waves);
+  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / threads / a.n_loops);
+  int e = (int)hipSuccess;
+  while (n_tiles > 0 && e == (int)hipSuccess) {
+    const uint32_t now = n_tiles < most ? n_tiles : most;
+    e = launch(fn, now * a.n_loops, threads, lds_bytes, a, stream);
+    a.work_begin += now;
+    n_tiles -= now;
+  }
+  return e;
+}
+
 int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& a, uint32_t n_work,
                 uint32_t lds_bytes, void* stream) {
+  if (a.n_loops > 0) return launch_loops(xdt, gdt, phase, shape, a, n_work, lds_bytes, stream);
   // A handle with more than 64 rows or sources keeps its pointer tables in device memory and runs kernels
   // compiled for that (kernels of their own, so that the small handles' register budget is not theirs).
   KernelFn fn = nullptr;

@@ -25,4 +25,8 @@ KernelFn DADAM_JOIN(direct_kernel_, DADAM_PART_NAME)(int phase, bool shared) {
                 : direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
 }
 
+KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase) {
+  return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
+}
+
 }  // namespace dadam

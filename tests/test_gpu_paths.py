@@ -72,3 +72,43 @@ def test_weight_decay_finds_the_rows_own_parameters_wherever_the_list_has_them(d
     worst = H.run_parity(f"own-{deg}-{self_at}-{dtype}", n, n, layout, H.HyperF32(s=2), [csr], lambda t: 0, 3, seed=91, param_dtype=dtype,
                          grad_dtype=dtype, flags=B.DADAM_FUSE_ACCUM | B.DADAM_FORCE_DIRECT, weight_decay=[0.1, 0.0, 0.05])
     print("worst error / tolerance:", worst, flush=True)
+
+
+@pytest.mark.parametrize("case", ["complete9", "complete8-bf16", "complete64", "complete33-decay", "aer32-inplace", "aer96", "aer24-bf16-decay",
+                                  "gather-12x20", "broadcast-9", "weights-12", "complete160-bf16"])
+def test_rows_of_a_loop_share_one_neighbour_sum(case):
+    """The loop kernel against the oracle: loops of fewer and of more sources than a workgroup has wavefronts, several
+    loops of different length, rows that all copy one source, unequal weights, sources that are no row's own, in place,
+    with decay, on a ragged layout, in a whole accumulation loop."""
+    print("case", case, flush=True)
+    layout = WL.pack([("a", (1501,)), ("b", (5,)), ("c", (770,))])
+    dtype = "bf16" if "bf16" in case else "f32"
+    inplace, rng = "inplace" in case, np.random.default_rng(5)
+    slot_of_t = lambda t: 0
+    wd = [0.1, 0.0, 0.02] if "decay" in case else None
+    if case.startswith("complete"):
+        R = C = int(case[8:].split("-")[0])
+        csrs = [WL.complete(R)]
+    elif case.startswith("aer"):
+        R = C = int(case[3:].split("-")[0])
+        csrs, slot_of_t = [WL.aer(R // 4, k) for k in range(4)], lambda t: t % 4
+    elif case.startswith("gather"):
+        R, C = 12, 20
+        csrs = [(np.arange(0, 37, 3, dtype=np.int32), np.tile(np.array([2, 19, 14], np.int32), 12), np.tile(np.array([0.5, 0.25, 0.25], np.float32), 12))]
+    elif case.startswith("broadcast"):
+        R = C = 9
+        csrs = [(np.arange(10, dtype=np.int32), np.full(9, 4, np.int32), np.ones(9, np.float32))]
+    else:                                # two loops of six rows with random weights, listed in a different order by every row
+        R = C = 12
+        w = (rng.random(6) + 0.1).astype(np.float32)
+        w = (w / w.sum(dtype=np.float32)).astype(np.float32)
+        col, ws = [], []
+        for i in range(12):
+            p = rng.permutation(6)
+            col += [int(q) * 2 + i % 2 for q in p]
+            ws += [w[q] for q in p]
+        csrs = [(np.arange(0, 73, 6, dtype=np.int32), np.array(col, np.int32), np.array(ws, np.float32))]
+    worst = H.run_parity(f"loop-{case}", R, C, layout, H.HyperF32(s=2), csrs, slot_of_t, 3, seed=88, param_dtype=dtype, grad_dtype=dtype,
+                         flags=B.DADAM_FUSE_ACCUM, inplace=inplace, refresh_extra_sources=R != C, weight_decay=wd,
+                         pad_fill=None if inplace or C != R else 777.0, free_running=C == R)
+    print("worst error / tolerance:", worst, flush=True)
