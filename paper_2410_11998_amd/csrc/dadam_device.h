@@ -296,26 +296,51 @@ struct Needs {
   static constexpr bool moments_out = PHASE == kFold || PHASE == kAlg1;
 };
 
-// Which segment does work item `work` belong to, and which tile of the launch's grid is it?
-// (Fields are read one by one through the pointer: copying the struct would put it in scratch.)
+// Which segment does work item `work` belong to, and which tile of the launch's grid is it?  Every lane of the
+// wavefront is active here.  In small launches, whose time is a chain of trips to memory, all lanes search the
+// segments' first work items at once, 64 to a step: one trip for up to 64 segments, two for up to 4096, where a binary
+// search takes one for each halving (8 replicas of 300 odd-sized tensors 74 -> 68 us a loop of four steps).  In large ones
+// the binary search is served by the scalar cache and leaves the vector memory path alone.
+// (Fields are read one by one through the pointer: copying the struct would put it in scratch.  The cast names global
+// memory: the compiler would otherwise merge a read of a segment with the same read of the argument block into one
+// through a generic pointer.)
 __device__ __forceinline__ void locate(const StepArgs& a, uint32_t work, uint64_t& tile_index,
                                        uint64_t& lo, uint64_t& hi, float& weight_decay) {
-  const uint32_t grid = a.grid;
-  const Segment* seg = a.seg;
-  uint32_t s = 0;
-  if (a.n_seg > 1) {
-    uint32_t l = 0, r = a.n_seg;
-    while (r - l > 1) {
-      uint32_t mid = (l + r) >> 1;
-      if (seg[mid].work0[grid] <= work) l = mid; else r = mid;
+  if (a.n_seg == 1) {  // the launch's range lies inside the only segment
+    tile_index = a.first_tile + work;
+    lo = a.clip_lo;
+    hi = a.clip_hi;
+    weight_decay = a.weight_decay;
+  } else {
+    typedef const Segment __attribute__((address_space(1))) * GlobalSegments;
+    const GlobalSegments seg = (GlobalSegments)a.seg;
+    const uint32_t grid = a.grid;
+    uint32_t s = 0, n = a.n_seg;  // the segment is one of [s, s + n)
+    if (a.wide_search) {
+      const uint32_t lane = threadIdx.x & (kWave - 1);
+      const uint32_t* begin = a.seg_work + (uint64_t)grid * a.n_seg;  // first work item of each segment, increasing
+      while (n > 1) {
+        const uint32_t step = (n + kWave - 1) / kWave, at = lane * step;
+        const bool not_after = at < n && begin[s + (at < n ? at : 0)] <= work;
+        const uint32_t last = (uint32_t)__popcll(__ballot(not_after)) - 1;  // lane 0 is always among them
+        s += last * step;
+        n = step < n - last * step ? step : n - last * step;
+      }
+      s = __builtin_amdgcn_readfirstlane((int)s);
+    } else {
+      while (n > 1) {
+        const uint32_t half = n >> 1;
+        const bool right = seg[s + half].work0[grid] <= work;
+        s = right ? s + half : s;
+        n = right ? n - half : half;
+      }
     }
-    s = l;
+    tile_index = seg[s].first_tile[grid] + (work - seg[s].work0[grid]);
+    const uint64_t slo = seg[s].lo, shi = seg[s].hi;
+    lo = slo > a.clip_lo ? slo : a.clip_lo;
+    hi = shi < a.clip_hi ? shi : a.clip_hi;
+    weight_decay = seg[s].weight_decay;
   }
-  tile_index = seg[s].first_tile[grid] + (work - seg[s].work0[grid]);
-  const uint64_t slo = seg[s].lo, shi = seg[s].hi;
-  lo = slo > a.clip_lo ? slo : a.clip_lo;
-  hi = shi < a.clip_hi ? shi : a.clip_hi;
-  weight_decay = seg[s].weight_decay;
 }
 
 // Pointers of the bound buffers.  EXT = false: from the argument block (at most kInlineRows rows and
@@ -378,14 +403,15 @@ __device__ __forceinline__ void load_list_chunk(const StepArgs& a, RowList& r, i
   r.w_v = a.w[idx];
 }
 
-__device__ __forceinline__ RowList load_row_list(const StepArgs& a, int row, int lane) {
-  // row_ptr entries are read by every lane from the same address (one broadcast transaction)
-  int k0 = __builtin_amdgcn_readfirstlane(a.row_ptr[row]);
-  int k1 = __builtin_amdgcn_readfirstlane(a.row_ptr[row + 1]);
+// First chunk of the list of the row at `position` of a direct launch.  The lists lie at a fixed distance, so that
+// nothing has to be known about the row before its list can be loaded (padding lists source 0).
+__device__ __forceinline__ RowList load_position_list(const StepArgs& a, int position, int lane) {
   RowList r;
-  r.deg = k1 - k0;  // host guarantees 1 <= deg <= n_cols
-  r.k0 = k0;
-  load_list_chunk(a, r, 0, lane);
+  r.k0 = position * (int)a.list_stride;
+  const int idx = r.k0 + (lane < (int)a.list_stride ? lane : 0);
+  r.col_v = a.col[idx];
+  r.w_v = a.w[idx];
+  r.deg = __builtin_amdgcn_readfirstlane(a.row_len[position]);  // host guarantees 1 <= deg <= n_cols
   return r;
 }
 
@@ -776,7 +802,7 @@ __device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int la
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
 template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT>
-__device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t tbase, uint64_t lo,
+__device__ __forceinline__ void direct_body(const StepArgs& a, int position, int row, uint64_t tbase, uint64_t lo,
                                             uint64_t hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
   constexpr int VEC = XT::vec, H = kHalfWave;
@@ -787,7 +813,7 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int row, uint64_t
   // every access masked off instead of returning early.  (With an early return the compiler is
   // free to sink the list's load below it, into the lanes that stay - and a row whose leading
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
-  RowList rl = load_row_list(a, row, lane);
+  RowList rl = load_position_list(a, position, lane);
   float g[VEC], mh[VEC], vh[VEC], b[VEC];
   if constexpr (Needs<PHASE>::grad) load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e, lo, hi, g);
   if constexpr (Needs<PHASE>::moments_in) {
@@ -827,8 +853,7 @@ template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
 __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
   const int lane = threadIdx.x;
   const uint32_t n_rows = a.n_rows;
-  uint32_t t;
-  int row;
+  uint32_t t, position;
   bool active = true;
   if (a.order == kOrderDieBlocks) {
     // Rows share sources: every row of a piece runs on one die, one after the other in the sharing order, so that
@@ -838,7 +863,7 @@ __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
     const uint32_t index = j / n_rows * X + x;
     active = index < a.n_pieces;
     t = active ? die_block_order(index, a.n_pieces, X, a.xcd_block) : 0;
-    row = __builtin_amdgcn_readfirstlane(a.row_order[j % n_rows]);
+    position = j % n_rows;
   } else if (a.order == kOrderDieGroups) {
     // Rows share sources.  Consecutive workgroup ids go to the device's X dies in turn; die x takes the
     // rows at positions [x R / X, (x + 1) R / X) of the sharing order (R = n_rows), tile after tile: the
@@ -846,20 +871,19 @@ __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
     // source in that die's L2.  Every die gets G = ceil(R / X) workgroups per tile; where R / X is not whole,
     // the last workgroup of some dies has no row and does nothing (the whole workgroup, so no lane leaves
     // a wavefront early).
-    uint32_t position;
     active = die_group_order(blockIdx.x, n_rows, a.n_xcd, a.order_group, t, position);
-    row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
   } else {
     // Nothing is shared: workgroups in launch order.  (Tile mode's orders were measured here too, on one row with
     // three sources: runs of 2, 4, 8 pieces per die 0.79, 0.77, 0.77 against 0.795, one contiguous X-th of the
     // pieces per die 0.73.)
     t = blockIdx.x / n_rows;
-    row = (int)(blockIdx.x - t * n_rows);
+    position = blockIdx.x - t * n_rows;
   }
+  const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
   const PieceAt p = locate_piece<XT::vec>(a, t);
   if (active && p.any) {  // uniform over the workgroup
-    if (p.full) direct_body<XT, GT, PHASE, false, HINT, EXT>(a, row, p.tbase, p.lo, p.hi, p.wd, lane);
-    else direct_body<XT, GT, PHASE, true, HINT, EXT>(a, row, p.tbase, p.lo, p.hi, p.wd, lane);
+    if (p.full) direct_body<XT, GT, PHASE, false, HINT, EXT>(a, (int)position, row, p.tbase, p.lo, p.hi, p.wd, lane);
+    else direct_body<XT, GT, PHASE, true, HINT, EXT>(a, (int)position, row, p.tbase, p.lo, p.hi, p.wd, lane);
   }
 }
 
@@ -888,9 +912,9 @@ __device__ __forceinline__ void loop_body(const StepArgs& a, f4* lds, int loop, 
   rl.deg = wave < l.n_entries ? (l.n_entries - wave + waves - 1) / waves : 0;
   const int my_rows = wave < l.n_rows ? (l.n_rows - wave + waves - 1) / waves : 0;
   const int entry = l.first_entry + (lane < rl.deg ? wave + lane * waves : 0);
-  rl.col_v = a.loop_col[entry];
-  rl.w_v = a.loop_w[entry];
-  const int row_v = a.loop_rows[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
+  rl.col_v = a.col[entry];
+  rl.w_v = a.w[entry];
+  const int row_v = a.row_order[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
   float g[1][VEC], mh[1][VEC], vh[1][VEC], b[1][VEC];
   int row = __builtin_amdgcn_readlane(row_v, 0);
   if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);

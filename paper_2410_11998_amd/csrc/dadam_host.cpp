@@ -28,22 +28,23 @@ struct Slot {
   bool set = false;
   std::vector<int32_t> row_ptr, col;
   std::vector<float> w;
-  int32_t* d_row_ptr = nullptr;
-  int32_t* d_col = nullptr;
-  float* d_w = nullptr;
   int32_t max_degree = 0;             // longest row
   std::vector<int32_t> order;         // rows ordered so that neighbours share sources (empty: nothing is shared)
-  int32_t* d_order = nullptr;
   bool reuse = false;                 // some source is read by two or more rows
   // Loops: rows that list the same sources with the same weights.  Filled only where the loop kernel may take the
   // slot (see find_loops).
   std::vector<Loop> loops;
   std::vector<int32_t> loop_of_row, loop_of_source;  // the loop a row is in / that reads a source (-1: none)
-  Loop* d_loops = nullptr;
-  int32_t* d_loop_col = nullptr;
-  float* d_loop_w = nullptr;
-  int32_t* d_loop_rows = nullptr;
   std::vector<int32_t> sole_reader;   // per source: the only row reading it, -1 none, -2 several
+  // one device allocation holding everything the kernels read (see StepArgs)
+  char* d_lists = nullptr;
+  const int32_t *d_row_ptr = nullptr, *d_col = nullptr;                                    // tile kernel
+  const float* d_w = nullptr;
+  const int32_t *d_row_len = nullptr, *d_list_col = nullptr, *d_row_order = nullptr;        // direct kernel
+  const float* d_list_w = nullptr;
+  const int32_t *d_loop_col = nullptr, *d_loop_rows = nullptr;                              // loop kernel
+  const float* d_loop_w = nullptr;
+  const Loop* d_loops = nullptr;
 };
 
 struct DeviceGuard {
@@ -69,7 +70,8 @@ struct dadam_handle {
   std::vector<dadam_tensor_desc> tensors;
   std::vector<uint32_t> tensor_seg;  // segment of each non-empty tensor, UINT32_MAX for empty ones
   std::vector<Segment> segs;
-  Segment* d_segs = nullptr;
+  Segment* d_segs = nullptr;     // the segments, and behind them
+  uint32_t* d_seg_work = nullptr;  // their first work items, per Grid (what the kernels search)
   double* d_partials = nullptr;  // kConsensusPartials doubles of scratch for the consensus error
   // Handles with more than kInlineRows rows or sources: device copies of the bound pointer tables, two per
   // binding (as bound, and with x_src / x_dst exchanged), DADAM_BINDINGS_KEPT bindings in a ring.
@@ -253,7 +255,7 @@ int check_grads(dadam_handle* h, const void* const* grads) {
   return DADAM_OK;
 }
 
-void fill_args(const dadam_handle* h, const Slot* slot, const void* const* grads, StepArgs* a) {
+void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
   memset(a, 0, sizeof(*a));
   const uint32_t R = h->cfg.n_rows, C = h->cfg.n_cols;
   if (h->d_tables) {
@@ -268,17 +270,8 @@ void fill_args(const dadam_handle* h, const Slot* slot, const void* const* grads
     }
   }
   for (uint32_t i = 0; i < R; ++i) a->grad[i] = grads ? grads[i] : nullptr;
-  if (slot) {
-    a->row_ptr = slot->d_row_ptr;
-    a->col = slot->d_col;
-    a->w = slot->d_w;
-    // rows that share sources: the launch walks the sharing order (see step_impl)
-    if (slot->d_order && h->n_xcds > 1) {
-      a->row_order = slot->d_order;
-      a->order_group = (R + h->n_xcds - 1) / h->n_xcds;
-    }
-  }
   a->seg = h->d_segs;
+  a->seg_work = h->d_seg_work;
   a->n_seg = (uint32_t)h->segs.size();
   a->n_rows = R;
   a->n_cols = C;
@@ -322,6 +315,19 @@ bool direct_is_legal(const dadam_handle* h, const Slot& slot) {
       if (!(sr == -1 || sr == (int32_t)i)) return false;
     }
   return true;
+}
+
+// Do direct launches of this slot walk its rows in the sharing order?
+bool ordered_rows(const dadam_handle* h, const Slot& slot) { return !slot.order.empty() && h->n_xcds > 1; }
+
+void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t lo, uint64_t hi, StepArgs* a) {
+  a->wide_search = (hi - lo) * h->cfg.n_rows / h->tile_elems <= kWideSearchTiles ? 1u : 0u;
+  a->grid = grid;
+  a->work_begin = work_begin;
+  a->clip_lo = lo;
+  a->clip_hi = hi;
+  a->first_tile = h->segs.front().first_tile[grid];
+  a->weight_decay = h->segs.front().weight_decay;
 }
 
 // Decide tile or direct mode for this slot and these flags; checks in-place legality.
@@ -483,15 +489,12 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const Grid grid = !tile_mode ? kGridDirect : mix_only && !by_loops ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
-  fill_args(h, &slot, mix_only ? nullptr : grads, &a);
+  fill_args(h, mix_only ? nullptr : grads, &a);
   // Rows that share sources: in a small launch every row of a piece runs on one die, in a large one each die has a
   // group of rows.  us, pieces / groups: 64 rows of two sources 244 tiles 83 / 87; 96 rows of 7 sources 81 tiles
   // 53 / 74, 325 tiles 186 / 215, 1220 tiles 792 / 780; 32 rows of two sources in bfloat16, 18000 tiles, 5160 / 4970.
-  if (a.row_order) a.order = n_tiles < kManyTiles ? kOrderDieBlocks : kOrderDieGroups;
-  a.grid = grid;
-  a.work_begin = w0;
-  a.clip_lo = lo;
-  a.clip_hi = hi;
+  if (!tile_mode && ordered_rows(h, slot)) a.order = n_tiles < kManyTiles ? kOrderDieBlocks : kOrderDieGroups;
+  set_range(h, grid, w0, lo, hi, &a);
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
   fill_scalars(h, mix_only ? 1 : t, &a.s);
@@ -499,13 +502,24 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   uint32_t lds = mix_only ? h->mix_lds_bytes : h->lds_bytes;
   if (by_loops) {
     a.loops = slot.d_loops;
-    a.loop_col = slot.d_loop_col;
-    a.loop_w = slot.d_loop_w;
-    a.loop_rows = slot.d_loop_rows;
     a.n_loops = (uint32_t)slot.loops.size();
+    a.col = slot.d_loop_col;
+    a.w = slot.d_loop_w;
+    a.row_order = slot.d_loop_rows;
     shape.ut = 1;
     shape.waves = loop_waves;
     lds = (uint32_t)(shape.waves * kWave * h->vec * 4);
+  } else if (tile_mode) {
+    a.row_ptr = slot.d_row_ptr;
+    a.col = slot.d_col;
+    a.w = slot.d_w;
+  } else {
+    a.row_len = slot.d_row_len;
+    a.col = slot.d_list_col;
+    a.w = slot.d_list_w;
+    a.row_order = slot.d_row_order;
+    a.list_stride = (uint32_t)slot.max_degree;
+    a.order_group = (h->cfg.n_rows + h->n_xcds - 1) / h->n_xcds;
   }
   int e = tile_mode
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
@@ -581,15 +595,47 @@ void find_loops(uint32_t R, uint32_t C, Slot& s, std::vector<int32_t>& col, std:
   s.loop_of_source = of_source;
 }
 
+// Device copies of everything the kernels read of a slot, in one allocation.
+hipError_t upload_lists(const dadam_handle* h, Slot& s, const std::vector<int32_t>& loop_col, const std::vector<float>& loop_w,
+                        const std::vector<int32_t>& loop_rows) {
+  const int32_t R = (int32_t)h->cfg.n_rows, stride = s.max_degree;
+  std::vector<int32_t> rows(R), len(R), lcol((size_t)R * stride, 0);
+  std::vector<float> lw((size_t)R * stride, 0.0f);
+  for (int32_t p = 0; p < R; ++p) {
+    const int32_t i = ordered_rows(h, s) ? s.order[p] : p;
+    rows[p] = i;
+    len[p] = s.row_ptr[i + 1] - s.row_ptr[i];
+    std::copy_n(s.col.begin() + s.row_ptr[i], len[p], lcol.begin() + (size_t)p * stride);
+    std::copy_n(s.w.begin() + s.row_ptr[i], len[p], lw.begin() + (size_t)p * stride);
+  }
+  std::vector<char> image;
+  auto add = [&image](const auto& v) {
+    const size_t at = image.size();
+    image.resize(at + (v.size() * sizeof(v[0]) + 255) / 256 * 256);
+    memcpy(image.data() + at, v.data(), v.size() * sizeof(v[0]));
+    return at;
+  };
+  const size_t row_ptr = add(s.row_ptr), col = add(s.col), w = add(s.w);
+  const size_t row_len = add(len), list_col = add(lcol), list_w = add(lw), row_order = add(rows);
+  const bool has_loops = !s.loops.empty();
+  const size_t l = has_loops ? add(s.loops) : 0, lc = has_loops ? add(loop_col) : 0, lww = has_loops ? add(loop_w) : 0,
+               lr = has_loops ? add(loop_rows) : 0;
+  hipError_t e = hipMalloc((void**)&s.d_lists, image.size());
+  if (e == hipSuccess) e = hipMemcpy(s.d_lists, image.data(), image.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return e;
+  auto ints = [&s](size_t at) { return reinterpret_cast<const int32_t*>(s.d_lists + at); };
+  auto floats = [&s](size_t at) { return reinterpret_cast<const float*>(s.d_lists + at); };
+  s.d_row_ptr = ints(row_ptr); s.d_col = ints(col); s.d_w = floats(w);
+  s.d_row_len = ints(row_len); s.d_list_col = ints(list_col); s.d_list_w = floats(list_w); s.d_row_order = ints(row_order);
+  if (has_loops) {
+    s.d_loops = reinterpret_cast<const Loop*>(s.d_lists + l);
+    s.d_loop_col = ints(lc); s.d_loop_w = floats(lww); s.d_loop_rows = ints(lr);
+  }
+  return hipSuccess;
+}
+
 void free_slot(Slot& s) {
-  if (s.d_loops) (void)hipFree(s.d_loops);
-  if (s.d_loop_col) (void)hipFree(s.d_loop_col);
-  if (s.d_loop_w) (void)hipFree(s.d_loop_w);
-  if (s.d_loop_rows) (void)hipFree(s.d_loop_rows);
-  if (s.d_row_ptr) (void)hipFree(s.d_row_ptr);
-  if (s.d_col) (void)hipFree(s.d_col);
-  if (s.d_w) (void)hipFree(s.d_w);
-  if (s.d_order) (void)hipFree(s.d_order);
+  if (s.d_lists) (void)hipFree(s.d_lists);
   s = Slot();
 }
 
@@ -715,9 +761,15 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     DeviceGuard guard(cfg->device);
     hipError_t e = guard.err;
     if (e == hipSuccess && !h->segs.empty()) {
-      e = hipMalloc((void**)&h->d_segs, h->segs.size() * sizeof(Segment));
-      if (e == hipSuccess)
-        e = hipMemcpy(h->d_segs, h->segs.data(), h->segs.size() * sizeof(Segment), hipMemcpyHostToDevice);
+      const size_t n = h->segs.size(), bytes = n * sizeof(Segment);
+      std::vector<char> image(bytes + 3 * n * sizeof(uint32_t));
+      memcpy(image.data(), h->segs.data(), bytes);
+      for (int g = 0; g < 3; ++g)
+        for (size_t k = 0; k < n; ++k)
+          memcpy(image.data() + bytes + (g * n + k) * sizeof(uint32_t), &h->segs[k].work0[g], sizeof(uint32_t));
+      e = hipMalloc((void**)&h->d_segs, image.size());
+      if (e == hipSuccess) e = hipMemcpy(h->d_segs, image.data(), image.size(), hipMemcpyHostToDevice);
+      h->d_seg_work = reinterpret_cast<uint32_t*>(h->d_segs + n);
     }
     if (e == hipSuccess && (cfg->n_rows > (uint32_t)kInlineRows || cfg->n_cols > (uint32_t)kInlineRows))
       e = hipMalloc((void**)&h->d_tables, 2 * DADAM_BINDINGS_KEPT * sizeof(BoundTables));
@@ -786,26 +838,7 @@ int dadam_set_topology(dadam_handle* h, uint32_t slot_id, const int32_t* row_ptr
   if (h->cfg.device != DADAM_DEVICE_NONE) {
     DeviceGuard guard(h->cfg.device);
     hipError_t e = guard.err;
-    if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_row_ptr, (R + 1) * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_col, (size_t)nnz * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_w, (size_t)nnz * sizeof(float));
-    if (e == hipSuccess) e = hipMemcpy(fresh.d_row_ptr, row_ptr, (R + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(fresh.d_col, col_idx, (size_t)nnz * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(fresh.d_w, w, (size_t)nnz * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !fresh.order.empty()) {
-      e = hipMalloc((void**)&fresh.d_order, R * sizeof(int32_t));
-      if (e == hipSuccess) e = hipMemcpy(fresh.d_order, fresh.order.data(), R * sizeof(int32_t), hipMemcpyHostToDevice);
-    }
-    auto upload = [&e](auto** to, const auto& from) {
-      if (e == hipSuccess) e = hipMalloc((void**)to, from.size() * sizeof(from[0]));
-      if (e == hipSuccess) e = hipMemcpy(*to, from.data(), from.size() * sizeof(from[0]), hipMemcpyHostToDevice);
-    };
-    if (!fresh.loops.empty()) {
-      upload(&fresh.d_loops, fresh.loops);
-      upload(&fresh.d_loop_col, loop_col);
-      upload(&fresh.d_loop_w, loop_w);
-      upload(&fresh.d_loop_rows, loop_rows);
-    }
+    if (e == hipSuccess) e = upload_lists(h, fresh, loop_col, loop_w, loop_rows);
     if (e != hipSuccess) {
       free_slot(fresh);
       return fail(h, DADAM_EHIP, "uploading the neighbour list failed: %s", hipGetErrorString(e));
@@ -966,13 +999,10 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   if (rc) return rc;
   if (h->segs.empty()) return DADAM_OK;
   StepArgs a;
-  fill_args(h, nullptr, grads, &a);
+  fill_args(h, grads, &a);
   uint32_t w0 = 0, w1 = 0;
   work_range(h, kGridDirect, 0, (uint32_t)h->segs.size() - 1, h->segs.front().lo, h->segs.back().hi, &w0, &w1);
-  a.grid = kGridDirect;
-  a.work_begin = w0;
-  a.clip_lo = h->segs.front().lo;
-  a.clip_hi = h->segs.back().hi;
+  set_range(h, kGridDirect, w0, h->segs.front().lo, h->segs.back().hi, &a);
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));

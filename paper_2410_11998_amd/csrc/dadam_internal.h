@@ -57,8 +57,8 @@ static_assert(kConsensusPartials * sizeof(double) == DADAM_STATIC_SCRATCH_BYTES,
 
 // Rows that list the same sources with the same weights.
 struct Loop {
-  int32_t first_entry, n_entries;  // in StepArgs::loop_col / loop_w
-  int32_t first_row, n_rows;       // in StepArgs::loop_rows
+  int32_t first_entry, n_entries;  // in StepArgs::col / w
+  int32_t first_row, n_rows;       // in StepArgs::row_order
 };
 constexpr int kMaxLoopWaves = 16;  // wavefronts of a loop kernel's workgroup
 
@@ -85,24 +85,28 @@ struct StepArgs {
   float* acc[kInlineRows];
   const void* grad[kMaxRows];
   const BoundTables* ext;
-  const int32_t* row_ptr;  // device CSR of the slot
+  // The slot's neighbour lists (device).  Tile kernel: CSR.  Direct kernel: the lists by position, list_stride
+  // entries apart, row_len their lengths and row_order the rows: where rows share sources, positions follow an order
+  // in which neighbours share them, so that the rows which read a source run on the die whose L2 already holds it.
+  // Loop kernel: the loops' entries, row_order their rows.
+  const int32_t* row_ptr;
+  const int32_t* row_len;
   const int32_t* col;
   const float* w;
-  // Direct kernels: the rows in an order in which neighbours share sources (device; null: rows as numbered),
-  // so that the rows which read a source run on the die whose L2 already holds it.
   const int32_t* row_order;
-  // Loop kernel (n_loops > 0, see launch_tile): the slot's loops
-  const Loop* loops;  // device
-  const int32_t* loop_col;
-  const float* loop_w;
-  const int32_t* loop_rows;
-  uint32_t n_loops;
+  const Loop* loops;
+  uint32_t list_stride;
+  uint32_t n_loops;      // > 0: the loop kernel's launch (see launch_tile)
   uint32_t order;        // Order: how a launch of the row kernel walks pieces and rows
   uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
   uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
   uint32_t reserve_lds;  // direct kernels: LDS a workgroup reserves (see bounded_occupancy_lds)
-  const Segment* seg;  // device
+  const Segment* seg;        // device
+  const uint32_t* seg_work;  // device: per Grid, the first work item of every segment
+  uint32_t wide_search;      // small launch: all lanes search the segments (see locate)
+  uint64_t first_tile;       // one segment: its first tile of this launch's grid ...
+  float weight_decay;        // ... and its decay
   uint32_t n_seg;
   uint32_t n_rows, n_cols;
   uint32_t grid;        // Grid: which tile numbering work items refer to
@@ -119,6 +123,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see step_impl
 constexpr uint32_t kManyTiles = 1024;    // measured, see step_impl
+constexpr uint32_t kWideSearchTiles = 8192;  // tiles up to which a launch is a few rounds of workgroups
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
 

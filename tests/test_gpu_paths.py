@@ -112,3 +112,16 @@ def test_rows_of_a_loop_share_one_neighbour_sum(case):
                          flags=B.DADAM_FUSE_ACCUM, inplace=inplace, refresh_extra_sources=R != C, weight_decay=wd,
                          pad_fill=None if inplace or C != R else 777.0, free_running=C == R)
     print("worst error / tolerance:", worst, flush=True)
+
+
+@pytest.mark.parametrize("segments,rows,mode", [(2, 2, "tile"), (64, 2, "direct"), (65, 9, "auto"), (200, 4, "tile"), (4097, 2, "direct"),
+                                                (4097, 64, "tile")])
+def test_every_work_item_finds_its_segment(segments, rows, mode):
+    """Layouts of many segments (contiguous tensors of a few elements whose weight decay alternates): the search by
+    all lanes, 64 segments to a step, in small launches, and the binary search of large ones (64 rows)."""
+    print("case", segments, rows, mode, flush=True)
+    flag = {"tile": B.DADAM_FORCE_TILE, "direct": B.DADAM_FORCE_DIRECT, "auto": 0}[mode]
+    layout = WL.pack([(f"t{k}", (1 + (7 * k) % 23,)) for k in range(segments)], align_elems=1)
+    worst = H.run_parity(f"segments-{segments}-{rows}-{mode}", rows, rows, layout, H.HyperF32(s=2), [WL.ring(rows)], lambda t: 0, 2, seed=63,
+                         flags=B.DADAM_FUSE_ACCUM | flag, weight_decay=[0.1 * (k % 2) for k in range(segments)], pad_fill=None)
+    print("worst error / tolerance:", worst, flush=True)
