@@ -73,6 +73,9 @@ struct dadam_handle {
   Segment* d_segs = nullptr;     // the segments, and behind them
   uint32_t* d_seg_work = nullptr;  // their first work items, per Grid (what the kernels search)
   double* d_partials = nullptr;  // kConsensusPartials doubles of scratch for the consensus error
+  // Cleared when the handle is made and by every pass after use; false after a pass that could not be enqueued whole,
+  // and the next one clears them itself.
+  bool partials_clear = true;
   // Handles with more than kInlineRows rows or sources: device copies of the bound pointer tables, two per
   // binding (as bound, and with x_src / x_dst exchanged), DADAM_BINDINGS_KEPT bindings in a ring.
   BoundTables* d_tables = nullptr;
@@ -464,10 +467,12 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (!partials) partials = h->d_partials;
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  if (consensus_out) {
+  const bool own_partials = partials == h->d_partials;
+  if (consensus_out && !(own_partials && h->partials_clear)) {
     int e0 = launch_consensus_zero(partials, stream);
     if (e0 != (int)hipSuccess) return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e0));
   }
+  if (consensus_out && own_partials) h->partials_clear = false;
   if (empty) {
     if (consensus_out) (void)launch_consensus_sum(partials, consensus_out, stream);
     return DADAM_OK;
@@ -527,6 +532,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
                               // where rows share sources the re-reads must find them in the cache
                               h->nontemporal, slot.reuse, a, w1 - w0, stream);
   if (e == (int)hipSuccess && consensus_out) e = launch_consensus_sum(partials, consensus_out, stream);
+  if (e == (int)hipSuccess && consensus_out && own_partials) h->partials_clear = true;
   if (e != (int)hipSuccess)
     return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e));
   return DADAM_OK;
@@ -774,6 +780,10 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     if (e == hipSuccess && (cfg->n_rows > (uint32_t)kInlineRows || cfg->n_cols > (uint32_t)kInlineRows))
       e = hipMalloc((void**)&h->d_tables, 2 * DADAM_BINDINGS_KEPT * sizeof(BoundTables));
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_partials, kConsensusPartials * sizeof(double));
+    if (e == hipSuccess) {
+      const std::vector<double> zeros(kConsensusPartials, 0.0);
+      e = hipMemcpy(h->d_partials, zeros.data(), kConsensusPartials * sizeof(double), hipMemcpyHostToDevice);
+    }
     // the array in the device image: its address on THIS device (the guard has made it current)
     if (e == hipSuccess) e = (hipError_t)static_partials(&h->d_static_partials, &h->static_capacity);
     if (e != hipSuccess) {

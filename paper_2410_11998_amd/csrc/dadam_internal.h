@@ -147,7 +147,7 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nontemporal, bool shared, 
 int launch_accumulate(int gdt, Phase phase, bool nontemporal, const StepArgs& a, uint32_t n_work_tiles,
                       void* stream, int vec);
 
-// Consensus error: clear the partial sums / add them up in a fixed order into *out (device).
+// Consensus error: clear the partial sums / add them up in a fixed order into *out (device) and clear them.
 int launch_consensus_zero(double* partials, void* stream);
 int launch_consensus_sum(const double* partials, double* out, void* stream);
 

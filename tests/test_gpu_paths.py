@@ -125,3 +125,34 @@ def test_every_work_item_finds_its_segment(segments, rows, mode):
     worst = H.run_parity(f"segments-{segments}-{rows}-{mode}", rows, rows, layout, H.HyperF32(s=2), [WL.ring(rows)], lambda t: 0, 2, seed=63,
                          flags=B.DADAM_FUSE_ACCUM | flag, weight_decay=[0.1 * (k % 2) for k in range(segments)], pad_fill=None)
     print("worst error / tolerance:", worst, flush=True)
+
+
+def test_consensus_passes_follow_each_other_on_one_handle():
+    """A pass leaves the handle's partial sums cleared for the next: repeated passes, also right behind a recorded one
+    that has not run yet, report the same error as a fresh handle and as the entry point with the static array."""
+    n, layout = 8, WL.pack([("a", (5003,)), ("b", (77,))])
+    dev = torch.device("cuda:0")
+    outs = torch.zeros(6, dtype=torch.float64, device=dev)
+    sim = H.GpuSim(n, n, layout, H.HyperF32(s=2), [WL.ring(n)])
+    for c in range(n):
+        sim.x_src[c].copy_(H.to_device(WL.normal_np(900 + c, layout.d, 0.5), "f32", dev))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sim.mix_consensus(outs[0:1])
+    for k in (1, 2):
+        sim.mix_consensus(outs[k:k + 1])
+    B.dadam_mix_consensus_static(sim.h, 0, outs[3:4], 0, sim.stream())
+    torch.cuda.synchronize()
+    for _ in range(3):
+        graph.replay()
+    sim.mix_consensus(outs[4:5])
+    torch.cuda.synchronize()
+    mask = H.valid_mask(layout)
+    xs = [x.to(torch.float64).cpu().numpy()[mask] for x in sim.x_src]
+    mean = sum(xs) / n
+    want = sum(float(((x - mean) ** 2).sum()) for x in xs)
+    got = [float(v) for v in outs[:5]]
+    print("consensus errors", got, want, flush=True)
+    assert all(abs(v - want) <= 1e-5 * want for v in got), (got, want)   # float32 per element (2^-24 x a few), double sums
+    sim.close()
