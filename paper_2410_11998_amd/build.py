@@ -35,7 +35,8 @@ for _x in ("f32", "bf16"):
                 UNITS.append((f"dadam_kernels_part_{_name}", "dadam_kernels_part.hip",
                               [f"-DDADAM_PART_XT={TYPES[_x]}", f"-DDADAM_PART_GT={TYPES[_g]}",
                                f"-DDADAM_PART_NT={'true' if _nt else 'false'}",
-                               f"-DDADAM_PART_EXT={'true' if _ext else 'false'}", f"-DDADAM_PART_NAME={_name}"]))
+                               f"-DDADAM_PART_EXT={'true' if _ext else 'false'}", f"-DDADAM_PART_NAME={_name}",
+                               f"-DDADAM_PART_FEW={0 if _nt or _ext else 1}"]))
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -304,7 +304,8 @@ struct Needs {
 // (Fields are read one by one through the pointer: copying the struct would put it in scratch.  The cast names global
 // memory: the compiler would otherwise merge a read of a segment with the same read of the argument block into one
 // through a generic pointer.)
-__device__ __forceinline__ void locate(const StepArgs& a, uint32_t work, uint64_t& tile_index,
+template <typename A>
+__device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile_index,
                                        uint64_t& lo, uint64_t& hi, float& weight_decay) {
   if (a.n_seg == 1) {  // the launch's range lies inside the only segment
     tile_index = a.first_tile + work;
@@ -360,28 +361,28 @@ __device__ __forceinline__ P table_entry(const BoundTables* ext, TableOf which, 
   typedef typename std::remove_pointer<P>::type __attribute__((address_space(1))) * Global;
   return (P)(Global)v;
 }
-template <bool EXT>
-__device__ __forceinline__ const void* src_of(const StepArgs& a, int c) {
+template <bool EXT, typename A>
+__device__ __forceinline__ const void* src_of(const A& a, int c) {
   if constexpr (EXT) return table_entry<const void*>(a.ext, kSrc, c);
   else return a.x_src[c];
 }
-template <bool EXT>
-__device__ __forceinline__ void* dst_of(const StepArgs& a, int i) {
+template <bool EXT, typename A>
+__device__ __forceinline__ void* dst_of(const A& a, int i) {
   if constexpr (EXT) return table_entry<void*>(a.ext, kDst, i);
   else return a.x_dst[i];
 }
-template <bool EXT>
-__device__ __forceinline__ float* m_hat_of(const StepArgs& a, int i) {
+template <bool EXT, typename A>
+__device__ __forceinline__ float* m_hat_of(const A& a, int i) {
   if constexpr (EXT) return table_entry<float*>(a.ext, kMHat, i);
   else return a.m_hat[i];
 }
-template <bool EXT>
-__device__ __forceinline__ float* v_hat_of(const StepArgs& a, int i) {
+template <bool EXT, typename A>
+__device__ __forceinline__ float* v_hat_of(const A& a, int i) {
   if constexpr (EXT) return table_entry<float*>(a.ext, kVHat, i);
   else return a.v_hat[i];
 }
-template <bool EXT>
-__device__ __forceinline__ float* acc_of(const StepArgs& a, int i) {
+template <bool EXT, typename A>
+__device__ __forceinline__ float* acc_of(const A& a, int i) {
   if constexpr (EXT) return table_entry<float*>(a.ext, kAcc, i);
   else return a.acc[i];
 }
@@ -396,7 +397,8 @@ struct RowList {
 };
 
 // Entries [k0 + first, k0 + first + 64) of a row of `deg` entries, one per lane.
-__device__ __forceinline__ void load_list_chunk(const StepArgs& a, RowList& r, int first, int lane) {
+template <typename A>
+__device__ __forceinline__ void load_list_chunk(const A& a, RowList& r, int first, int lane) {
   const int left = r.deg - first;  // >= 1
   const int idx = r.k0 + first + (lane < left ? lane : 0);
   r.col_v = a.col[idx];
@@ -405,7 +407,8 @@ __device__ __forceinline__ void load_list_chunk(const StepArgs& a, RowList& r, i
 
 // First chunk of the list of the row at `position` of a direct launch.  The lists lie at a fixed distance, so that
 // nothing has to be known about the row before its list can be loaded (padding lists source 0).
-__device__ __forceinline__ RowList load_position_list(const StepArgs& a, int position, int lane) {
+template <typename A>
+__device__ __forceinline__ RowList load_position_list(const A& a, int position, int lane) {
   RowList r;
   r.k0 = position * (int)a.list_stride;
   const int idx = r.k0 + (lane < (int)a.list_stride ? lane : 0);
@@ -425,8 +428,8 @@ struct RowPtrs {
   int32_t lo[pairs], hi[pairs];
 };
 
-template <bool EXT>
-__device__ __forceinline__ RowPtrs<EXT> load_row_ptrs(const StepArgs& a, int lane) {
+template <bool EXT, typename A>
+__device__ __forceinline__ RowPtrs<EXT> load_row_ptrs(const A& a, int lane) {
   RowPtrs<EXT> p;
 #pragma unroll
   for (int j = 0; j < RowPtrs<EXT>::pairs; ++j) {
@@ -438,8 +441,8 @@ __device__ __forceinline__ RowPtrs<EXT> load_row_ptrs(const StepArgs& a, int lan
 }
 
 // First chunk of row `row`'s list (row is wave-uniform).
-template <bool EXT>
-__device__ __forceinline__ RowList load_row_list(const StepArgs& a, const RowPtrs<EXT>& p, int row, int lane) {
+template <bool EXT, typename A>
+__device__ __forceinline__ RowList load_row_list(const A& a, const RowPtrs<EXT>& p, int row, int lane) {
   int k0 = 0, k1 = 0;
   if constexpr (!EXT) {
     k0 = __builtin_amdgcn_readlane(p.lo[0], row);
@@ -471,8 +474,8 @@ __device__ __forceinline__ float list_w(const RowList& r, int k) {
 // tile mode
 // ---------------------------------------------------------------------------------------------
 // The stream inputs of one row of a tile: gradient, moments, accumulator (whatever the phase needs).
-template <typename GT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT>
-__device__ __forceinline__ void load_row_inputs(const StepArgs& a, int i, const uint64_t (&e)[UT], uint64_t lo,
+template <typename GT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void load_row_inputs(const A& a, int i, const uint64_t (&e)[UT], uint64_t lo,
                                                 uint64_t hi, float (&g)[UT][VEC], float (&mh)[UT][VEC],
                                                 float (&vh)[UT][VEC], float (&b)[UT][VEC]) {
   if constexpr (Needs<PHASE>::grad) {
@@ -496,8 +499,8 @@ __device__ __forceinline__ void load_row_inputs(const StepArgs& a, int i, const 
 }
 
 // Mixing from LDS, the update of Algorithm 3 and the stores of one row of a tile.
-template <typename XT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT>
-__device__ __forceinline__ void finish_row(const StepArgs& a, const u4* lds, int i, RowList rl,
+template <typename XT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, RowList rl,
                                            const uint64_t (&e)[UT], uint64_t lo, uint64_t hi, float wd, int lane,
                                            float (&g)[UT][VEC], float (&mh)[UT][VEC], float (&vh)[UT][VEC],
                                            float (&b)[UT][VEC]) {
@@ -564,8 +567,8 @@ __device__ __forceinline__ void finish_row(const StepArgs& a, const u4* lds, int
   }
 }
 
-template <typename XT, typename GT, int PHASE, int W, int UT, bool MASKED, bool NT, bool EXT>
-__device__ __forceinline__ void tile_body(const StepArgs& a, u4* lds, uint64_t tbase, uint64_t lo,
+template <typename XT, typename GT, int PHASE, int W, int UT, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t tbase, uint64_t lo,
                                           uint64_t hi, float wd, uint32_t tile_id, int lane, int wave) {
   constexpr int VEC = XT::vec;
   uint64_t e[UT];
@@ -669,8 +672,8 @@ __device__ __forceinline__ void tile_body(const StepArgs& a, u4* lds, uint64_t t
   }
 }
 
-template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT>
-__global__ __launch_bounds__(kWave* W) void k_tile(const StepArgs a) {
+template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void tile_entry(const A& a) {
   constexpr int VEC = XT::vec;
   constexpr uint64_t TILE = (uint64_t)kWave * VEC * UT;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
@@ -712,8 +715,8 @@ struct PieceAt {
   float wd;
   bool any, full;  // some / all elements of the piece lie in [lo, hi)
 };
-template <int VEC>
-__device__ __forceinline__ PieceAt locate_piece(const StepArgs& a, uint32_t tile) {
+template <int VEC, typename A>
+__device__ __forceinline__ PieceAt locate_piece(const A& a, uint32_t tile) {
   constexpr uint64_t PIECE = (uint64_t)kWave * VEC;
   PieceAt p;
   uint64_t tile_index;
@@ -733,8 +736,8 @@ struct OwnSource {
   bool found = false;
   float x[VEC];
 };
-template <typename XT, int N, bool FIRST, bool MASKED, bool NT, bool EXT>  // NT: hint on the source loads
-__device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl, int k, uint64_t e, uint64_t lo,
+template <typename XT, int N, bool FIRST, bool MASKED, bool NT, bool EXT, typename A>  // NT: hint on the source loads
+__device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, uint64_t e, uint64_t lo,
                                             uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
   constexpr int VEC = XT::vec;
   u4 r[N];
@@ -760,8 +763,8 @@ __device__ __forceinline__ void mix_entries(const StepArgs& a, const RowList& rl
 }
 
 // Neighbour sum of one row, in the order the row lists its entries.
-template <typename XT, bool MASKED, bool NT, bool EXT>
-__device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int lane, uint64_t e, uint64_t lo,
+template <typename XT, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, uint64_t e, uint64_t lo,
                                            uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
 #define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
   switch (rl.deg) {
@@ -801,8 +804,8 @@ __device__ __forceinline__ void mix_direct(const StepArgs& a, RowList rl, int la
 
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
-template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT>
-__device__ __forceinline__ void direct_body(const StepArgs& a, int position, int row, uint64_t tbase, uint64_t lo,
+template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT, typename A>
+__device__ __forceinline__ void direct_body(const A& a, int position, int row, uint64_t tbase, uint64_t lo,
                                             uint64_t hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
   constexpr int VEC = XT::vec, H = kHalfWave;
@@ -849,8 +852,8 @@ __device__ __forceinline__ void direct_body(const StepArgs& a, int position, int
 
 // Pieces are numbered element-major, row-minor, so that workgroups running at the same time work
 // on the same elements of different rows.
-template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
-__global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT, typename A>
+__device__ __forceinline__ void direct_entry(const A& a) {
   const int lane = threadIdx.x;
   const uint32_t n_rows = a.n_rows;
   uint32_t t, position;
@@ -899,8 +902,8 @@ __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
 // All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM where rows are
 // many; measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
-template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT>
-__device__ __forceinline__ void loop_body(const StepArgs& a, f4* lds, int loop, uint64_t tbase, uint64_t lo, uint64_t hi,
+template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT, typename A>
+__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t tbase, uint64_t lo, uint64_t hi,
                                           float wd, int lane, int wave, int waves) {
   constexpr bool NT = HINT != 0;
   constexpr int VEC = XT::vec, H = kHalfWave;
@@ -1000,8 +1003,8 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
   }
 }
 
-template <typename GT, int VEC, int PHASE, bool MASKED, bool NT, bool EXT>
-__device__ __forceinline__ void acc_body(const StepArgs& a, int row, uint64_t tbase, uint64_t lo,
+template <typename GT, int VEC, int PHASE, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void acc_body(const A& a, int row, uint64_t tbase, uint64_t lo,
                                          uint64_t hi) {
   constexpr int H = kHalfWave;
   const uint64_t e = tbase + 4u * threadIdx.x;
@@ -1023,8 +1026,8 @@ __device__ __forceinline__ void acc_body(const StepArgs& a, int row, uint64_t tb
 
 // VEC is the element count of a parameter vector of this handle, so that the accumulate kernel walks the
 // same grid as the direct kernel.
-template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
-__global__ __launch_bounds__(kWave) void k_acc(const StepArgs a) {
+template <typename GT, int VEC, int PHASE, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void acc_entry(const A& a) {
   const uint32_t n_rows = a.n_rows;
   const uint32_t t = blockIdx.x / n_rows;
   const int row = (int)(blockIdx.x - t * n_rows);
@@ -1036,19 +1039,81 @@ __global__ __launch_bounds__(kWave) void k_acc(const StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// the kernels
+// ---------------------------------------------------------------------------------------------
+template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT>
+__global__ __launch_bounds__(kWave* W) void k_tile(const StepArgs a) {
+  tile_entry<XT, GT, PHASE, W, UT, NT, EXT>(a);
+}
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
+  direct_entry<XT, GT, PHASE, HINT, EXT>(a);
+}
+template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
+__global__ __launch_bounds__(kWave) void k_acc(const StepArgs a) {
+  acc_entry<GT, VEC, PHASE, NT, EXT>(a);
+}
+// The same on the short argument block (small handles: no streaming hints, tables in the block).
+template <typename XT, typename GT, int PHASE, int W, int UT>
+__global__ __launch_bounds__(kWave* W) void k_tile_few(const StepArgsFew a) {
+  tile_entry<XT, GT, PHASE, W, UT, false, false>(a);
+}
+template <typename XT, typename GT, int PHASE>
+__global__ __launch_bounds__(kWave) void k_direct_few(const StepArgsFew a) {
+  direct_entry<XT, GT, PHASE, 0, false>(a);
+}
+template <typename GT, int VEC, int PHASE>
+__global__ __launch_bounds__(kWave) void k_acc_few(const StepArgsFew a) {
+  acc_entry<GT, VEC, PHASE, false, false>(a);
+}
+
+// ---------------------------------------------------------------------------------------------
 // dispatch tables
 // ---------------------------------------------------------------------------------------------
 
 template <typename XT, typename GT, int W, int UT, bool NT, bool EXT>
 KernelFn tile_kernel_for_phase(int phase) {
   switch (phase) {
-    case kMixOnly: return k_tile<XT, GT, kMixOnly, W, UT, NT, EXT>;
-    case kMixConsensus: return k_tile<XT, GT, kMixConsensus, W, UT, NT, EXT>;
-    case kUpdateOnly: return k_tile<XT, GT, kUpdateOnly, W, UT, NT, EXT>;
-    case kPlain: return k_tile<XT, GT, kPlain, W, UT, NT, EXT>;
-    case kLoopStart: return k_tile<XT, GT, kLoopStart, W, UT, NT, EXT>;
-    case kFold: return k_tile<XT, GT, kFold, W, UT, NT, EXT>;
-    case kAlg1: return k_tile<XT, GT, kAlg1, W, UT, NT, EXT>;
+    case kMixOnly: return (KernelFn)k_tile<XT, GT, kMixOnly, W, UT, NT, EXT>;
+    case kMixConsensus: return (KernelFn)k_tile<XT, GT, kMixConsensus, W, UT, NT, EXT>;
+    case kUpdateOnly: return (KernelFn)k_tile<XT, GT, kUpdateOnly, W, UT, NT, EXT>;
+    case kPlain: return (KernelFn)k_tile<XT, GT, kPlain, W, UT, NT, EXT>;
+    case kLoopStart: return (KernelFn)k_tile<XT, GT, kLoopStart, W, UT, NT, EXT>;
+    case kFold: return (KernelFn)k_tile<XT, GT, kFold, W, UT, NT, EXT>;
+    case kAlg1: return (KernelFn)k_tile<XT, GT, kAlg1, W, UT, NT, EXT>;
+  }
+  return nullptr;
+}
+
+template <typename XT, typename GT, int W, int UT>
+KernelFn few_tile_kernel_for_phase(int phase) {
+  switch (phase) {
+    case kMixOnly: return (KernelFn)k_tile_few<XT, GT, kMixOnly, W, UT>;
+    case kMixConsensus: return (KernelFn)k_tile_few<XT, GT, kMixConsensus, W, UT>;
+    case kUpdateOnly: return (KernelFn)k_tile_few<XT, GT, kUpdateOnly, W, UT>;
+    case kPlain: return (KernelFn)k_tile_few<XT, GT, kPlain, W, UT>;
+    case kLoopStart: return (KernelFn)k_tile_few<XT, GT, kLoopStart, W, UT>;
+    case kFold: return (KernelFn)k_tile_few<XT, GT, kFold, W, UT>;
+    case kAlg1: return (KernelFn)k_tile_few<XT, GT, kAlg1, W, UT>;
+  }
+  return nullptr;
+}
+template <typename XT, typename GT>
+KernelFn few_tile_kernel(int phase, TileShape s) {
+  if (s.waves == 4 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 4, 1>(phase);
+  if (s.waves == 4 && s.ut == 2) return few_tile_kernel_for_phase<XT, GT, 4, 2>(phase);
+  if (s.waves == 8 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 8, 1>(phase);
+  return nullptr;  // no handle of few rows has another shape
+}
+template <typename XT, typename GT>
+KernelFn few_direct_kernel(int phase) {
+  switch (phase) {
+    case kMixOnly: return (KernelFn)k_direct_few<XT, GT, kMixOnly>;
+    case kUpdateOnly: return (KernelFn)k_direct_few<XT, GT, kUpdateOnly>;
+    case kPlain: return (KernelFn)k_direct_few<XT, GT, kPlain>;
+    case kLoopStart: return (KernelFn)k_direct_few<XT, GT, kLoopStart>;
+    case kFold: return (KernelFn)k_direct_few<XT, GT, kFold>;
+    case kAlg1: return (KernelFn)k_direct_few<XT, GT, kAlg1>;
   }
   return nullptr;
 }
@@ -1072,24 +1137,24 @@ KernelFn tile_kernel_for_shape_nt(int phase, TileShape s) {
 template <typename XT, typename GT, int HINT, bool EXT>
 KernelFn loop_kernel_for_phase(int phase) {
   switch (phase) {
-    case kMixOnly: return k_loop<XT, GT, kMixOnly, HINT, EXT>;
-    case kUpdateOnly: return k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
-    case kPlain: return k_loop<XT, GT, kPlain, HINT, EXT>;
-    case kLoopStart: return k_loop<XT, GT, kLoopStart, HINT, EXT>;
-    case kFold: return k_loop<XT, GT, kFold, HINT, EXT>;
-    case kAlg1: return k_loop<XT, GT, kAlg1, HINT, EXT>;
+    case kMixOnly: return (KernelFn)k_loop<XT, GT, kMixOnly, HINT, EXT>;
+    case kUpdateOnly: return (KernelFn)k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return (KernelFn)k_loop<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return (KernelFn)k_loop<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return (KernelFn)k_loop<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return (KernelFn)k_loop<XT, GT, kAlg1, HINT, EXT>;
   }
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>
 KernelFn direct_kernel_for_phase(int phase) {
   switch (phase) {
-    case kMixOnly: return k_direct<XT, GT, kMixOnly, HINT, EXT>;
-    case kUpdateOnly: return k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
-    case kPlain: return k_direct<XT, GT, kPlain, HINT, EXT>;
-    case kLoopStart: return k_direct<XT, GT, kLoopStart, HINT, EXT>;
-    case kFold: return k_direct<XT, GT, kFold, HINT, EXT>;
-    case kAlg1: return k_direct<XT, GT, kAlg1, HINT, EXT>;
+    case kMixOnly: return (KernelFn)k_direct<XT, GT, kMixOnly, HINT, EXT>;
+    case kUpdateOnly: return (KernelFn)k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return (KernelFn)k_direct<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return (KernelFn)k_direct<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return (KernelFn)k_direct<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return (KernelFn)k_direct<XT, GT, kAlg1, HINT, EXT>;
   }
   return nullptr;
 }

@@ -77,13 +77,15 @@ struct BoundTables {
 // Kernel argument block (passed by value; 3.9 KB of the 4 KB kernarg segment).  The tables of the bound
 // buffers are used when `ext` is null (at most kInlineRows rows and sources); otherwise `ext` holds them.
 // The gradient pointers change from call to call and always travel here.
-struct StepArgs {
-  const void* x_src[kInlineRows];
-  void* x_dst[kInlineRows];
-  float* m_hat[kInlineRows];
-  float* v_hat[kInlineRows];
-  float* acc[kInlineRows];
-  const void* grad[kMaxRows];
+// N rows and sources travel in the block's tables, G gradients.
+template <int N, int G>
+struct StepArgsFor {
+  const void* x_src[N];
+  void* x_dst[N];
+  float* m_hat[N];
+  float* v_hat[N];
+  float* acc[N];
+  const void* grad[G];
   const BoundTables* ext;
   // The slot's neighbour lists (device).  Tile kernel: CSR.  Direct kernel: the lists by position, list_stride
   // entries apart, row_len their lengths and row_order the rows: where rows share sources, positions follow an order
@@ -118,6 +120,12 @@ struct StepArgs {
   Scalars s;
 };
 
+using StepArgs = StepArgsFor<kInlineRows, kMaxRows>;
+// The block of handles with few rows and sources whose launches are small: the runtime copies it to the device on every
+// launch, which for 4 KB takes 1.1 us longer than for 1 KB (of 5.5 us a call through the binding).
+constexpr int kFewRows = 16;
+using StepArgsFew = StepArgsFor<kFewRows, kFewRows>;
+
 static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 KB");
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
@@ -127,7 +135,7 @@ constexpr uint32_t kWideSearchTiles = 8192;  // tiles up to which a launch is a 
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
 
-typedef void (*KernelFn)(const StepArgs);
+typedef const void* KernelFn;  // address of a kernel taking a StepArgs, or a StepArgsFew where the name says so
 
 struct TileShape {
   int waves;  // wavefronts per workgroup (rows are dealt round-robin to them)

@@ -3,6 +3,8 @@
 // (dadam_kernels_part.hip, once per pair of element types and streaming hint) from dadam_device.h.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -35,6 +37,14 @@ DADAM_PART(bf16_bf16);
 DADAM_PART(bf16_f32_nt);
 DADAM_PART(bf16_f32);
 DADAM_PART(f32_bf16_nt);
+DADAM_PART(f32_bf16);
+#undef DADAM_PART
+#define DADAM_PART(name)                                   \
+  KernelFn tile_kernel_##name##_few(int phase, TileShape s); \
+  KernelFn direct_kernel_##name##_few(int phase)
+DADAM_PART(f32_f32);
+DADAM_PART(bf16_bf16);
+DADAM_PART(bf16_f32);
 DADAM_PART(f32_bf16);
 #undef DADAM_PART
 
@@ -78,12 +88,43 @@ __global__ __launch_bounds__(256) void k_consensus_sum(double* partials, double*
 template <typename GT, int VEC, bool NT, bool EXT>
 KernelFn acc_kernel_for_phase(int phase) {
   switch (phase) {
-    case kPlain: return k_acc<GT, VEC, kPlain, NT, EXT>;
-    case kLoopStart: return k_acc<GT, VEC, kLoopStart, NT, EXT>;
-    case kFold: return k_acc<GT, VEC, kFold, NT, EXT>;
-    case kAlg1: return k_acc<GT, VEC, kAlg1, NT, EXT>;
+    case kPlain: return (KernelFn)k_acc<GT, VEC, kPlain, NT, EXT>;
+    case kLoopStart: return (KernelFn)k_acc<GT, VEC, kLoopStart, NT, EXT>;
+    case kFold: return (KernelFn)k_acc<GT, VEC, kFold, NT, EXT>;
+    case kAlg1: return (KernelFn)k_acc<GT, VEC, kAlg1, NT, EXT>;
   }
   return nullptr;
+}
+
+template <typename GT, int VEC>
+KernelFn few_acc_kernel(int phase) {
+  switch (phase) {
+    case kPlain: return (KernelFn)k_acc_few<GT, VEC, kPlain>;
+    case kLoopStart: return (KernelFn)k_acc_few<GT, VEC, kLoopStart>;
+    case kFold: return (KernelFn)k_acc_few<GT, VEC, kFold>;
+    case kAlg1: return (KernelFn)k_acc_few<GT, VEC, kAlg1>;
+  }
+  return nullptr;
+}
+
+// Does this launch go out on the short argument block?
+bool few(const StepArgs& a, bool nt) {
+  return !nt && a.ext == nullptr && a.n_loops == 0 && a.n_rows <= (uint32_t)kFewRows && a.n_cols <= (uint32_t)kFewRows;
+}
+
+// The short block of a launch: the used part of every table, and everything behind the tables.
+StepArgsFew shortened(const StepArgs& a) {
+  StepArgsFew f;
+  memcpy(f.x_src, a.x_src, sizeof(f.x_src));
+  memcpy(f.x_dst, a.x_dst, sizeof(f.x_dst));
+  memcpy(f.m_hat, a.m_hat, sizeof(f.m_hat));
+  memcpy(f.v_hat, a.v_hat, sizeof(f.v_hat));
+  memcpy(f.acc, a.acc, sizeof(f.acc));
+  memcpy(f.grad, a.grad, sizeof(f.grad));
+  static_assert(sizeof(StepArgs) - offsetof(StepArgs, ext) == sizeof(StepArgsFew) - offsetof(StepArgsFew, ext),
+                "the two blocks are alike behind the tables");
+  memcpy((void*)&f.ext, (const void*)&a.ext, sizeof(f) - offsetof(StepArgsFew, ext));
+  return f;
 }
 
 // A kernel may use more than 64 KB of dynamic LDS only after its limit has been raised; that is done
@@ -95,27 +136,32 @@ int raise_lds_limit(KernelFn fn, uint32_t lds) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return (int)e;
   std::lock_guard<std::mutex> lock(mu);
-  uint32_t& have = raised[{dev, reinterpret_cast<const void*>(fn)}];
+  uint32_t& have = raised[{dev, fn}];
   if (have >= lds) return (int)hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e == hipSuccess) have = lds;
   return (int)e;
 }
 
-int launch(KernelFn fn, uint32_t grid, uint32_t block, uint32_t lds, const StepArgs& a, void* stream) {
+int launch(KernelFn fn, bool short_block, uint32_t grid, uint32_t block, uint32_t lds, const StepArgs& a, void* stream) {
   if (fn == nullptr) return (int)hipErrorInvalidDeviceFunction;
   if (grid == 0) return (int)hipSuccess;
   if (lds > 65536u) {
     const int e = raise_lds_limit(fn, lds);
     if (e != (int)hipSuccess) return e;
   }
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, reinterpret_cast<hipStream_t>(stream), a);
-  return (int)hipGetLastError();
+  if (short_block) {
+    StepArgsFew f = shortened(a);
+    void* args[] = {&f};
+    return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
+  }
+  void* args[] = {const_cast<StepArgs*>(&a)};
+  return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
 }
 
 // Launch of a kernel whose workgroups are one-wavefront pieces of work items, for every row.  A grid holds less
 // than 2^32 threads (17 billion float32 elements), so what is larger goes out in several launches.
-int launch_pieces(KernelFn fn, StepArgs a, uint32_t n_items, void* stream) {
+int launch_pieces(KernelFn fn, bool short_block, StepArgs a, uint32_t n_items, void* stream) {
   // with a sharing order every die gets the same number of workgroups (see k_direct)
   const uint32_t X = a.n_xcd;
   const uint64_t per_piece = a.order == kOrderDieGroups ? X * a.order_group : a.n_rows;
@@ -125,7 +171,7 @@ int launch_pieces(KernelFn fn, StepArgs a, uint32_t n_items, void* stream) {
     const uint32_t now = n_items < most ? n_items : most;
     a.n_pieces = now * kDirectItem;
     const uint32_t pieces = a.order == kOrderDieBlocks ? (a.n_pieces + X - 1) / X * X : a.n_pieces;
-    e = launch(fn, (uint32_t)(pieces * per_piece), kWave, a.reserve_lds, a, stream);
+    e = launch(fn, short_block, (uint32_t)(pieces * per_piece), kWave, a.reserve_lds, a, stream);
     a.work_begin += now;
     n_items -= now;
   }
@@ -194,7 +240,7 @@ static int launch_loops(int xdt, int gdt, Phase phase, TileShape shape, StepArgs
   int e = (int)hipSuccess;
   while (n_tiles > 0 && e == (int)hipSuccess) {
     const uint32_t now = n_tiles < most ? n_tiles : most;
-    e = launch(fn, now * a.n_loops, threads, lds_bytes, a, stream);
+    e = launch(fn, false, now * a.n_loops, threads, lds_bytes, a, stream);
     a.work_begin += now;
     n_tiles -= now;
   }
@@ -208,43 +254,46 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
   // compiled for that (kernels of their own, so that the small handles' register budget is not theirs).
   KernelFn fn = nullptr;
   const bool nt = shape.nontemporal, ext = a.ext != nullptr;
-#define DADAM_PICK(name) (ext ? (nt ? tile_kernel_##name##_nt_ext(phase, shape) : tile_kernel_##name##_ext(phase, shape)) \
+  const bool short_block = few(a, nt);
+#define DADAM_PICK(name) (short_block ? tile_kernel_##name##_few(phase, shape) : ext ? (nt ? tile_kernel_##name##_nt_ext(phase, shape) : tile_kernel_##name##_ext(phase, shape)) \
                               : (nt ? tile_kernel_##name##_nt(phase, shape) : tile_kernel_##name(phase, shape)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
-  return launch(fn, n_work, (uint32_t)(kWave * shape.waves), lds_bytes, a, stream);
+  return launch(fn, short_block, n_work, (uint32_t)(kWave * shape.waves), lds_bytes, a, stream);
 }
 
 int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const StepArgs& a, uint32_t n_work_tiles,
                   void* stream) {
   KernelFn fn = nullptr;
   const bool ext = a.ext != nullptr;
-#define DADAM_PICK(name) (ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared) : direct_kernel_##name##_ext(phase, shared)) \
+  const bool short_block = few(a, nt);
+#define DADAM_PICK(name) (short_block ? direct_kernel_##name##_few(phase) : ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared) : direct_kernel_##name##_ext(phase, shared)) \
                               : (nt ? direct_kernel_##name##_nt(phase, shared) : direct_kernel_##name(phase, shared)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
-  return launch_pieces(fn, a, n_work_tiles, stream);
+  return launch_pieces(fn, short_block, a, n_work_tiles, stream);
 }
 
 int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t n_work_tiles, void* stream,
                       int vec) {
   KernelFn fn = nullptr;
   const bool ext = a.ext != nullptr;
+  const bool short_block = few(a, nt);
 #define DADAM_PICK(GT, VEC)                                                                                      \
-  (ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase) : acc_kernel_for_phase<GT, VEC, false, true>(phase)) \
+  (short_block ? few_acc_kernel<GT, VEC>(phase) : ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase) : acc_kernel_for_phase<GT, VEC, false, true>(phase)) \
        : (nt ? acc_kernel_for_phase<GT, VEC, true, false>(phase) : acc_kernel_for_phase<GT, VEC, false, false>(phase)))
   if (gdt == DADAM_F32 && vec == 4) fn = DADAM_PICK(TF32, 4);
   if (gdt == DADAM_F32 && vec == 8) fn = DADAM_PICK(TF32, 8);
   if (gdt == DADAM_BF16 && vec == 4) fn = DADAM_PICK(TBF16, 4);
   if (gdt == DADAM_BF16 && vec == 8) fn = DADAM_PICK(TBF16, 8);
 #undef DADAM_PICK
-  return launch_pieces(fn, a, n_work_tiles, stream);
+  return launch_pieces(fn, short_block, a, n_work_tiles, stream);
 }
 
 }  // namespace dadam

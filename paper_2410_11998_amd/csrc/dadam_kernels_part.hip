@@ -2,7 +2,7 @@
 // without the streaming hint, chosen by the build (paper_2410_11998_amd/build.py compiles this file once
 // per part, in parallel; together the parts hold every instantiation the launchers can ask for).
 //   -DDADAM_PART_XT=TF32|TBF16 -DDADAM_PART_GT=TF32|TBF16 -DDADAM_PART_NT=true|false -DDADAM_PART_EXT=true|false
-//   -DDADAM_PART_NAME=<suffix>
+//   -DDADAM_PART_NAME=<suffix> [-DDADAM_PART_FEW=1: also the kernels on the short argument block]
 #include "dadam_device.h"
 
 #if !defined(DADAM_PART_XT) || !defined(DADAM_PART_GT) || !defined(DADAM_PART_NT) || !defined(DADAM_PART_EXT) || \
@@ -24,6 +24,15 @@ KernelFn DADAM_JOIN(direct_kernel_, DADAM_PART_NAME)(int phase, bool shared) {
   return shared ? direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase)
                 : direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
 }
+
+#if DADAM_PART_FEW
+KernelFn DADAM_JOIN(DADAM_JOIN(tile_kernel_, DADAM_PART_NAME), _few)(int phase, TileShape s) {
+  return few_tile_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase, s);
+}
+KernelFn DADAM_JOIN(DADAM_JOIN(direct_kernel_, DADAM_PART_NAME), _few)(int phase) {
+  return few_direct_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase);
+}
+#endif
 
 KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase) {
   return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
