@@ -313,7 +313,7 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
     hi = a.clip_hi;
     weight_decay = a.weight_decay;
   } else {
-    typedef const Segment __attribute__((address_space(1))) * GlobalSegments;
+    typedef const Segment __attribute__((address_space(4))) * GlobalSegments;  // constant memory: scalar loads
     const GlobalSegments seg = (GlobalSegments)a.seg;
     const uint32_t grid = a.grid;
     uint32_t s = 0, n = a.n_seg;  // the segment is one of [s, s + n)
@@ -736,67 +736,76 @@ struct OwnSource {
   bool found = false;
   float x[VEC];
 };
-template <typename XT, int N, bool FIRST, bool MASKED, bool NT, bool EXT, typename A>  // NT: hint on the source loads
-__device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, uint64_t e, uint64_t lo,
-                                            uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
+template <typename XT, int N, bool FIRST, int U, bool MASKED, bool NT, bool EXT, typename A>  // NT: hint on the source loads
+__device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, const uint64_t (&e)[U], uint64_t lo,
+                                            uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
   constexpr int VEC = XT::vec;
-  u4 r[N];
+  u4 r[N][U];
   float wk[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     const void* src = src_of<EXT>(a, list_col(rl, k + q));
     wk[q] = list_w(rl, k + q);
-    r[q] = load_raw<XT, kHalfWave, MASKED, NT>(src, e, lo, hi);
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[q][u] = load_raw<XT, kHalfWave, MASKED, NT>(src, e[u], lo, hi);
   }
 #pragma unroll
-  for (int q = 0; q < N; ++q) {
-    float xs[VEC];
-    unpack_raw<XT>(r[q], xs);
-    if (list_col(rl, k + q) == own.col) {
-      own.found = true;
+  for (int q = 0; q < N; ++q)
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) own.x[j] = xs[j];
+    for (int u = 0; u < U; ++u) {
+      float xs[VEC];
+      unpack_raw<XT>(r[q][u], xs);
+      if constexpr (U == 1)
+        if (list_col(rl, k + q) == own.col) {
+          own.found = true;
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) own.x[j] = xs[j];
+        }
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) mix[u][j] = (FIRST && q == 0) ? wk[0] * xs[j] : fmaf(wk[q], xs[j], mix[u][j]);
     }
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) mix[j] = (FIRST && q == 0) ? wk[0] * xs[j] : fmaf(wk[q], xs[j], mix[j]);
-  }
 }
 
-// Neighbour sum of one row, in the order the row lists its entries.
-template <typename XT, bool MASKED, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, uint64_t e, uint64_t lo,
-                                           uint64_t hi, float (&mix)[XT::vec], OwnSource<XT::vec>& own) {
-#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
-  switch (rl.deg) {
-    case 1: DADAM_MIX(1, true, 0); break;
-    case 2: DADAM_MIX(2, true, 0); break;
-    case 3: DADAM_MIX(3, true, 0); break;
-    case 4: DADAM_MIX(4, true, 0); break;
-    case 5: DADAM_MIX(5, true, 0); break;
-    case 6: DADAM_MIX(6, true, 0); break;
-    case 7: DADAM_MIX(7, true, 0); break;
-    default: {
-      DADAM_MIX(8, true, 0);
-      int k = 8, first = 0;
-      for (; k + 4 <= rl.deg; k += 4) {
-        if constexpr (EXT) {
-          if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them (64 = 8 + 14 x 4)
-            first = k;
-            load_list_chunk(a, rl, first, lane);
-          }
+// Neighbour sum of one row, in the order the row lists its entries, for U vectors per lane.
+template <typename XT, int U, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, const uint64_t (&e)[U], uint64_t lo,
+                                           uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
+#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, U, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
+  constexpr int FIRST_BATCH = U == 1 ? 8 : 4;
+  if (rl.deg < FIRST_BATCH) {
+    switch (rl.deg) {
+      case 1: DADAM_MIX(1, true, 0); break;
+      case 2: DADAM_MIX(2, true, 0); break;
+      case 3: DADAM_MIX(3, true, 0); break;
+      default:
+        if constexpr (FIRST_BATCH > 4) switch (rl.deg) {
+          case 4: DADAM_MIX(4, true, 0); break;
+          case 5: DADAM_MIX(5, true, 0); break;
+          case 6: DADAM_MIX(6, true, 0); break;
+          default: DADAM_MIX(7, true, 0); break;
         }
-        DADAM_MIX(4, false, k - first);
-      }
-      if (k < rl.deg) {
-        if constexpr (EXT) {
-          if (k - first == kWave) {
-            first = k;
-            load_list_chunk(a, rl, first, lane);
-          }
+    }
+  } else {
+    DADAM_MIX(FIRST_BATCH, true, 0);
+    int k = FIRST_BATCH, first = 0;
+    for (; k + 4 <= rl.deg; k += 4) {
+      if constexpr (EXT) {
+        if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them (64 is 4 or 8 and fours)
+          first = k;
+          load_list_chunk(a, rl, first, lane);
         }
-        if ((rl.deg - k) & 2) DADAM_MIX(2, false, k - first);
-        if ((rl.deg - k) & 1) DADAM_MIX(1, false, k - first + ((rl.deg - k) & 2));
       }
+      DADAM_MIX(4, false, k - first);
+    }
+    if (k < rl.deg) {
+      if constexpr (EXT) {
+        if (k - first == kWave) {
+          first = k;
+          load_list_chunk(a, rl, first, lane);
+        }
+      }
+      if ((rl.deg - k) & 2) DADAM_MIX(2, false, k - first);
+      if ((rl.deg - k) & 1) DADAM_MIX(1, false, k - first + ((rl.deg - k) & 2));
     }
   }
 #undef DADAM_MIX
@@ -824,13 +833,15 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
     load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
   if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
-  float mix[VEC];
   // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
   // sum where the row lists itself (loading them again would be a second trip to memory after the first).
   const bool decays = !Needs<PHASE>::mixing_only && wd != 0.0f;
   OwnSource<VEC> own;
   own.col = decays ? row : -1;
-  mix_direct<XT, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
+  const uint64_t es[1] = {e};
+  float mixes[1][VEC];
+  mix_direct<XT, 1, MASKED, NTSRC, EXT>(a, rl, lane, es, lo, hi, mixes, own);
+  const float(&mix)[VEC] = mixes[0];
   float decay[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
@@ -890,6 +901,42 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   }
 }
 
+// Mixing only, of rows that share sources: a wavefront has little to do for one vector (two or three loads, one store),
+// and what bounds the launch is how fast the chip starts workgroups (about 1.7 a nanosecond).  So a workgroup of four
+// wavefronts takes a whole work item, two vectors a lane.  us, two rounds, one-wavefront pieces / this: 72 rows
+// in pairs 631 / 465, 96 rows of three sources 608 / 500, 96 replicas of a one-peer graph, one round of each hop, 2030 / 1640.
+constexpr int kWideWaves = kDirectItem / 2;
+template <typename XT, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a) {
+  constexpr int VEC = XT::vec;
+  constexpr uint64_t PIECE = (uint64_t)kWave * VEC, ITEM = PIECE * kDirectItem;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t item, position;
+  const bool active = die_group_order(blockIdx.x, a.n_rows, a.n_xcd, a.order_group, item, position);
+  const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate(a, a.work_begin + item, tile_index, lo, hi, wd);
+  const uint64_t tbase = tile_index * ITEM;
+  if (active) {  // uniform over the workgroup
+    const RowList rl = load_position_list(a, (int)position, lane);
+    const uint64_t e0 = tbase + wave * PIECE + 4u * (uint32_t)lane;
+    const uint64_t e[2] = {e0, e0 + kWideWaves * PIECE};
+    OwnSource<VEC> none;
+    none.col = -1;
+    float mix[2][VEC];
+    void* to = dst_of<EXT>(a, row);
+    if (tbase >= lo && tbase + ITEM <= hi) {
+      mix_direct<XT, 2, false, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      store_vectors<XT, VEC, kHalfWave, false, HINT != 0>(to, e, lo, hi, mix);
+    } else {
+      mix_direct<XT, 2, true, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      store_vectors<XT, VEC, kHalfWave, true, HINT != 0>(to, e, lo, hi, mix);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // loops: groups of rows that list the same sources with the same weights
 // ---------------------------------------------------------------------------------------------
@@ -922,13 +969,13 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   int row = __builtin_amdgcn_readlane(row_v, 0);
   if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
   if (rl.deg > 0) {
-    float part[VEC];
+    float part[1][VEC];
     OwnSource<VEC> none;
     none.col = -1;
-    mix_direct<XT, MASKED, HINT == 1, EXT>(a, rl, lane, e[0], lo, hi, part, none);
+    mix_direct<XT, 1, MASKED, HINT == 1, EXT>(a, rl, lane, e, lo, hi, part, none);
 #pragma unroll
     for (int h = 0; h < VEC / 4; ++h) {
-      f4 v = {part[4 * h], part[4 * h + 1], part[4 * h + 2], part[4 * h + 3]};
+      f4 v = {part[0][4 * h], part[0][4 * h + 1], part[0][4 * h + 2], part[0][4 * h + 3]};
       lds[(wave * (VEC / 4) + h) * kWave + lane] = v;
     }
   }
@@ -1150,6 +1197,7 @@ template <typename XT, typename GT, int HINT, bool EXT>
 KernelFn direct_kernel_for_phase(int phase) {
   switch (phase) {
     case kMixOnly: return (KernelFn)k_direct<XT, GT, kMixOnly, HINT, EXT>;
+    case kMixRows: return (KernelFn)k_mix_rows<XT, HINT, EXT>;
     case kUpdateOnly: return (KernelFn)k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
     case kPlain: return (KernelFn)k_direct<XT, GT, kPlain, HINT, EXT>;
     case kLoopStart: return (KernelFn)k_direct<XT, GT, kLoopStart, HINT, EXT>;

@@ -495,10 +495,13 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
-  // Rows that share sources: in a small launch every row of a piece runs on one die, in a large one each die has a
-  // group of rows.  us, pieces / groups: 64 rows of two sources 244 tiles 83 / 87; 96 rows of 7 sources 81 tiles
-  // 53 / 74, 325 tiles 186 / 215, 1220 tiles 792 / 780; 32 rows of two sources in bfloat16, 18000 tiles, 5160 / 4970.
-  if (!tile_mode && ordered_rows(h, slot)) a.order = n_tiles < kManyTiles ? kOrderDieBlocks : kOrderDieGroups;
+  // Rows that share sources: in small launches and steps of many rows every row of a piece runs on one die, otherwise
+  // each die has a group of rows.  us, groups / pieces, small: 64 rows of two sources 244 tiles 87 / 83; 96
+  // rows of 7 sources 81 tiles 74 / 53, 325 tiles 215 / 186.  Large, 6e8 elements, steps: rows of two sources, 32 of
+  // them: 12550 / 12690, bfloat16 9990 / 10400; 64: 13030 / 12790, bfloat16 equal; 96: 13490 / 12790, bfloat16 9980 /
+  // 9570; ring of 96: 12110 / 11590, 96 rows of 7 sources 14980 / 14620; 64 replicas of ResNet-50 with decay 18040 / 17610.
+  if (!tile_mode && ordered_rows(h, slot))
+    a.order = n_tiles < kManyTiles || (!mix_only && h->cfg.n_rows >= 64) ? kOrderDieBlocks : kOrderDieGroups;
   set_range(h, grid, w0, lo, hi, &a);
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);

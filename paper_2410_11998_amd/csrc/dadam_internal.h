@@ -49,7 +49,8 @@ enum Phase : int {
   kFold = 4,        // lines 6-13, last iteration of a loop (s > 1)
   kAlg1 = 5,        // s == 1: Algorithm 1, moments updated every iteration, no accumulator
   kMixConsensus = 6,  // x_dst = W x_src and, on the side, sum_c ||x_src[c] - mean||^2 (tile mode only)
-  kNumPhases = 7
+  kMixRows = 7,       // kMixOnly, as the direct kernel of large launches over rows that share sources does it
+  kNumPhases = 8
 };
 
 constexpr uint32_t kConsensusPartials = 1024;  // partial sums the tiles scatter their contributions over

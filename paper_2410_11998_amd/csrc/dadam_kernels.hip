@@ -159,19 +159,20 @@ int launch(KernelFn fn, bool short_block, uint32_t grid, uint32_t block, uint32_
   return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
 }
 
-// Launch of a kernel whose workgroups are one-wavefront pieces of work items, for every row.  A grid holds less
+// Launch of a kernel whose workgroups are one-wavefront pieces of work items (wide: whole items), for every row.  A grid holds less
 // than 2^32 threads (17 billion float32 elements), so what is larger goes out in several launches.
-int launch_pieces(KernelFn fn, bool short_block, StepArgs a, uint32_t n_items, void* stream) {
+int launch_pieces(KernelFn fn, bool short_block, StepArgs a, uint32_t n_items, void* stream, bool wide = false) {
   // with a sharing order every die gets the same number of workgroups (see k_direct)
   const uint32_t X = a.n_xcd;
+  const uint32_t threads = wide ? kWave * kWideWaves : kWave, per_item = wide ? 1 : kDirectItem;  // workgroups per item and row
   const uint64_t per_piece = a.order == kOrderDieGroups ? X * a.order_group : a.n_rows;
-  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / kWave / per_piece / kDirectItem - X);
+  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / threads / per_piece / per_item - X);
   int e = (int)hipSuccess;
   while (n_items > 0 && e == (int)hipSuccess) {
     const uint32_t now = n_items < most ? n_items : most;
-    a.n_pieces = now * kDirectItem;
+    a.n_pieces = now * per_item;
     const uint32_t pieces = a.order == kOrderDieBlocks ? (a.n_pieces + X - 1) / X * X : a.n_pieces;
-    e = launch(fn, short_block, (uint32_t)(pieces * per_piece), kWave, a.reserve_lds, a, stream);
+    e = launch(fn, short_block, (uint32_t)(pieces * per_piece), threads, a.reserve_lds, a, stream);
     a.work_begin += now;
     n_items -= now;
   }
@@ -268,8 +269,9 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
 int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const StepArgs& a, uint32_t n_work_tiles,
                   void* stream) {
   KernelFn fn = nullptr;
-  const bool ext = a.ext != nullptr;
-  const bool short_block = few(a, nt);
+  const bool ext = a.ext != nullptr, wide = phase == kMixOnly && a.order == kOrderDieGroups;
+  if (wide) phase = kMixRows;
+  const bool short_block = few(a, nt) && !wide;
 #define DADAM_PICK(name) (short_block ? direct_kernel_##name##_few(phase) : ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared) : direct_kernel_##name##_ext(phase, shared)) \
                               : (nt ? direct_kernel_##name##_nt(phase, shared) : direct_kernel_##name(phase, shared)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
@@ -277,7 +279,7 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const Ste
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
-  return launch_pieces(fn, short_block, a, n_work_tiles, stream);
+  return launch_pieces(fn, short_block, a, n_work_tiles, stream, wide);
 }
 
 int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t n_work_tiles, void* stream,

@@ -156,3 +156,40 @@ def test_consensus_passes_follow_each_other_on_one_handle():
     print("consensus errors", got, want, flush=True)
     assert all(abs(v - want) <= 1e-5 * want for v in got), (got, want)   # float32 per element (2^-24 x a few), double sums
     sim.close()
+
+
+@pytest.mark.parametrize("rows,deg,dtype", [(24, 2, "f32"), (100, 3, "bf16"), (90, 8, "f32"), (96, 5, "bf16"), (20, 1, "f32")])
+def test_large_mixing_of_rows_that_share_sources(rows, deg, dtype):
+    """Mixing only, more than 1024 tiles and rows that stream directly: whole items by workgroups of four wavefronts,
+    ragged ends included, against the tile kernel where it fits and against the sums in 64 bits."""
+    print("case", rows, deg, dtype, flush=True)
+    elems = 64 * (8 if dtype == "bf16" else 4)
+    layout = WL.pack([("a", (1030 * elems + 13,)), ("b", (3 * elems - 5,)), ("c", (8 * elems,))])
+    csr = rows_of_degree(rows, deg)
+    if deg == 1:
+        csr = (csr[0], np.array([i // 2 for i in range(rows)], np.int32), csr[2])   # two rows copy one source
+    sim = H.GpuSim(rows, rows, layout, H.HyperF32(s=1), [csr], dtype, dtype)
+    assert not B.dadam_slot_uses_tile_mode(sim.h, 0)
+    for c in range(rows):
+        sim.x_src[c].copy_(H.to_device(WL.normal_np(40 + c, layout.d, 0.5), dtype, "cuda:0"))
+    for t in sim.x_dst:
+        t.fill_(7.0)
+    sim.mix(0, 0)
+    torch.cuda.synchronize()
+    mask = torch.from_numpy(H.valid_mask(layout)).to("cuda:0")
+    for i in range(rows):
+        want = torch.zeros(layout.d, dtype=torch.float64, device="cuda:0")
+        size = torch.zeros_like(want)
+        for k in range(csr[0][i], csr[0][i + 1]):
+            x = sim.x_src[int(csr[1][k])].double()
+            want += float(csr[2][k]) * x
+            size += abs(float(csr[2][k])) * x.abs()
+        err = (sim.x_dst[i].double() - want).abs()
+        assert bool((err <= (1e-6 if dtype == "f32" else 1e-2) * size)[mask].all()), i     # a float32 sum; one bfloat16 rounding
+        assert bool((sim.x_dst[i][~mask] == 7.0).all()), i
+    got = [t.clone() for t in sim.x_dst]
+    sim.mix(0, B.DADAM_FORCE_TILE)
+    torch.cuda.synchronize()
+    for i in range(rows):
+        assert torch.equal(got[i], sim.x_dst[i]), i
+    sim.close()
