@@ -324,7 +324,6 @@ bool direct_is_legal(const dadam_handle* h, const Slot& slot) {
 bool ordered_rows(const dadam_handle* h, const Slot& slot) { return !slot.order.empty() && h->n_xcds > 1; }
 
 void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t lo, uint64_t hi, StepArgs* a) {
-  a->wide_search = (hi - lo) * h->cfg.n_rows / h->tile_elems <= kWideSearchTiles ? 1u : 0u;
   a->grid = grid;
   a->work_begin = work_begin;
   a->clip_lo = lo;
@@ -529,6 +528,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.list_stride = (uint32_t)slot.max_degree;
     a.order_group = (h->cfg.n_rows + h->n_xcds - 1) / h->n_xcds;
   }
+  const uint64_t wavefronts = (uint64_t)(w1 - w0) * (tile_mode ? shape.waves * (by_loops ? slot.loops.size() : 1) : kDirectItem * (uint64_t)h->cfg.n_rows);
+  a.wide_search = wavefronts <= kWideSearchWaves ? 1u : 0u;
   int e = tile_mode
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
               : launch_direct((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase,
@@ -1016,6 +1017,7 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   uint32_t w0 = 0, w1 = 0;
   work_range(h, kGridDirect, 0, (uint32_t)h->segs.size() - 1, h->segs.front().lo, h->segs.back().hi, &w0, &w1);
   set_range(h, kGridDirect, w0, h->segs.front().lo, h->segs.back().hi, &a);
+  a.wide_search = (uint64_t)(w1 - w0) * kDirectItem * h->cfg.n_rows <= kWideSearchWaves ? 1u : 0u;
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));

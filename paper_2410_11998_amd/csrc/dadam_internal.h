@@ -132,7 +132,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see step_impl
 constexpr uint32_t kManyTiles = 1024;    // measured, see step_impl
-constexpr uint32_t kWideSearchTiles = 8192;  // tiles up to which a launch is a few rounds of workgroups
+constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
 
