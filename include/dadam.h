@@ -260,7 +260,8 @@ int dadam_slot_uses_tile_mode(const dadam_handle* h, uint32_t slot);
 
 /* The order in which direct mode takes the rows of this slot (order_out: n_rows entries, a permutation of
  * 0 .. n_rows-1).  When rows share sources (and the device has more than one die), rows that
- * share sources are neighbours in this order and each die works on one contiguous group of it, so that a
+ * share sources are neighbours in this order and run on one die at about the same time - all rows of a piece of the
+ * vector, or one contiguous group of the order per die, by size - so that a
  * source two rows read comes from memory once and from that die's L2 the second time (one-peer graph on 64
  * replicas, mixing only: 0.54-0.61 of peak with rows as numbered when the two readers sit on different dies,
  * 0.76 when they share one).  The order changes nothing in what is computed.  Returns 1 if such an order is

@@ -3,7 +3,7 @@
 //
 //
 // The work is streaming and elementwise over the packed parameter vector; neighbour mixing couples
-// replicas, never elements.  Four kernels:
+// replicas, never elements.  The kernels:
 //
 //   k_tile    one workgroup owns a tile of elements for ALL rows: every source buffer's slice of the
 //             tile is read from HBM once and parked in LDS, then the wavefronts of the group deal the
@@ -15,6 +15,7 @@
 //             memory (a node's own parameters plus receive buffers: no source is shared by two rows).
 //   k_loop    one workgroup owns a piece of one loop: rows that list the same sources with the same weights share
 //             one neighbour sum.
+//   k_mix_rows  large mixing-only launches of what k_direct does for rows that share sources.
 //   k_acc     accumulate / fold only (Algorithm 3 lines 9-13).
 //
 // Every access of a full tile is a 128-bit (float32) or 64-bit (bfloat16) load or store per lane,

@@ -362,11 +362,14 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool* t
   return DADAM_OK;
 }
 
+uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(waves * kWave * h->vec * 4); }
+
 // Wavefronts of a loop kernel's workgroup, 0: another kernel takes the launch.  Depends on the slot and on the whole
 // layout, never on the range of a launch: the order in which a loop is summed follows from it, and a step issued
 // range by range has the bits of the whole one.
 // Legal: a row updated in place overwrites sources that only its own loop may read (the loop reads them all before
-// it writes), and with weight decay a row reads its own parameters again after that.
+// it writes), and with weight decay a row reads its own parameters again after that; the partial sums fit the LDS the
+// configuration grants.
 // Faster: with 16 rows to a loop on average.  us, other kernels / 4 / 8 / 16 wavefronts, 3e8 elements, mixing:
 // 32 rows in one loop 1349 / 862 / 837 / 900, 64 rows 3163 / 881 / 871 / 865, 96 rows in loops of 48, 24, 24 8486 /
 // 1764 / 1737 / 2091, but 32 rows in loops of 16, 8, 8 1756 / 1667 / 1933 / 3531 and 16 rows in loops of 8, 4, 4
@@ -380,7 +383,8 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot) {
   for (uint32_t i = 0; i < R; ++i)
     for (int32_t c : h->inplace_cols[i])
       if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
-  return h->n_work_t * G <= 2 * kFewTiles ? 16 : 8;
+  const int waves = h->n_work_t * G <= 2 * kFewTiles ? 16 : 8;
+  return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
@@ -515,7 +519,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.row_order = slot.d_loop_rows;
     shape.ut = 1;
     shape.waves = loop_waves;
-    lds = (uint32_t)(shape.waves * kWave * h->vec * 4);
+    lds = loop_lds_bytes(h, shape.waves);
   } else if (tile_mode) {
     a.row_ptr = slot.d_row_ptr;
     a.col = slot.d_col;
