@@ -136,7 +136,8 @@ typedef struct {
  * Every buffer holds cfg.d elements and is 16-byte aligned.
  * x_dst[i] may be the very same buffer as one x_src[c] (update in place); any other overlap
  * between two different buffers is rejected with DADAM_EALIAS.  In-place update is legal when the
- * step runs in tile mode, or when source c is read by row i only. */
+ * step runs in tile mode, or when source c is read by row i only (a step over tensors with weight decay
+ * also reads source k for every row k). */
 typedef struct {
   const void* const* x_src; /* [n_cols] x^(t-1) */
   void* const* x_dst;       /* [n_rows] x^(t)   */

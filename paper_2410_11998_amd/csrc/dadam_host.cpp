@@ -310,14 +310,23 @@ Phase fused_phase(const dadam_handle* h, uint64_t t) {
 
 // A row updated in place overwrites every source buffer that shares its memory (two source
 // entries may name one buffer); the direct kernel may do that only if nobody but the row itself
-// reads any of them.
-bool direct_is_legal(const dadam_handle* h, const Slot& slot) {
+// reads any of them: neither from a list nor, where the launch decays, as the row whose own parameters they are.
+bool direct_is_legal(const dadam_handle* h, const Slot& slot, bool decays) {
   for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
     for (int32_t c : h->inplace_cols[i]) {
       const int32_t sr = slot.sole_reader[c];
       if (!(sr == -1 || sr == (int32_t)i)) return false;
+      if (decays && (uint32_t)c < h->cfg.n_rows && c != (int32_t)i) return false;
     }
   return true;
+}
+
+// Does a step over tensors [tb, te) of the layout (whole: all of them) apply weight decay?
+bool range_decays(const dadam_handle* h, bool whole, uint32_t tb, uint32_t te) {
+  if (whole || !h->decays) return h->decays;
+  for (size_t k = tb; k < te && k < h->tensors.size(); ++k)
+    if (h->tensors[k].numel && h->tensors[k].weight_decay != 0.f) return true;
+  return false;
 }
 
 // Do direct launches of this slot walk its rows in the sharing order?
@@ -332,11 +341,12 @@ void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t l
   a->weight_decay = h->segs.front().weight_decay;
 }
 
-// Decide tile or direct mode for this slot and these flags; checks in-place legality.
-int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool* tile_mode) {
+// Decide tile or direct mode for this slot and these flags; checks in-place legality.  decays: the launch applies
+// weight decay.
+int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool decays, bool* tile_mode) {
   if ((flags & DADAM_FORCE_DIRECT) && (flags & DADAM_FORCE_TILE))
     return fail(h, DADAM_EINVAL, "DADAM_FORCE_DIRECT and DADAM_FORCE_TILE are exclusive");
-  const bool direct_legal = direct_is_legal(h, slot);
+  const bool direct_legal = direct_is_legal(h, slot, decays);
   if (flags & DADAM_FORCE_TILE) {
     if (!h->tile_possible) return fail(h, DADAM_EINVAL, "tile mode needs the source tile to fit in LDS");
     *tile_mode = true;
@@ -453,7 +463,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   bool tile_mode = false;
   // the consensus error is computed from the staged tile: ask for tile mode unless the caller chose
   if (consensus_out && !(flags & DADAM_FORCE_DIRECT) && h->tile_possible && slot.reuse) flags |= DADAM_FORCE_TILE;
-  rc = choose_mode(h, slot, flags, &tile_mode);
+  const bool decays = !mix_only && range_decays(h, whole, tb, te);
+  rc = choose_mode(h, slot, flags, decays, &tile_mode);
   if (rc) return rc;
   if (consensus_out) {
     if (!tile_mode)
@@ -491,7 +502,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot);
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
-                         n_tiles <= kFewTiles && direct_is_legal(h, slot);
+                         n_tiles <= kFewTiles && direct_is_legal(h, slot, decays);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
   const Grid grid = !tile_mode ? kGridDirect : mix_only && !by_loops ? kGridMix : kGridTile;
@@ -1064,7 +1075,7 @@ int dadam_slot_uses_tile_mode(const dadam_handle* h, uint32_t slot) {
   if (!h) return DADAM_EINVAL;
   if (slot >= DADAM_MAX_SLOTS || !h->slots[slot].set) return fail(h, DADAM_ESTATE, "topology slot %u is not set", slot);
   bool tile = false;
-  int rc = choose_mode(h, h->slots[slot], 0, &tile);
+  int rc = choose_mode(h, h->slots[slot], 0, h->decays, &tile);
   if (rc) return rc;
   return tile ? 1 : 0;
 }

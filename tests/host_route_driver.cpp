@@ -1,0 +1,164 @@
+// Which kernel the host code gives a launch to, and what it assumes about device memory between calls, without a GPU:
+// dadam_host.cpp linked against a modelled HIP runtime (memory is the host's) and modelled launchers that note what they
+// were asked to do.  Launches on a stream that is "being captured" are recorded and run when the graph is replayed; a
+// launch can be made to fail.  Prints one line per question; tests/test_host_abi.py holds the answers.
+#include "dadam.h"
+#include "dadam_internal.h"
+#include <hip/hip_runtime_api.h>
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <string>
+#include <vector>
+
+// ---- modelled runtime ----
+static bool capturing = false;
+static std::vector<std::function<void()>> recorded;
+static const char* fail_launch = nullptr;  // name of the launcher whose next call fails
+static std::string route;
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeNumberOfXccs ? 8 : 160 * 1024;
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) { *p = malloc(n); memset(*p, 0xA5, n); return hipSuccess; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "modelled"; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+}
+static int enqueue(const char* name, std::function<void()> work) {
+  if (fail_launch && !strcmp(fail_launch, name)) { fail_launch = nullptr; return (int)hipErrorLaunchFailure; }
+  if (capturing) recorded.push_back(work); else work();
+  return 0;
+}
+namespace dadam {
+static double static_scratch[kConsensusPartials];
+int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint32_t, uint32_t, void*) {
+  route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
+  double* p = a.partials;
+  return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
+}
+int launch_direct(int, int, Phase, bool, bool, const StepArgs& a, uint32_t, void*) {
+  route = a.order == kOrderDieBlocks ? "direct-blocks" : a.order == kOrderDieGroups ? "direct-groups" : "direct";
+  return enqueue("direct", [] {});
+}
+int launch_accumulate(int, Phase, bool, const StepArgs&, uint32_t, void*, int) { return enqueue("accumulate", [] {}); }
+int launch_consensus_zero(double* p, void*) {
+  return enqueue("zero", [=] { for (uint32_t i = 0; i < kConsensusPartials; ++i) p[i] = 0.0; });
+}
+int launch_consensus_sum(const double* cp, double* out, void*) {
+  double* p = const_cast<double*>(cp);
+  return enqueue("sum", [=] {
+    double s = 0.0;
+    for (uint32_t i = 0; i < kConsensusPartials; ++i) { s += p[i]; p[i] = 0.0; }
+    *out = s;
+  });
+}
+int static_partials(double** out, uint32_t* capacity) { *out = static_scratch; *capacity = kConsensusPartials; return 0; }
+int vec_elems(int xdt) { return xdt == DADAM_BF16 ? 8 : 4; }
+bool tile_shape_supported(TileShape s) { return (s.waves == 4 || s.waves == 8) && (s.ut == 1 || s.ut == 2); }
+}  // namespace dadam
+
+// ---- a handle and its buffers (addresses only: nothing reads or writes through them) ----
+struct Rows { std::vector<int32_t> ptr{0}, col; std::vector<float> w; };
+static void add_row(Rows& r, const std::vector<int32_t>& cols, float tilt = 0.f) {  // tilt: unequal weights
+  const float each = 1.0f / (float)cols.size();
+  for (size_t k = 0; k < cols.size(); ++k) {
+    r.col.push_back(cols[k]);
+    r.w.push_back(each + (cols.size() < 2 ? 0.f : k == 0 ? tilt : k == 1 ? -tilt : 0.f));
+  }
+  r.ptr.push_back((int32_t)r.col.size());
+}
+struct Sim {
+  dadam_handle* h = nullptr;
+  uint32_t R, C;
+  size_t pitch;
+  std::vector<const void*> xs, g;
+  std::vector<void*> xd;
+  std::vector<float*> m, v, b;
+  Sim(uint32_t rows, uint32_t cols, const std::vector<dadam_tensor_desc>& ts, const Rows& lists, uint32_t dtype = DADAM_F32)
+      : R(rows), C(cols) {
+    dadam_config cfg{};
+    cfg.abi_version = DADAM_ABI_VERSION; cfg.n_rows = R; cfg.n_cols = C;
+    cfg.d = ts.back().offset_elems + ts.back().numel; cfg.n_tensors = (uint32_t)ts.size(); cfg.tensors = ts.data();
+    cfg.param_dtype = cfg.grad_dtype = dtype; cfg.lr = 1e-3f; cfg.beta1 = 0.9f; cfg.beta2 = 0.999f; cfg.eps = 1e-8f;
+    cfg.accum_s = 2; cfg.beta_vhat = -1.f; cfg.device = 0;
+    if (dadam_init(&cfg, &h) != DADAM_OK) { printf("init failed: %s\n", dadam_last_error(nullptr)); exit(1); }
+    if (dadam_set_topology(h, 0, lists.ptr.data(), lists.col.data(), lists.w.data(), nullptr) != DADAM_OK) {
+      printf("topology refused: %s\n", dadam_last_error(h)); exit(1);
+    }
+    pitch = (cfg.d * 4 + 4095) / 4096 * 4096;
+    size_t k = 0;
+    auto address = [&] { return (char*)(1ull << 30) + pitch * k++; };
+    for (uint32_t c = 0; c < C; ++c) xs.push_back(address());
+    for (uint32_t i = 0; i < R; ++i) { xd.push_back(address()); m.push_back((float*)address()); v.push_back((float*)address()); }
+    for (uint32_t i = 0; i < R; ++i) { b.push_back((float*)address()); g.push_back(address()); }
+  }
+  ~Sim() { dadam_destroy(h); }
+  void bind() {
+    dadam_buffers bufs{xs.data(), xd.data(), m.data(), v.data(), b.data()};
+    if (dadam_bind(h, &bufs) != DADAM_OK) { printf("bind refused: %s\n", dadam_last_error(h)); exit(1); }
+  }
+  std::string step(uint32_t flags, uint32_t begin = 0, uint32_t end = ~0u) {
+    route = "nothing";
+    const int rc = end == ~0u ? dadam_gossip_step(h, 0, g.data(), 1, flags, nullptr)
+                              : dadam_gossip_step_range(h, 0, g.data(), 1, flags, begin, end, nullptr);
+    return rc == DADAM_OK ? route : "error " + std::to_string(rc);
+  }
+  std::string mix(uint32_t flags) {
+    route = "nothing";
+    const int rc = dadam_mix(h, 0, flags, nullptr);
+    return rc == DADAM_OK ? route : "error " + std::to_string(rc);
+  }
+};
+static void say(const char* what, const std::string& answer) { printf("%s: %s\n", what, answer.c_str()); }
+
+// Row 0 is updated in place in source 1, which only row 0 lists; row 1's decay reads source 1 all the same.
+static void foreign_in_place() {
+  Rows shared, alone;
+  for (int i = 0; i < 16; ++i) {
+    add_row(shared, i == 0 ? std::vector<int32_t>{0, 1, 2} : i == 1 ? std::vector<int32_t>{2, 3, 4} : std::vector<int32_t>{i, i == 15 ? 2 : i + 1, 0});
+    add_row(alone, {i == 0 ? 1 : i == 1 ? 0 : i});
+  }
+  const std::vector<dadam_tensor_desc> ts = {{0, 700, 0.1f, 0}, {700, 900, 0.f, 0}};
+  Sim s(16, 16, ts, shared), a(16, 16, ts, alone);
+  for (Sim* x : {&s, &a}) { x->xd[0] = const_cast<void*>(x->xs[1]); x->bind(); }
+  const uint32_t F = DADAM_FUSE_ACCUM, D = DADAM_FORCE_DIRECT;
+  say("shared, step", s.step(F));
+  say("shared, update only", s.step(0));
+  say("shared, range with decay", s.step(F, 0, 1));
+  say("shared, range without decay", s.step(F, 1, 2));
+  say("shared, mixing", s.mix(0));
+  say("shared, step forced direct", s.step(F | D));
+  say("shared, range without decay forced direct", s.step(F | D, 1, 2));
+  say("shared, mixing forced direct", s.mix(D));
+  say("shared, step forced tile", s.step(F | DADAM_FORCE_TILE));
+  say("alone, step", a.step(F));
+  say("alone, range without decay", a.step(F, 1, 2));
+  say("alone, step forced direct", a.step(F | D));
+  say("alone, mixing", a.mix(0));
+  Sim own(16, 16, ts, shared);  // every row in place in its own buffer, which others read: the tile as ever
+  for (int i = 0; i < 16; ++i) own.xd[i] = const_cast<void*>(own.xs[i]);
+  own.bind();
+  say("all in place, step", own.step(F));
+  Sim solo(1, 3, {{0, 700, 0.1f, 0}}, [] { Rows r; add_row(r, {0, 1, 2}); return r; }());  // one node's share
+  solo.xd[0] = const_cast<void*>(solo.xs[0]);
+  solo.bind();
+  say("one row in place with decay", solo.step(F));
+  say("one row in place with decay forced direct", solo.step(F | D));
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "foreign_in_place") foreign_in_place();
+  else { printf("unknown question\n"); return 2; }
+  return 0;
+}

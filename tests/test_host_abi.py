@@ -499,6 +499,41 @@ def test_host_code_under_address_and_ub_sanitizers(tmp_path):
     assert "ERROR" not in r.stderr and "runtime error" not in r.stderr, r.stderr[-3000:]
 
 
+def _route_answers(tmp_path, question):
+    """What tests/host_route_driver.cpp (the host code on a modelled runtime, under ASan + UBSan) answers."""
+    import subprocess
+    clang = "/opt/rocm/lib/llvm/bin/clang++"
+    if not os.path.exists(clang):
+        pytest.skip("clang++ of the ROCm toolchain not available")
+    exe = str(tmp_path / "route_driver")
+    cmd = [clang, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2410_11998_amd", "csrc"),
+           "-I", "/opt/rocm/include", os.path.join(ROOT, "tests", "host_route_driver.cpp"),
+           os.path.join(ROOT, "paper_2410_11998_amd", "csrc", "dadam_host.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe, question], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0 and "ERROR" not in r.stderr, (r.stdout[-500:], r.stderr[-3000:])
+    return dict(line.split(": ", 1) for line in r.stdout.strip().splitlines())
+
+
+def test_a_row_updated_in_place_where_another_rows_decay_reads(tmp_path):
+    """With weight decay row i reads source buffer i although its list does not name it.  A row updated in place in
+    that buffer may then run without the staged tile only where no decay is read: not in a step over tensors that
+    decay, but in one over tensors that do not and in mixing."""
+    got = _route_answers(tmp_path, "foreign_in_place")
+    refused = f"error {B.DADAM_EALIAS}"
+    assert got == {
+        "shared, step": "tile", "shared, update only": "tile", "shared, range with decay": "tile",
+        "shared, range without decay": "direct-blocks", "shared, mixing": "direct-blocks",
+        "shared, step forced direct": refused, "shared, range without decay forced direct": "direct-blocks",
+        "shared, mixing forced direct": "direct-blocks", "shared, step forced tile": "tile",
+        "alone, step": "tile", "alone, range without decay": "direct", "alone, step forced direct": refused, "alone, mixing": "direct",
+        "all in place, step": "tile",
+        "one row in place with decay": "direct", "one row in place with decay forced direct": "direct",
+    }
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
