@@ -942,8 +942,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a
 // loops: groups of rows that list the same sources with the same weights
 // ---------------------------------------------------------------------------------------------
 // The rows of an All-Reduce loop (the complete graph; the loops of the alternating exponential ring) share one
-// neighbour sum.  A workgroup takes one piece of one loop: its wavefronts share out the loop's sources, each sums
-// its own straight from memory, the partial sums (one vector per lane and wavefront) meet in LDS, and after one
+// neighbour sum.  A workgroup takes one piece of one loop: its wavefronts share out the loop's sources, three or more
+// each, each sums its own straight from memory, the partial sums (one vector per lane and wavefront) meet in LDS, and after one
 // barrier the wavefronts deal the loop's rows among themselves.  Every source is read once and summed once, where
 // the tile kernel sums it once per row from a staged copy.  What that costs there: 64 rows of 64 sources read 64 x
 // the tile from LDS, and beyond 80 sources a CU holds one workgroup of the tile, whose phases nothing overlaps.
@@ -957,12 +957,17 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   constexpr int VEC = XT::vec, H = kHalfWave;
   const uint64_t e[1] = {tbase + 4u * (uint32_t)lane};
   const Loop l = a.loops[loop];
-  // this wavefront's sources and rows: every `waves`-th of the loop's, one per lane (at most 160 / 8 of each)
+  // This wavefront's rows, every `waves`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
+  // each).  A wavefront that sums has at least three sources, so that the sum is never less accurate than the listed
+  // order: a partial sum starts with a rounded product and is added with a rounded sum, where the chain of fused
+  // multiply-adds rounds once.  Mean error against 64 bits, relative to that chain, 3 / 9 / 13 / 20 sources of
+  // independent values and unequal weights: one wavefront a source 1.39 / 1.13 / 1.09 / 1.02, as it is 1 / 0.89 / 0.82 / 0.76.
+  const int parts = l.n_entries < 6 ? 1 : l.n_entries / 3 < waves ? l.n_entries / 3 : waves;
   RowList rl;
   rl.k0 = 0;
-  rl.deg = wave < l.n_entries ? (l.n_entries - wave + waves - 1) / waves : 0;
+  rl.deg = wave < parts ? (l.n_entries - wave + parts - 1) / parts : 0;
   const int my_rows = wave < l.n_rows ? (l.n_rows - wave + waves - 1) / waves : 0;
-  const int entry = l.first_entry + (lane < rl.deg ? wave + lane * waves : 0);
+  const int entry = l.first_entry + (lane < rl.deg ? wave + lane * parts : 0);
   rl.col_v = a.col[entry];
   rl.w_v = a.w[entry];
   const int row_v = a.row_order[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
@@ -982,7 +987,6 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   }
   __syncthreads();
   float mix[VEC];
-  const int parts = waves < l.n_entries ? waves : l.n_entries;
   for (int p = 0; p < parts; ++p)
 #pragma unroll
     for (int h = 0; h < VEC / 4; ++h) {

@@ -115,6 +115,36 @@ def test_rows_of_a_loop_share_one_neighbour_sum(case):
     print("worst error / tolerance:", worst, flush=True)
 
 
+@pytest.mark.parametrize("tiles", [512, 1030])            # 16 and 8 wavefronts
+@pytest.mark.parametrize("sources", [1, 2, 3, 5, 6, 8, 9, 11, 13, 17, 20, 23, 24, 47, 48, 96])
+def test_a_loops_shared_sum_is_as_accurate_as_the_listed_order(sources, tiles):
+    """The order in which the loop kernel adds a loop's sources is no further from 64 bits than the tile kernel's chain
+    of fused multiply-adds, whatever the number of sources; up to five are that chain."""
+    print("case", sources, tiles, flush=True)
+    R, d = 16, tiles * 256
+    rng = np.random.default_rng(sources)
+    w = (rng.random(sources) + 0.1).astype(np.float32)
+    w = (w / w.sum(dtype=np.float64)).astype(np.float32)
+    csr = (np.arange(0, R * sources + 1, sources, dtype=np.int32), np.tile(np.arange(sources, dtype=np.int32), R), np.tile(w, R))
+    sim = H.GpuSim(R, sources, WL.pack([("a", (d,))]), H.HyperF32(s=1), [csr])
+    for c in range(sources):
+        sim.x_src[c].copy_(H.to_device(WL.normal_np(300 + c, d, 1.0), "f32", "cuda:0"))
+    want = sum(float(w[c]) * sim.x_src[c].double() for c in range(sources))
+    errors = []
+    for flags in (0, B.DADAM_FORCE_TILE):
+        sim.mix(0, flags)
+        torch.cuda.synchronize()
+        got = [x.clone() for x in sim.x_dst]
+        assert all(torch.equal(x, got[0]) for x in got)
+        errors.append((got[0], float((got[0].double() - want).square().mean().sqrt())))
+    print("error of the shared sum / of the chain", errors[0][1], errors[1][1], flush=True)
+    if sources <= 5:
+        assert torch.equal(errors[0][0], errors[1][0])
+    # 131072 elements: the ratio of the two means is known to better than 1 %
+    assert errors[0][1] <= 1.01 * errors[1][1]
+    sim.close()
+
+
 @pytest.mark.parametrize("segments,rows,mode", [(2, 2, "tile"), (64, 2, "direct"), (65, 9, "auto"), (200, 4, "tile"), (4097, 2, "direct"),
                                                 (4097, 64, "tile")])
 def test_every_work_item_finds_its_segment(segments, rows, mode):
