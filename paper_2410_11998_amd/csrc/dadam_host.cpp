@@ -74,7 +74,7 @@ struct dadam_handle {
   uint32_t* d_seg_work = nullptr;  // their first work items, per Grid (what the kernels search)
   double* d_partials = nullptr;  // kConsensusPartials doubles of scratch for the consensus error
   // Cleared when the handle is made and by every pass after use; false after a pass that could not be enqueued whole,
-  // and the next one clears them itself.
+  // and the next one clears them itself.  Passes that are recorded into a graph neither rely on it nor change it.
   bool partials_clear = true;
   // Handles with more than kInlineRows rows or sources: device copies of the bound pointer tables, two per
   // binding (as bound, and with x_src / x_dst exchanged), DADAM_BINDINGS_KEPT bindings in a ring.
@@ -481,12 +481,24 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (!partials) partials = h->d_partials;
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  const bool own_partials = partials == h->d_partials;
-  if (consensus_out && !(own_partials && h->partials_clear)) {
+  // The handle's own partial sums are clear after every pass that ran whole, so the next one needs no launch to clear
+  // them.  What a pass under stream capture records runs later, any number of times and behind whatever came in
+  // between: it always clears first, and says nothing about what the memory holds now.
+  const bool own_partials = consensus_out && partials == h->d_partials;
+  bool recorded = false;
+  if (own_partials) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(reinterpret_cast<hipStream_t>(stream), &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      recorded = true;
+    }
+    if (capture != hipStreamCaptureStatusNone) recorded = true;
+  }
+  if (consensus_out && !(own_partials && !recorded && h->partials_clear)) {
     int e0 = launch_consensus_zero(partials, stream);
     if (e0 != (int)hipSuccess) return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e0));
   }
-  if (consensus_out && own_partials) h->partials_clear = false;
+  if (own_partials && !recorded) h->partials_clear = false;
   if (empty) {
     if (consensus_out) (void)launch_consensus_sum(partials, consensus_out, stream);
     return DADAM_OK;
@@ -551,7 +563,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
                               // where rows share sources the re-reads must find them in the cache
                               h->nontemporal, slot.reuse, a, w1 - w0, stream);
   if (e == (int)hipSuccess && consensus_out) e = launch_consensus_sum(partials, consensus_out, stream);
-  if (e == (int)hipSuccess && consensus_out && own_partials) h->partials_clear = true;
+  if (e == (int)hipSuccess && own_partials && !recorded) h->partials_clear = true;
   if (e != (int)hipSuccess)
     return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e));
   return DADAM_OK;

@@ -29,6 +29,7 @@ hipError_t hipMalloc(void** p, size_t n) { *p = malloc(n); memset(*p, 0xA5, n); 
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "modelled"; }
+hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
   *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
@@ -156,9 +157,72 @@ static void foreign_in_place() {
   say("one row in place with decay forced direct", solo.step(F | D));
 }
 
+// Consensus passes over partial sums that live in (modelled) device memory: every pass must report 3.
+static void consensus() {
+  Rows ring;
+  for (int i = 0; i < 4; ++i) add_row(ring, {i, (i + 1) % 4, (i + 3) % 4});
+  const std::vector<dadam_tensor_desc> ts = {{0, 700, 0.f, 0}};
+  auto pass = [](Sim& s, double* out, const char* failing = nullptr) {
+    *out = -1.0;
+    fail_launch = failing;
+    const int rc = dadam_mix_consensus(s.h, 0, 0, out, nullptr);
+    fail_launch = nullptr;
+    return rc;
+  };
+  auto run = [](std::vector<std::function<void()>>& graph) { for (auto& launch : graph) launch(); };
+  auto record = [&](Sim& s, double* out) {
+    capturing = true;
+    recorded.clear();
+    (void)pass(s, out);
+    capturing = false;
+    return recorded;
+  };
+  double out[8];
+  {
+    Sim s(4, 4, ts, ring);
+    s.bind();
+    pass(s, &out[0]);
+    pass(s, &out[1]);
+    say("one after the other", std::to_string(out[0]) + " " + std::to_string(out[1]));
+    auto graph = record(s, &out[2]);
+    run(graph);
+    const double first = out[2];
+    run(graph);
+    pass(s, &out[3]);
+    say("two replays, then a pass", std::to_string(first) + " " + std::to_string(out[2]) + " " + std::to_string(out[3]));
+  }
+  for (const char* failing : {"zero", "tile", "sum"}) {
+    Sim s(4, 4, ts, ring);
+    s.bind();
+    auto graph = record(s, &out[0]);
+    const int rc = pass(s, &out[1], failing);
+    run(graph);
+    say((std::string("replay after a pass that failed in ") + failing).c_str(), (rc == DADAM_OK ? "accepted " : "refused ") + std::to_string(out[0]));
+  }
+  {
+    Sim s(4, 4, ts, ring);
+    s.bind();
+    pass(s, &out[0], "sum");
+    auto graph = record(s, &out[1]);  // recorded, not yet run
+    pass(s, &out[2]);
+    run(graph);
+    pass(s, &out[3]);
+    say("pass behind a recorded one after a failed one", std::to_string(out[2]) + " " + std::to_string(out[1]) + " " + std::to_string(out[3]));
+  }
+  {
+    Sim s(4, 4, ts, ring);
+    s.bind();
+    (void)dadam_mix_consensus_static(s.h, 0, 0, &out[0], nullptr);
+    pass(s, &out[1]);
+    (void)dadam_mix_consensus_static(s.h, 0, 0, &out[2], nullptr);
+    say("static array in between", std::to_string(out[0]) + " " + std::to_string(out[1]) + " " + std::to_string(out[2]));
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
+  else if (what == "consensus") consensus();
   else { printf("unknown question\n"); return 2; }
   return 0;
 }

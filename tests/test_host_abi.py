@@ -534,6 +534,22 @@ def test_a_row_updated_in_place_where_another_rows_decay_reads(tmp_path):
     }
 
 
+def test_consensus_passes_assume_nothing_about_memory_that_a_launch_has_yet_to_write(tmp_path):
+    """Whether the partial sums are clear when a pass begins, over failed launches, recorded passes that have not run
+    and replays of graphs recorded before a failure: every pass that is accepted reports its own error alone."""
+    got = _route_answers(tmp_path, "consensus")
+    three = "3.000000"
+    assert got == {
+        "one after the other": f"{three} {three}",
+        "two replays, then a pass": f"{three} {three} {three}",
+        "replay after a pass that failed in zero": f"accepted {three}",      # cleared by the pass before: no clearing launch
+        "replay after a pass that failed in tile": f"refused {three}",
+        "replay after a pass that failed in sum": f"refused {three}",
+        "pass behind a recorded one after a failed one": f"{three} {three} {three}",
+        "static array in between": f"{three} {three} {three}",
+    }
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
