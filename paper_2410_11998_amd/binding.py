@@ -325,19 +325,19 @@ def grad_table(h, grads):
 
 
 def dadam_gossip_step(h, slot: int, grads, t: int, flags: int = DADAM_FUSE_ACCUM, stream: int = 0) -> None:
-    _check(h, lib.dadam_gossip_step(h, slot, _grad_ptrs(h, grads), t, flags, stream))
+    _check(h, lib.dadam_gossip_step(h, slot, _grad_ptrs(h, grads), t, flags, stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_gossip_step_range(h, slot: int, grads, t: int, flags: int, tensor_begin: int, tensor_end: int, stream: int = 0) -> None:
-    _check(h, lib.dadam_gossip_step_range(h, slot, _grad_ptrs(h, grads), t, flags, tensor_begin, tensor_end, stream))
+    _check(h, lib.dadam_gossip_step_range(h, slot, _grad_ptrs(h, grads), t, flags, tensor_begin, tensor_end, stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_accumulate(h, grads, t: int, stream: int = 0) -> None:
-    _check(h, lib.dadam_accumulate(h, _grad_ptrs(h, grads), t, stream))
+    _check(h, lib.dadam_accumulate(h, _grad_ptrs(h, grads), t, stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_mix(h, slot: int, flags: int = 0, stream: int = 0) -> None:
-    _check(h, lib.dadam_mix(h, slot, flags, stream))
+    _check(h, lib.dadam_mix(h, slot, flags, stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_mix_consensus(h, slot: int, out, flags: int = 0, stream: int = 0) -> None:
@@ -346,7 +346,7 @@ def dadam_mix_consensus(h, slot: int, out, flags: int = 0, stream: int = 0) -> N
         if out.numel() < 1 or out.element_size() != 8:
             raise ValueError("consensus output must hold one float64")
         out = out.data_ptr()
-    _check(h, lib.dadam_mix_consensus(h, slot, flags, C.c_void_p(out), stream))
+    _check(h, lib.dadam_mix_consensus(h, slot, flags, C.c_void_p(out), stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_mix_consensus_static(h, slot: int, out, flags: int = 0, stream: int = 0) -> None:
@@ -355,7 +355,7 @@ def dadam_mix_consensus_static(h, slot: int, out, flags: int = 0, stream: int = 
         if out.numel() < 1 or out.element_size() != 8:
             raise ValueError("consensus output must hold one float64")
         out = out.data_ptr()
-    _check(h, lib.dadam_mix_consensus_static(h, slot, flags, C.c_void_p(out), stream))
+    _check(h, lib.dadam_mix_consensus_static(h, slot, flags, C.c_void_p(out), stream if type(stream) is int else C.c_void_p(stream)))
 
 
 def dadam_set_lr(h, lr: float) -> None:

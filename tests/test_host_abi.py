@@ -348,6 +348,26 @@ def test_binding_rejects_short_or_mistyped_tensors():
     B.dadam_destroy(h)
 
 
+def test_a_stream_is_an_address_or_none():
+    """What is no address is refused before the library is called; an integer or None goes through."""
+    h, L = host_handle(2, 2)
+    P = lambda k: (1 << 20) + k * (L.d * 4 + 256)
+    B.dadam_bind(h, [P(0), P(1)], [P(2), P(3)], [P(4), P(5)], [P(6), P(7)])
+    B.dadam_set_topology(h, 0, *WL.complete(2))
+    g = [P(8), P(9)]
+    calls = [lambda s: B.dadam_gossip_step(h, 0, g, 1, B.DADAM_FUSE_ACCUM, s),
+             lambda s: B.dadam_gossip_step_range(h, 0, g, 1, B.DADAM_FUSE_ACCUM, 0, 1, s),
+             lambda s: B.dadam_accumulate(h, g, 1, s), lambda s: B.dadam_mix(h, 0, 0, s),
+             lambda s: B.dadam_mix_consensus(h, 0, P(10), 0, s), lambda s: B.dadam_mix_consensus_static(h, 0, P(10), 0, s)]
+    for call in calls:
+        for bad in ("a stream", b"a stream", C.c_void_p(64), C.byref(C.c_int(1)), (C.c_char * 8)(), 1.5):
+            with pytest.raises(TypeError):
+                call(bad)
+        for good in (0, None, 1 << 40, True):
+            assert "host-only" in expect(B.DADAM_ESTATE, call, good)
+    B.dadam_destroy(h)
+
+
 def test_spread_offsets_properties():
     unit = 2 << 20
     rng = np.random.default_rng(3)
