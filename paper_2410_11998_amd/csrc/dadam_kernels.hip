@@ -143,6 +143,14 @@ int raise_lds_limit(KernelFn fn, uint32_t lds) {
   return (int)e;
 }
 
+// The status of the launch itself.  The runtime also keeps a failure for whoever asks for the last error next: it is
+// taken away here, because the call that reports it is this one.
+int enqueue(KernelFn fn, uint32_t grid, uint32_t block, void** args, uint32_t lds, void* stream) {
+  const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
+  if (e != hipSuccess) (void)hipGetLastError();
+  return (int)e;
+}
+
 int launch(KernelFn fn, bool short_block, uint32_t grid, uint32_t block, uint32_t lds, const StepArgs& a, void* stream) {
   if (fn == nullptr) return (int)hipErrorInvalidDeviceFunction;
   if (grid == 0) return (int)hipSuccess;
@@ -153,10 +161,10 @@ int launch(KernelFn fn, bool short_block, uint32_t grid, uint32_t block, uint32_
   if (short_block) {
     StepArgsFew f = shortened(a);
     void* args[] = {&f};
-    return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
+    return enqueue(fn, grid, block, args, lds, stream);
   }
   void* args[] = {const_cast<StepArgs*>(&a)};
-  return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, reinterpret_cast<hipStream_t>(stream));
+  return enqueue(fn, grid, block, args, lds, stream);
 }
 
 // Launch of a kernel whose workgroups are one-wavefront pieces of work items (wide: whole items), for every row.  A grid holds less
@@ -207,13 +215,13 @@ int static_partials(double** out, uint32_t* capacity) {
 }
 
 int launch_consensus_zero(double* partials, void* stream) {
-  hipLaunchKernelGGL(k_consensus_zero, dim3(1), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), partials);
-  return (int)hipGetLastError();
+  void* args[] = {&partials};
+  return enqueue((KernelFn)k_consensus_zero, 1, 256, args, 0, stream);
 }
 
 int launch_consensus_sum(const double* partials, double* out, void* stream) {
-  hipLaunchKernelGGL(k_consensus_sum, dim3(1), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), const_cast<double*>(partials), out);
-  return (int)hipGetLastError();
+  void* args[] = {&partials, &out};
+  return enqueue((KernelFn)k_consensus_sum, 1, 256, args, 0, stream);
 }
 
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? TBF16::vec : TF32::vec; }

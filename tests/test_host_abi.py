@@ -570,6 +570,29 @@ def test_consensus_passes_assume_nothing_about_memory_that_a_launch_has_yet_to_w
     }
 
 
+def test_a_failed_launch_is_reported_by_the_call_and_nowhere_else(tmp_path):
+    """The runtime keeps the error of a failed launch for whoever asks next.  A call that returns DADAM_EHIP has taken it
+    away, and an error that somebody else left neither fails a call nor is swallowed by it."""
+    import subprocess
+    clang, rocm = "/opt/rocm/lib/llvm/bin/clang++", "/opt/rocm/lib"
+    if not os.path.exists(clang):
+        pytest.skip("clang++ of the ROCm toolchain not available")
+    exe, libdir = str(tmp_path / "launch_driver"), os.path.dirname(B.LIB_PATH)
+    cmd = [clang, "-std=c++17", "-O1", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", "/opt/rocm/include",
+           os.path.join(ROOT, "tests", "host_launch_driver.cpp"), "-o", exe, "-L", libdir, "-ldadam", f"-Wl,-rpath,{libdir}",
+           f"-Wl,-rpath,{rocm}", f"-Wl,-rpath-link,{rocm}"]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-500:], r.stderr[-2000:])
+    not_ready = 600
+    want = []
+    for name, n in (("step", 1), ("direct", 1), ("accumulate", 1), ("mix", 1), ("consensus", 2), ("static", 3)):
+        want += [f"{name}, launch {k} fails: rc {B.DADAM_EHIP} pending 0" for k in range(1, n + 1)]
+        want.append(f"{name}, another's error pending: rc 0 launches {n} pending {not_ready}")
+    assert r.stdout.strip().splitlines() == want
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
