@@ -383,13 +383,22 @@ uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(wa
 // Faster: with 16 rows to a loop on average.  us, other kernels / 4 / 8 / 16 wavefronts, 3e8 elements, mixing:
 // 32 rows in one loop 1349 / 862 / 837 / 900, 64 rows 3163 / 881 / 871 / 865, 96 rows in loops of 48, 24, 24 8486 /
 // 1764 / 1737 / 2091, but 32 rows in loops of 16, 8, 8 1756 / 1667 / 1933 / 3531 and 16 rows in loops of 8, 4, 4
-// 1709 / 1850 / 3098; four steps, 3e7 elements: 32 rows 667 / 655 / 634 / 663, 64 rows 926 / 669 / 623 / 631, 96 rows
-// 1416 / 731 / 706 / 743.  In small launches each wavefront walks its rows in turn, so more of them, from 8 rows a
-// loop on: 64 rows 4e5 elements 85 / 121 / 75 / 52, 4e6 225 / 176 / 118 / 84; 32 rows in loops of 16, 8, 8 4e5 36 /
-// 44 / 32 / 27.
-int loop_kernel_waves(const dadam_handle* h, const Slot& slot) {
+// 1709 / 1850 / 3098.  Steps, tile / this, four of 3e8 elements, one loop of 16, 32, 48, 64 rows: 6288 / 6167, 6512 / 6419,
+// 6749 / 6654, 7978 / 6561 (bfloat16 5069 / 4905, 5256 / 5095, 5650 / 5241, 6710 / 5201), 64 rows in loops of 32, 16, 16 6428 /
+// 6541 (5257 / 5175), 96 in loops of 48, 24, 24 13221 / 6635.  In small launches each wavefront walks its rows in turn, so
+// more of them, from 8 rows a loop on: 64 rows 4e5 elements 85 / 121 / 75 / 52, 4e6 225 / 176 / 118 / 84; 32 rows in
+// loops of 16, 8, 8 4e5 36 / 44 / 32 / 27.
+// A step with decay reads each row's own parameters again, from memory: 12 % of it.  In large layouts that is more than the
+// shared sum saves, until the tile kernel's own sums get long or few workgroups of its tile share a compute unit: tile /
+// this, 3e8 elements, one loop of 32, 48, 52, 56, 64 rows 6489 / 7311, 0.91, 0.92, 1.01, 8000 / 7442; 64 rows in loops of
+// 32, 16, 16 6433 / 7332, but 72, 80, 96 rows of such loops 1.01, 1.05, 13239 / 7536 (bfloat16 0.95 / 1.03 / 1.06 / 1.14 /
+// 1.18 and 0.93, 0.94, 0.98, 1.47).  In small ones the tile kernel has other troubles; they are even at about 32 tiles for
+// every row of a loop: 24 rows 1.21, 1.07, 1.04, 1.00, 0.97 at 400, 500, 700, 1000, 1500 tiles, 48 rows 1.62, 1.37, 1.33,
+// 1.21, 1.13, 64 in loops of 32, 16, 16 1.14, 1.02, 1.08, 0.92, 0.83.
+int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   const uint64_t R = h->cfg.n_rows, G = slot.loops.size();
   if (G == 0 || (R < 16 * G && (R < 8 * G || h->n_work_t > kFewTiles))) return 0;
+  if (!mix_only && h->decays && h->n_work_t * G > 32 * R && R < 56 * G && h->cfg.n_cols <= (uint32_t)kInlineRows) return 0;
   for (uint32_t i = 0; i < R; ++i)
     for (int32_t c : h->inplace_cols[i])
       if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
@@ -511,7 +520,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   // row takes the launch instead, with the same sums in the same order.  A loop of four steps, us, tile / direct, by
   // tiles: 16 rows of 5 sources 98: 27 / 24, 488: 48 / 48; 32 rows of 6 sources 49: 45 / 24, 244: 65 / 48, 977:
   // 158 / 165; 64 rows of 7 sources 24: 82 / 27, 122: 108 / 48, 488: 173 / 171; 8 rows the same up to 195 tiles.
-  const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot);
+  const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot, mix_only);
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= kFewTiles && direct_is_legal(h, slot, decays);

@@ -219,10 +219,53 @@ static void consensus() {
   }
 }
 
+// Which launches of an All-Reduce loop, or of several, share one sum.
+static void loops() {
+  auto complete = [](int n) {
+    Rows r;
+    std::vector<int32_t> all;
+    for (int c = 0; c < n; ++c) all.push_back(c);
+    for (int i = 0; i < n; ++i) add_row(r, all);
+    return r;
+  };
+  auto halves = [](int n) {  // loops of n/2, n/4, n/4 rows
+    Rows r;
+    const int from[] = {0, n / 2, n / 2 + n / 4, n};
+    for (int l = 0; l < 3; ++l) {
+      std::vector<int32_t> own;
+      for (int c = from[l]; c < from[l + 1]; ++c) own.push_back(c);
+      for (size_t i = 0; i < own.size(); ++i) add_row(r, own);
+    }
+    return r;
+  };
+  struct { const char* kind; int rows; uint64_t tiles; } cases[] = {
+      {"complete", 15, 256}, {"complete", 16, 256}, {"complete", 16, 257}, {"complete", 16, 512}, {"complete", 16, 513},
+      {"complete", 28, 257}, {"complete", 28, 512}, {"complete", 28, 513}, {"complete", 32, 1024}, {"complete", 32, 1025}, {"complete", 55, 1761},
+      {"complete", 56, 4000}, {"complete", 68, 4000}, {"halves", 32, 256}, {"halves", 32, 257}, {"halves", 64, 170},
+      {"halves", 64, 171}, {"halves", 64, 682}, {"halves", 64, 683}, {"halves", 72, 4000}, {"halves", 24, 100}};
+  for (const auto& c : cases)
+    for (uint32_t dtype : {DADAM_F32, DADAM_BF16}) {
+      const uint64_t d = c.tiles * (dtype == DADAM_BF16 ? 512 : 256);
+      const Rows rows = !strcmp(c.kind, "complete") ? complete(c.rows) : halves(c.rows);
+      Sim plain(c.rows, c.rows, {{0, d - 300, 0.f, 0}, {d - 300, 300, 0.f, 0}}, rows, dtype);
+      Sim decay(c.rows, c.rows, {{0, d - 300, 0.1f, 0}, {d - 300, 300, 0.1f, 0}}, rows, dtype);
+      plain.bind();
+      decay.bind();
+      const uint32_t F = DADAM_FUSE_ACCUM;
+      std::string ranges = decay.step(F, 0, 1);  // the sum's order does not depend on the range
+      const bool shared = decay.step(F).substr(0, 4) == "loop";
+      auto differs = [&](const std::string& r) { return (r.substr(0, 4) == "loop") != shared; };
+      ranges = differs(ranges) || differs(decay.step(F, 1, 2)) || differs(decay.step(0)) ? " but ranges differ" : "";
+      say((std::string(c.kind) + std::to_string(c.rows) + " " + std::to_string(c.tiles) + (dtype == DADAM_BF16 ? " bf16" : " f32")).c_str(),
+          plain.step(F) + " " + plain.mix(0) + " decay " + decay.step(F) + " " + decay.mix(0) + ranges);
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
   else if (what == "consensus") consensus();
+  else if (what == "loops") loops();
   else { printf("unknown question\n"); return 2; }
   return 0;
 }

@@ -593,6 +593,25 @@ def test_a_failed_launch_is_reported_by_the_call_and_nowhere_else(tmp_path):
     assert r.stdout.strip().splitlines() == want
 
 
+def test_which_launches_of_a_loop_share_one_sum(tmp_path):
+    """Steps, mixing and steps with decay of All-Reduce loops: a step with decay of a large layout goes to the tile kernel
+    unless its loops are long or its tile leaves a compute unit few workgroups; the choice does not depend on the range."""
+    got = _route_answers(tmp_path, "loops")
+    want = {                  # step, mixing, step with decay; mixing takes what a step without decay takes
+        "complete15 256": ("loop16", "loop16"), "complete16 256": ("loop16", "loop16"), "complete16 257": ("loop16", "loop16"),
+        "complete16 512": ("loop16", "loop16"), "complete16 513": ("loop8", "tile"), "complete28 257": ("loop16", "loop16"),
+        "complete28 512": ("loop16", "loop16"), "complete28 513": ("loop8", "loop8"), "complete32 1024": ("loop8", "loop8"),
+        "complete32 1025": ("loop8", "tile"), "complete55 1761": ("loop8", "tile"), "complete56 4000": ("loop8", "loop8"),
+        "complete68 4000": ("loop8", "loop8"), "halves32 256": ("loop8", "loop8"), "halves32 257": ("tile", "tile"),
+        "halves64 170": ("loop16", "loop16"), "halves64 171": ("loop8", "loop8"), "halves64 682": ("loop8", "loop8"),
+        "halves64 683": ("loop8", "tile"), "halves72 4000": ("loop8", "loop8"), "halves24 100": ("loop16", "loop16"),
+    }
+    for name, (plain, decay) in want.items():
+        for dtype in ("f32", "bf16"):
+            assert got.pop(f"{name} {dtype}") == f"{plain} {plain} decay {decay} {plain}", (name, dtype)
+    assert not got
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
