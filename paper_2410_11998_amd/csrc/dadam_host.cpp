@@ -387,7 +387,9 @@ uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(wa
 // 6749 / 6654, 7978 / 6561 (bfloat16 5069 / 4905, 5256 / 5095, 5650 / 5241, 6710 / 5201), 64 rows in loops of 32, 16, 16 6428 /
 // 6541 (5257 / 5175), 96 in loops of 48, 24, 24 13221 / 6635.  In small launches each wavefront walks its rows in turn, so
 // more of them, from 8 rows a loop on: 64 rows 4e5 elements 85 / 121 / 75 / 52, 4e6 225 / 176 / 118 / 84; 32 rows in
-// loops of 16, 8, 8 4e5 36 / 44 / 32 / 27.
+// loops of 16, 8, 8 4e5 36 / 44 / 32 / 27.  One loop of fewer than 28 rows leaves 16 of them little to do beyond one tile
+// per compute unit: tile time over 8 / 16, 16 rows of 366, 488 tiles 1.00 / 0.88, 0.98 / 0.88 (bfloat16 1.08 / 0.96, 1.02 /
+// 0.88), 24 rows of 488 1.22 / 1.11, 28 rows 1.20 / 1.26, 64 rows in three loops of 275 1.98 / 2.29.
 // A step with decay reads each row's own parameters again, from memory: 12 % of it.  In large layouts that is more than the
 // shared sum saves, until the tile kernel's own sums get long or few workgroups of its tile share a compute unit: tile /
 // this, 3e8 elements, one loop of 32, 48, 52, 56, 64 rows 6489 / 7311, 0.91, 0.92, 1.01, 8000 / 7442; 64 rows in loops of
@@ -402,7 +404,7 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   for (uint32_t i = 0; i < R; ++i)
     for (int32_t c : h->inplace_cols[i])
       if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
-  const int waves = h->n_work_t * G <= 2 * kFewTiles ? 16 : 8;
+  const int waves = h->n_work_t * G <= (G == 1 && R < 28 ? 1 : 2) * kFewTiles ? 16 : 8;
   return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 

@@ -598,8 +598,8 @@ def test_which_launches_of_a_loop_share_one_sum(tmp_path):
     unless its loops are long or its tile leaves a compute unit few workgroups; the choice does not depend on the range."""
     got = _route_answers(tmp_path, "loops")
     want = {                  # step, mixing, step with decay; mixing takes what a step without decay takes
-        "complete15 256": ("loop16", "loop16"), "complete16 256": ("loop16", "loop16"), "complete16 257": ("loop16", "loop16"),
-        "complete16 512": ("loop16", "loop16"), "complete16 513": ("loop8", "tile"), "complete28 257": ("loop16", "loop16"),
+        "complete15 256": ("loop16", "loop16"), "complete16 256": ("loop16", "loop16"), "complete16 257": ("loop8", "loop8"),
+        "complete16 512": ("loop8", "loop8"), "complete16 513": ("loop8", "tile"), "complete28 257": ("loop16", "loop16"),
         "complete28 512": ("loop16", "loop16"), "complete28 513": ("loop8", "loop8"), "complete32 1024": ("loop8", "loop8"),
         "complete32 1025": ("loop8", "tile"), "complete55 1761": ("loop8", "tile"), "complete56 4000": ("loop8", "loop8"),
         "complete68 4000": ("loop8", "loop8"), "halves32 256": ("loop8", "loop8"), "halves32 257": ("tile", "tile"),
