@@ -408,6 +408,18 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 
+// A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: up to this many tiles and with
+// more rows than a workgroup has wavefronts, the direct kernel's one wavefront per row takes the launch from the tile
+// kernel, with the same sums in the same order.  A loop of four steps, us, tile / direct, by tiles: 16 rows of 5 sources 98:
+// 27 / 24, 488: 48 / 48; 32 rows of 6 sources 49: 45 / 24, 244: 65 / 48, 977: 158 / 165; 64 rows of 7 sources 24: 82 / 27,
+// 122: 108 / 48, 488: 173 / 171; 8 rows the same up to 195 tiles.  Every row reads its sources through the caches, so long
+// rows and the wider vectors of bfloat16 end this sooner; direct time over tile time at 128, 192, 256 tiles: float32 rows
+// of 12 at most 0.76, 0.85, 1.00, 24 of 128 rows 0.59, 0.80, 1.01, 64 of 128 0.67, 0.94, 1.22, 128 of 128 0.69, 1.00, 1.32;
+// bfloat16 rows of 6 at most 0.77, 0.96, 1.02, 24 of 128 0.63, 0.87, 1.21, 64 of 128 0.74, 1.06, 1.43.
+uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
+  return slot.max_degree > 24 ? kFewTiles / 2 : slot.max_degree > 12 || h->vec == 8 ? kFewTiles * 3 / 4 : kFewTiles;
+}
+
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
 // holds: with all 32 of them the row's 8 or 9 streams are requested over too wide a window of memory.  What counts
 // is the bytes of loads in flight per unit; about 90 KB is best.  Fraction of 8 TB/s, by wavefronts per unit,
@@ -517,15 +529,10 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   uint32_t w0 = 0, w1 = 0;
   work_range(h, kGridTile, s0, s1, lo, hi, &w0, &w1);
   const uint32_t n_tiles = w1 - w0;
-  // A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: with no more than
-  // one tile per compute unit and more rows than a workgroup has wavefronts, the direct kernel's one wavefront per
-  // row takes the launch instead, with the same sums in the same order.  A loop of four steps, us, tile / direct, by
-  // tiles: 16 rows of 5 sources 98: 27 / 24, 488: 48 / 48; 32 rows of 6 sources 49: 45 / 24, 244: 65 / 48, 977:
-  // 158 / 165; 64 rows of 7 sources 24: 82 / 27, 122: 108 / 48, 488: 173 / 171; 8 rows the same up to 195 tiles.
   const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot, mix_only);
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
-                         n_tiles <= kFewTiles && direct_is_legal(h, slot, decays);
+                         n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
   const Grid grid = !tile_mode ? kGridDirect : mix_only && !by_loops ? kGridMix : kGridTile;

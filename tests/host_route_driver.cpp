@@ -261,11 +261,32 @@ static void loops() {
     }
 }
 
+// How many tiles a launch of rows that share sources may have and still go row by row.
+static void few() {
+  for (uint32_t dtype : {DADAM_F32, DADAM_BF16})
+    for (int degree : {3, 12, 13, 24, 25, 64}) {
+      Rows r;
+      for (int i = 0; i < 64; ++i) {
+        std::vector<int32_t> cols;
+        for (int k = 0; k < degree; ++k) cols.push_back((i + k) % 64);
+        add_row(r, cols, 0.001f * (float)(i % 7));
+      }
+      uint64_t most = 0;
+      for (uint64_t tiles = 120; tiles <= 260; ++tiles) {
+        Sim s(64, 64, {{0, tiles * (dtype == DADAM_BF16 ? 512 : 256), 0.f, 0}}, r, dtype);
+        s.bind();
+        if (s.step(DADAM_FUSE_ACCUM) != "tile") most = tiles;
+      }
+      say(((dtype == DADAM_BF16 ? "bf16 " : "f32 ") + std::to_string(degree)).c_str(), std::to_string(most));
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
   else if (what == "consensus") consensus();
   else if (what == "loops") loops();
+  else if (what == "few") few();
   else { printf("unknown question\n"); return 2; }
   return 0;
 }

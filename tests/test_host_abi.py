@@ -612,6 +612,13 @@ def test_which_launches_of_a_loop_share_one_sum(tmp_path):
     assert not got
 
 
+def test_how_many_tiles_count_as_few(tmp_path):
+    """Rows that share sources go row by row in launches of at most 256 tiles; fewer with bfloat16, whose vectors are
+    wider, and with long rows, which read every source through the caches."""
+    assert _route_answers(tmp_path, "few") == {"f32 3": "256", "f32 12": "256", "f32 13": "192", "f32 24": "192", "f32 25": "128", "f32 64": "128",
+                                               "bf16 3": "192", "bf16 12": "192", "bf16 13": "192", "bf16 24": "192", "bf16 25": "128", "bf16 64": "128"}
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
