@@ -420,6 +420,29 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
   return slot.max_degree > 24 ? kFewTiles / 2 : slot.max_degree > 12 || h->vec == 8 ? kFewTiles * 3 / 4 : kFewTiles;
 }
 
+// Direct launches of rows that share sources: does every row of a piece run on one die (die blocks), or does each die have a
+// group of the rows (die groups)?  Small launches, us, groups / blocks: 64 rows of two sources 244 tiles 87 / 83; 96 rows
+// of 7 sources 81 tiles 74 / 53, 325 tiles 215 / 186.  Large ones: mixing is far slower in blocks (0.75 to 0.9 of the rate).
+// Steps of 64 rows and more, groups' time over blocks' on the same buffers by elements of all rows together, rows of two:
+//   float32    5e7   1.5e8  6e8   1.8e9        bfloat16   5e7   1.5e8  6e8   1.8e9
+//   64 rows    0.98  1.10   1.03               64 rows    0.94  1.05   0.99
+//   65 rows    1.00  1.16   1.11  1.10         65 rows    0.98  1.14   1.06  1.08     (9 rows on one die, 8 on the others)
+//   72 rows    0.97  0.95   0.98  1.01         72 rows    0.96  0.95   0.98  0.99
+//   80 rows    0.95  0.96   1.07  1.02         80 rows    0.94  0.93   1.05  1.03
+//   96 rows    0.95  1.04   1.03  1.01         96 rows    0.97  1.00   1.06  1.02     (3e8: 1.07)
+//   112 rows   0.90  1.05   0.99  0.99         112 rows   0.94  1.02   1.00  0.99
+//   128 rows   1.00  1.03   0.98  0.98         128 rows   0.95  1.04   1.02  1.01     (3e8: 1.08)
+//   160 rows   0.98  0.99   1.04  0.99         160 rows   0.88  0.99   0.98  0.98
+bool rows_stay_on_one_die(const dadam_handle* h, bool mix_only, uint32_t n_tiles) {
+  if (n_tiles < kManyTiles) return true;
+  const uint32_t R = h->cfg.n_rows;
+  if (mix_only || R < 64) return false;
+  const bool wide = h->vec == 8;
+  if (wide && R >= 72 && (R < 80 || R > 128)) return false;
+  const uint64_t elems = (uint64_t)n_tiles * h->tile_elems * R;
+  return elems >= (R < 72 ? 100000000u : R < 96 ? 500000000u : wide ? 250000000u : 100000000u);
+}
+
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
 // holds: with all 32 of them the row's 8 or 9 streams are requested over too wide a window of memory.  What counts
 // is the bytes of loads in flight per unit; about 90 KB is best.  Fraction of 8 TB/s, by wavefronts per unit,
@@ -539,13 +562,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
-  // Rows that share sources: in small launches and steps of many rows every row of a piece runs on one die, otherwise
-  // each die has a group of rows.  us, groups / pieces, small: 64 rows of two sources 244 tiles 87 / 83; 96
-  // rows of 7 sources 81 tiles 74 / 53, 325 tiles 215 / 186.  Large, 6e8 elements, steps: rows of two sources, 32 of
-  // them: 12550 / 12690, bfloat16 9990 / 10400; 64: 13030 / 12790, bfloat16 equal; 96: 13490 / 12790, bfloat16 9980 /
-  // 9570; ring of 96: 12110 / 11590, 96 rows of 7 sources 14980 / 14620; 64 replicas of ResNet-50 with decay 18040 / 17610.
-  if (!tile_mode && ordered_rows(h, slot))
-    a.order = n_tiles < kManyTiles || (!mix_only && h->cfg.n_rows >= 64) ? kOrderDieBlocks : kOrderDieGroups;
+  if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
   set_range(h, grid, w0, lo, hi, &a);
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);

@@ -131,7 +131,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
-constexpr uint32_t kManyTiles = 1024;    // measured, see step_impl
+constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
 constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules

@@ -281,12 +281,34 @@ static void few() {
     }
 }
 
+// The order in which large direct launches of rows in pairs walk rows and pieces: from how many million elements of all
+// rows together a step keeps a piece's rows on one die.
+static void die_order() {
+  for (uint32_t dtype : {DADAM_F32, DADAM_BF16})
+    for (int n : {40, 63, 64, 71, 72, 79, 80, 95, 96, 128, 129, 160}) {
+      Rows r;
+      for (int i = 0; i < n; ++i) add_row(r, {i, (i + 1) % n});
+      uint32_t from = 0;
+      std::string other = "none";
+      for (uint32_t million = 90; million <= 1200 && !from; million += 5) {
+        const uint64_t d = (million * 1000000ull + n - 1) / n;
+        Sim s(n, n, {{0, d, 0.f, 0}}, r, dtype);
+        s.bind();
+        const std::string step = s.step(DADAM_FUSE_ACCUM);
+        if (step == "direct-blocks") from = million; else other = step;
+        if (s.mix(0) != "direct-groups") other = "mixing " + s.mix(0);
+      }
+      say(((dtype == DADAM_BF16 ? "bf16 " : "f32 ") + std::to_string(n)).c_str(), other + " then blocks from " + std::to_string(from));
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
   else if (what == "consensus") consensus();
   else if (what == "loops") loops();
   else if (what == "few") few();
+  else if (what == "die_order") die_order();
   else { printf("unknown question\n"); return 2; }
   return 0;
 }
