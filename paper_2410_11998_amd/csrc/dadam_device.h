@@ -767,7 +767,10 @@ __device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k
     }
 }
 
-// Neighbour sum of one row, in the order the row lists its entries, for U vectors per lane.
+// Neighbour sum of one row, in the order the row lists its entries, for U vectors per lane.  Batches of sources in flight:
+// with two bfloat16 vectors a lane (16 sums live) they are two sources after the first four: four more cost 76 registers
+// and with them the seventh wavefront (mixing in pairs, 24 to 64 rows, 0.96-0.98 -> 1.00-1.02 of the rate of workgroups of
+// 67 registers, 96 rows of three 1.07 -> 1.13, rows of seven the same).
 template <typename XT, int U, bool MASKED, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, const uint64_t (&e)[U], uint64_t lo,
                                            uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
@@ -788,15 +791,16 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, con
     }
   } else {
     DADAM_MIX(FIRST_BATCH, true, 0);
+    constexpr int BATCH = U == 2 && XT::vec == 8 ? 2 : 4;
     int k = FIRST_BATCH, first = 0;
-    for (; k + 4 <= rl.deg; k += 4) {
+    for (; k + BATCH <= rl.deg; k += BATCH) {
       if constexpr (EXT) {
-        if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them (64 is 4 or 8 and fours)
+        if (k - first == kWave) {  // a row of more than 64 entries: the next 64 of them (64 is 4 or 8 and batches)
           first = k;
           load_list_chunk(a, rl, first, lane);
         }
       }
-      DADAM_MIX(4, false, k - first);
+      DADAM_MIX(BATCH, false, k - first);
     }
     if (k < rl.deg) {
       if constexpr (EXT) {
@@ -805,7 +809,8 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, con
           load_list_chunk(a, rl, first, lane);
         }
       }
-      if ((rl.deg - k) & 2) DADAM_MIX(2, false, k - first);
+      if constexpr (BATCH > 2)
+        if ((rl.deg - k) & 2) DADAM_MIX(2, false, k - first);
       if ((rl.deg - k) & 1) DADAM_MIX(1, false, k - first + ((rl.deg - k) & 2));
     }
   }
