@@ -15,7 +15,7 @@
 //             memory (a node's own parameters plus receive buffers: no source is shared by two rows).
 //   k_loop    one workgroup owns a piece of one loop: rows that list the same sources with the same weights share
 //             one neighbour sum.
-//   k_mix_rows  large mixing-only launches of what k_direct does for rows that share sources.
+//   k_mix_rows, k_rows  large launches of what k_direct does for rows that share sources, whole items by four wavefronts.
 //   k_acc     accumulate / fold only (Algorithm 3 lines 9-13).
 //
 // Every access of a full tile is a 128-bit (float32) or 64-bit (bfloat16) load or store per lane,
@@ -819,12 +819,11 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, con
 
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
-template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT, typename A>
-__device__ __forceinline__ void direct_body(const A& a, int position, int row, uint64_t tbase, uint64_t lo,
+template <typename XT, typename GT, int PHASE, int U, bool MASKED, int HINT, bool EXT, typename A>
+__device__ __forceinline__ void direct_body(const A& a, int position, int row, const uint64_t (&e)[U], uint64_t lo,
                                             uint64_t hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
   constexpr int VEC = XT::vec, H = kHalfWave;
-  const uint64_t e = tbase + 4u * (uint32_t)lane;
   // The neighbour list sits one entry per lane and is handed out with readlane, which must find a
   // loaded value in whichever lane it asks.  So no lane may leave before the last readlane: a
   // thread of a clipped tile whose vectors all lie outside the range runs through the body with
@@ -832,38 +831,35 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
   // free to sink the list's load below it, into the lanes that stay - and a row whose leading
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_position_list(a, position, lane);
-  float g[VEC], mh[VEC], vh[VEC], b[VEC];
-  if constexpr (Needs<PHASE>::grad) load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e, lo, hi, g);
-  if constexpr (Needs<PHASE>::moments_in) {
-    load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
-  }
-  if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
+  load_row_inputs<GT, PHASE, VEC, U, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
   // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
   // sum where the row lists itself (loading them again would be a second trip to memory after the first).
   const bool decays = !Needs<PHASE>::mixing_only && wd != 0.0f;
   OwnSource<VEC> own;
   own.col = decays ? row : -1;
-  const uint64_t es[1] = {e};
-  float mixes[1][VEC];
-  mix_direct<XT, 1, MASKED, NTSRC, EXT>(a, rl, lane, es, lo, hi, mixes, own);
-  const float(&mix)[VEC] = mixes[0];
-  float decay[VEC];
+  float mix[U][VEC];
+  mix_direct<XT, U, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
+  float xo[U][VEC];
 #pragma unroll
-  for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
-  if (decays) {
-    if (!own.found) unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e, lo, hi), own.x);
+  for (int u = 0; u < U; ++u) {
+    float decay[VEC];
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
+    for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
+    if (decays) {
+      if (!own.found) unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e[u], lo, hi), own.x);
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
+    }
+#pragma unroll
+    for (int j = 0; j < VEC; ++j)
+      xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[j]);
   }
-  float xo[VEC];
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[j], mh[j], vh[j], b[j], decay[j]);
-  store_vals<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  store_vectors<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
@@ -901,9 +897,10 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   }
   const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
   const PieceAt p = locate_piece<XT::vec>(a, t);
+  const uint64_t e[1] = {p.tbase + 4u * (uint32_t)lane};
   if (active && p.any) {  // uniform over the workgroup
-    if (p.full) direct_body<XT, GT, PHASE, false, HINT, EXT>(a, (int)position, row, p.tbase, p.lo, p.hi, p.wd, lane);
-    else direct_body<XT, GT, PHASE, true, HINT, EXT>(a, (int)position, row, p.tbase, p.lo, p.hi, p.wd, lane);
+    if (p.full) direct_body<XT, GT, PHASE, 1, false, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
+    else direct_body<XT, GT, PHASE, 1, true, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
   }
 }
 
@@ -940,6 +937,28 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a
       mix_direct<XT, 2, true, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
       store_vectors<XT, VEC, kHalfWave, true, HINT != 0>(to, e, lo, hi, mix);
     }
+  }
+}
+
+// Steps in the same geometry (33 to 63 float32 rows, see whole_items).
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
+  constexpr int VEC = XT::vec;
+  constexpr uint64_t PIECE = (uint64_t)kWave * VEC, ITEM = PIECE * kDirectItem;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t item, position;
+  const bool active = die_group_order(blockIdx.x, a.n_rows, a.n_xcd, a.order_group, item, position);
+  const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate(a, a.work_begin + item, tile_index, lo, hi, wd);
+  const uint64_t tbase = tile_index * ITEM;
+  const uint64_t e0 = tbase + wave * PIECE + 4u * (uint32_t)lane;
+  const uint64_t e[2] = {e0, e0 + kWideWaves * PIECE};
+  if (active) {  // uniform over the workgroup
+    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, false, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
+    else direct_body<XT, GT, PHASE, 2, true, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
   }
 }
 
@@ -1207,12 +1226,26 @@ template <typename XT, typename GT, int HINT, bool EXT>
 KernelFn direct_kernel_for_phase(int phase) {
   switch (phase) {
     case kMixOnly: return (KernelFn)k_direct<XT, GT, kMixOnly, HINT, EXT>;
-    case kMixRows: return (KernelFn)k_mix_rows<XT, HINT, EXT>;
     case kUpdateOnly: return (KernelFn)k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
     case kPlain: return (KernelFn)k_direct<XT, GT, kPlain, HINT, EXT>;
     case kLoopStart: return (KernelFn)k_direct<XT, GT, kLoopStart, HINT, EXT>;
     case kFold: return (KernelFn)k_direct<XT, GT, kFold, HINT, EXT>;
     case kAlg1: return (KernelFn)k_direct<XT, GT, kAlg1, HINT, EXT>;
+  }
+  return nullptr;
+}
+// Whole items by four wavefronts: mixing (no gradient: built once per parameter type), and the large float32 steps that
+// the host gives it (streaming, tables in the argument block).
+template <typename XT, typename GT, int HINT, bool EXT>
+KernelFn rows_kernel_for_phase(int phase) {
+  if constexpr (XT::bytes == GT::bytes)
+    if (phase == kMixOnly) return (KernelFn)k_mix_rows<XT, HINT, EXT>;
+  if constexpr (XT::bytes == 4 && HINT == 2 && !EXT) switch (phase) {
+    case kUpdateOnly: return (KernelFn)k_rows<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return (KernelFn)k_rows<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return (KernelFn)k_rows<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return (KernelFn)k_rows<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return (KernelFn)k_rows<XT, GT, kAlg1, HINT, EXT>;
   }
   return nullptr;
 }

@@ -440,7 +440,16 @@ bool rows_stay_on_one_die(const dadam_handle* h, bool mix_only, uint32_t n_tiles
   const bool wide = h->vec == 8;
   if (wide && R >= 72 && (R < 80 || R > 128)) return false;
   const uint64_t elems = (uint64_t)n_tiles * h->tile_elems * R;
-  return elems >= (R < 72 ? 100000000u : R < 96 ? 500000000u : wide ? 250000000u : 100000000u);
+  return elems >= (R < 72 ? kManyElems : R < 96 ? 5 * kManyElems : wide ? kManyElems * 5 / 2 : kManyElems);
+}
+
+// Do workgroups of four wavefronts take whole items of a launch over die groups, instead of eight workgroups of one?
+// Mixing always (see k_rows).  Steps of 33 to 63 float32 rows of 1e8 elements and more: time of one-wavefront pieces over
+// this, 3e8 elements, rows in pairs, update only / whole step: 24 rows 0.98 / 0.99, 32 rows 0.99 / 1.00, 40 rows 1.04 / 1.03,
+// 48 rows 1.01 / 1.01, 56 rows 1.00 / 1.01, 72 rows 1.00 / 0.98; 3e7 elements 0.98 to 1.00; bfloat16 0.98 to 1.01, 3e7 0.95 to 0.98.
+bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t elems) {
+  if (order != kOrderDieGroups) return false;
+  return mix_only || (h->cfg.n_rows > 32 && h->cfg.n_rows < 64 && h->vec == 4 && h->d_tables == nullptr && h->nontemporal && elems >= kManyElems);
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
@@ -596,7 +605,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
               : launch_direct((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase,
                               // where rows share sources the re-reads must find them in the cache
-                              h->nontemporal, slot.reuse, a, w1 - w0, stream);
+                              h->nontemporal, slot.reuse, whole_items(h, mix_only, a.order, (uint64_t)n_tiles * h->tile_elems * h->cfg.n_rows),
+                              a, w1 - w0, stream);
   if (e == (int)hipSuccess && consensus_out) e = launch_consensus_sum(partials, consensus_out, stream);
   if (e == (int)hipSuccess && own_partials && !recorded) h->partials_clear = true;
   if (e != (int)hipSuccess)

@@ -49,8 +49,7 @@ enum Phase : int {
   kFold = 4,        // lines 6-13, last iteration of a loop (s > 1)
   kAlg1 = 5,        // s == 1: Algorithm 1, moments updated every iteration, no accumulator
   kMixConsensus = 6,  // x_dst = W x_src and, on the side, sum_c ||x_src[c] - mean||^2 (tile mode only)
-  kMixRows = 7,       // kMixOnly, as the direct kernel of large launches over rows that share sources does it
-  kNumPhases = 8
+  kNumPhases = 7
 };
 
 constexpr uint32_t kConsensusPartials = 1024;  // partial sums the tiles scatter their contributions over
@@ -132,6 +131,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
+constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there and whole_items
 constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
@@ -150,7 +150,8 @@ struct TileShape {
 int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& a, uint32_t n_work,
                 uint32_t lds_bytes, void* stream);
 // shared: rows share sources; a streaming launch then keeps the hint off the source loads.
-int launch_direct(int xdt, int gdt, Phase phase, bool nontemporal, bool shared, const StepArgs& a,
+// whole_items: one workgroup of four wavefronts takes a work item instead of eight of one (see k_rows).
+int launch_direct(int xdt, int gdt, Phase phase, bool nontemporal, bool shared, bool whole_items, const StepArgs& a,
                   uint32_t n_work_tiles, void* stream);
 // vec = elements per direct-mode parameter vector of the handle (fixes the tile grid).
 int launch_accumulate(int gdt, Phase phase, bool nontemporal, const StepArgs& a, uint32_t n_work_tiles,

@@ -26,6 +26,8 @@ namespace dadam {
 #define DADAM_PART(name)                                       \
   KernelFn tile_kernel_##name(int phase, TileShape s);         \
   KernelFn direct_kernel_##name(int phase, bool shared);       \
+  KernelFn rows_kernel_##name(int phase);                      \
+  KernelFn rows_kernel_##name##_ext(int phase);                \
   KernelFn loop_kernel_##name(int phase);                      \
   KernelFn loop_kernel_##name##_ext(int phase);                \
   KernelFn tile_kernel_##name##_ext(int phase, TileShape s);   \
@@ -274,12 +276,21 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
   return launch(fn, short_block, n_work, (uint32_t)(kWave * shape.waves), lds_bytes, a, stream);
 }
 
-int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const StepArgs& a, uint32_t n_work_tiles,
-                  void* stream) {
+int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, bool whole_items, const StepArgs& a,
+                  uint32_t n_work_tiles, void* stream) {
   KernelFn fn = nullptr;
-  const bool ext = a.ext != nullptr, wide = phase == kMixOnly && a.order == kOrderDieGroups;
-  if (wide) phase = kMixRows;
-  const bool short_block = few(a, nt) && !wide;
+  const bool ext = a.ext != nullptr;
+  if (whole_items) {
+    if (phase == kMixOnly) gdt = xdt;  // no gradient: one kernel per parameter type
+#define DADAM_PICK(name) (ext ? (nt ? rows_kernel_##name##_nt_ext(phase) : rows_kernel_##name##_ext(phase)) \
+                              : (nt ? rows_kernel_##name##_nt(phase) : rows_kernel_##name(phase)))
+    if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
+    if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
+    if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
+#undef DADAM_PICK
+    return launch_pieces(fn, false, a, n_work_tiles, stream, true);
+  }
+  const bool short_block = few(a, nt);
 #define DADAM_PICK(name) (short_block ? direct_kernel_##name##_few(phase) : ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared) : direct_kernel_##name##_ext(phase, shared)) \
                               : (nt ? direct_kernel_##name##_nt(phase, shared) : direct_kernel_##name(phase, shared)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
@@ -287,7 +298,7 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, const Ste
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
-  return launch_pieces(fn, short_block, a, n_work_tiles, stream, wide);
+  return launch_pieces(fn, short_block, a, n_work_tiles, stream);
 }
 
 int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t n_work_tiles, void* stream,

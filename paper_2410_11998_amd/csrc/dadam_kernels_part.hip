@@ -34,6 +34,10 @@ KernelFn DADAM_JOIN(DADAM_JOIN(direct_kernel_, DADAM_PART_NAME), _few)(int phase
 }
 #endif
 
+KernelFn DADAM_JOIN(rows_kernel_, DADAM_PART_NAME)(int phase) {
+  return rows_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase);
+}
+
 KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase) {
   return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
 }

@@ -47,8 +47,9 @@ int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint3
   double* p = a.partials;
   return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
 }
-int launch_direct(int, int, Phase, bool, bool, const StepArgs& a, uint32_t, void*) {
+int launch_direct(int, int, Phase, bool, bool, bool whole_items, const StepArgs& a, uint32_t, void*) {
   route = a.order == kOrderDieBlocks ? "direct-blocks" : a.order == kOrderDieGroups ? "direct-groups" : "direct";
+  if (whole_items) route += " whole";
   return enqueue("direct", [] {});
 }
 int launch_accumulate(int, Phase, bool, const StepArgs&, uint32_t, void*, int) { return enqueue("accumulate", [] {}); }
@@ -285,20 +286,22 @@ static void few() {
 // rows together a step keeps a piece's rows on one die.
 static void die_order() {
   for (uint32_t dtype : {DADAM_F32, DADAM_BF16})
-    for (int n : {40, 63, 64, 71, 72, 79, 80, 95, 96, 128, 129, 160}) {
+    for (int n : {32, 33, 63, 64, 71, 72, 79, 80, 95, 96, 128, 129, 160}) {
       Rows r;
       for (int i = 0; i < n; ++i) add_row(r, {i, (i + 1) % n});
       uint32_t from = 0;
       std::string other = "none";
+      uint32_t whole_from = 0;
       for (uint32_t million = 90; million <= 1200 && !from; million += 5) {
         const uint64_t d = (million * 1000000ull + n - 1) / n;
         Sim s(n, n, {{0, d, 0.f, 0}}, r, dtype);
         s.bind();
         const std::string step = s.step(DADAM_FUSE_ACCUM);
         if (step == "direct-blocks") from = million; else other = step;
-        if (s.mix(0) != "direct-groups") other = "mixing " + s.mix(0);
+        if (step == "direct-groups whole" && !whole_from) whole_from = million;
+        if (s.mix(0) != "direct-groups whole") other = "mixing " + s.mix(0);
       }
-      say(((dtype == DADAM_BF16 ? "bf16 " : "f32 ") + std::to_string(n)).c_str(), other + " then blocks from " + std::to_string(from));
+      say(((dtype == DADAM_BF16 ? "bf16 " : "f32 ") + std::to_string(n)).c_str(), other + ", whole items from " + std::to_string(whole_from) + ", blocks from " + std::to_string(from));
     }
 }
 

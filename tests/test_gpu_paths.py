@@ -224,3 +224,35 @@ def test_large_mixing_of_rows_that_share_sources(rows, deg, dtype):
     for i in range(rows):
         assert torch.equal(got[i], sim.x_dst[i]), i
     sim.close()
+
+
+@pytest.mark.parametrize("rows,grads,s", [(33, "f32", 2), (40, "bf16", 3), (63, "f32", 1)])
+def test_large_steps_by_whole_items_give_the_tile_kernels_bits(rows, grads, s):
+    """Steps of 33 to 63 float32 rows in pairs over 1e8 elements go by whole items of four wavefronts, two vectors a lane:
+    every phase, an update-only pass, decay, ragged ends and rows that do not divide among the dies, against the tile
+    kernel, which does the same sums in the same order."""
+    print("case", rows, grads, s, flush=True)
+    d = 100_000_000 // rows + 2000
+    layout = WL.pack([("a", (d - 1001,)), ("b", (5,)), ("c", (990,))])
+    csr = rows_of_degree(rows, 2)
+    sims = [H.GpuSim(rows, rows, layout, H.HyperF32(s=s), [csr], "f32", grads, weight_decay=[0.1, 0.0, 0.05], pad_fill=777.0) for _ in range(2)]
+    assert not B.dadam_slot_uses_tile_mode(sims[0].h, 0)
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    for c in range(rows):
+        sims[0].x_src[c].normal_(0.0, 0.02, generator=gen)
+        sims[1].x_src[c].copy_(sims[0].x_src[c])
+    pool = [[torch.empty(layout.d, device=dev).normal_(0.0, 1e-2, generator=gen).to(H.TORCH_DT[grads]) for _ in range(rows)] for _ in range(2)]
+    for t in range(1, 2 * s + 2):
+        flags = B.DADAM_FUSE_ACCUM if t <= 2 * s else 0
+        for sim, mode in zip(sims, (0, B.DADAM_FORCE_TILE)):
+            sim.step(pool[t % 2], t, 0, flags | mode)
+        torch.cuda.synchronize()
+        for i in range(rows):
+            for name in ("x_dst", "m", "v") + (("b",) if s > 1 else ()):
+                assert torch.equal(getattr(sims[0], name)[i], getattr(sims[1], name)[i]), (t, i, name)
+        for sim in sims:
+            sim.swap()
+    for sim in sims:
+        sim.close()

@@ -621,12 +621,15 @@ def test_how_many_tiles_count_as_few(tmp_path):
 
 def test_which_large_steps_keep_the_rows_of_a_piece_on_one_die(tmp_path):
     """Large direct launches of rows that share sources: groups of rows per die, for mixing always and for steps below the
-    numbers of rows and elements from which blocks of pieces per die were measured faster."""
+    numbers of rows and elements from which blocks of pieces per die were measured faster.  Within groups, mixing and the
+    large float32 steps of 33 to 63 rows go by whole items."""
     got = _route_answers(tmp_path, "die_order")
     never = 0
-    f32 = {40: never, 63: never, 64: 100, 71: 100, 72: 500, 79: 500, 80: 500, 95: 500, 96: 100, 128: 100, 129: 100, 160: 100}
+    f32 = {32: never, 33: never, 63: never, 64: 100, 71: 100, 72: 500, 79: 500, 80: 500, 95: 500, 96: 100, 128: 100, 129: 100, 160: 100}
     bf16 = {**f32, 72: never, 79: never, 96: 250, 128: 250, 129: never, 160: never}
-    assert got == {f"{t} {n}": f"direct-groups then blocks from {m}" for t, rule in (("f32", f32), ("bf16", bf16)) for n, m in rule.items()}
+    whole = {("f32", 33): 100, ("f32", 63): 100}                          # whole items by four wavefronts
+    assert got == {f"{t} {n}": f"direct-groups{' whole' if (t, n) in whole else ''}, whole items from {whole.get((t, n), 0)}, blocks from {m}"
+                   for t, rule in (("f32", f32), ("bf16", bf16)) for n, m in rule.items()}
 
 
 def _model_plan(offsets, numels, wds, tile, direct):
