@@ -1079,24 +1079,30 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
   }
 }
 
-template <typename GT, int VEC, int PHASE, bool MASKED, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void acc_body(const A& a, int row, uint64_t tbase, uint64_t lo,
-                                         uint64_t hi) {
+template <typename GT, int VEC, int PHASE, int U, bool MASKED, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi) {
   constexpr int H = kHalfWave;
-  const uint64_t e = tbase + 4u * threadIdx.x;
-  float g[VEC], mh[VEC], vh[VEC], b[VEC];
-  load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e, lo, hi, g);
-  if constexpr (Needs<PHASE>::moments_out) {
-    load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
-  }
-  if constexpr (Needs<PHASE>::acc_in) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
 #pragma unroll
-  for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[j], mh[j], vh[j], b[j]);
-  if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e[u], lo, hi, g[u]);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e[u], lo, hi, mh[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e[u], lo, hi, vh[u]);
+  }
+  if constexpr (Needs<PHASE>::acc_in) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e[u], lo, hi, b[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  if constexpr (Needs<PHASE>::moments_out) {
+    store_vectors<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
@@ -1108,10 +1114,30 @@ __device__ __forceinline__ void acc_entry(const A& a) {
   const uint32_t t = blockIdx.x / n_rows;
   const int row = (int)(blockIdx.x - t * n_rows);
   const PieceAt p = locate_piece<VEC>(a, t);
+  const uint64_t e[1] = {p.tbase + 4u * threadIdx.x};
   if (p.any) {
-    if (p.full) acc_body<GT, VEC, PHASE, false, NT, EXT>(a, row, p.tbase, p.lo, p.hi);
-    else acc_body<GT, VEC, PHASE, true, NT, EXT>(a, row, p.tbase, p.lo, p.hi);
+    if (p.full) acc_body<GT, VEC, PHASE, 1, false, NT, EXT>(a, row, e, p.lo, p.hi);
+    else acc_body<GT, VEC, PHASE, 1, true, NT, EXT>(a, row, e, p.lo, p.hi);
   }
+}
+
+// The same, whole items by four wavefronts, two vectors a lane (see accumulate_whole_items).
+template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
+__global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a) {
+  constexpr uint64_t PIECE = (uint64_t)kWave * VEC, ITEM = PIECE * kDirectItem;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t n_rows = a.n_rows;
+  const uint32_t item = blockIdx.x / n_rows;
+  const int row = (int)(blockIdx.x - item * n_rows);
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate(a, a.work_begin + item, tile_index, lo, hi, wd);
+  const uint64_t tbase = tile_index * ITEM;
+  const uint64_t e0 = tbase + wave * PIECE + 4u * (uint32_t)lane;
+  const uint64_t e[2] = {e0, e0 + kWideWaves * PIECE};
+  if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, false, NT, EXT>(a, row, e, lo, hi);
+  else acc_body<GT, VEC, PHASE, 2, true, NT, EXT>(a, row, e, lo, hi);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -452,6 +452,14 @@ bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t 
   return mix_only || (h->cfg.n_rows > 32 && h->cfg.n_rows < 64 && h->vec == 4 && h->d_tables == nullptr && h->nontemporal && elems >= kManyElems);
 }
 
+// The same question for accumulation.  Time of one-wavefront pieces over whole items, 3e8 elements: 1 row 0.90, 16 rows 0.96,
+// 24 rows 0.98, 32 rows 0.98, 40 rows 1.03, 48 rows 1.02, 64 rows 1.01, 72 rows 0.99, 96 rows 1.03, 128 rows 1.00, 160 rows
+// 1.00 (bfloat16 0.96, 0.93, 0.97, 0.97, 1.00, 1.00, 1.01, 0.98, 1.01, 0.99, 0.99); 3e7 elements 0.92 to 1.01.
+bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
+  const uint32_t R = h->cfg.n_rows;
+  return h->nontemporal && elems >= kManyElems && ((R > 32 && R <= 64) || (R > 80 && R < 128));
+}
+
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
 // holds: with all 32 of them the row's 8 or 9 streams are requested over too wide a window of memory.  What counts
 // is the bytes of loads in flight per unit; about 90 KB is best.  Fraction of 8 TB/s, by wavefronts per unit,
@@ -1093,7 +1101,8 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  int e = launch_accumulate((int)h->cfg.grad_dtype, fused_phase(h, t), h->nontemporal, a, w1 - w0, hip_stream, h->vec);
+  const uint64_t elems = (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows;
+  int e = launch_accumulate((int)h->cfg.grad_dtype, fused_phase(h, t), h->nontemporal, accumulate_whole_items(h, elems), a, w1 - w0, hip_stream, h->vec);
   if (e != (int)hipSuccess)
     return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e));
   return DADAM_OK;

@@ -131,7 +131,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
-constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there and whole_items
+constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there, whole_items, accumulate_whole_items
 constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
@@ -154,7 +154,7 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
 int launch_direct(int xdt, int gdt, Phase phase, bool nontemporal, bool shared, bool whole_items, const StepArgs& a,
                   uint32_t n_work_tiles, void* stream);
 // vec = elements per direct-mode parameter vector of the handle (fixes the tile grid).
-int launch_accumulate(int gdt, Phase phase, bool nontemporal, const StepArgs& a, uint32_t n_work_tiles,
+int launch_accumulate(int gdt, Phase phase, bool nontemporal, bool whole_items, const StepArgs& a, uint32_t n_work_tiles,
                       void* stream, int vec);
 
 // Consensus error: clear the partial sums / add them up in a fixed order into *out (device) and clear them.

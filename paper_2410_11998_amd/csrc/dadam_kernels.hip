@@ -98,6 +98,17 @@ KernelFn acc_kernel_for_phase(int phase) {
   return nullptr;
 }
 
+template <typename GT, int VEC, bool EXT>  // only streaming launches are large enough
+KernelFn acc_rows_kernel(int phase) {
+  switch (phase) {
+    case kPlain: return (KernelFn)k_acc_rows<GT, VEC, kPlain, true, EXT>;
+    case kLoopStart: return (KernelFn)k_acc_rows<GT, VEC, kLoopStart, true, EXT>;
+    case kFold: return (KernelFn)k_acc_rows<GT, VEC, kFold, true, EXT>;
+    case kAlg1: return (KernelFn)k_acc_rows<GT, VEC, kAlg1, true, EXT>;
+  }
+  return nullptr;
+}
+
 template <typename GT, int VEC>
 KernelFn few_acc_kernel(int phase) {
   switch (phase) {
@@ -301,20 +312,21 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, bool whol
   return launch_pieces(fn, short_block, a, n_work_tiles, stream);
 }
 
-int launch_accumulate(int gdt, Phase phase, bool nt, const StepArgs& a, uint32_t n_work_tiles, void* stream,
+int launch_accumulate(int gdt, Phase phase, bool nt, bool whole_items, const StepArgs& a, uint32_t n_work_tiles, void* stream,
                       int vec) {
   KernelFn fn = nullptr;
   const bool ext = a.ext != nullptr;
-  const bool short_block = few(a, nt);
+  const bool short_block = !whole_items && few(a, nt);
 #define DADAM_PICK(GT, VEC)                                                                                      \
-  (short_block ? few_acc_kernel<GT, VEC>(phase) : ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase) : acc_kernel_for_phase<GT, VEC, false, true>(phase)) \
+  (whole_items ? (ext ? acc_rows_kernel<GT, VEC, true>(phase) : acc_rows_kernel<GT, VEC, false>(phase))             \
+   : short_block ? few_acc_kernel<GT, VEC>(phase) : ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase) : acc_kernel_for_phase<GT, VEC, false, true>(phase)) \
        : (nt ? acc_kernel_for_phase<GT, VEC, true, false>(phase) : acc_kernel_for_phase<GT, VEC, false, false>(phase)))
   if (gdt == DADAM_F32 && vec == 4) fn = DADAM_PICK(TF32, 4);
   if (gdt == DADAM_F32 && vec == 8) fn = DADAM_PICK(TF32, 8);
   if (gdt == DADAM_BF16 && vec == 4) fn = DADAM_PICK(TBF16, 4);
   if (gdt == DADAM_BF16 && vec == 8) fn = DADAM_PICK(TBF16, 8);
 #undef DADAM_PICK
-  return launch_pieces(fn, short_block, a, n_work_tiles, stream);
+  return launch_pieces(fn, short_block, a, n_work_tiles, stream, whole_items);
 }
 
 }  // namespace dadam

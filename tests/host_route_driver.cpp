@@ -52,7 +52,10 @@ int launch_direct(int, int, Phase, bool, bool, bool whole_items, const StepArgs&
   if (whole_items) route += " whole";
   return enqueue("direct", [] {});
 }
-int launch_accumulate(int, Phase, bool, const StepArgs&, uint32_t, void*, int) { return enqueue("accumulate", [] {}); }
+int launch_accumulate(int, Phase, bool, bool whole_items, const StepArgs&, uint32_t, void*, int) {
+  route = whole_items ? "whole" : "pieces";
+  return enqueue("accumulate", [] {});
+}
 int launch_consensus_zero(double* p, void*) {
   return enqueue("zero", [=] { for (uint32_t i = 0; i < kConsensusPartials; ++i) p[i] = 0.0; });
 }
@@ -305,6 +308,22 @@ static void die_order() {
     }
 }
 
+// From how many million elements of all rows together accumulation goes by whole items.
+static void accumulation() {
+  for (int n : {1, 32, 33, 64, 65, 80, 81, 127, 128, 160}) {
+    Rows r;
+    for (int i = 0; i < n; ++i) add_row(r, {i});
+    uint32_t from = 0;
+    for (uint32_t million = 20; million <= 400 && !from; million += 5) {
+      Sim s(n, n, {{0, (million * 1000000ull + n - 1) / n, 0.f, 0}}, r);
+      s.bind();
+      if (dadam_accumulate(s.h, s.g.data(), 1, nullptr) != DADAM_OK) { printf("refused\n"); exit(1); }
+      if (route == "whole") from = million;
+    }
+    say(std::to_string(n).c_str(), std::to_string(from));
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
@@ -312,6 +331,7 @@ int main(int argc, char** argv) {
   else if (what == "loops") loops();
   else if (what == "few") few();
   else if (what == "die_order") die_order();
+  else if (what == "accumulation") accumulation();
   else { printf("unknown question\n"); return 2; }
   return 0;
 }

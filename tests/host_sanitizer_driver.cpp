@@ -13,7 +13,7 @@
 namespace dadam {
 int launch_tile(int, int, Phase, TileShape, const StepArgs&, uint32_t, uint32_t, void*) { return 0; }
 int launch_direct(int, int, Phase, bool, bool, bool, const StepArgs&, uint32_t, void*) { return 0; }
-int launch_accumulate(int, Phase, bool, const StepArgs&, uint32_t, void*, int) { return 0; }
+int launch_accumulate(int, Phase, bool, bool, const StepArgs&, uint32_t, void*, int) { return 0; }
 int launch_consensus_zero(double*, void*) { return 0; }
 int launch_consensus_sum(const double*, double*, void*) { return 0; }
 int static_partials(double** out, uint32_t* capacity) { *out = nullptr; *capacity = kConsensusPartials; return 0; }

@@ -256,3 +256,40 @@ def test_large_steps_by_whole_items_give_the_tile_kernels_bits(rows, grads, s):
             sim.swap()
     for sim in sims:
         sim.close()
+
+
+@pytest.mark.parametrize("rows,params,grads,s", [(33, "f32", "f32", 3), (40, "bf16", "bf16", 2), (90, "bf16", "f32", 1), (127, "f32", "bf16", 2)])
+def test_large_accumulation_by_whole_items(rows, params, grads, s):
+    """Accumulation of 33 to 64 and 81 to 127 rows over 1e8 elements goes by whole items of four wavefronts: against the same call on
+    a handle of the first row alone (one-wavefront pieces; elements never interact), bit for bit, ragged ends included."""
+    print("case", rows, params, grads, s, flush=True)
+    d = 100_000_000 // rows + 5000
+    layout = WL.pack([("a", (d - 1001,)), ("b", (5,)), ("c", (990,))])
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    sim = H.GpuSim(rows, rows, layout, H.HyperF32(s=s), [WL.identity(rows)], params, grads, pad_fill=777.0)
+    picked = (0, rows // 2, rows - 1)
+    alone = [H.GpuSim(1, 1, layout, H.HyperF32(s=s), [WL.identity(1)], params, grads, pad_fill=777.0) for _ in picked]
+    pool = [[torch.empty(layout.d, device=dev).normal_(0.0, 1e-2, generator=gen).to(H.TORCH_DT[grads]) for _ in range(rows)] for _ in range(2)]
+    for t in range(1, 2 * s + 2):
+        B.dadam_accumulate(sim.h, pool[t % 2], t, sim.stream())
+        for one, i in zip(alone, picked):
+            B.dadam_accumulate(one.h, [pool[t % 2][i]], t, one.stream())
+        torch.cuda.synchronize()
+        for one, i in zip(alone, picked):
+            assert torch.equal(sim.m[i], one.m[0]) and torch.equal(sim.v[i], one.v[0]), (t, i)
+            assert s == 1 or torch.equal(sim.b[i], one.b[0]), (t, i)
+    # and the other rows against the recurrence itself in float64: b and m are sums of a few terms
+    b, m = torch.zeros(layout.d, dtype=torch.float64, device=dev), torch.zeros(layout.d, dtype=torch.float64, device=dev)
+    i, beta1 = 1, float(np.float32(0.9))
+    for t in range(1, 2 * s + 2):
+        b += pool[t % 2][i].double() / s
+        if t % s == 0:
+            m = beta1 * m + (1 - beta1) * b
+            b.zero_()
+    mask = torch.from_numpy(H.valid_mask(layout)).to(dev)
+    assert float((sim.m[i].double() - m)[mask].abs().max()) < 1e-6 * 0.1       # |terms| below 0.1
+    sim.close()
+    for one in alone:
+        one.close()

@@ -632,6 +632,12 @@ def test_which_large_steps_keep_the_rows_of_a_piece_on_one_die(tmp_path):
                    for t, rule in (("f32", f32), ("bf16", bf16)) for n, m in rule.items()}
 
 
+def test_which_accumulations_go_by_whole_items(tmp_path):
+    """33 to 64 and 81 to 127 rows of 1e8 elements and more together, as measured."""
+    assert _route_answers(tmp_path, "accumulation") == {"1": "0", "32": "0", "33": "100", "64": "100", "65": "0", "80": "0",
+                                                        "81": "100", "127": "100", "128": "0", "160": "0"}
+
+
 def _model_plan(offsets, numels, wds, tile, direct):
     """Python model of the planner: maximal runs of contiguous tensors with equal weight decay, and the
     number of tiles of a grid anchored at element 0 that each run touches."""
