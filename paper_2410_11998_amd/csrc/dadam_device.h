@@ -74,6 +74,32 @@ __device__ __forceinline__ bool die_group_order(uint32_t b, uint32_t R, uint32_t
   return q < count;
 }
 
+// Direct mode in die blocks: all R rows of a piece run on one die, one after the other in the sharing order, and the dies
+// take runs of B pieces in turn, as in tile mode.  The grid is rounded up to whole dies (X ceil(n / X) R workgroups for n
+// pieces); a workgroup beyond the last piece has nothing to do (returns false).
+__device__ __forceinline__ bool die_block_piece(uint32_t b, uint32_t R, uint32_t X, uint32_t n, uint32_t B, uint32_t& piece,
+                                                uint32_t& position) {
+  const uint32_t x = b % X, j = b / X, index = j / R * X + x;
+  const bool active = index < n;
+  piece = active ? die_block_order(index, n, X, B) : 0;
+  position = j % R;
+  return active;
+}
+
+// One step of the search of all lanes of a wavefront for the segment of work item `work` among [s, s + n): lane k looks at
+// every step-th segment's first work item (begin, increasing), the ballot of the answers narrows the range.
+__device__ __forceinline__ uint32_t search_step(uint32_t n) { return (n + kWave - 1) / kWave; }
+__device__ __forceinline__ bool search_not_after(const uint32_t* begin, uint32_t s, uint32_t n, uint32_t step, uint32_t lane,
+                                                 uint32_t work) {
+  const uint32_t at = lane * step;
+  return at < n && begin[s + (at < n ? at : 0)] <= work;
+}
+__device__ __forceinline__ void search_narrow(uint64_t ballot, uint32_t step, uint32_t& s, uint32_t& n) {
+  const uint32_t last = (uint32_t)__builtin_popcountll(ballot) - 1;  // lane 0 is always among them
+  s += last * step;
+  n = step < n - last * step ? step : n - last * step;
+}
+
 // Element types, with the elements per lane and vector of a handle whose parameters have that type:
 // float32 4 (one 128-bit access); bfloat16 8, held as two groups of four (two 64-bit accesses of x and
 // g, two 128-bit accesses of each float32 state vector; see load_vals for where the groups lie).
@@ -322,11 +348,8 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
       const uint32_t lane = threadIdx.x & (kWave - 1);
       const uint32_t* begin = a.seg_work + (uint64_t)grid * a.n_seg;  // first work item of each segment, increasing
       while (n > 1) {
-        const uint32_t step = (n + kWave - 1) / kWave, at = lane * step;
-        const bool not_after = at < n && begin[s + (at < n ? at : 0)] <= work;
-        const uint32_t last = (uint32_t)__popcll(__ballot(not_after)) - 1;  // lane 0 is always among them
-        s += last * step;
-        n = step < n - last * step ? step : n - last * step;
+        const uint32_t step = search_step(n);
+        search_narrow(__ballot(search_not_after(begin, s, n, step, lane, work)), step, s, n);
       }
       s = __builtin_amdgcn_readfirstlane((int)s);
     } else {
@@ -872,14 +895,8 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   uint32_t t, position;
   bool active = true;
   if (a.order == kOrderDieBlocks) {
-    // Rows share sources: every row of a piece runs on one die, one after the other in the sharing order, so that
-    // a source comes from memory once and from that die's L2 for its other readers.  Runs of B = 32 pieces go to
-    // the dies in turn, as in tile mode.
-    const uint32_t X = a.n_xcd, x = blockIdx.x % X, j = blockIdx.x / X;
-    const uint32_t index = j / n_rows * X + x;
-    active = index < a.n_pieces;
-    t = active ? die_block_order(index, a.n_pieces, X, a.xcd_block) : 0;
-    position = j % n_rows;
+    // Rows share sources: a source comes from memory once and from the die's L2 for its other readers.
+    active = die_block_piece(blockIdx.x, n_rows, a.n_xcd, a.n_pieces, a.xcd_block, t, position);
   } else if (a.order == kOrderDieGroups) {
     // Rows share sources.  Consecutive workgroup ids go to the device's X dies in turn; die x takes the
     // rows at positions [x R / X, (x + 1) R / X) of the sharing order (R = n_rows), tile after tile: the

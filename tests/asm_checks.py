@@ -3,7 +3,7 @@
 import re
 
 
-def readlanes_of_loads_under_narrowed_exec(asm_path, kernel_re=r"^(_ZN5dadam[A-Za-z0-9_]*k_direct[A-Za-z0-9_]*):"):
+def readlanes_of_loads_under_narrowed_exec(asm_path, kernel_re=r"^(_ZN5dadam[A-Za-z0-9_]*k_(?:direct|mix_rows|rows|loop)[A-Za-z0-9_]*):"):
     """Follows the exec-mask nesting of every matching kernel along its control flow (basic blocks, branch
     targets and fall-through; s_and_saveexec pushes the register pair the mask is saved in, restoring exec
     from a pair pops back to where it was pushed; where paths meet, the deeper nesting is kept).  Returns

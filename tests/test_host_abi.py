@@ -400,7 +400,7 @@ def test_kernels_use_no_scratch_memory_and_load_neighbour_lists_with_all_lanes(t
     must run with every lane active.  The direct kernel once let threads of a clipped tile return
     early; a later build sank the list's load below that exit and rows whose leading lanes lay before
     the segment read indices from lanes that had never loaded.  The source must have no early exit
-    in device code, and in the direct kernels' assembly no register that readlane reads may be
+    in device code, and in the assembly of the kernels that hand lists out so no register that readlane reads may be
     loaded between a narrowing of the exec mask and its restoration."""
     import shutil
     import subprocess
@@ -451,30 +451,38 @@ def test_kernels_use_no_scratch_memory_and_load_neighbour_lists_with_all_lanes(t
     import subprocess as sp
     names = sorted(hints)
     plain_names = sp.run(["c++filt"], input="\n".join(names), capture_output=True, text=True).stdout.split("\n")
-    streaming, other = 0, 0
+    streaming, other, seen = 0, 0, set()
     for mangled, plain in zip(names, plain_names):
         st_nt, st_plain, ld_nt, ld_plain = hints[mangled]
-        m = re.search(r"\b(k_tile|k_direct|k_acc)<(.*)>\(", plain)
+        m = re.search(r"\b(k_tile|k_direct|k_acc|k_rows|k_mix_rows|k_acc_rows|k_loop|k_tile_few|k_direct_few|k_acc_few)<(.*)>\(", plain)
         if not m:
             continue
+        seen.add(m.group(1))
         targs = [x.strip() for x in m.group(2).split(",")]
-        nt, ext = targs[-2] in ("true", "1", "2"), targs[-1] == "true"     # <..., hints, tables in device memory>
-        if targs[-2] == "2":               # direct kernel for rows that share sources: source loads stay plain
+        few = m.group(1).endswith("_few")                                  # kernels on the short argument block never stream
+        nt, ext = not few and targs[-2] in ("true", "1", "2"), not few and targs[-1] == "true"     # <..., hints, tables in device memory>
+        if nt and targs[-2] == "2":        # direct kernels for rows that share sources: source loads stay plain
             streaming += 1
             assert st_plain == 0 and st_nt > 0 and ld_plain > 0, f"{plain}: stores {st_nt}/{st_plain}, loads {ld_nt}/{ld_plain}"
             continue
         if nt:
             streaming += 1
             assert st_plain == 0 and st_nt > 0, f"{plain}: {st_plain} vector stores without the hint"
-            assert ld_plain <= (60 if ext else 8) and ld_nt >= (1 if ext else 4) * ld_plain, \
+            # (the loop kernel has two bodies of row inputs, each with its look-ups in the tables)
+            assert ld_plain <= ((80 if m.group(1) == "k_loop" else 60) if ext else 8) and ld_nt >= (1 if ext else 4) * ld_plain, \
                 f"{plain}: {ld_plain} vector loads without the hint, {ld_nt} with"
         else:
             other += 1
             assert st_nt == 0 and ld_nt == 0, f"{plain}: hints in a kernel built without them"
     assert streaming > 150 and other > 150, (streaming, other)
+    assert len(seen) == 10, seen
 
+    # the kernels in which neighbour lists are handed out with readlane from what the lanes loaded: direct, whole items, loops
+    asm_names = [n for n in names if re.search(r"k_(direct|mix_rows|rows|loop)", n)]
+    for kernel in ("k_direct", "k_direct_few", "k_mix_rows", "k_rows", "k_loop"):
+        assert any(kernel in n for n in asm_names), kernel
     checked, bad = asm_checks.readlanes_of_loads_under_narrowed_exec(str(asm))
-    assert checked > 1000, "no readlane of a loaded register found in the direct kernels"
+    assert checked > 2000, "no readlane of a loaded register found in the direct and loop kernels"
     assert not bad, f"neighbour list loaded under a narrowed exec mask in {len(set(bad))} kernels, e.g. {bad[0]}"
 
 
@@ -495,6 +503,31 @@ def test_bench_byte_accounting_matches_the_workload_table():
         for p in loop:
             assert bench.path_bytes_per_replica_param(wl, p, "fused") == bench.algorithmic_bytes_per_replica_param(wl, p)
             assert bench.path_bytes_per_replica_param(wl, p, "unfused") > bench.algorithmic_bytes_per_replica_param(wl, p)
+
+
+def test_the_profile_summary_names_every_kernel_of_the_library():
+    """rocprof_summary.parse_kernel on the demangled names of the kernels in the source: none is dropped from a summary."""
+    from paper_2410_11998_amd import build as bld
+    from paper_2410_11998_amd import rocprof_summary as RS
+    src = "".join(open(os.path.join(bld.CSRC, f)).read() for f in ("dadam_device.h", "dadam_kernels.hip"))
+    kernels = set(re.findall(r"__global__ __launch_bounds__\([^)]*\) void (k_\w+)\(", src)) - {"k_consensus_zero", "k_consensus_sum"}
+    assert kernels == set(RS.KERNELS.split("|"))
+    n = "dadam::(anonymous namespace)::"
+    want = {
+        f"void {n}k_tile<{n}TF32, {n}TBF16, 2, 8, 1, true, false>(dadam::StepArgsFor<64, 160>)": ("k_tile<TF32,TBF16,8,1,true>", "plain"),
+        f"void {n}k_tile_few<{n}TF32, {n}TF32, 5, 4, 1>(dadam::StepArgsFor<16, 16>)": ("k_tile_few<TF32,TF32,4,1>", "alg1"),
+        f"void {n}k_direct<{n}TBF16, {n}TF32, 3, 2, true>(dadam::StepArgsFor<64, 160>)": ("k_direct<TBF16,TF32,shared>", "loopstart"),
+        f"void {n}k_direct_few<{n}TF32, {n}TF32, 4>(dadam::StepArgsFor<16, 16>)": ("k_direct_few<TF32,TF32>", "fold"),
+        f"void {n}k_mix_rows<{n}TBF16, 2, true>(dadam::StepArgsFor<64, 160>)": ("k_mix_rows<TBF16,shared>", "mix"),
+        f"void {n}k_rows<{n}TF32, {n}TF32, 1, 2, false>(dadam::StepArgsFor<64, 160>)": ("k_rows<TF32,TF32,shared>", "updateonly"),
+        f"void {n}k_loop<{n}TF32, {n}TF32, 0, 1, true>(dadam::StepArgsFor<64, 160>)": ("k_loop<TF32,TF32,true>", "mix"),
+        f"void {n}k_acc<{n}TF32, 4, 2, true, false>(dadam::StepArgsFor<64, 160>)": ("k_acc<TF32,4,true>", "plain"),
+        f"void {n}k_acc_rows<{n}TBF16, 8, 4, true, true>(dadam::StepArgsFor<64, 160>)": ("k_acc_rows<TBF16,8,true>", "fold"),
+        f"void {n}k_acc_few<{n}TBF16, 4, 3>(dadam::StepArgsFor<16, 16>)": ("k_acc_few<TBF16,4>", "loopstart"),
+        "void at::native::vectorized_elementwise_kernel<4, float>(int)": (None, None),
+    }
+    for name, parsed in want.items():
+        assert RS.parse_kernel(name) == parsed, name
 
 
 def test_host_code_under_address_and_ub_sanitizers(tmp_path):
@@ -902,8 +935,8 @@ def test_thirds_are_found_from_timings_of_a_modelled_memory():
 
 def test_device_access_helpers_on_the_cpu_under_sanitizers(tmp_path):
     """The kernels' vector load / store helpers (the lane-to-element layout, clipping at segment
-    edges, the two-group layout of 8-element lanes) and the maps from workgroup id to work item,
-    compiled for the host from the kernel source's own text and run on exact-size buffers under
+    edges, the two-group layout of 8-element lanes), the maps from workgroup id to work item and the search for
+    a work item's segment, compiled for the host from the kernel source's own text and run on exact-size buffers under
     ASan + UBSan."""
     import shutil
     import subprocess
@@ -924,4 +957,4 @@ def test_device_access_helpers_on_the_cpu_under_sanitizers(tmp_path):
     env["ASAN_OPTIONS"] = "detect_leaks=0"
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode == 0 and "fails 0" in r.stdout, (r.stdout[-1500:], r.stderr[-1500:])
-    assert r.stdout.count(" ok") == 11 and "work orders ok" in r.stdout
+    assert r.stdout.count(" ok") == 13 and all(f"{what} ok" in r.stdout for what in ("work orders", "segment search", "pieces"))
