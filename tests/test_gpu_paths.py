@@ -293,3 +293,154 @@ def test_large_accumulation_by_whole_items(rows, params, grads, s):
     sim.close()
     for one in alone:
         one.close()
+
+
+def rows_of_matrix(csr, i):
+    return [(int(csr[1][k]), float(csr[2][k])) for k in range(csr[0][i], csr[0][i + 1])]
+
+
+@pytest.mark.parametrize("kind,rows,tiles,params,grads,decay", [
+    ("complete", 28, 520, "f32", "f32", False),            # 8 wavefronts, ordinary accesses
+    ("complete", 60, 530, "f32", "f32", True),
+    ("aer", 72, 200, "bf16", "f32", True),                 # the same with tables in device memory
+    ("complete", 32, 2800, "f32", "f32", False),           # streaming
+    ("aer", 64, 800, "bf16", "bf16", False),
+    ("complete", 58, 1600, "f32", "bf16", True),
+    ("aer", 96, 960, "f32", "f32", True),                  # streaming, tables in device memory
+    ("complete", 68, 700, "bf16", "bf16", True),
+])
+def test_the_loop_kernels_of_large_layouts(kind, rows, tiles, params, grads, decay):
+    """Loops in layouts that take 8 wavefronts, below and above the size from which accesses stream, with the pointer
+    tables in the argument block and in device memory: mixing and a step against the same in 64 bits at every element."""
+    print("case", kind, rows, tiles, params, grads, decay, flush=True)
+    dev, elems = torch.device("cuda:0"), 64 * (8 if params == "bf16" else 4)
+    d = tiles * elems - 77
+    layout = WL.pack([("a", (d - 2003,)), ("b", (5,)), ("c", (1990,))])
+    csr = WL.complete(rows) if kind == "complete" else WL.aer(rows // 4, 0)
+    wd = [0.1, 0.0, 0.05] if decay else None
+    hp = H.HyperF32(s=1)
+    sim = H.GpuSim(rows, rows, layout, hp, [csr], params, grads, weight_decay=wd, pad_fill=777.0)
+    assert B.dadam_get_plan_info(sim.h).streaming == (layout.d * rows * 24 > 512 << 20)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    mask = torch.from_numpy(H.valid_mask(layout)).to(dev)
+    lam = torch.from_numpy(H.per_coordinate_decay(layout, wd)).to(dev) if decay else torch.zeros(layout.d, dtype=torch.float64, device=dev)
+    g = []
+    for i in range(rows):
+        sim.x_src[i].copy_(torch.empty(layout.d, device=dev).normal_(0.0, 0.5, generator=gen))
+        for t, (lo, hi) in ((sim.m[i], (-1e-3, 1e-3)), (sim.v[i], (3e-5, 1.7e-4))):
+            t[mask] = torch.empty(layout.d, device=dev).uniform_(lo, hi, generator=gen)[mask]
+        g.append(torch.empty(layout.d, device=dev).normal_(0.0, 1e-2, generator=gen).to(H.TORCH_DT[grads]))
+    m0, v0 = [t.clone() for t in sim.m], [t.clone() for t in sim.v]
+    tol = 1e-6 if params == "f32" else 1e-2               # float32 sums; one rounding to bfloat16
+
+    def mixed(i):
+        want, size = torch.zeros(layout.d, dtype=torch.float64, device=dev), torch.zeros(layout.d, dtype=torch.float64, device=dev)
+        for c, w in rows_of_matrix(csr, i):
+            want.add_(sim.x_src[c].double(), alpha=w)
+            size.add_(sim.x_src[c].double().abs(), alpha=w)
+        return want, size
+
+    some = sorted({0, 1, rows // 4, rows // 2, rows - 1})
+    sim.mix(0, 0)
+    torch.cuda.synchronize()
+    first = {i: sim.x_dst[i].clone() for i in some}
+    for i in some:
+        want, size = mixed(i)
+        assert bool(((sim.x_dst[i].double() - want).abs() <= tol * size)[mask].all()), i
+        assert bool((sim.x_dst[i][~mask] == 777.0).all()), i
+    sim.mix(0, B.DADAM_FORCE_TILE)
+    torch.cuda.synchronize()
+    if params == "f32":                                     # another order of the same sum: another kernel has run
+        assert any(not torch.equal(first[i], sim.x_dst[i]) for i in some)
+    f = lambda q: float(np.float32(q))
+    b1, b2, lr, eps, t = f(hp.beta1), f(hp.beta2), f(hp.lr), f(hp.eps), 7
+    sim.step(g, t, 0, B.DADAM_FUSE_ACCUM)
+    torch.cuda.synchronize()
+    for i in some:
+        want, size = mixed(i)
+        gi = g[i].double()
+        m, v = b1 * m0[i].double() + (1 - b1) * gi, b2 * v0[i].double() + (1 - b2) * gi * gi
+        move = lr * (m / (1 - b1 ** t) / ((v / (1 - b2 ** t)).sqrt() + eps) + lam * sim.x_src[i].double())
+        size = size + lr * ((b1 * m0[i].double().abs() + (1 - b1) * gi.abs()) / (1 - b1 ** t) / ((v / (1 - b2 ** t)).sqrt() + eps)
+                            + lam * sim.x_src[i].double().abs())
+        assert bool(((sim.x_dst[i].double() - (want - move)).abs() <= tol * size)[mask].all()), i
+        assert bool(((sim.m[i].double() - m).abs() <= 1e-6 * (b1 * m0[i].double().abs() + (1 - b1) * gi.abs()))[mask].all()), i
+        assert bool(((sim.v[i].double() - v).abs() <= 1e-6 * v)[mask].all()), i
+        for out in (sim.x_dst[i], sim.m[i], sim.v[i]):
+            assert bool((out[~mask] == 777.0).all()), i
+    sim.close()
+
+
+@pytest.mark.parametrize("case", ["loop16-f32", "loop8-f32", "loop8-decay-f32", "loop8-bf16", "tile-decay-f32", "tile-decay-bf16", "foreign-f32"])
+def test_a_step_issued_range_by_range_has_the_bits_of_the_whole_one(case):
+    """In automatic mode, where the whole step and its ranges are large and small launches: slots of loops (one order of
+    the sum for both), and shared rows whose whole step is staged in LDS while its ranges go row by row, with decay; also
+    with a row updated in place in the buffer of another row, against the same step out of place."""
+    print("case", case, flush=True)
+    dtype = "bf16" if "bf16" in case else "f32"
+    elems = 64 * (8 if dtype == "bf16" else 4)
+    tiles = 210 if "16" in case.split("-")[0] else 700
+    n = 12 if not case.startswith("loop") else 24 if "decay" not in case else 60
+    sizes = [90 * elems + 7, 200 * elems - 3, 1, (tiles - 400) * elems + 13, 95 * elems] if tiles > 500 else [90 * elems + 7, 61, 60 * elems - 3, 60 * elems]
+    layout = WL.pack([(f"t{k}", (s,)) for k, s in enumerate(sizes)])
+    wd = [0.1 * (k % 2) for k in range(len(sizes))] if "decay" in case or case.startswith("foreign") else None
+    if case.startswith("loop"):
+        csr = WL.complete(n)
+    elif case.startswith("tile"):
+        csr = rows_of_degree(n, 3)
+    else:                                                   # only row 0 lists source 1
+        col = [[0, 1, 2], [2, 3, 4]] + [[i, 2 if i == n - 1 else i + 1, 0] for i in range(2, n)]
+        csr = (np.arange(0, 3 * n + 1, 3, dtype=np.int32), np.array(sum(col, []), np.int32), np.full(3 * n, np.float32(1) / np.float32(3), np.float32))
+    sims = [H.GpuSim(n, n, layout, H.HyperF32(s=2), [csr], dtype, dtype, weight_decay=wd) for _ in range(3)]
+    for c in range(n):
+        x0 = H.to_device(WL.normal_np(700 + c, layout.d, 0.02), dtype, "cuda:0")
+        for sim in sims:
+            sim.x_src[c].copy_(x0)
+    if case.startswith("foreign"):
+        for sim in sims[1:]:
+            sim.x_dst[0] = sim.x_src[1]
+            sim.bind()
+    mask = torch.from_numpy(H.valid_mask(layout)).to("cuda:0")
+    ranges = [(0, 1), (2, 4), (1, 2), (4, len(sizes))] if len(sizes) > 4 else [(3, 4), (0, 2), (2, 3)]
+    for t in range(1, 3 if not case.startswith("foreign") else 2):
+        grads = [H.to_device(WL.normal_np(800 + t * 100 + i, layout.d, 1e-3), dtype, "cuda:0") for i in range(n)]
+        sims[0].step(grads, t, 0, B.DADAM_FUSE_ACCUM)
+        sims[1].step(grads, t, 0, B.DADAM_FUSE_ACCUM)
+        for lo, hi in ranges:
+            B.dadam_gossip_step_range(sims[2].h, 0, grads, t, B.DADAM_FUSE_ACCUM, lo, hi, sims[2].stream())
+        torch.cuda.synchronize()
+        for i in range(n):
+            for name in ("x_dst", "m", "v", "b"):
+                a, whole, parts = (getattr(sim, name)[i][mask] for sim in sims)     # padding is what the buffer held before
+                assert torch.equal(a, whole) and torch.equal(a, parts), (t, i, name)
+        for sim in sims:
+            sim.swap()
+    for sim in sims:
+        sim.close()
+
+
+@pytest.mark.parametrize("kind,rows", [("complete", 24), ("aer", 64)])
+def test_mixing_with_and_without_the_consensus_error_on_loops(kind, rows):
+    """dadam_mix takes the shared sum of a loop, dadam_mix_consensus the listed order: the same within the rounding of a
+    float32 sum, and the reported error is that of the sources."""
+    print("case", kind, rows, flush=True)
+    layout = WL.pack([("a", (70001,)), ("b", (77,))])
+    csr = WL.complete(rows) if kind == "complete" else WL.aer(rows // 4, 0)
+    sim = H.GpuSim(rows, rows, layout, H.HyperF32(s=1), [csr])
+    out = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    for c in range(rows):
+        sim.x_src[c].copy_(H.to_device(WL.normal_np(40 + c, layout.d, 0.5), "f32", "cuda:0"))
+    sim.mix(0, 0)
+    torch.cuda.synchronize()
+    plain = [t.clone() for t in sim.x_dst]
+    sim.mix_consensus(out)
+    torch.cuda.synchronize()
+    mask = torch.from_numpy(H.valid_mask(layout)).to("cuda:0")
+    for i in range(rows):
+        size = sum(w * sim.x_src[c].double().abs() for c, w in rows_of_matrix(csr, i))
+        assert bool(((plain[i].double() - sim.x_dst[i].double()).abs() <= 1e-6 * size)[mask].all()), i
+    xs = torch.stack([t.double()[mask] for t in sim.x_src])
+    want = float((xs - xs.mean(0)).square().sum())
+    assert abs(float(out) - want) <= 1e-5 * want           # float32 per element, double sums
+    sim.close()
