@@ -127,7 +127,10 @@ typedef struct {
   uint32_t lds_limit_bytes; /* LDS one workgroup may use.  0: what the device reports (a host-only handle
                                assumes 65536).  A non-zero value plans for that much instead (e.g. to keep
                                room for other kernels' LDS); on a device handle it must not exceed what the
-                               device reports. */
+                               device reports.  Large steps of a single row reserve up to 154 KB of every
+                               compute unit's LDS without using it, to bound how many of their wavefronts
+                               are in flight (5 % faster): a kernel on another stream that needs more than is
+                               left waits for them.  A limit below the device's turns that off. */
   uint32_t n_xcds;          /* accelerator complex dies (each with its own L2) that consecutive workgroup
                                ids are dealt over.  0: what the device reports (host-only handle: 8). */
 } dadam_config;
@@ -224,14 +227,16 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
  * of DADAM_FORCE_DIRECT / DADAM_FORCE_TILE. */
 int dadam_mix(dadam_handle* h, uint32_t slot, uint32_t flags, void* hip_stream);
 
-/* dadam_mix plus, at no extra HBM traffic, the consensus error of the SOURCES,
+/* The gossip round of dadam_mix and, at no extra HBM traffic, the consensus error of the SOURCES,
  *     *consensus_out = sum over source buffers c and elements e of (x_src[c][e] - mean_c x_src[.][e])^2,
  * the squared distance of the replicas from their average whose decay per gossip round the paper
  * plots to compare topologies (section "Important aspects ...", heterogeneous communication; the
  * consensus lemma bounds the same quantity).  consensus_out is a DEVICE pointer to one double,
  * written by work enqueued on the stream; per-element arithmetic is float32, the sum double.
  * Available in tile mode only (the sources of a tile are then on chip together); DADAM_ESTATE
- * otherwise.  Calls on one handle must not overlap in time: they share the handle's partial sums. */
+ * otherwise.  x_dst has dadam_mix's bits except where dadam_mix lets many rows share one sum (All-Reduce loops, see the top
+ * of this file): this call always sums in the order the row lists, and the two differ there by the rounding of a float32
+ * sum.  Calls on one handle must not overlap in time: they share the handle's partial sums. */
 int dadam_mix_consensus(dadam_handle* h, uint32_t slot, uint32_t flags, double* consensus_out,
                         void* hip_stream);
 
@@ -255,8 +260,9 @@ int dadam_set_lr(dadam_handle* h, float lr);
 /* Planner facts for this handle. */
 int dadam_get_plan_info(const dadam_handle* h, dadam_plan_info* out);
 
-/* 1 if a step with this slot would run in tile mode when no FORCE flag is given, 0 for direct
- * mode, negative status on error. */
+/* The choice between tile and direct mode for a step with this slot when no FORCE flag is given, as described at the
+ * flags above: 1 tile, 0 direct, negative status on error.  Launches of rows that share whole neighbour lists and launches
+ * of few tiles may then run in other kernels all the same. */
 int dadam_slot_uses_tile_mode(const dadam_handle* h, uint32_t slot);
 
 /* The order in which direct mode takes the rows of this slot (order_out: n_rows entries, a permutation of

@@ -12,7 +12,8 @@
 //             reads what another lane wrote, one barrier separates staging from use.  All sources
 //             of the tile are read before anything is written, so updating in place is legal.
 //   k_direct  one wavefront updates one vector per lane of one row and streams the row's sources from global
-//             memory (a node's own parameters plus receive buffers: no source is shared by two rows).
+//             memory: a node's own parameters plus receive buffers, and rows that share sources where the
+//             caches serve the second reader better than the staged tile does.
 //   k_loop    one workgroup owns a piece of one loop: rows that list the same sources with the same weights share
 //             one neighbour sum.
 //   k_mix_rows, k_rows  large launches of what k_direct does for rows that share sources, whole items by four wavefronts.
@@ -923,7 +924,9 @@ __device__ __forceinline__ void direct_entry(const A& a) {
 
 // Mixing only, of rows that share sources: a wavefront has little to do for one vector (two or three loads, one store),
 // and what bounds the launch is how fast the chip starts workgroups (about 1.7 a nanosecond).  So a workgroup of four
-// wavefronts takes a whole work item, two vectors a lane.  us, two rounds, one-wavefront pieces / this: 72 rows
+// wavefronts takes a whole work item, two vectors a lane.  With pairs it is then bound by HBM (72 rows, 3e8 elements: 1.33 GB
+// read, 1.20 written in 449 us); longer rows fetch a source once for every die that has a reader, and those bytes bound them
+// (96 rows of seven sources: 4.84 GB read for 1.20 of sources, 897 us, 6.7 TB/s).  us, two rounds, one-wavefront pieces / this: 72 rows
 // in pairs 631 / 465, 96 rows of three sources 608 / 500, 96 replicas of a one-peer graph, one round of each hop, 2030 / 1640.
 constexpr int kWideWaves = kDirectItem / 2;
 template <typename XT, int HINT, bool EXT>
@@ -988,8 +991,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // barrier the wavefronts deal the loop's rows among themselves.  Every source is read once and summed once, where
 // the tile kernel sums it once per row from a staged copy.  What that costs there: 64 rows of 64 sources read 64 x
 // the tile from LDS, and beyond 80 sources a CU holds one workgroup of the tile, whose phases nothing overlaps.
-// All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM where rows are
-// many; measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
+// All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM: the bytes moved are
+// those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
 template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT, typename A>
 __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t tbase, uint64_t lo, uint64_t hi,

@@ -159,7 +159,7 @@ int launch_accumulate(int gdt, Phase phase, bool nontemporal, bool whole_items, 
 
 // Consensus error: clear the partial sums / add them up in a fixed order into *out (device) and clear them.
 int launch_consensus_zero(double* partials, void* stream);
-int launch_consensus_sum(const double* partials, double* out, void* stream);
+int launch_consensus_sum(double* partials, double* out, void* stream);
 
 // The partial-sum array that lives in the library's device image (no allocation): its address on the
 // current device and its capacity in doubles.  Returns a hipError_t as int.

@@ -200,8 +200,6 @@ int launch_pieces(KernelFn fn, bool short_block, StepArgs a, uint32_t n_items, v
   return e;
 }
 
-static_assert(sizeof(StepArgs) <= 4096, "kernel argument block must fit the kernarg segment");
-
 }  // namespace
 
 // Address and capacity (in doubles) of `scratch` on the CURRENT device, resolved once per device.
@@ -232,7 +230,7 @@ int launch_consensus_zero(double* partials, void* stream) {
   return enqueue((KernelFn)k_consensus_zero, 1, 256, args, 0, stream);
 }
 
-int launch_consensus_sum(const double* partials, double* out, void* stream) {
+int launch_consensus_sum(double* partials, double* out, void* stream) {
   void* args[] = {&partials, &out};
   return enqueue((KernelFn)k_consensus_sum, 1, 256, args, 0, stream);
 }

@@ -59,8 +59,7 @@ int launch_accumulate(int, Phase, bool, bool whole_items, const StepArgs&, uint3
 int launch_consensus_zero(double* p, void*) {
   return enqueue("zero", [=] { for (uint32_t i = 0; i < kConsensusPartials; ++i) p[i] = 0.0; });
 }
-int launch_consensus_sum(const double* cp, double* out, void*) {
-  double* p = const_cast<double*>(cp);
+int launch_consensus_sum(double* p, double* out, void*) {
   return enqueue("sum", [=] {
     double s = 0.0;
     for (uint32_t i = 0; i < kConsensusPartials; ++i) { s += p[i]; p[i] = 0.0; }
