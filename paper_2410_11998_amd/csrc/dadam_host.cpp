@@ -466,7 +466,7 @@ bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
 // one row with three sources, 3e8 elements: float32 (7 KB a wavefront) 32: 0.772, 18: 0.791, 14: 0.800, 11: 0.809,
 // 9: 0.780; bfloat16 (10 KB) 32: 0.744, 14: 0.770, 11: 0.787, 9: 0.805; s = 1 0.767 -> 0.809.  Short launches need
 // every wavefront (12000 pieces: 0.725 -> 0.670; 25000 in buckets 0.743 -> 0.713; 117000: 0.755 -> 0.779), and so do
-// the passes that load little (mixing 0.828 -> 0.625, accumulation).
+// the passes that load little (mixing 0.828 -> 0.625, accumulation).  Only one row was measured.
 uint32_t bounded_occupancy_lds(const dadam_handle* h, const Slot& slot, Phase phase, uint32_t n_pieces) {
   if (h->cfg.n_rows != 1 || phase == kMixOnly || !h->nontemporal || n_pieces < kBoundedPieces) return 0;
   if (h->lds_limit < kLdsPerUnit) return 0;  // the configuration keeps LDS for other kernels
