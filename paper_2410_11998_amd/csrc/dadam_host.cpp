@@ -92,7 +92,7 @@ struct dadam_handle {
   int vec = 4;
   uint32_t tile_elems = 0, direct_elems = 0, lds_bytes = 0;
   bool tile_possible = false;
-  uint64_t n_work_t = 0, n_work_d = 0;
+  uint64_t n_work_t = 0, n_work_d = 0, n_work_v = 0;
   Slot slots[DADAM_MAX_SLOTS];
   bool bound = false;
   const void* x_src[kMaxRows] = {};
@@ -154,6 +154,9 @@ int env_int(const char* name, int fallback) {
 constexpr int env_int(const char*, int fallback) { return fallback; }
 #endif
 
+// Elements of a tile of one vector a lane: what the loop kernel walks, and what the rules below count launches in.
+uint32_t vector_elems(const dadam_handle* h) { return (uint32_t)(kWave * h->vec); }
+
 // Build maximal runs of contiguous tensors and number the tiles of both tile grids.
 int plan(dadam_handle* h) {
   h->segs.clear();
@@ -172,24 +175,28 @@ int plan(dadam_handle* h) {
     }
     h->tensor_seg[k] = (uint32_t)(h->segs.size() - 1);
   }
-  uint64_t wt = 0, wd = 0, wm = 0;
+  uint64_t wt = 0, wd = 0, wm = 0, wv = 0;
   for (Segment& s : h->segs) {
     if (s.weight_decay != 0.f) h->decays = true;
     s.first_tile[kGridTile] = s.lo / h->tile_elems;
     s.first_tile[kGridDirect] = s.lo / h->direct_elems;
     s.first_tile[kGridMix] = s.lo / h->mix_tile_elems;
-    if (wt > 0x7fffffffull || wd > 0x7fffffffull) break;
+    s.first_tile[kGridVector] = s.lo / vector_elems(h);
+    if (wv > 0x7fffffffull || wd > 0x7fffffffull) break;
     s.work0[kGridTile] = (uint32_t)wt;
     s.work0[kGridDirect] = (uint32_t)wd;
     s.work0[kGridMix] = (uint32_t)wm;
+    s.work0[kGridVector] = (uint32_t)wv;
     wt += (s.hi - 1) / h->tile_elems - s.first_tile[kGridTile] + 1;
     wd += (s.hi - 1) / h->direct_elems - s.first_tile[kGridDirect] + 1;
+    wv += (s.hi - 1) / vector_elems(h) - s.first_tile[kGridVector] + 1;
     wm += (s.hi - 1) / h->mix_tile_elems - s.first_tile[kGridMix] + 1;
   }
   h->n_work_t = wt;
   h->n_work_d = wd;
   h->n_work_m = wm;
-  if (wt > 0x7fffffffull || wd * (h->cfg.n_rows + h->n_xcds) > 0x7fffffffull)  // direct mode pads rows up to the dies
+  h->n_work_v = wv;
+  if (wv > 0x7fffffffull || wd * (h->cfg.n_rows + h->n_xcds) > 0x7fffffffull)  // direct mode pads rows up to the dies
     return fail(nullptr, DADAM_EINVAL, "layout too large: more than 2^31-1 work items");
   return DADAM_OK;
 }
@@ -198,7 +205,7 @@ int plan(dadam_handle* h) {
 // s0 and end in segment s1.
 void work_range(const dadam_handle* h, Grid grid, uint32_t s0, uint32_t s1, uint64_t lo,
                 uint64_t hi, uint32_t* w0, uint32_t* w1) {
-  const uint64_t T = grid == kGridTile ? h->tile_elems : grid == kGridDirect ? h->direct_elems : h->mix_tile_elems;
+  const uint64_t T = grid == kGridTile ? h->tile_elems : grid == kGridDirect ? h->direct_elems : grid == kGridMix ? h->mix_tile_elems : vector_elems(h);
   const Segment& a = h->segs[s0];
   const Segment& b = h->segs[s1];
   *w0 = a.work0[grid] + (uint32_t)(lo / T - a.first_tile[grid]);
@@ -364,7 +371,7 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool de
     // at most eight sources (128 replicas: the step 0.76-0.79 against 0.48-0.49, mixing 0.50-0.74 against 0.40).
     const bool ordered = slot.reuse && direct_legal && h->n_xcds > 1;
     const bool pairs_stream = ordered && slot.max_degree <= 2 && h->cfg.n_cols > 16;
-    const bool lone_tile = ordered && slot.max_degree <= 8 && 2 * (uint64_t)h->lds_bytes > h->lds_limit;
+    const bool lone_tile = ordered && slot.max_degree <= 8 && 2 * (uint64_t)h->cfg.n_cols * kWave * 16u > h->lds_limit;
     *tile_mode = h->tile_possible && ((slot.reuse && !pairs_stream && !lone_tile) || !direct_legal);
     if (!*tile_mode && !direct_legal)
       return fail(h, DADAM_EALIAS, "in-place update of a shared source is impossible: tile does not fit in LDS");
@@ -399,12 +406,12 @@ uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(wa
 // 1.21, 1.13, 64 in loops of 32, 16, 16 1.14, 1.02, 1.08, 0.92, 0.83.
 int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   const uint64_t R = h->cfg.n_rows, G = slot.loops.size();
-  if (G == 0 || (R < 16 * G && (R < 8 * G || h->n_work_t > kFewTiles))) return 0;
-  if (!mix_only && h->decays && h->n_work_t * G > 32 * R && R < 56 * G && h->cfg.n_cols <= (uint32_t)kInlineRows) return 0;
+  if (G == 0 || (R < 16 * G && (R < 8 * G || h->n_work_v > kFewTiles))) return 0;
+  if (!mix_only && h->decays && h->n_work_v * G > 32 * R && R < 56 * G && h->cfg.n_cols <= (uint32_t)kInlineRows) return 0;
   for (uint32_t i = 0; i < R; ++i)
     for (int32_t c : h->inplace_cols[i])
       if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
-  const int waves = h->n_work_t * G <= (G == 1 && R < 28 ? 1 : 2) * kFewTiles ? 16 : 8;
+  const int waves = h->n_work_v * G <= (G == 1 && R < 28 ? 1 : 2) * kFewTiles ? 16 : 8;
   return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 
@@ -439,7 +446,7 @@ bool rows_stay_on_one_die(const dadam_handle* h, bool mix_only, uint32_t n_tiles
   if (mix_only || R < 64) return false;
   const bool wide = h->vec == 8;
   if (wide && R >= 72 && (R < 80 || R > 128)) return false;
-  const uint64_t elems = (uint64_t)n_tiles * h->tile_elems * R;
+  const uint64_t elems = (uint64_t)n_tiles * vector_elems(h) * R;
   return elems >= (R < 72 ? kManyElems : R < 96 ? 5 * kManyElems : wide ? kManyElems * 5 / 2 : kManyElems);
 }
 
@@ -567,7 +574,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     return DADAM_OK;
   }
   uint32_t w0 = 0, w1 = 0;
-  work_range(h, kGridTile, s0, s1, lo, hi, &w0, &w1);
+  work_range(h, kGridVector, s0, s1, lo, hi, &w0, &w1);
   const uint32_t n_tiles = w1 - w0;
   const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot, mix_only);
   const bool by_loops = loop_waves > 0;
@@ -575,7 +582,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
                          n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
-  const Grid grid = !tile_mode ? kGridDirect : mix_only && !by_loops ? kGridMix : kGridTile;
+  const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mix_only ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
@@ -594,8 +601,10 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.row_order = slot.d_loop_rows;
     shape.ut = 1;
     shape.waves = loop_waves;
+    if (h->nontemporal) a.xcd_block = kDieBlockLoops;
     lds = loop_lds_bytes(h, shape.waves);
   } else if (tile_mode) {
+    if (mix_only && h->nontemporal && shape.ut == 2) a.xcd_block = kDieBlockMix;
     a.row_ptr = slot.d_row_ptr;
     a.col = slot.d_col;
     a.w = slot.d_w;
@@ -613,7 +622,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
               : launch_direct((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase,
                               // where rows share sources the re-reads must find them in the cache
-                              h->nontemporal, slot.reuse, whole_items(h, mix_only, a.order, (uint64_t)n_tiles * h->tile_elems * h->cfg.n_rows),
+                              h->nontemporal, slot.reuse, whole_items(h, mix_only, a.order, (uint64_t)n_tiles * vector_elems(h) * h->cfg.n_rows),
                               a, w1 - w0, stream);
   if (e == (int)hipSuccess && consensus_out) e = launch_consensus_sum(partials, consensus_out, stream);
   if (e == (int)hipSuccess && own_partials && !recorded) h->partials_clear = true;
@@ -822,6 +831,15 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     delete h;
     return fail(nullptr, DADAM_EINVAL, "unsupported tile shape (waves %d, ut %d)", shape.waves, shape.ut);
   }
+  // Streaming float32 steps: two vectors a lane, which lie the way the memory serves best (see lane_start), up to the
+  // sources whose tile fits; sixteen wavefronts from 16 rows on.  Fraction of 8 TB/s, one vector by eight wavefronts / two by
+  // eight / two by sixteen, 3e8 to 2e9 elements: 16 rows 0.710 / 0.802 / 0.814, 24 rows 0.801 / 0.802 / 0.809, 48 rows 0.783 / 0.806 /
+  // 0.805, 72 rows 0.72 / 0.725 / 0.779; 8 rows 0.817 / 0.825 / 0.802, 4 rows by four wavefronts 0.816 / 0.820, by sixteen 0.794.
+  // In bfloat16 one vector has that layout already, and sixteen wavefronts lose (8 rows 0.813 / 0.783, 16 rows 0.780 / 0.770).
+  if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
+    shape.ut = 2;
+    if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
+  }
   h->shape = shape;
   h->tile_elems = (uint32_t)(kWave * h->vec * shape.ut);
   h->direct_elems = (uint32_t)(kWave * h->vec * kDirectItem);
@@ -831,13 +849,16 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // wavefront: two vectors per lane and four wavefronts, as long as that tile stays small enough
   // (32 KB) for five workgroups to share a CU's LDS.  Measured: 16 sources (32 KB) +3 % over the
   // step's shape; 64 sources (128 KB, one workgroup per CU) 0.68-0.75 of peak against 0.76 with the
-  // step's one-vector tile, so large source counts keep that.
+  // step's one-vector tile, so large source counts keep that.  Streaming float32 passes spread the lanes and take eight
+  // wavefronts up to 32 sources, then the step's sixteen (four / eight / sixteen: 12 sources 0.815 / 0.814, 16 sources 0.810 / 0.819, with
+  // the error 0.750 / 0.778, 24 sources 0.797 / 0.812 / 0.809, with the error 0.73 / 0.80 / 0.74, 48 sources 0.63 / 0.745 / 0.780).
   h->mix_shape = shape;
   if (cfg->n_cols * 2u * kWave * 16u <= 32768u && h->lds_limit >= 32768u && env_int("DADAM_TILE_UT", 0) == 0 &&
       env_int("DADAM_TILE_WAVES", 0) == 0) {
     h->mix_shape.ut = 2;
     h->mix_shape.waves = 4;
   }
+  if (h->nontemporal && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2) h->mix_shape.waves = 8;
   h->mix_shape.ut = env_int("DADAM_MIX_UT", h->mix_shape.ut);
   h->mix_shape.waves = env_int("DADAM_MIX_WAVES", h->mix_shape.waves);
   if (!tile_shape_supported(h->mix_shape) || cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u > h->lds_limit)
@@ -852,9 +873,9 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     hipError_t e = guard.err;
     if (e == hipSuccess && !h->segs.empty()) {
       const size_t n = h->segs.size(), bytes = n * sizeof(Segment);
-      std::vector<char> image(bytes + 3 * n * sizeof(uint32_t));
+      std::vector<char> image(bytes + kNumGrids * n * sizeof(uint32_t));
       memcpy(image.data(), h->segs.data(), bytes);
-      for (int g = 0; g < 3; ++g)
+      for (int g = 0; g < (int)kNumGrids; ++g)
         for (size_t k = 0; k < n; ++k)
           memcpy(image.data() + bytes + (g * n + k) * sizeof(uint32_t), &h->segs[k].work0[g], sizeof(uint32_t));
       e = hipMalloc((void**)&h->d_segs, image.size());

@@ -14,19 +14,19 @@ constexpr int kInlineRows = 64;           // up to this many, every pointer tabl
 constexpr int kWave = 64;            // gfx950 wavefront
 constexpr int kDirectItem = 8;  // direct and accumulate kernels: wavefronts (16-byte vectors per lane) per work item
 
+// Which of the four tile grids a launch walks: the fused step's tiles, the direct/accumulate
+// kernels' tiles, the tiles of the mixing-only launch, or tiles of one vector a lane (loop kernel).
+enum Grid : uint32_t { kGridTile = 0, kGridDirect = 1, kGridMix = 2, kGridVector = 3, kNumGrids = 4 };
+
 // A maximal run of contiguous tensors with the same hyper-parameters: elements [lo, hi) of every buffer.  Work items are tiles of a
 // fixed grid anchored at element 0, so that vector accesses are 16-byte aligned whenever the
 // buffers are; a tile that sticks out of [lo, hi) is clipped element by element.
 struct Segment {
   uint64_t lo, hi;
-  uint64_t first_tile[3];  // per Grid: index of the first tile of that grid that intersects the segment
-  uint32_t work0[3];       // per Grid: number of work items (tiles; per row in direct mode) in earlier segments
+  uint64_t first_tile[kNumGrids];  // per Grid: index of the first tile of that grid that intersects the segment
+  uint32_t work0[kNumGrids];       // per Grid: number of work items (tiles; per row in direct mode) in earlier segments
   float weight_decay;      // decoupled weight decay of the tensors in this segment
 };
-
-// Which of the three tile grids a launch walks: the fused step's tiles, the direct/accumulate
-// kernels' tiles, or the wider tiles of the mixing-only launch.
-enum Grid : uint32_t { kGridTile = 0, kGridDirect = 1, kGridMix = 2 };
 
 // How the workgroups of a direct-kernel launch walk the (piece, row) pairs.
 enum Order : uint32_t { kOrderLinear = 0, kOrderDieGroups = 1, kOrderDieBlocks = 2 };
@@ -129,6 +129,7 @@ using StepArgsFew = StepArgsFor<kFewRows, kFewRows>;
 static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 KB");
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
+constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
 constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there, whole_items, accumulate_whole_items
