@@ -80,15 +80,18 @@ __device__ __forceinline__ bool die_group_order(uint32_t b, uint32_t R, uint32_t
   return q < count;
 }
 
-// Direct mode in die blocks: all R rows of a piece run on one die, one after the other in the sharing order, and the dies
-// take runs of B pieces in turn, as in tile mode.  The grid is rounded up to whole dies (X ceil(n / X) R workgroups for n
-// pieces); a workgroup beyond the last piece has nothing to do (returns false).
+// Direct mode in die blocks: all R rows of a piece run on one die, and the dies take runs of B pieces in turn, as in tile
+// mode.  A die walks `run` of its pieces at a time, row after row in the sharing order (1: all rows of a piece, then the
+// next piece).  The grid is rounded up to whole dies (X ceil(n / X) R workgroups for n pieces); a workgroup beyond the last
+// piece has nothing to do (returns false).
 __device__ __forceinline__ bool die_block_piece(uint32_t b, uint32_t R, uint32_t X, uint32_t n, uint32_t B, uint32_t& piece,
-                                                uint32_t& position) {
-  const uint32_t x = b % X, j = b / X, index = j / R * X + x;
+                                                uint32_t& position, uint32_t run = 1) {
+  const uint32_t x = b % X, j = b / X, each = (n + X - 1) / X;  // pieces of a die
+  const uint32_t first = j / (run * R) * run, w = j - first * R, length = each - first < run ? each - first : run;
+  position = w / length;
+  const uint32_t index = (first + (w - position * length)) * X + x;
   const bool active = index < n;
   piece = active ? die_block_order(index, n, X, B) : 0;
-  position = j % R;
   return active;
 }
 
@@ -923,8 +926,7 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
   }
 }
 
-// Pieces are numbered element-major, row-minor, so that workgroups running at the same time work
-// on the same elements of different rows.
+// Which piece and row a workgroup takes is the launch's order (see rows_stay_on_one_die).
 template <typename XT, typename GT, int PHASE, int HINT, bool EXT, typename A>
 __device__ __forceinline__ void direct_entry(const A& a) {
   const int lane = threadIdx.x;
@@ -932,8 +934,9 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   uint32_t t, position;
   bool active = true;
   if (a.order == kOrderDieBlocks) {
-    // Rows share sources: a source comes from memory once and from the die's L2 for its other readers.
-    active = die_block_piece(blockIdx.x, n_rows, a.n_xcd, a.n_pieces, a.xcd_block, t, position);
+    // Rows share sources: a source comes from memory once and from the die's L2 for its other readers, whose turn
+    // comes at once or a run of pieces later.
+    active = die_block_piece(blockIdx.x, n_rows, a.n_xcd, a.n_pieces, a.xcd_block, t, position, a.die_run);
   } else if (a.order == kOrderDieGroups) {
     // Rows share sources.  Consecutive workgroup ids go to the device's X dies in turn; die x takes the
     // rows at positions [x R / X, (x + 1) R / X) of the sharing order (R = n_rows), tile after tile: the
@@ -1170,11 +1173,18 @@ __device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e
 template <typename GT, int VEC, int PHASE, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void acc_entry(const A& a) {
   const uint32_t n_rows = a.n_rows;
-  const uint32_t t = blockIdx.x / n_rows;
-  const int row = (int)(blockIdx.x - t * n_rows);
+  uint32_t t, row_at;
+  bool active = true;
+  if (a.order == kOrderDieBlocks) {
+    active = die_block_piece(blockIdx.x, n_rows, a.n_xcd, a.n_pieces, a.xcd_block, t, row_at, a.die_run);
+  } else {
+    t = blockIdx.x / n_rows;
+    row_at = blockIdx.x - t * n_rows;
+  }
+  const int row = (int)row_at;
   const PieceAt p = locate_piece<VEC>(a, t);
   const uint64_t e[1] = {lane_start<VEC, 1, NT>(p.index, p.lo, p.hi, (int)threadIdx.x)};
-  if (p.any) {
+  if (active && p.any) {
     if (p.full) acc_body<GT, VEC, PHASE, 1, false, NT, EXT>(a, row, e, p.lo, p.hi);
     else acc_body<GT, VEC, PHASE, 1, true, NT, EXT>(a, row, e, p.lo, p.hi);
   }
@@ -1186,17 +1196,19 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   constexpr uint64_t PIECE = (uint64_t)kWave * VEC, ITEM = PIECE * kDirectItem;
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t n_rows = a.n_rows;
-  const uint32_t item = blockIdx.x / n_rows;
-  const int row = (int)(blockIdx.x - item * n_rows);
+  uint32_t item, row_at;
+  const bool active = die_block_piece(blockIdx.x, a.n_rows, a.n_xcd, a.n_pieces, a.xcd_block, item, row_at, a.die_run);
+  const int row = (int)row_at;
   uint64_t tile_index, lo, hi;
   float wd;
   locate(a, a.work_begin + item, tile_index, lo, hi, wd);
   const uint64_t tbase = tile_index * ITEM;
   const uint64_t e0 = lane_start<VEC, 2, NT>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, NT>};
-  if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, false, NT, EXT>(a, row, e, lo, hi);
-  else acc_body<GT, VEC, PHASE, 2, true, NT, EXT>(a, row, e, lo, hi);
+  if (active) {  // uniform over the workgroup
+    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, false, NT, EXT>(a, row, e, lo, hi);
+    else acc_body<GT, VEC, PHASE, 2, true, NT, EXT>(a, row, e, lo, hi);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1288,10 +1300,6 @@ KernelFn tile_kernel_for_shape_nt(int phase, TileShape s) {
     if (s.waves == 8 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 8, 2, NT, EXT>(phase);
     if (s.waves == 16 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 16, 2, NT, EXT>(phase);
   }
-#ifdef DADAM_TUNING  // further shapes for measurements, same-type pairs only to bound the build time
-  if constexpr (XT::bytes == GT::bytes)
-    if (s.waves == 16 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 16, 1, NT, EXT>(phase);
-#endif
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>

@@ -286,6 +286,7 @@ void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
   a->n_rows = R;
   a->n_cols = C;
   a->n_xcd = h->n_xcds;
+  a->die_run = 1;
   a->xcd_block = (uint32_t)env_int("DADAM_XCD_BLOCK", (int)kDieBlockTiles);
 }
 
@@ -335,6 +336,9 @@ bool range_decays(const dadam_handle* h, bool whole, uint32_t tb, uint32_t te) {
     if (h->tensors[k].numel && h->tensors[k].weight_decay != 0.f) return true;
   return false;
 }
+
+// Large launches in die blocks: a die takes runs of `run` pieces (or items), row after row (see rows_stay_on_one_die).
+void set_die_run(uint32_t run, StepArgs* a) { a->die_run = a->xcd_block = run; }
 
 // Do direct launches of this slot walk its rows in the sharing order?
 bool ordered_rows(const dadam_handle* h, const Slot& slot) { return !slot.order.empty() && h->n_xcds > 1; }
@@ -440,10 +444,22 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
 //   112 rows   0.90  1.05   0.99  0.99         112 rows   0.94  1.02   1.00  0.99
 //   128 rows   1.00  1.03   0.98  0.98         128 rows   0.95  1.04   1.02  1.01     (3e8: 1.08)
 //   160 rows   0.98  0.99   1.04  0.99         160 rows   0.88  0.99   0.98  0.98
-bool rows_stay_on_one_die(const dadam_handle* h, bool mix_only, uint32_t n_tiles) {
+// That was with all rows of a piece one after the other.  Since large launches walk runs of 256 pieces a die row after row,
+// blocks are ahead of groups nearly everywhere: a die has the arrays of few rows in use at a time instead of those of all
+// (64 rows of 6 arrays are more pages than a compute unit's address translation holds), and rows that do not divide among the dies leave none
+// waiting.  Fraction of 8 TB/s, groups / piece by piece / runs of 64 / 256 / 512, two rows to a source: 64 rows of 26 million elements
+// 0.83 / 0.78 / 0.83 / 0.84 / 0.84, 18 rows 0.67 / - / 0.81 / 0.80 / 0.81, 32 rows 0.82 / 0.82 / 0.83 / 0.83 / 0.84, 40 rows 0.79 / - / 0.79 / 0.82 /
+// 0.82, bfloat16 18 rows 0.67 / - / 0.78 / 0.80 / 0.80; rings of 48 in bfloat16 0.79 / - / 0.80 / 0.80 / 0.80, of 64 0.80 / 0.72 / 0.80 /
+// 0.80 / 0.80, of 128 0.80 / 0.76 / 0.79 / 0.78 / 0.79 (bfloat16 0.76 / 0.78 / 0.79 / 0.79 / 0.79).  Launches that do not stream, groups' time
+// over that of runs of 256: 18 rows 1.24, 26 rows (bfloat16) 1.04, 64 rows 1.03-1.07, ring of 100 1.03-1.07, 20 rows of 250 thousand
+// elements 1.02, 32 rows 1.03 and 0.96.  Pairs of 32 to 63 rows and the larger numbers of rows below the sizes of the table have stayed
+// with groups, 1 to 4 % behind.
+bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles) {
   if (n_tiles < kManyTiles) return true;
   const uint32_t R = h->cfg.n_rows;
-  if (mix_only || R < 64) return false;
+  if (mix_only) return false;
+  if (!h->nontemporal) return true;
+  if (R < 64) return R < 32 || slot.max_degree > 2;
   const bool wide = h->vec == 8;
   if (wide && R >= 72 && (R < 80 || R > 128)) return false;
   const uint64_t elems = (uint64_t)n_tiles * vector_elems(h) * R;
@@ -586,7 +602,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
-  if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
+  if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
+  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
@@ -1122,8 +1139,15 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  const uint64_t elems = (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows;
-  int e = launch_accumulate((int)h->cfg.grad_dtype, fused_phase(h, t), h->nontemporal, accumulate_whole_items(h, elems), a, w1 - w0, hip_stream, h->vec);
+  const bool whole_items = accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
+  // Rows share nothing here, but a die that walks run after run row by row has few arrays in use at a time.  Fraction of 8 TB/s of
+  // the bytes moved, one row of a piece after the other / runs, 3e8 elements: 2 rows 0.80 / 0.79, 4 rows 0.80 / 0.82, 16 rows
+  // 0.75 / 0.80, 40 rows 0.61 / 0.81, 64 rows 0.67 / 0.81, 100 rows 0.63 / 0.80, bfloat16 parameters 24 rows 0.66 / 0.73, 128 rows 0.56 / 0.75.
+  if (h->nontemporal && h->cfg.n_rows >= 4) {  // whole items always go this way
+    a.order = kOrderDieBlocks;
+    set_die_run(whole_items ? kDieRunPieces / kDirectItem : kDieRunPieces, &a);
+  }
+  int e = launch_accumulate((int)h->cfg.grad_dtype, fused_phase(h, t), h->nontemporal, whole_items, a, w1 - w0, hip_stream, h->vec);
   if (e != (int)hipSuccess)
     return fail(h, DADAM_EHIP, "kernel launch failed: %s", hipGetErrorString((hipError_t)e));
   return DADAM_OK;

@@ -101,6 +101,7 @@ struct StepArgsFor {
   uint32_t n_loops;      // > 0: the loop kernel's launch (see launch_tile)
   uint32_t order;        // Order: how a launch of the row kernel walks pieces and rows
   uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
+  uint32_t die_run;      // pieces a die walks row after row (kOrderDieBlocks)
   uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
   uint32_t reserve_lds;  // direct kernels: LDS a workgroup reserves (see bounded_occupancy_lds)
@@ -129,6 +130,7 @@ using StepArgsFew = StepArgsFor<kFewRows, kFewRows>;
 static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 KB");
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
+constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks; measured, see rows_stay_on_one_die
 constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die

@@ -1,6 +1,7 @@
 // Where the lanes of a wavefront lie over a tile (lane_start and the distances between a lane's groups and vectors), compiled
 // for the host from the kernel source's own text: over the tiles of a launch every element of the range comes up once,
-// groups of four are whole, tiles that are full touch nothing outside the range, and whole blocks are spread.
+// groups of four are whole, tiles that are full touch nothing outside the range, and whole blocks are spread.  And the order
+// in which a die walks runs of pieces row after row: every piece of every row once, and rows outside, pieces inside a run.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -11,6 +12,31 @@ namespace emu {
 #include "layout.inc"
 }
 using namespace emu;
+
+static void runs() {
+  long bad = 0;
+  for (uint32_t X : {1u, 2u, 8u})
+    for (uint32_t R : {1u, 2u, 18u, 64u, 160u})
+      for (uint32_t n : {1u, 7u, 8u, 9u, 255u, 2047u, 2048u, 2049u, 5000u})
+        for (uint32_t run : {1u, 3u, 32u, 256u})
+          for (uint32_t B : {32u, 256u}) {
+            std::vector<int> seen((size_t)n * R, 0);
+            const uint32_t grid = (n + X - 1) / X * X * R;
+            uint32_t last = 0;
+            for (uint32_t b = 0; b < grid; ++b) {
+              uint32_t piece = n, position = R;
+              const bool active = die_block_piece(b, R, X, n, B, piece, position, run);
+              if (piece >= n || position >= R) { ++bad; continue; }
+              if (active) ++seen[(size_t)piece * R + position];
+              if (b % X == 0) {  // the first die: its positions rise within a run and start again with the next
+                bad += position < last && position != 0;
+                last = position;
+              }
+            }
+            for (int c : seen) bad += c != 1;
+          }
+  printf("runs: %s\n", bad ? "FAIL" : "right");
+}
 
 template <int VEC, int U, bool STREAM>
 long run(uint64_t lo, uint64_t hi) {
@@ -50,6 +76,7 @@ void sweep() {
 }
 
 int main() {
+  runs();
   sweep<4, 1, false>();
   sweep<4, 2, false>();
   sweep<8, 1, false>();

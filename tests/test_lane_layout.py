@@ -5,6 +5,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 import torch
 
@@ -22,12 +23,45 @@ def test_every_element_has_one_lane(tmp_path):
     src = open(os.path.join(bld.CSRC, "dadam_device.h")).read()
     cut = lambda a, b: src[src.index(a):src.index(b, src.index(a))]
     (tmp_path / "layout.inc").write_text(cut("template <bool STREAM>\nconstexpr int kGroupStep", "typedef float f4")
+                                         + cut("__device__ __forceinline__ uint32_t die_block_order", "// Direct mode with a sharing order")
+                                         + cut("__device__ __forceinline__ bool die_block_piece", "// Where a lane's first group")
                                          + cut("template <int VEC, int U, bool STREAM>", "// One step of the search of all lanes"))
     exe = str(tmp_path / "layout")
     subprocess.run([clang, "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-I", str(tmp_path),
                     os.path.join(os.path.dirname(os.path.abspath(__file__)), "emulate_lane_layout.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and r.stdout.count(": right") == 8, (r.stdout, r.stderr[-2000:])
+    assert r.returncode == 0 and r.stdout.count(": right") == 9, (r.stdout, r.stderr[-2000:])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,deg,tiles,dtype", [(18, 2, 1024, "f32"), (26, 2, 1100, "bf16"), (100, 3, 1027, "f32"), (65, 2, 1500, "f32")])
+def test_rows_walked_in_runs_give_the_tile_kernels_bits(rows, deg, tiles, dtype):
+    """Launches of 1024 tiles and more that do not stream: a die walks runs of pieces row after row, the last run shorter,
+    dies with a piece fewer; a step of every phase against the tile kernel, with decay and ragged ends."""
+    print("case", rows, deg, tiles, dtype, flush=True)
+    elems = 64 * (8 if dtype == "bf16" else 4)
+    layout = WL.pack([("a", (900 * elems + 13,)), ("b", (5,)), ("c", ((tiles - 901) * elems - 40,))])
+    w = np.float32(1.0) / np.float32(deg)
+    csr = (np.arange(0, rows * deg + 1, deg, dtype=np.int32), np.array([(i + k) % rows for i in range(rows) for k in range(deg)], np.int32),
+           np.full(rows * deg, w, np.float32))
+    sims = [H.GpuSim(rows, rows, layout, H.HyperF32(s=2), [csr], dtype, dtype, weight_decay=[0.1, 0.0, 0.05], pad_fill=777.0) for _ in range(2)]
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    for c in range(rows):
+        sims[0].x_src[c].normal_(0.0, 0.02, generator=gen)
+        sims[1].x_src[c].copy_(sims[0].x_src[c])
+    for t, flags in ((1, B.DADAM_FUSE_ACCUM), (2, B.DADAM_FUSE_ACCUM), (3, 0)):
+        grads = [torch.empty(layout.d, device="cuda:0").normal_(0.0, 1e-2, generator=gen).to(H.TORCH_DT[dtype]) for _ in range(rows)]
+        for sim, mode in zip(sims, (0, B.DADAM_FORCE_TILE)):
+            sim.step(grads, t, 0, flags | mode)
+        torch.cuda.synchronize()
+        for i in range(rows):
+            for name in ("x_dst", "m", "v", "b"):
+                assert torch.equal(getattr(sims[0], name)[i], getattr(sims[1], name)[i]), (t, i, name)
+        for sim in sims:
+            sim.swap()
+    for sim in sims:
+        sim.close()
 
 
 @pytest.mark.gpu
@@ -42,6 +76,8 @@ def test_every_element_has_one_lane(tmp_path):
     (32, "one_peer", "f32", "f32", False),      # direct kernel, rows in groups per die, mixing by whole items
     (64, "one_peer", "bf16", "f32", True),
     (40, "one_peer", "f32", "f32", True),
+    (18, "one_peer", "bf16", "bf16", True),     # runs of pieces row after row
+    (33, "ring", "f32", "f32", True),
 ])
 def test_streaming_kernels_give_the_bits_of_small_handles(rows, topology, params, grads, decay):
     """A layout that streams, cut into tensors at and beside the edges of tiles and blocks; the same buffers, piece by piece,
