@@ -84,9 +84,9 @@ extern "C" {
  * by two or more rows and the tile fits in LDS (also when an in-place row needs it), direct mode otherwise -
  * and also, where measured faster, for rows of at most two sources on more than 16 sources and for rows of at
  * most eight sources when a CU would hold only one workgroup of the tile (see dadam_get_row_order).
- * dadam_slot_uses_tile_mode reports the choice.  Two kinds of launch are then given to other kernels where that was
- * measured faster: rows that share whole neighbour lists (one sum for all of them), and launches of few tiles
- * (a wavefront per row; the same sums in the same order). */
+ * dadam_slot_uses_tile_mode reports the choice.  Three kinds of launch are then given to other kernels where that was
+ * measured faster: rows that share whole neighbour lists (one sum for all of them), launches of few tiles and very
+ * large ones (a wavefront per row in place of the tile, or the other way round; the same sums in the same order). */
 #define DADAM_FUSE_ACCUM 1u   /* also do lines 9-13 (accumulate and fold) in the same pass         */
 #define DADAM_FORCE_DIRECT 2u /* every row streams its sources from global memory                  */
 #define DADAM_FORCE_TILE 4u   /* stage each source tile once in LDS and update all rows from it    */

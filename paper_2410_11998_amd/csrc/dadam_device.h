@@ -1300,6 +1300,8 @@ KernelFn tile_kernel_for_shape_nt(int phase, TileShape s) {
     if (s.waves == 8 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 8, 2, NT, EXT>(phase);
     if (s.waves == 16 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 16, 2, NT, EXT>(phase);
   }
+  if constexpr (EXT)
+    if (s.waves == 16 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 16, 1, NT, EXT>(phase);
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>

@@ -352,6 +352,9 @@ void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t l
   a->weight_decay = h->segs.front().weight_decay;
 }
 
+// Does a compute unit hold one workgroup of the tile, even with one vector a lane?
+bool lone_tile(const dadam_handle* h) { return 2 * (uint64_t)h->cfg.n_cols * kWave * 16u > h->lds_limit; }
+
 // Decide tile or direct mode for this slot and these flags; checks in-place legality.  decays: the launch applies
 // weight decay.
 int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool decays, bool* tile_mode) {
@@ -375,8 +378,8 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool de
     // at most eight sources (128 replicas: the step 0.76-0.79 against 0.48-0.49, mixing 0.50-0.74 against 0.40).
     const bool ordered = slot.reuse && direct_legal && h->n_xcds > 1;
     const bool pairs_stream = ordered && slot.max_degree <= 2 && h->cfg.n_cols > 16;
-    const bool lone_tile = ordered && slot.max_degree <= 8 && 2 * (uint64_t)h->cfg.n_cols * kWave * 16u > h->lds_limit;
-    *tile_mode = h->tile_possible && ((slot.reuse && !pairs_stream && !lone_tile) || !direct_legal);
+    const bool alone_streams = ordered && slot.max_degree <= 8 && lone_tile(h);
+    *tile_mode = h->tile_possible && ((slot.reuse && !pairs_stream && !alone_streams) || !direct_legal);
     if (!*tile_mode && !direct_legal)
       return fail(h, DADAM_EALIAS, "in-place update of a shared source is impossible: tile does not fit in LDS");
   }
@@ -481,6 +484,24 @@ bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t 
 bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
   const uint32_t R = h->cfg.n_rows;
   return h->nontemporal && elems >= kManyElems && ((R > 32 && R <= 64) || (R > 80 && R < 128));
+}
+
+// Streaming launches of rows that share sources for which the tile kernel and the direct one have changed places since
+// lanes are spread, sixteen wavefronts share a tile and dies walk runs of pieces.  usual: what choose_mode says.
+// Fraction of 8 TB/s, tile / direct, 3e8 elements:
+//   steps of rows of three sources: 24 of them 0.80 / 0.80, 32 0.78 / 0.80, 48 0.78 / 0.80, 64 0.78 / 0.80, bfloat16 32 0.78 / 0.80, 48 0.77 /
+//   0.80; of six (32 rows) and seven (64 rows) the tile stays ahead, 0.80 / 0.74;
+//   mixing in pairs: 18 rows 0.81 / 0.57, 24 rows 0.80 / 0.74, 28 rows 0.80 / 0.72 (bfloat16 0.72 / 0.58, 0.73 / 0.70, 0.75 / 0.70);
+//   96 rows, whose tile leaves a compute unit one workgroup: steps with four sources a row 0.71 / 0.71, five 0.71 / 0.67, six 0.70 /
+//   0.64, seven 0.70 / 0.60 (bfloat16 four 0.73 / 0.75, five 0.73 / 0.74, six 0.74 / 0.73, seven 0.73 / 0.68), mixing with
+//   three (128 rows) 0.63 / 0.66, four 0.59 / 0.48, seven 0.51 / 0.36 (bfloat16 four 0.46 / 0.48, six 0.41 / 0.39).
+// Launches that do not stream stay: 128 rows of seven, 1e7 elements, 0.48 / 0.60.
+bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles, bool usual) {
+  if (!h->nontemporal || n_tiles < kManyTiles) return usual;
+  const uint32_t C = h->cfg.n_cols;
+  if (usual) return mix_only || slot.max_degree > 3 || C < 32;
+  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5);
+  return mix_only && C < 32;
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
@@ -596,6 +617,9 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
+  if (!by_loops && !few_tiles && !consensus_out && !(flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) && slot.reuse &&
+      h->n_xcds > 1 && h->tile_possible && direct_is_legal(h, slot, decays))
+    tile_mode = staging_is_faster(h, slot, mix_only, n_tiles, tile_mode);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
   const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mix_only ? kGridMix : kGridTile;
@@ -856,6 +880,11 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
     shape.ut = 2;
     if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
+  } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
+    // A compute unit holds one workgroup of the tile: sixteen wavefronts keep more of it busy.  us, eight / sixteen: steps of 96
+    // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
+    // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
+    shape.waves = env_int("DADAM_TILE_WAVES", 16);
   }
   h->shape = shape;
   h->tile_elems = (uint32_t)(kWave * h->vec * shape.ut);

@@ -238,6 +238,7 @@ int launch_consensus_sum(double* partials, double* out, void* stream) {
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? TBF16::vec : TF32::vec; }
 bool tile_shape_supported(TileShape s) {
   if (s.ut == 2 && (s.waves == 8 || s.waves == 16)) return s.nontemporal;  // of float32 parameters
+  if (s.ut == 1 && s.waves == 16) return true;                            // of more than 64 sources
   return (s.waves == 4 && s.ut == 2) || ((s.waves == 4 || s.waves == 8) && s.ut == 1);
 }
 

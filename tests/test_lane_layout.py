@@ -78,6 +78,8 @@ def test_rows_walked_in_runs_give_the_tile_kernels_bits(rows, deg, tiles, dtype)
     (40, "one_peer", "f32", "f32", True),
     (18, "one_peer", "bf16", "bf16", True),     # runs of pieces row after row
     (33, "ring", "f32", "f32", True),
+    (96, "exp", "f32", "f32", True),            # tile of sixteen wavefronts, one workgroup to a compute unit
+    (96, "exp", "bf16", "bf16", False),
 ])
 def test_streaming_kernels_give_the_bits_of_small_handles(rows, topology, params, grads, decay):
     """A layout that streams, cut into tensors at and beside the edges of tiles and blocks; the same buffers, piece by piece,
