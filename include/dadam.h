@@ -98,7 +98,8 @@ typedef struct dadam_handle dadam_handle; /* opaque, owned by the library */
 
 /* One tensor of the packed layout: elements [offset_elems, offset_elems + numel) of every
  * per-replica buffer.  Tensors must be listed in increasing offset order and must not overlap;
- * elements between tensors (padding) are never read or written.  weight_decay >= 0 is the decoupled
+ * elements between tensors (padding) are never written, and what they hold is never used (a 16-byte load at the edge of
+ * a tensor may take up to three of them along).  weight_decay >= 0 is the decoupled
  * weight decay of this tensor (0 = plain Adam; e.g. 3e-5 on all but the normalisation parameters in
  * the paper's ResNet-50 recipe).  flags is reserved and must be 0. */
 typedef struct {

@@ -86,10 +86,15 @@ __device__ __forceinline__ bool die_group_order(uint32_t b, uint32_t R, uint32_t
 // piece has nothing to do (returns false).
 __device__ __forceinline__ bool die_block_piece(uint32_t b, uint32_t R, uint32_t X, uint32_t n, uint32_t B, uint32_t& piece,
                                                 uint32_t& position, uint32_t run = 1) {
-  const uint32_t x = b % X, j = b / X, each = (n + X - 1) / X;  // pieces of a die
-  const uint32_t first = j / (run * R) * run, w = j - first * R, length = each - first < run ? each - first : run;
-  position = w / length;
-  const uint32_t index = (first + (w - position * length)) * X + x;
+  const uint32_t x = b % X, j = b / X;
+  uint32_t at = j / R;  // piece of the die
+  position = j - at * R;
+  if (run > 1) {
+    const uint32_t each = (n + X - 1) / X, first = at / run * run, w = j - first * R, length = each - first < run ? each - first : run;
+    position = w / length;
+    at = first + (w - position * length);
+  }
+  const uint32_t index = at * X + x;
   const bool active = index < n;
   piece = active ? die_block_order(index, n, X, B) : 0;
   return active;
@@ -181,8 +186,13 @@ __device__ __forceinline__ void store_elem(void* base, uint64_t e, float v) {
 // whole.  (Giving a lane 8 consecutive elements instead makes each float32 state access two
 // instructions that each touch half of every line: measured 5-13 % slower once stores are involved.)
 // e is a multiple of 4, so every group is 16-byte (float32) or 8-byte (bfloat16) aligned.
-// MASKED groups that are not wholly inside [lo, hi) touch only the elements that are; the others
-// read as zero.
+// Clipped tiles (CLIP) store only elements inside [lo, hi).  Their loads: kElements touches nothing else, and the rest reads
+// as zero; one load an element, each waited for before the next group's can be issued.  kGroups loads whole groups, from
+// the nearest group that holds an element of the range, so that all of a row's loads are in flight at once; what lies
+// outside the range is loaded with it or repeated, and never used.  kGroupsZeroed does the same for sources and clears what lies
+// outside (the consensus error counts on that).  Both need whole groups to end within the buffer (clip_of).  us, elements / groups:
+// 8 replicas of 300 odd-sized tensors, bfloat16, four steps 68.6 / 59.8, one row of 700 such tensors 32.3 / 28.1 (bfloat16 37.5 /
+// 33.8), ring of 12 x 20 tensors 26.2 / 22.0, 100 rows of seven sources x 400 tensors, bfloat16 1285 / 957.
 // Streaming accesses: every global datum of a step is touched exactly once, so full-group
 // accesses may carry the non-temporal hint (NT) and leave the caches to nobody in particular.
 // Which classes of access carry the hint when a handle streams (all eight combinations measured:
@@ -202,14 +212,20 @@ __device__ __forceinline__ void vstore(V* p, V v) {
   else *p = v;
 }
 
-template <typename T, int VEC, int H, bool MASKED, bool NT>
+enum Clip : int { kWhole = 0, kElements = 1, kGroups = 2, kGroupsZeroed = 3 };
+__device__ __forceinline__ uint64_t nearest_group(uint64_t e, uint64_t lo, uint64_t hi) {
+  const uint64_t first = lo & ~(uint64_t)3, last = (hi - 1) & ~(uint64_t)3;
+  return e < first ? first : e > last ? last : e;
+}
+
+template <typename T, int VEC, int H, int CLIP, bool NT>
 __device__ __forceinline__ void load_vals(const void* base, uint64_t e, uint64_t lo, uint64_t hi,
                                           float (&out)[VEC]) {
   static_assert(VEC == 4 || (VEC == 8 && H >= 4), "a lane holds one or two groups of four elements");
 #pragma unroll
   for (int h = 0; h < VEC / 4; ++h) {
-    const uint64_t eh = e + (uint64_t)h * H;
-    if (!MASKED || (eh >= lo && eh + 4 <= hi)) {
+    const uint64_t at = e + (uint64_t)h * H, eh = CLIP == kGroups ? nearest_group(at, lo, hi) : at;
+    if (CLIP != kElements || (eh >= lo && eh + 4 <= hi)) {
       if constexpr (T::bytes == 4) {
         f4 v = vload<NT && kNtStream>(reinterpret_cast<const f4*>(reinterpret_cast<const float*>(base) + eh));
         out[4 * h + 0] = v.x; out[4 * h + 1] = v.y; out[4 * h + 2] = v.z; out[4 * h + 3] = v.w;
@@ -228,14 +244,14 @@ __device__ __forceinline__ void load_vals(const void* base, uint64_t e, uint64_t
   }
 }
 
-template <typename T, int VEC, int H, bool MASKED, bool NT>
+template <typename T, int VEC, int H, int CLIP, bool NT>
 __device__ __forceinline__ void store_vals(void* base, uint64_t e, uint64_t lo, uint64_t hi,
                                            const float (&in)[VEC]) {
   static_assert(VEC == 4 || (VEC == 8 && H >= 4), "a lane holds one or two groups of four elements");
 #pragma unroll
   for (int h = 0; h < VEC / 4; ++h) {
     const uint64_t eh = e + (uint64_t)h * H;
-    if (!MASKED || (eh >= lo && eh + 4 <= hi)) {
+    if (CLIP == kWhole || (eh >= lo && eh + 4 <= hi)) {
       if constexpr (T::bytes == 4) {
         f4 v;
         v.x = in[4 * h + 0]; v.y = in[4 * h + 1]; v.z = in[4 * h + 2]; v.w = in[4 * h + 3];
@@ -260,24 +276,33 @@ __device__ __forceinline__ void store_vals(void* base, uint64_t e, uint64_t lo, 
 // that runs once has a loop-invariant address, the compiler's loop-invariant code motion then "promotes" the
 // location to a register and re-creates the store behind the loop - without the non-temporal hint (seen with
 // the bfloat16 one-vector tile kernels: 1.2 % slower on the ring of 8; the compile test counts the hints).
-template <typename T, int VEC, int H, bool MASKED, bool NT, int UT>
+template <typename T, int VEC, int H, int CLIP, bool NT, int UT>
 __device__ __forceinline__ void store_vectors(void* base, const uint64_t (&e)[UT], uint64_t lo, uint64_t hi,
                                               const float (&in)[UT][VEC]) {
   if constexpr (UT == 1) {
-    store_vals<T, VEC, H, MASKED, NT>(base, e[0], lo, hi, in[0]);
+    store_vals<T, VEC, H, CLIP, NT>(base, e[0], lo, hi, in[0]);
   } else {
 #pragma unroll
-    for (int u = 0; u < UT; ++u) store_vals<T, VEC, H, MASKED, NT>(base, e[u], lo, hi, in[u]);
+    for (int u = 0; u < UT; ++u) store_vals<T, VEC, H, CLIP, NT>(base, e[u], lo, hi, in[u]);
   }
 }
 
 // The 16 raw bytes of a lane's parameter vector (4 float32, or 2 x 4 bfloat16 in the two groups
 // described above), as they are parked in LDS.
-template <typename XT, int H, bool MASKED, bool NT>
+template <typename XT, int H, int CLIP, bool NT>
 __device__ __forceinline__ u4 load_raw(const void* base, uint64_t e, uint64_t lo, uint64_t hi) {
   if constexpr (XT::bytes == 4) {
-    if (!MASKED || (e >= lo && e + 4 <= hi))
-      return vload<NT && kNtSource>(reinterpret_cast<const u4*>(reinterpret_cast<const float*>(base) + e));
+    if (CLIP != kElements || (e >= lo && e + 4 <= hi)) {
+      const uint64_t eh = CLIP >= kGroups ? nearest_group(e, lo, hi) : e;
+      u4 v = vload<NT && kNtSource>(reinterpret_cast<const u4*>(reinterpret_cast<const float*>(base) + eh));
+      if constexpr (CLIP == kGroupsZeroed) {
+        v.x = e + 0 >= lo && e + 0 < hi ? v.x : 0u;
+        v.y = e + 1 >= lo && e + 1 < hi ? v.y : 0u;
+        v.z = e + 2 >= lo && e + 2 < hi ? v.z : 0u;
+        v.w = e + 3 >= lo && e + 3 < hi ? v.w : 0u;
+      }
+      return v;
+    }
     u4 r = {0u, 0u, 0u, 0u};
     const uint32_t* p = reinterpret_cast<const uint32_t*>(base);
     if (e + 0 >= lo && e + 0 < hi) r.x = p[e + 0];
@@ -291,9 +316,13 @@ __device__ __forceinline__ u4 load_raw(const void* base, uint64_t e, uint64_t lo
     u2 half[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const uint64_t eh = e + (uint64_t)h * H;
-      if (!MASKED || (eh >= lo && eh + 4 <= hi)) {
+      const uint64_t at = e + (uint64_t)h * H, eh = CLIP >= kGroups ? nearest_group(at, lo, hi) : at;
+      if (CLIP != kElements || (eh >= lo && eh + 4 <= hi)) {
         half[h] = vload<NT && kNtSource>(reinterpret_cast<const u2*>(p + eh));
+        if constexpr (CLIP == kGroupsZeroed) {
+          half[h].x &= (at + 0 >= lo && at + 0 < hi ? 0xFFFFu : 0u) | (at + 1 >= lo && at + 1 < hi ? 0xFFFF0000u : 0u);
+          half[h].y &= (at + 2 >= lo && at + 2 < hi ? 0xFFFFu : 0u) | (at + 3 >= lo && at + 3 < hi ? 0xFFFF0000u : 0u);
+        }
       } else {
         uint32_t q[4];
 #pragma unroll
@@ -401,6 +430,12 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
     hi = shi < a.clip_hi ? shi : a.clip_hi;
     weight_decay = seg[s].weight_decay;
   }
+}
+
+// How the loads of a tile that [lo, hi) cuts are done.
+template <typename A>
+__device__ __forceinline__ int clip_of(const A& a, bool full, uint64_t hi) {
+  return full ? kWhole : hi + 3 <= (a.d | 3) ? kGroups : kElements;
 }
 
 // Pointers of the bound buffers.  EXT = false: from the argument block (at most kInlineRows rows and
@@ -533,32 +568,32 @@ __device__ __forceinline__ float list_w(const RowList& r, int k) {
 // tile mode
 // ---------------------------------------------------------------------------------------------
 // The stream inputs of one row of a tile: gradient, moments, accumulator (whatever the phase needs).
-template <typename GT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT, typename A>
+template <typename GT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void load_row_inputs(const A& a, int i, const uint64_t (&e)[UT], uint64_t lo,
                                                 uint64_t hi, float (&g)[UT][VEC], float (&mh)[UT][VEC],
                                                 float (&vh)[UT][VEC], float (&b)[UT][VEC]) {
   if constexpr (Needs<PHASE>::grad) {
     const void* gp = a.grad[i];
 #pragma unroll
-    for (int u = 0; u < UT; ++u) load_vals<GT, VEC, kGroupStep<NT>, MASKED, NT>(gp, e[u], lo, hi, g[u]);
+    for (int u = 0; u < UT; ++u) load_vals<GT, VEC, kGroupStep<NT>, CLIP, NT>(gp, e[u], lo, hi, g[u]);
   }
   if constexpr (Needs<PHASE>::moments_in) {
     const float* mp = m_hat_of<EXT>(a, i);
     const float* vp = v_hat_of<EXT>(a, i);
 #pragma unroll
-    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, MASKED, NT>(mp, e[u], lo, hi, mh[u]);
+    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(mp, e[u], lo, hi, mh[u]);
 #pragma unroll
-    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, MASKED, NT>(vp, e[u], lo, hi, vh[u]);
+    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(vp, e[u], lo, hi, vh[u]);
   }
   if constexpr (Needs<PHASE>::acc_in) {
     const float* bp = acc_of<EXT>(a, i);
 #pragma unroll
-    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, MASKED, NT>(bp, e[u], lo, hi, b[u]);
+    for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(bp, e[u], lo, hi, b[u]);
   }
 }
 
 // Mixing from LDS, the update of Algorithm 3 and the stores of one row of a tile.
-template <typename XT, int PHASE, int VEC, int UT, bool MASKED, bool NT, bool EXT, typename A>
+template <typename XT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, RowList rl,
                                            const uint64_t (&e)[UT], uint64_t lo, uint64_t hi, float wd, int lane,
                                            float (&g)[UT][VEC], float (&mh)[UT][VEC], float (&vh)[UT][VEC],
@@ -618,15 +653,15 @@ __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, Row
     for (int j = 0; j < VEC; ++j)
       xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[u][j]);
 
-  store_vectors<XT, VEC, kGroupStep<NT>, MASKED, NT>(dst_of<EXT>(a, i), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, MASKED, NT>(acc_of<EXT>(a, i), e, lo, hi, b);
+  store_vectors<XT, VEC, kGroupStep<NT>, CLIP, NT>(dst_of<EXT>(a, i), e, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(acc_of<EXT>(a, i), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, kGroupStep<NT>, MASKED, NT>(m_hat_of<EXT>(a, i), e, lo, hi, mh);
-    store_vectors<TF32, VEC, kGroupStep<NT>, MASKED, NT>(v_hat_of<EXT>(a, i), e, lo, hi, vh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(m_hat_of<EXT>(a, i), e, lo, hi, mh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(v_hat_of<EXT>(a, i), e, lo, hi, vh);
   }
 }
 
-template <typename XT, typename GT, int PHASE, int W, int UT, bool MASKED, bool NT, bool EXT, typename A>
+template <typename XT, typename GT, int PHASE, int W, int UT, int CLIP, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, uint64_t lo,
                                           uint64_t hi, float wd, uint32_t tile_id, int lane, int wave) {
   constexpr int VEC = XT::vec;
@@ -652,7 +687,7 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
         if (c < n_cols) {
           const void* src = src_of<EXT>(a, c);
 #pragma unroll
-          for (int u = 0; u < UT; ++u) r[k][u] = load_raw<XT, kGroupStep<NT>, MASKED, NT>(src, e[u], lo, hi);
+          for (int u = 0; u < UT; ++u) r[k][u] = load_raw<XT, kGroupStep<NT>, CLIP, NT>(src, e[u], lo, hi);
         }
       }
 #pragma unroll
@@ -669,7 +704,7 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
       const void* src = src_of<EXT>(a, c);
       u4 r[UT];
 #pragma unroll
-      for (int u = 0; u < UT; ++u) r[u] = load_raw<XT, kGroupStep<NT>, MASKED, NT>(src, e[u], lo, hi);
+      for (int u = 0; u < UT; ++u) r[u] = load_raw<XT, kGroupStep<NT>, CLIP, NT>(src, e[u], lo, hi);
 #pragma unroll
       for (int u = 0; u < UT; ++u) lds[(c * UT + u) * kWave + lane] = r[u];
     }
@@ -726,8 +761,8 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
     const RowList rl = rl_next;
     rl_next = load_row_list(a, rp, i + W < n_rows ? i + W : i, lane);
     float g[UT][VEC], mh[UT][VEC], vh[UT][VEC], b[UT][VEC];
-    load_row_inputs<GT, PHASE, VEC, UT, MASKED, NT, EXT>(a, i, e, lo, hi, g, mh, vh, b);
-    finish_row<XT, PHASE, VEC, UT, MASKED, NT, EXT>(a, lds, i, rl, e, lo, hi, wd, lane, g, mh, vh, b);
+    load_row_inputs<GT, PHASE, VEC, UT, CLIP, NT, EXT>(a, i, e, lo, hi, g, mh, vh, b);
+    finish_row<XT, PHASE, VEC, UT, CLIP, NT, EXT>(a, lds, i, rl, e, lo, hi, wd, lane, g, mh, vh, b);
   }
 }
 
@@ -755,8 +790,12 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
   const uint64_t start = lane_start<VEC, UT, NT>(tile_index, lo, hi, lane);
-  if (full) tile_body<XT, GT, PHASE, W, UT, false, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
-  else tile_body<XT, GT, PHASE, W, UT, true, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
+  // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
+  constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
+  const int clip = clip_of(a, full, hi);
+  if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
+  else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
+  else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -800,7 +839,7 @@ struct OwnSource {
   bool found = false;
   float x[VEC];
 };
-template <typename XT, int N, bool FIRST, int U, int H, bool MASKED, bool NT, bool EXT, typename A>  // NT: hint on the source loads
+template <typename XT, int N, bool FIRST, int U, int H, int CLIP, bool NT, bool EXT, typename A>  // NT: hint on the source loads
 __device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, const uint64_t (&e)[U], uint64_t lo,
                                             uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
   constexpr int VEC = XT::vec;
@@ -811,7 +850,7 @@ __device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k
     const void* src = src_of<EXT>(a, list_col(rl, k + q));
     wk[q] = list_w(rl, k + q);
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[q][u] = load_raw<XT, H, MASKED, NT>(src, e[u], lo, hi);
+    for (int u = 0; u < U; ++u) r[q][u] = load_raw<XT, H, CLIP, NT>(src, e[u], lo, hi);
   }
 #pragma unroll
   for (int q = 0; q < N; ++q)
@@ -834,10 +873,10 @@ __device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k
 // with two bfloat16 vectors a lane (16 sums live) they are two sources after the first four: four more cost 76 registers
 // and with them the seventh wavefront (mixing in pairs, 24 to 64 rows, 0.96-0.98 -> 1.00-1.02 of the rate of workgroups of
 // 67 registers, 96 rows of three 1.07 -> 1.13, rows of seven the same).
-template <typename XT, int U, int H, bool MASKED, bool NT, bool EXT, typename A>
+template <typename XT, int U, int H, int CLIP, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, const uint64_t (&e)[U], uint64_t lo,
                                            uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
-#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, U, H, MASKED, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
+#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, U, H, CLIP, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
   constexpr int FIRST_BATCH = U == 1 ? 8 : 4;
   if (rl.deg < FIRST_BATCH) {
     switch (rl.deg) {
@@ -882,7 +921,7 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, con
 
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
-template <typename XT, typename GT, int PHASE, int U, bool MASKED, int HINT, bool EXT, typename A>
+template <typename XT, typename GT, int PHASE, int U, int CLIP, int HINT, bool EXT, typename A>
 __device__ __forceinline__ void direct_body(const A& a, int position, int row, const uint64_t (&e)[U], uint64_t lo,
                                             uint64_t hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
@@ -895,14 +934,14 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_position_list(a, position, lane);
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
-  load_row_inputs<GT, PHASE, VEC, U, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+  load_row_inputs<GT, PHASE, VEC, U, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
   // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
   // sum where the row lists itself (loading them again would be a second trip to memory after the first).
   const bool decays = !Needs<PHASE>::mixing_only && wd != 0.0f;
   OwnSource<VEC> own;
   own.col = decays ? row : -1;
   float mix[U][VEC];
-  mix_direct<XT, U, H, MASKED, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
+  mix_direct<XT, U, H, CLIP, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
   float xo[U][VEC];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -910,7 +949,7 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
 #pragma unroll
     for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
     if (decays) {
-      if (!own.found) unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e[u], lo, hi), own.x);
+      if (!own.found) unpack_raw<XT>(load_raw<XT, H, CLIP, false>(src_of<EXT>(a, row), e[u], lo, hi), own.x);
 #pragma unroll
       for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
     }
@@ -918,11 +957,11 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
     for (int j = 0; j < VEC; ++j)
       xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[j]);
   }
-  store_vectors<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  store_vectors<XT, VEC, H, CLIP, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
@@ -956,8 +995,11 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   const PieceAt p = locate_piece<XT::vec>(a, t);
   const uint64_t e[1] = {lane_start<XT::vec, 1, HINT != 0>(p.index, p.lo, p.hi, lane)};
   if (active && p.any) {  // uniform over the workgroup
-    if (p.full) direct_body<XT, GT, PHASE, 1, false, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
-    else direct_body<XT, GT, PHASE, 1, true, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
+    constexpr int CUT = HINT == 1 && EXT ? kElements : kGroups;  // see tile_entry
+    const int clip = clip_of(a, p.full, p.hi);
+    if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
+    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
+    else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
   }
 }
 
@@ -990,11 +1032,11 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a
     float mix[2][VEC];
     void* to = dst_of<EXT>(a, row);
     if (tbase >= lo && tbase + ITEM <= hi) {
-      mix_direct<XT, 2, kGroupStep<HINT != 0>, false, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
-      store_vectors<XT, VEC, kGroupStep<HINT != 0>, false, HINT != 0>(to, e, lo, hi, mix);
+      mix_direct<XT, 2, kGroupStep<HINT != 0>, kWhole, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kWhole, HINT != 0>(to, e, lo, hi, mix);
     } else {
-      mix_direct<XT, 2, kGroupStep<HINT != 0>, true, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
-      store_vectors<XT, VEC, kGroupStep<HINT != 0>, true, HINT != 0>(to, e, lo, hi, mix);
+      mix_direct<XT, 2, kGroupStep<HINT != 0>, kElements, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kElements, HINT != 0>(to, e, lo, hi, mix);
     }
   }
 }
@@ -1016,8 +1058,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
   const uint64_t e0 = lane_start<VEC, 2, HINT != 0>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, HINT != 0>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, false, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
-    else direct_body<XT, GT, PHASE, 2, true, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
+    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, kWhole, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
+    else direct_body<XT, GT, PHASE, 2, kElements, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
   }
 }
 
@@ -1033,7 +1075,7 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM: the bytes moved are
 // those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
-template <typename XT, typename GT, int PHASE, bool MASKED, int HINT, bool EXT, typename A>
+template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A>
 __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t start, uint64_t lo, uint64_t hi,
                                           float wd, int lane, int wave, int waves) {
   constexpr bool NT = HINT != 0;
@@ -1056,12 +1098,12 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   const int row_v = a.row_order[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
   float g[1][VEC], mh[1][VEC], vh[1][VEC], b[1][VEC];
   int row = __builtin_amdgcn_readlane(row_v, 0);
-  if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+  if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
   if (rl.deg > 0) {
     float part[1][VEC];
     OwnSource<VEC> none;
     none.col = -1;
-    mix_direct<XT, 1, H, MASKED, HINT == 1, EXT>(a, rl, lane, e, lo, hi, part, none);
+    mix_direct<XT, 1, H, CLIP, HINT == 1, EXT>(a, rl, lane, e, lo, hi, part, none);
 #pragma unroll
     for (int h = 0; h < VEC / 4; ++h) {
       f4 v = {part[0][4 * h], part[0][4 * h + 1], part[0][4 * h + 2], part[0][4 * h + 3]};
@@ -1083,21 +1125,21 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
     for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
     if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
       float own[VEC];
-      unpack_raw<XT>(load_raw<XT, H, MASKED, false>(src_of<EXT>(a, row), e[0], lo, hi), own);
+      unpack_raw<XT>(load_raw<XT, H, CLIP, false>(src_of<EXT>(a, row), e[0], lo, hi), own);
 #pragma unroll
       for (int j = 0; j < VEC; ++j) decay[j] = wd * own[j];
     }
 #pragma unroll
     for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[0][j], mh[0][j], vh[0][j], b[0][j], decay[j]);
-    store_vals<XT, VEC, H, MASKED, NT>(dst_of<EXT>(a, row), e[0], lo, hi, xo);
-    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e[0], lo, hi, b[0]);
+    store_vals<XT, VEC, H, CLIP, NT>(dst_of<EXT>(a, row), e[0], lo, hi, xo);
+    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e[0], lo, hi, b[0]);
     if constexpr (Needs<PHASE>::moments_out) {
-      store_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e[0], lo, hi, mh[0]);
-      store_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e[0], lo, hi, vh[0]);
+      store_vals<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e[0], lo, hi, mh[0]);
+      store_vals<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e[0], lo, hi, vh[0]);
     }
     if (r + 1 < my_rows) {
       row = __builtin_amdgcn_readlane(row_v, r + 1);
-      load_row_inputs<GT, PHASE, VEC, 1, MASKED, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+      load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
     }
   }
 }
@@ -1122,8 +1164,11 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   const bool full = tbase >= lo && tbase + TILE <= hi;
   const int waves = (int)(blockDim.x / kWave);
   const uint64_t start = lane_start<XT::vec, 1, HINT != 0>(tile_index, lo, hi, lane);
-  if (full) loop_body<XT, GT, PHASE, false, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
-  else loop_body<XT, GT, PHASE, true, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
+  constexpr int CUT = HINT != 0 && EXT ? kElements : kGroups;  // see tile_entry
+  const int clip = clip_of(a, full, hi);
+  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
+  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1141,30 +1186,30 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
   }
 }
 
-template <typename GT, int VEC, int PHASE, int U, bool MASKED, bool NT, bool EXT, typename A>
+template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A>
 __device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi) {
   constexpr int H = kGroupStep<NT>;
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
 #pragma unroll
-  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, MASKED, NT>(a.grad[row], e[u], lo, hi, g[u]);
+  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(a.grad[row], e[u], lo, hi, g[u]);
   if constexpr (Needs<PHASE>::moments_out) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e[u], lo, hi, mh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e[u], lo, hi, mh[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e[u], lo, hi, vh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e[u], lo, hi, vh[u]);
   }
   if constexpr (Needs<PHASE>::acc_in) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e[u], lo, hi, b[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e[u], lo, hi, b[u]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, MASKED, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, MASKED, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, MASKED, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
@@ -1185,8 +1230,11 @@ __device__ __forceinline__ void acc_entry(const A& a) {
   const PieceAt p = locate_piece<VEC>(a, t);
   const uint64_t e[1] = {lane_start<VEC, 1, NT>(p.index, p.lo, p.hi, (int)threadIdx.x)};
   if (active && p.any) {
-    if (p.full) acc_body<GT, VEC, PHASE, 1, false, NT, EXT>(a, row, e, p.lo, p.hi);
-    else acc_body<GT, VEC, PHASE, 1, true, NT, EXT>(a, row, e, p.lo, p.hi);
+    constexpr int CUT = NT && EXT ? kElements : kGroups;  // see tile_entry
+    const int clip = clip_of(a, p.full, p.hi);
+    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi);
+    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi);
+    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi);
   }
 }
 
@@ -1206,8 +1254,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   const uint64_t e0 = lane_start<VEC, 2, NT>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, NT>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, false, NT, EXT>(a, row, e, lo, hi);
-    else acc_body<GT, VEC, PHASE, 2, true, NT, EXT>(a, row, e, lo, hi);
+    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, e, lo, hi);
+    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, e, lo, hi);
   }
 }
 

@@ -89,6 +89,10 @@ struct dadam_handle {
   uint64_t n_work_m = 0;
   bool nontemporal = false;
   bool decays = false;  // some tensor carries weight decay
+  // Few blocks of elements lie in one segment: lanes are hardly ever spread and every tile needs its segment searched, so
+  // streaming launches keep the shapes and orders of contiguous lanes.  Fraction of 8 TB/s, contiguous / spread choices, segments of
+  // 1100 elements: exp. graph of 16 0.74 / 0.70, of 64 0.68 / 0.66, pairs of 64 0.53 / 0.51.
+  bool short_segments = false;
   int vec = 4;
   uint32_t tile_elems = 0, direct_elems = 0, lds_bytes = 0;
   bool tile_possible = false;
@@ -157,8 +161,8 @@ constexpr int env_int(const char*, int fallback) { return fallback; }
 // Elements of a tile of one vector a lane: what the loop kernel walks, and what the rules below count launches in.
 uint32_t vector_elems(const dadam_handle* h) { return (uint32_t)(kWave * h->vec); }
 
-// Build maximal runs of contiguous tensors and number the tiles of both tile grids.
-int plan(dadam_handle* h) {
+// Build maximal runs of contiguous tensors.
+void find_segments(dadam_handle* h) {
   h->segs.clear();
   h->tensor_seg.assign(h->tensors.size(), UINT32_MAX);
   for (size_t k = 0; k < h->tensors.size(); ++k) {
@@ -175,6 +179,11 @@ int plan(dadam_handle* h) {
     }
     h->tensor_seg[k] = (uint32_t)(h->segs.size() - 1);
   }
+  h->short_segments = h->segs.size() * (uint64_t)kLongSegment > h->cfg.d;
+}
+
+// Number the tiles of every tile grid.
+int plan(dadam_handle* h) {
   uint64_t wt = 0, wd = 0, wm = 0, wv = 0;
   for (Segment& s : h->segs) {
     if (s.weight_decay != 0.f) h->decays = true;
@@ -286,6 +295,7 @@ void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
   a->n_rows = R;
   a->n_cols = C;
   a->n_xcd = h->n_xcds;
+  a->d = h->cfg.d;
   a->die_run = 1;
   a->xcd_block = (uint32_t)env_int("DADAM_XCD_BLOCK", (int)kDieBlockTiles);
 }
@@ -462,7 +472,7 @@ bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only
   const uint32_t R = h->cfg.n_rows;
   if (mix_only) return false;
   if (!h->nontemporal) return true;
-  if (R < 64) return R < 32 || slot.max_degree > 2;
+  if (R < 64) return !h->short_segments && (R < 32 || slot.max_degree > 2);
   const bool wide = h->vec == 8;
   if (wide && R >= 72 && (R < 80 || R > 128)) return false;
   const uint64_t elems = (uint64_t)n_tiles * vector_elems(h) * R;
@@ -497,11 +507,12 @@ bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
 //   three (128 rows) 0.63 / 0.66, four 0.59 / 0.48, seven 0.51 / 0.36 (bfloat16 four 0.46 / 0.48, six 0.41 / 0.39).
 // Launches that do not stream stay: 128 rows of seven, 1e7 elements, 0.48 / 0.60.
 bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles, bool usual) {
-  if (!h->nontemporal || n_tiles < kManyTiles) return usual;
+  if (n_tiles < kManyTiles) return usual;
   const uint32_t C = h->cfg.n_cols;
+  if (usual && h->short_segments) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
   if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5);
-  return mix_only && C < 32;
+  return mix_only && C < 32 && !h->short_segments;
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
@@ -617,8 +628,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
-  if (!by_loops && !few_tiles && !consensus_out && !(flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) && slot.reuse &&
-      h->n_xcds > 1 && h->tile_possible && direct_is_legal(h, slot, decays))
+  if (h->nontemporal && !by_loops && !few_tiles && !consensus_out &&
+      !(flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) && slot.reuse && h->n_xcds > 1 && h->tile_possible && direct_is_legal(h, slot, decays))
     tile_mode = staging_is_faster(h, slot, mix_only, n_tiles, tile_mode);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
@@ -627,7 +638,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
-  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles) set_die_run(kDieRunPieces, &a);
+  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
@@ -877,7 +888,8 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // eight / two by sixteen, 3e8 to 2e9 elements: 16 rows 0.710 / 0.802 / 0.814, 24 rows 0.801 / 0.802 / 0.809, 48 rows 0.783 / 0.806 /
   // 0.805, 72 rows 0.72 / 0.725 / 0.779; 8 rows 0.817 / 0.825 / 0.802, 4 rows by four wavefronts 0.816 / 0.820, by sixteen 0.794.
   // In bfloat16 one vector has that layout already, and sixteen wavefronts lose (8 rows 0.813 / 0.783, 16 rows 0.780 / 0.770).
-  if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
+  find_segments(h);
+  if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
     shape.ut = 2;
     if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
   } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
@@ -904,7 +916,8 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     h->mix_shape.ut = 2;
     h->mix_shape.waves = 4;
   }
-  if (h->nontemporal && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2) h->mix_shape.waves = 8;
+  if (h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2)
+    h->mix_shape.waves = 8;
   h->mix_shape.ut = env_int("DADAM_MIX_UT", h->mix_shape.ut);
   h->mix_shape.waves = env_int("DADAM_MIX_WAVES", h->mix_shape.waves);
   if (!tile_shape_supported(h->mix_shape) || cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u > h->lds_limit)
@@ -1168,11 +1181,11 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  const bool whole_items = accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
+  const bool whole_items = !h->short_segments && accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
   // Rows share nothing here, but a die that walks run after run row by row has few arrays in use at a time.  Fraction of 8 TB/s of
   // the bytes moved, one row of a piece after the other / runs, 3e8 elements: 2 rows 0.80 / 0.79, 4 rows 0.80 / 0.82, 16 rows
   // 0.75 / 0.80, 40 rows 0.61 / 0.81, 64 rows 0.67 / 0.81, 100 rows 0.63 / 0.80, bfloat16 parameters 24 rows 0.66 / 0.73, 128 rows 0.56 / 0.75.
-  if (h->nontemporal && h->cfg.n_rows >= 4) {  // whole items always go this way
+  if (h->nontemporal && !h->short_segments && h->cfg.n_rows >= 4) {  // whole items always go this way
     a.order = kOrderDieBlocks;
     set_die_run(whole_items ? kDieRunPieces / kDirectItem : kDieRunPieces, &a);
   }

@@ -116,6 +116,7 @@ struct StepArgsFor {
   uint32_t work_begin;  // first work item (in tiles) of this launch
   uint32_t n_xcd;       // dies that consecutive workgroup ids are dealt over (tile order)
   uint32_t xcd_block;   // tile mode: tiles per block; blocks go to the dies in turn (0: one contiguous share each)
+  uint64_t d;                 // elements of a buffer
   uint64_t clip_lo, clip_hi;  // element range of this launch (whole layout or a tensor range)
   double* partials;           // kConsensusPartials doubles (device), used by kMixConsensus only
   Scalars s;
@@ -130,6 +131,7 @@ using StepArgsFew = StepArgsFor<kFewRows, kFewRows>;
 static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 KB");
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
+constexpr uint32_t kLongSegment = 65536;  // elements of two blocks of spread lanes; measured, see dadam_handle::short_segments
 constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks; measured, see rows_stay_on_one_die
 constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves

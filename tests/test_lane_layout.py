@@ -33,6 +33,22 @@ def test_every_element_has_one_lane(tmp_path):
     assert r.returncode == 0 and r.stdout.count(": right") == 9, (r.stdout, r.stderr[-2000:])
 
 
+def test_groups_at_the_edges_of_a_range(tmp_path):
+    clang = "/opt/rocm/llvm/bin/clang++" if os.path.exists("/opt/rocm/llvm/bin/clang++") else shutil.which("clang++")
+    if clang is None:
+        pytest.skip("no clang++")
+    src = open(os.path.join(bld.CSRC, "dadam_device.h")).read()
+    b = src.index("// Algorithm 3, lines 6-13, for one element.")
+    (tmp_path / "helpers.inc").write_text(src[src.index("typedef float f4 __attribute__"):src.rindex("// ----", 0, b)])
+    a = src.index("template <typename A>\n__device__ __forceinline__ int clip_of")
+    (tmp_path / "clip.inc").write_text(src[a:src.index("// Pointers of the bound buffers.", a)])
+    exe = str(tmp_path / "clip")
+    subprocess.run([clang, "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-I", str(tmp_path),
+                    os.path.join(os.path.dirname(os.path.abspath(__file__)), "emulate_group_clip.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout == "bad 0, tiles by groups many, by elements some\n", (r.stdout, r.stderr[-2000:])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,deg,tiles,dtype", [(18, 2, 1024, "f32"), (26, 2, 1100, "bf16"), (100, 3, 1027, "f32"), (65, 2, 1500, "f32")])
 def test_rows_walked_in_runs_give_the_tile_kernels_bits(rows, deg, tiles, dtype):
@@ -90,7 +106,7 @@ def test_streaming_kernels_give_the_bits_of_small_handles(rows, topology, params
     cols = 3 if share else rows
     chunk = (512 << 20) // (24 * rows) // 65536 * 65536          # the largest piece that does not stream, less than a block
     sizes = [40003, 1, 65536 - 40004 - 40, 32768, 3 * 32768 - 5, 16384 + 2]
-    sizes.append(chunk + 70001 - sum(sizes))
+    sizes.append(max(chunk + 70001, 8 * 65536) - sum(sizes))       # and long segments on average
     layout = WL.pack([("t%d" % k, (n,)) for k, n in enumerate(sizes)])
     wd = [0.1 * (k % 2) for k in range(len(sizes))] if decay else None
     csr = {"ring": lambda: WL.ring(rows), "exp": lambda: WL.static_exponential(rows), "share": WL.node_share_ring,
@@ -108,10 +124,10 @@ def test_streaming_kernels_give_the_bits_of_small_handles(rows, topology, params
         for sim in sims:
             sim.x_src[c][mask] = x.to(sim.x_src[c].dtype)[mask]
     grad = [noise(1e-2).to(H.TORCH_DT[grads]) for _ in range(rows)]
-    # handles over [0, chunk) and [chunk, d) of the reference's buffers
+    # handles over [0, chunk), [chunk, 2 chunk), ... of the reference's buffers
     xdt, gdt = [B.DADAM_BF16 if t == "bf16" else B.DADAM_F32 for t in (params, grads)]
     small = []
-    for lo, hi in ((0, chunk), (chunk, layout.d)):
+    for lo, hi in [(k, min(k + chunk, layout.d)) for k in range(0, layout.d, chunk)]:
         parts = [(max(int(o), lo), min(int(o) + int(n), hi), 0.0 if wd is None else wd[k])
                  for k, (o, n) in enumerate(zip(layout.offsets, layout.numels)) if int(o) < hi and int(o) + int(n) > lo]
         h = B.dadam_init(rows, cols, hi - lo, [a - lo for a, _, _ in parts], [b - a for a, b, _ in parts], xdt, gdt, hp.lr, hp.beta1,
