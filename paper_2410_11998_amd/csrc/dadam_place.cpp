@@ -7,6 +7,9 @@
 // sixteen 64 MiB sources and sixteen outputs runs at 0.78-0.80 of peak when half of its buffers sit in one third
 // and half in another and at 0.61-0.73 when all sit in one, repeatably, and timing it over pairs of 1 GiB chunks
 // tells which chunks share a third.
+// Those figures are of passes with contiguous lanes.  Since streaming kernels spread a wavefront over two places they run at
+// 0.77-0.83 wherever their arrays lie, the pass included: on such a card the timings find no consistent picture, and the rule
+// for an allocation that covers the device places the buffers.
 //
 // This file holds the bookkeeping around such timings (host only, testable with a model of the memory in place
 // of the GPU) and the probe that produces them.  Nothing of the method is computed here; the probe calls the
