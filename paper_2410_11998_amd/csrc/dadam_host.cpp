@@ -865,8 +865,8 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   if (h->n_xcds > 64) { delete h; return fail(nullptr, DADAM_EINVAL, "n_xcds out of range"); }
 
   // tile geometry: 16 bytes per lane and vector, `ut` vectors per lane, all source buffers' slices
-  // of one tile resident in LDS.  Measured on MI355X: one vector per lane (many small workgroups)
-  // streams best; eight wavefronts per group, four when there are fewer than eight rows to deal out.
+  // of one tile resident in LDS.  One vector per lane (many small workgroups) and eight wavefronts per group, four when there
+  // are fewer than eight rows to deal out; larger launches below.
   h->vec = vec_elems((int)cfg->param_dtype);
   TileShape shape;
   shape.ut = 1;
