@@ -35,8 +35,8 @@
  *     moments, accumulator) are DEVICE memory owned by the caller; the library never allocates,
  *     frees or copies them and never synchronises a stream.  The library owns only small metadata
  *     (segment table, CSR slots) on host and device.  (One set-up call is the exception and says so:
- *     dadam_place_by_timing overwrites the empty arena it is given, holds 2 GiB of its own while it runs
- *     and returns when its measurements are done.)
+ *     dadam_place_by_timing overwrites the empty arena it is given and returns when its measurements
+ *     are done.)
  *   - Launching entry points enqueue work on the given HIP stream (a hipStream_t passed as
  *     void*; NULL = the default stream) and return at once.  The caller keeps every buffer alive
  *     and unmodified until that work has finished.
@@ -289,11 +289,14 @@ int dadam_pack_offsets(const uint64_t* numel, uint32_t n, uint32_t align_elems, 
  * Errors: DADAM_EINVAL if a pointer is null, n == 0, or the buffers do not fit. */
 int dadam_spread_offsets(const uint64_t* nbytes, uint32_t n, uint64_t arena_bytes, uint64_t* offsets);
 
-/* Layout advice for HBM, part 2: where to put the buffers.  Measured on MI355X: the same step over
- * the same bytes sustains 0.62-0.66 of peak bandwidth when the buffers it streams together all lie
+/* Layout advice for HBM, part 2: where to put the buffers.  Measured on MI355X: a pass whose wavefronts read and
+ * write contiguous kilobytes sustains 0.62-0.66 of peak bandwidth when the buffers it streams together all lie
  * inside one third (96 GiB) of the device's physical memory - which is where a fresh process's
  * allocations land - and 0.78-0.79 when every group of buffers that is streamed together lies half
- * in one third and half in another.  Nobody outside the driver sees physical addresses, and where the
+ * in one third and half in another.  The library's own streaming kernels have their lanes apart (two places 32 or 64 KB
+ * from each other) and depend on it little: placed / ordinary allocations 0.795 / 0.806 (16 float32 replicas of 124
+ * million elements), 0.795 / 0.815 (one row of 355 million), 0.813 / 0.833 (64 replicas of 26 million), 0.801 / 0.780 (8
+ * bfloat16 replicas of 774 million).  Placement is for the last kind, and for a caller's own passes over the same buffers.  Nobody outside the driver sees physical addresses, and where the
  * driver puts one allocation relative to another is not predictable (measured: an arena pushed into
  * place by an allocation made before it, or placed by the amount of memory in use, lands elsewhere and
  * runs at 0.64-0.72).  What does hold is that ONE allocation of nearly the whole device (within 16 GiB of
@@ -341,9 +344,9 @@ int dadam_deal_offsets(const uint64_t* nbytes, uint32_t n, uint64_t lo0, uint64_
  *
  * Where the thirds of the physical memory begin inside a caller's allocation cannot be computed (a large
  * allocation is pieced together from whatever is free: made first, its bytes [0, 96 GiB) lie in one third; made
- * after 100 GiB of other allocations, the second boundary was seen at 160 GiB), but it can be measured: the
- * library's mixing pass over sixteen 64 MiB sources and sixteen outputs runs at 0.78-0.80 of peak when half of
- * its buffers sit in one third and half in another, and at 0.61-0.73 when all sit in one.
+ * after 100 GiB of other allocations, the second boundary was seen at 160 GiB), but it can be measured: a copy of
+ * sixteen 64 MiB sources to sixteen outputs by contiguous kilobytes runs at 0.80-0.82 of peak when half of
+ * its buffers sit in one third and half in another, and at 0.61-0.75 when all sit in one.
  *
  * dadam_find_stretches: the bookkeeping.  `rate(off_a, off_b, ctx)` is the fraction of peak a streaming pass
  * sustains with half of its buffers in the DADAM_PROBE_CHUNK_BYTES at arena offset off_a and half in those at
@@ -362,8 +365,8 @@ int dadam_deal_offsets(const uint64_t* nbytes, uint32_t n, uint64_t lo0, uint64_
  *
  * dadam_place_by_timing: the whole procedure on a device.  `arena` is DEVICE memory (2 MiB aligned,
  * arena_bytes long, contents are overwritten: call it before anything is stored there).  The library times
- * its own pass over the arena (about half a second, some hundreds of short launches on the null stream, 2 GiB
- * of temporary device memory), finds the stretches, chooses the regions, confirms them with one more pass
+ * such a pass over the arena (about half a second, some hundreds of short launches on the null stream, no
+ * memory besides the arena), finds the stretches, chooses the regions, confirms them with one more pass
  * across the two regions and one inside each, and deals the buffers; if that yields nothing it falls back to
  * dadam_place_offsets (device_total_bytes is passed on).  offsets[n] and *report say what was done.  Synchronous.
  * Errors: DADAM_EINVAL, DADAM_EALIGN, DADAM_EHIP. */
@@ -373,7 +376,7 @@ int dadam_deal_offsets(const uint64_t* nbytes, uint32_t n, uint64_t lo0, uint64_
 #define DADAM_POLICY_TIMED_REGIONS 1u  /* two regions found by timing, dealt with report.every             */
 #define DADAM_POLICY_RULE_REGIONS 2u   /* dadam_place_offsets' two regions (arena covers the device)        */
 #define DADAM_POLICY_EQUAL_DISTANCES 3u
-#define DADAM_NOTE_NO_PROBE 1u         /* arena too small for the probe, one buffer only, or no 2 GiB to spare */
+#define DADAM_NOTE_NO_PROBE 1u         /* arena too small for the probe, or one buffer only                   */
 #define DADAM_NOTE_NO_PICTURE 2u       /* the timings gave no consistent picture of the thirds              */
 #define DADAM_NOTE_NO_ROOM 3u          /* no two stretches of different thirds hold the buffers             */
 #define DADAM_NOTE_NOT_CONFIRMED 4u    /* the confirming passes disagreed with the stretches                */
@@ -389,7 +392,7 @@ typedef struct {
   uint32_t every;          /* DADAM_POLICY_TIMED_REGIONS: every `every`-th buffer lies in the second region */
   uint32_t note;           /* 0, or why the timing was not used: DADAM_NOTE_* */
   uint32_t n_stretches;
-  uint32_t probe_launches; /* mixing passes the probe launched */
+  uint32_t probe_launches; /* passes the probe launched */
   dadam_stretch stretches[DADAM_MAX_STRETCHES];
   uint64_t regions[4];     /* lo0, hi0, lo1, hi1 (lo1 = hi1 = 0: one region) */
   float rate_across;       /* fraction of peak of the confirming pass across the regions, 0 if none ran */

@@ -149,6 +149,9 @@ struct TileShape {
   bool nontemporal;  // streaming hint on every full-vector global access
 };
 
+// The pass that the placement probe times: float32 streams of it, elements of a stream to a workgroup.
+constexpr uint32_t kProbeStreams = 16, kProbeTile = 512;
+
 // Launchers.  All of them enqueue on `stream` and return the hipError_t of the launch as int.
 // xdt / gdt are DADAM_F32 | DADAM_BF16.  n_work is the number of tiles in this launch.
 // launch_tile with a.n_loops > 0 launches the loop kernel, shape.waves wavefronts a workgroup.
@@ -165,6 +168,9 @@ int launch_accumulate(int gdt, Phase phase, bool nontemporal, bool whole_items, 
 // Consensus error: clear the partial sums / add them up in a fixed order into *out (device) and clear them.
 int launch_consensus_zero(double* partials, void* stream);
 int launch_consensus_sum(double* partials, double* out, void* stream);
+
+// The placement probe's pass: dst[k] = src[k] for kProbeStreams streams of `elems` (a multiple of kProbeTile) float32 elements.
+int launch_probe(const void* const* src, void* const* dst, uint64_t elems, uint32_t n_xcd, void* stream);
 
 // The partial-sum array that lives in the library's device image (no allocation): its address on the
 // current device and its capacity in doubles.  Returns a hipError_t as int.

@@ -85,6 +85,35 @@ __global__ __launch_bounds__(256) void k_consensus_sum(double* partials, double*
 }
 
 // ---------------------------------------------------------------------------------------------
+// the pass that the placement probe times: sixteen streams in, sixteen out
+// ---------------------------------------------------------------------------------------------
+// Two contiguous kilobytes of every stream to a workgroup of four wavefronts, all of them read before any is written.  Bound by
+// HBM, and with lanes side by side by where the arrays lie: 0.81 of 8 TB/s across two thirds of the memory, 0.72-0.75 inside
+// one.  (Mixing passes of the library spread their lanes, see lane_start, and run alike everywhere: timed in place of
+// this one they show no thirds.  LDS reserved to hold fewer workgroups a unit brings the two levels closer, 0.815 / 0.75 with 53 KB.)
+struct ProbeArgs {
+  const float* src[kProbeStreams];
+  float* dst[kProbeStreams];
+  uint32_t n_xcd;
+};
+__global__ __launch_bounds__(256) void k_probe(const ProbeArgs a) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t tile = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, kDieBlockTiles);
+  const uint64_t e = (uint64_t)tile * kProbeTile + 4 * lane;
+  f4 v[kProbeStreams / 4][2];
+#pragma unroll
+  for (uint32_t k = 0; k < kProbeStreams / 4; ++k)
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u) v[k][u] = vload<true>(reinterpret_cast<const f4*>(a.src[4 * k + wave] + e + u * 4 * kWave));
+  __syncthreads();
+#pragma unroll
+  for (uint32_t k = 0; k < kProbeStreams / 4; ++k)
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u) vstore<true>(reinterpret_cast<f4*>(a.dst[4 * k + wave] + e + u * 4 * kWave), v[k][u]);
+}
+
+// ---------------------------------------------------------------------------------------------
 // dispatch tables
 // ---------------------------------------------------------------------------------------------
 template <typename GT, int VEC, bool NT, bool EXT>
@@ -233,6 +262,18 @@ int launch_consensus_zero(double* partials, void* stream) {
 int launch_consensus_sum(double* partials, double* out, void* stream) {
   void* args[] = {&partials, &out};
   return enqueue((KernelFn)k_consensus_sum, 1, 256, args, 0, stream);
+}
+
+int launch_probe(const void* const* src, void* const* dst, uint64_t elems, uint32_t n_xcd, void* stream) {
+  if (elems % kProbeTile != 0 || n_xcd == 0) return (int)hipErrorInvalidValue;
+  ProbeArgs a;
+  for (uint32_t k = 0; k < kProbeStreams; ++k) {
+    a.src[k] = static_cast<const float*>(src[k]);
+    a.dst[k] = static_cast<float*>(dst[k]);
+  }
+  a.n_xcd = n_xcd;
+  void* args[] = {&a};
+  return enqueue((KernelFn)k_probe, (uint32_t)(elems / kProbeTile), 256, args, 0, stream);
 }
 
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? TBF16::vec : TF32::vec; }

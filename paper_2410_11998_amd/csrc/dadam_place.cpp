@@ -1,20 +1,15 @@
 // Placement of a caller's device buffers inside ONE large allocation ("arena"), by measurement.
 //
-// On an MI355X a streaming step sustains 0.62-0.66 of peak HBM bandwidth when the arrays it streams together lie
-// inside one third (96 GiB) of the card's physical memory and 0.78-0.79 when half of them lie in one third and
-// half in another.  Physical addresses are not visible and a large allocation is pieced together from whatever
-// is free, so where the thirds begin inside an arena has to be found out: the library's own mixing pass over
-// sixteen 64 MiB sources and sixteen outputs runs at 0.78-0.80 of peak when half of its buffers sit in one third
-// and half in another and at 0.61-0.73 when all sit in one, repeatably, and timing it over pairs of 1 GiB chunks
-// tells which chunks share a third.
-// Those figures are of passes with contiguous lanes.  Since streaming kernels spread a wavefront over two places they run at
-// 0.77-0.83 wherever their arrays lie, the pass included: on such a card the timings find no consistent picture, and the rule
-// for an allocation that covers the device places the buffers.
+// On an MI355X a pass over many arrays whose wavefronts read and write contiguous kilobytes sustains 0.61-0.73 of peak HBM
+// bandwidth when all its arrays lie inside one third (96 GiB) of the card's physical memory and 0.78-0.80 when half of them lie
+// in one third and half in another.  Physical addresses are not visible and a large allocation is pieced together from
+// whatever is free, so where the thirds begin inside an arena has to be found out: such a pass over sixteen 64 MiB sources and
+// sixteen outputs (k_probe), timed over pairs of 1 GiB chunks, tells which chunks share a third.
 //
 // This file holds the bookkeeping around such timings (host only, testable with a model of the memory in place
-// of the GPU) and the probe that produces them.  Nothing of the method is computed here; the probe calls the
-// public entry points of the library like any other client.
+// of the GPU) and the probe that produces them.  Nothing of the method is computed here.
 #include "dadam.h"
+#include "dadam_internal.h"
 
 #include <hip/hip_runtime.h>
 
@@ -26,7 +21,7 @@ namespace {
 
 constexpr uint64_t kUnit = 2ull << 20;
 constexpr uint64_t kGiB = 1ull << 30;
-constexpr uint32_t kProbeRows = 16;
+constexpr uint32_t kProbeRows = dadam::kProbeStreams;
 constexpr uint64_t kProbeElems = 16ull << 20;        // 64 MiB of float32
 constexpr uint64_t kProbeBuffer = kProbeElems * 4;
 static_assert(2 * (kProbeRows / 2) * kProbeBuffer == DADAM_PROBE_CHUNK_BYTES, "a chunk holds 8 sources and 8 outputs");
@@ -51,12 +46,11 @@ bool same_third_as(size_t ref, const std::vector<uint64_t>& offs, dadam_pair_rat
   return true;
 }
 
-// The library's mixing pass over 32 buffers of 64 MiB anywhere in the arena, timed with HIP events.
+// The pass over 32 buffers of 64 MiB anywhere in the arena, timed with HIP events.
 struct Probe {
   char* arena = nullptr;
   uint64_t span = 0;  // bytes of the arena the probe may touch
-  dadam_handle* h = nullptr;
-  char* state = nullptr;  // 32 x 64 MiB of moment buffers the handle wants bound (the pass does not touch them)
+  uint32_t n_xcd = 1;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   uint32_t launches = 0;
   int status = DADAM_OK;
@@ -64,55 +58,28 @@ struct Probe {
   int open(void* arena_base, uint64_t arena_span, int32_t device) {
     arena = static_cast<char*>(arena_base);
     span = arena_span;
-    if (hipMalloc((void**)&state, 2 * kProbeRows * kProbeBuffer) != hipSuccess) {
-      (void)hipGetLastError();
-      state = nullptr;
-      return 1;  // no room: the caller falls back to the rule
-    }
-    dadam_tensor_desc whole = {0, kProbeElems, 0.0f, 0};
-    dadam_config cfg;
-    memset(&cfg, 0, sizeof(cfg));
-    cfg.abi_version = DADAM_ABI_VERSION;
-    cfg.n_rows = cfg.n_cols = kProbeRows;
-    cfg.d = kProbeElems;
-    cfg.n_tensors = 1;
-    cfg.tensors = &whole;
-    cfg.lr = 1e-3f; cfg.beta1 = 0.9f; cfg.beta2 = 0.999f; cfg.eps = 1e-8f;
-    cfg.accum_s = 1;
-    cfg.beta_vhat = -1.0f;
-    cfg.device = device;
-    if (dadam_init(&cfg, &h) != DADAM_OK) return DADAM_EHIP;
-    // a ring: every source is read by three rows, so the pass stages them once (tile mode), 16 reads + 16 writes
-    std::vector<int32_t> rp(kProbeRows + 1), col;
-    std::vector<float> w;
-    for (uint32_t i = 0; i < kProbeRows; ++i) {
-      rp[i] = (int32_t)col.size();
-      for (int o : {-1, 0, 1}) { col.push_back((int32_t)((i + kProbeRows + o) % kProbeRows)); w.push_back(1.0f / 3.0f); }
-    }
-    rp[kProbeRows] = (int32_t)col.size();
-    if (dadam_set_topology(h, 0, rp.data(), col.data(), w.data(), nullptr) != DADAM_OK) return DADAM_EHIP;
+    int xcc = 0;
+    if (hipDeviceGetAttribute(&xcc, hipDeviceAttributeNumberOfXccs, device) != hipSuccess) return DADAM_EHIP;
+    n_xcd = xcc > 0 ? (uint32_t)xcc : 1u;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return DADAM_EHIP;
     return DADAM_OK;
   }
 
   // Fraction of the HBM peak the pass sustains with its sources at offsets[0..16) and its outputs at [16..32).
   double rate_of_layout(const uint64_t* offsets, int reps = 6) {
-    const void* xs[kProbeRows]; void* xd[kProbeRows]; float* m[kProbeRows]; float* v[kProbeRows];
+    const void* src[kProbeRows]; void* dst[kProbeRows];
     for (uint32_t k = 0; k < 2 * kProbeRows; ++k)
       if (offsets[k] % 16 != 0 || offsets[k] > span || span - offsets[k] < kProbeBuffer) { status = DADAM_EINVAL; return -1.0; }
     for (uint32_t k = 0; k < kProbeRows; ++k) {
-      xs[k] = arena + offsets[k];
-      xd[k] = arena + offsets[kProbeRows + k];
-      m[k] = reinterpret_cast<float*>(state + k * kProbeBuffer);
-      v[k] = reinterpret_cast<float*>(state + (kProbeRows + k) * kProbeBuffer);
+      src[k] = arena + offsets[k];
+      dst[k] = arena + offsets[kProbeRows + k];
     }
-    dadam_buffers b = {xs, xd, m, v, nullptr};
-    if (dadam_bind(h, &b) != DADAM_OK) { status = DADAM_EHIP; return -1.0; }
+    auto pass = [&] { return dadam::launch_probe(src, dst, kProbeElems, n_xcd, nullptr) == (int)hipSuccess; };
     for (int k = 0; k < 2; ++k)
-      if (dadam_mix(h, 0, 0, nullptr) != DADAM_OK) { status = DADAM_EHIP; return -1.0; }
+      if (!pass()) { status = DADAM_EHIP; return -1.0; }
     if (hipEventRecord(e0, nullptr) != hipSuccess) { status = DADAM_EHIP; return -1.0; }
     for (int k = 0; k < reps; ++k)
-      if (dadam_mix(h, 0, 0, nullptr) != DADAM_OK) { status = DADAM_EHIP; return -1.0; }
+      if (!pass()) { status = DADAM_EHIP; return -1.0; }
     float ms = 0.0f;
     if (hipEventRecord(e1, nullptr) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
         hipEventElapsedTime(&ms, e0, e1) != hipSuccess || !(ms > 0.0f)) { status = DADAM_EHIP; return -1.0; }
@@ -136,11 +103,9 @@ struct Probe {
 
   void close() {
     (void)hipDeviceSynchronize();
-    if (h) dadam_destroy(h);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (state) (void)hipFree(state);
-    h = nullptr; e0 = e1 = nullptr; state = nullptr;
+    e0 = e1 = nullptr;
   }
 };
 
@@ -239,12 +204,8 @@ int dadam_place_by_timing(void* arena, uint64_t arena_bytes, int32_t device, con
   bool placed = false;
   if (n >= 2 && span >= 2 * DADAM_PROBE_STEP_BYTES + DADAM_PROBE_CHUNK_BYTES) {
     Probe probe;
-    const int opened = probe.open(arena, span, device);
-    if (opened == 1) {
-      report->note = DADAM_NOTE_NO_PROBE;
-    } else if (opened != DADAM_OK) {
-      rc = DADAM_EHIP;
-    } else {
+    rc = probe.open(arena, span, device);
+    if (rc == DADAM_OK) {
       rc = dadam_find_stretches(span, probe_rate, &probe, report->stretches, &report->n_stretches);
       uint32_t every = 0;
       uint64_t reg[4];

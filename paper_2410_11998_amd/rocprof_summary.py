@@ -38,11 +38,14 @@ import sys
 PHASES = {0: "mix", 1: "updateonly", 2: "plain", 3: "loopstart", 4: "fold", 5: "alg1", 6: "mix_consensus"}
 
 
-KERNELS = "k_tile_few|k_direct_few|k_acc_few|k_mix_rows|k_acc_rows|k_tile|k_direct|k_rows|k_loop|k_acc"
+PROBE_PHASE = "placement probe"      # the passes with which the arena finds the thirds of the memory before a workload is set up
+KERNELS = "k_probe|k_tile_few|k_direct_few|k_acc_few|k_mix_rows|k_acc_rows|k_tile|k_direct|k_rows|k_loop|k_acc"
 
 
 def parse_kernel(name: str):
     """(kernel shape as bench.py names it, phase name) of one of the library's kernels, else (None, None)."""
+    if re.search(r"\bk_probe\(", name):
+        return "k_probe", PROBE_PHASE
     m = re.search(r"\b(" + KERNELS + r")<(.*)>\(", name)
     if not m:
         return None, None
@@ -92,35 +95,17 @@ def bench_command(directory: str) -> str:
     return "python3 bench.py ..."
 
 
-PROBE_SHAPE, PROBE_PHASE = "k_tile<TF32,TF32,4,2,true>", "mix"
-PROBE_LABEL = "mix (arena probe)"
-
-
-def probe_launches(directory: str) -> int:
-    """How many mixing passes the arena's timing probe launched before the workload's own kernels (bench.py
-    reports it); they are the first dispatches of that kernel shape and are listed apart."""
-    return int(bench_line(directory)["config"].get("placement_probe_launches") or 0)
-
-
 def library_dispatches(directory: str, pattern: str, name_col: str):
     """Rows of a per-dispatch CSV that belong to the library's kernels (or plain copies), in dispatch order,
-    as (shape, phase, row), with the arena probe's launches relabelled."""
-    left = probe_launches(directory)
+    as (shape, phase, row)."""
     with open(one_file(directory, pattern)) as f:
         rows = sorted(csv.DictReader(f), key=lambda r: int(r["Dispatch_Id"]))
-    probe_ids = set()
     for r in rows:
         shape, phase = parse_kernel(r[name_col])
         if shape is None and "copyBuffer" in r[name_col]:
             shape, phase = "copy", ""
-        if shape is None:
-            continue
-        if (shape, phase) == (PROBE_SHAPE, PROBE_PHASE) and (r["Dispatch_Id"] in probe_ids or left > 0):
-            if r["Dispatch_Id"] not in probe_ids:       # a counter file has one row per counter and dispatch
-                probe_ids.add(r["Dispatch_Id"])
-                left -= 1
-            phase = PROBE_LABEL
-        yield shape, phase, r
+        if shape is not None:
+            yield shape, phase, r
 
 
 def kernel_stats(directory: str):
@@ -156,7 +141,7 @@ def cmd_fused(a) -> int:
              "bench.py line of the kernel-trace run (per_config / packed / cpu_baseline left out):",
              "  " + json.dumps({k: v for k, v in j.items() if k not in ("per_config", "packed", "cpu_baseline")}), "",
              "Kernel statistics (from *_kernel_trace.csv, per dispatch), the library's kernels; shape = <param type, grad type,",
-             "[waves, vectors per lane,] non-temporal>; the arena's timing probe launches the 16-source mixing kernel on 2 GiB:",
+             "[waves, vectors per lane,] non-temporal>; k_probe: the placement probe's passes over 2 GiB:",
              f"  {'kernel':34s} {'phase':17s} {'calls':>5s} {'avg ms':>9s} {'min ms':>9s} {'max ms':>9s}"]
     for shape, phase, calls, avg, lo, hi in kernel_stats(a.kt):
         lines.append(f"  {shape:34s} {phase:17s} {calls:5d} {avg:9.3f} {lo:9.3f} {hi:9.3f}")
@@ -175,8 +160,8 @@ def cmd_fused(a) -> int:
         fb, wb = mean(fv) * kf * 1024, mean(wv) * kw * 1024
         lines.append(f"  {key[0]:34s} {key[1]:17s} dispatches {len(fv):3d}  FETCH_SIZE avg {mean(fv):12.0f} -> {fb / 1e9:7.2f} GB   "
                      f"WRITE_SIZE avg {mean(wv):12.0f} -> {wb / 1e9:7.2f} GB   total {(fb + wb) / 1e9:7.2f} GB"
-                     + ("" if key[1] == PROBE_LABEL else f" = {(fb + wb) / (R * d):.3f} B per replica-param"))
-        if key[1] != PROBE_LABEL:
+                     + ("" if key[1] == PROBE_PHASE else f" = {(fb + wb) / (R * d):.3f} B per replica-param"))
+        if key[1] != PROBE_PHASE:
             traffic.append((wl, key[0], key[1], fb + wb))
     ro = j["roofline"]
     lines += ["", f"Algorithmic bytes per dispatch, average over the timed steps (R*d = {R * d} elements): {ro['algorithmic_bytes_per_launch']:.0f}",
@@ -216,7 +201,7 @@ def cmd_counters(a) -> int:
             lines.append(f"      {j['config']['workload']}, {j['config']['hbm_layout']}: {j['ms_per_step']:.3f} ms per step, "
                          f"roofline fraction {j['roofline']['frac']:.3f}")
             for (shape, phase), cs in vals.items():
-                if shape == "copy" or phase == PROBE_LABEL:
+                if shape == "copy" or phase == PROBE_PHASE:
                     continue
                 for c, v in cs.items():
                     table[(shape, phase, c)][label] = mean(v)
@@ -253,8 +238,8 @@ def cmd_trace(a) -> int:
     lines = ["rocprofv3 kernel-trace summary of further bench.py runs (other entry points and call sequences), one MI355X", "",
              "Each section: rocprofv3 --kernel-trace --stats --output-format csv -d OUT -- <command> (from /tmp with TMPDIR=/tmp;",
              "written by python -m paper_2410_11998_amd.rocprof_summary trace).  Calls include warm-up steps and every timed region.",
-             "Kernel shape = <param type, grad type, [waves, vectors per lane,] non-temporal>.  \"mix (arena probe)\": the 16-source",
-             "mixing passes over 2 GiB with which the arena finds the thirds of the memory before the workload is set up."]
+             "Kernel shape = <param type, grad type, [waves, vectors per lane,] non-temporal>.  k_probe: the passes over 2 GiB with",
+             "which the arena finds the thirds of the memory before the workload is set up."]
     for directory in a.run:
         j = bench_line(directory)
         ro, c = j["roofline"], j["config"]
