@@ -110,7 +110,11 @@ __device__ __forceinline__ bool die_block_piece(uint32_t b, uint32_t R, uint32_t
 // with the lane's second group between; all others lie with or below the contiguous kilobyte.  Fraction of 8 TB/s,
 // contiguous / spread: 7 reads and 2 writes 0.79 / 0.85, 80 reads and 32 writes of a tile of 16 rows with two vectors a lane 0.67 / 0.82
 // (one vector 0.69 / 0.70), bfloat16 parameters with float32 state, 8 rows 0.69 / 0.80, one row 0.76 / 0.82, copy 0.85 / 0.86.
-// Blocks that [lo, hi) cuts keep their elements in order.
+// Blocks that [lo, hi) cuts keep their elements in order (lane_in_order: a lane's place in its tile then).
+template <int VEC, int U, bool STREAM>
+__device__ __forceinline__ uint32_t lane_in_order(uint32_t l) {
+  return STREAM && VEC * U > 4 ? 4 * (l & 15) + 8 * (l & 16) + (l >> 5) * 256 : 4 * l;
+}
 template <int VEC, int U, bool STREAM>
 __device__ __forceinline__ uint64_t lane_start(uint64_t index, uint64_t lo, uint64_t hi, int lane) {
   constexpr uint32_t N = kWave * VEC * U;
@@ -144,10 +148,12 @@ __device__ __forceinline__ void search_narrow(uint64_t ballot, uint32_t step, ui
 // float32 4 (one 128-bit access); bfloat16 8, held as two groups of four (two 64-bit accesses of x and
 // g, two 128-bit accesses of each float32 state vector; see load_vals for where the groups lie).
 struct TF32 {
+  typedef float elem;
   static constexpr int bytes = 4;
   static constexpr int vec = 4;
 };
 struct TBF16 {
+  typedef uint16_t elem;
   static constexpr int bytes = 2;
   static constexpr int vec = 8;
 };
@@ -177,6 +183,21 @@ __device__ __forceinline__ void store_elem(void* base, uint64_t e, float v) {
   } else {
     reinterpret_cast<uint16_t*>(base)[e] = (uint16_t)f32_to_bf16_bits(v);
   }
+}
+
+// Element e of type T (float or uint16_t).  An index of 32 bits counts from the tile's first element (see Index): the distance in
+// bytes then is 32 bits beside a uniform address.
+template <typename T>
+__device__ __forceinline__ const T* at(const void* base, uint64_t e) { return reinterpret_cast<const T*>(base) + e; }
+template <typename T>
+__device__ __forceinline__ T* at(void* base, uint64_t e) { return reinterpret_cast<T*>(base) + e; }
+template <typename T>
+__device__ __forceinline__ const T* at(const void* base, uint32_t e) {
+  return reinterpret_cast<const T*>(static_cast<const char*>(base) + e * (uint32_t)sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ T* at(void* base, uint32_t e) {
+  return reinterpret_cast<T*>(static_cast<char*>(base) + e * (uint32_t)sizeof(T));
 }
 
 // The VEC elements of one lane and vector, of type T, widened to float.  VEC = 4: elements
@@ -213,60 +234,64 @@ __device__ __forceinline__ void vstore(V* p, V v) {
 }
 
 enum Clip : int { kWhole = 0, kElements = 1, kGroups = 2, kGroupsZeroed = 3 };
-__device__ __forceinline__ uint64_t nearest_group(uint64_t e, uint64_t lo, uint64_t hi) {
-  const uint64_t first = lo & ~(uint64_t)3, last = (hi - 1) & ~(uint64_t)3;
-  return e < first ? first : e > last ? last : e;
+template <typename E>
+__device__ __forceinline__ E nearest_group(E e, E lo, E hi) {
+  const E first = lo & ~(E)3, last = (hi - 1) & ~(E)3;
+  const E up = e > first ? e : first;
+  return up < last ? up : last;
 }
 
-template <typename T, int VEC, int H, int CLIP, bool NT>
-__device__ __forceinline__ void load_vals(const void* base, uint64_t e, uint64_t lo, uint64_t hi,
-                                          float (&out)[VEC]) {
+template <typename T, int VEC, int H, int CLIP, bool NT, typename E>
+__device__ __forceinline__ void load_vals(const void* base, E e, E lo, E hi, float (&out)[VEC]) {
   static_assert(VEC == 4 || (VEC == 8 && H >= 4), "a lane holds one or two groups of four elements");
+  static_assert(CLIP != kGroupsZeroed, "only sources are cleared outside the range");
 #pragma unroll
   for (int h = 0; h < VEC / 4; ++h) {
-    const uint64_t at = e + (uint64_t)h * H, eh = CLIP == kGroups ? nearest_group(at, lo, hi) : at;
+    const E group = e + (E)h * H, eh = CLIP == kGroups ? nearest_group(group, lo, hi) : group;
     if (CLIP != kElements || (eh >= lo && eh + 4 <= hi)) {
       if constexpr (T::bytes == 4) {
-        f4 v = vload<NT && kNtStream>(reinterpret_cast<const f4*>(reinterpret_cast<const float*>(base) + eh));
+        f4 v = vload<NT && kNtStream>(reinterpret_cast<const f4*>(at<float>(base, eh)));
         out[4 * h + 0] = v.x; out[4 * h + 1] = v.y; out[4 * h + 2] = v.z; out[4 * h + 3] = v.w;
       } else {
-        u2 v = vload<NT && kNtStream>(reinterpret_cast<const u2*>(reinterpret_cast<const uint16_t*>(base) + eh));
+        u2 v = vload<NT && kNtStream>(reinterpret_cast<const u2*>(at<uint16_t>(base, eh)));
         out[4 * h + 0] = __uint_as_float(v.x << 16); out[4 * h + 1] = __uint_as_float(v.x & 0xFFFF0000u);
         out[4 * h + 2] = __uint_as_float(v.y << 16); out[4 * h + 3] = __uint_as_float(v.y & 0xFFFF0000u);
       }
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const uint64_t ej = eh + j;
+        const E ej = eh + j;
         out[4 * h + j] = (ej >= lo && ej < hi) ? load_elem<T>(base, ej) : 0.0f;
       }
     }
   }
 }
 
-template <typename T, int VEC, int H, int CLIP, bool NT>
-__device__ __forceinline__ void store_vals(void* base, uint64_t e, uint64_t lo, uint64_t hi,
-                                           const float (&in)[VEC]) {
+template <typename T, int VEC, int H, int CLIP, bool NT, typename E>
+__device__ __forceinline__ void store_vals(void* base, E e, E lo, E hi, const float (&in)[VEC]) {
   static_assert(VEC == 4 || (VEC == 8 && H >= 4), "a lane holds one or two groups of four elements");
 #pragma unroll
   for (int h = 0; h < VEC / 4; ++h) {
-    const uint64_t eh = e + (uint64_t)h * H;
+    const E eh = e + (E)h * H;
     if (CLIP == kWhole || (eh >= lo && eh + 4 <= hi)) {
       if constexpr (T::bytes == 4) {
         f4 v;
         v.x = in[4 * h + 0]; v.y = in[4 * h + 1]; v.z = in[4 * h + 2]; v.w = in[4 * h + 3];
-        vstore<NT && kNtStore>(reinterpret_cast<f4*>(reinterpret_cast<float*>(base) + eh), v);
+        vstore<NT && kNtStore>(reinterpret_cast<f4*>(at<float>(base, eh)), v);
       } else {
         u2 v;
         v.x = f32_to_bf16_bits(in[4 * h + 0]) | (f32_to_bf16_bits(in[4 * h + 1]) << 16);
         v.y = f32_to_bf16_bits(in[4 * h + 2]) | (f32_to_bf16_bits(in[4 * h + 3]) << 16);
-        vstore<NT && kNtStore>(reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(base) + eh), v);
+        vstore<NT && kNtStore>(reinterpret_cast<u2*>(at<uint16_t>(base, eh)), v);
       }
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const uint64_t ej = eh + j;
-        if (ej >= lo && ej < hi) store_elem<T>(base, ej, in[4 * h + j]);
+        const E ej = eh + j;
+        if (ej >= lo && ej < hi) {
+          if constexpr (sizeof(E) == 8) store_elem<T>(base, ej, in[4 * h + j]);
+          else store_elem<T>(at<typename T::elem>(base, eh), j, in[4 * h + j]);
+        }
       }
     }
   }
@@ -276,9 +301,8 @@ __device__ __forceinline__ void store_vals(void* base, uint64_t e, uint64_t lo, 
 // that runs once has a loop-invariant address, the compiler's loop-invariant code motion then "promotes" the
 // location to a register and re-creates the store behind the loop - without the non-temporal hint (seen with
 // the bfloat16 one-vector tile kernels: 1.2 % slower on the ring of 8; the compile test counts the hints).
-template <typename T, int VEC, int H, int CLIP, bool NT, int UT>
-__device__ __forceinline__ void store_vectors(void* base, const uint64_t (&e)[UT], uint64_t lo, uint64_t hi,
-                                              const float (&in)[UT][VEC]) {
+template <typename T, int VEC, int H, int CLIP, bool NT, int UT, typename E>
+__device__ __forceinline__ void store_vectors(void* base, const E (&e)[UT], E lo, E hi, const float (&in)[UT][VEC]) {
   if constexpr (UT == 1) {
     store_vals<T, VEC, H, CLIP, NT>(base, e[0], lo, hi, in[0]);
   } else {
@@ -289,12 +313,12 @@ __device__ __forceinline__ void store_vectors(void* base, const uint64_t (&e)[UT
 
 // The 16 raw bytes of a lane's parameter vector (4 float32, or 2 x 4 bfloat16 in the two groups
 // described above), as they are parked in LDS.
-template <typename XT, int H, int CLIP, bool NT>
-__device__ __forceinline__ u4 load_raw(const void* base, uint64_t e, uint64_t lo, uint64_t hi) {
+template <typename XT, int H, int CLIP, bool NT, typename E>
+__device__ __forceinline__ u4 load_raw(const void* base, E e, E lo, E hi) {
   if constexpr (XT::bytes == 4) {
     if (CLIP != kElements || (e >= lo && e + 4 <= hi)) {
-      const uint64_t eh = CLIP >= kGroups ? nearest_group(e, lo, hi) : e;
-      u4 v = vload<NT && kNtSource>(reinterpret_cast<const u4*>(reinterpret_cast<const float*>(base) + eh));
+      const E eh = CLIP >= kGroups ? nearest_group(e, lo, hi) : e;
+      u4 v = vload<NT && kNtSource>(reinterpret_cast<const u4*>(at<float>(base, eh)));
       if constexpr (CLIP == kGroupsZeroed) {
         v.x = e + 0 >= lo && e + 0 < hi ? v.x : 0u;
         v.y = e + 1 >= lo && e + 1 < hi ? v.y : 0u;
@@ -316,12 +340,12 @@ __device__ __forceinline__ u4 load_raw(const void* base, uint64_t e, uint64_t lo
     u2 half[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const uint64_t at = e + (uint64_t)h * H, eh = CLIP >= kGroups ? nearest_group(at, lo, hi) : at;
+      const E group = e + (E)h * H, eh = CLIP >= kGroups ? nearest_group(group, lo, hi) : group;
       if (CLIP != kElements || (eh >= lo && eh + 4 <= hi)) {
-        half[h] = vload<NT && kNtSource>(reinterpret_cast<const u2*>(p + eh));
+        half[h] = vload<NT && kNtSource>(reinterpret_cast<const u2*>(at<uint16_t>(base, eh)));
         if constexpr (CLIP == kGroupsZeroed) {
-          half[h].x &= (at + 0 >= lo && at + 0 < hi ? 0xFFFFu : 0u) | (at + 1 >= lo && at + 1 < hi ? 0xFFFF0000u : 0u);
-          half[h].y &= (at + 2 >= lo && at + 2 < hi ? 0xFFFFu : 0u) | (at + 3 >= lo && at + 3 < hi ? 0xFFFF0000u : 0u);
+          half[h].x &= (group + 0 >= lo && group + 0 < hi ? 0xFFFFu : 0u) | (group + 1 >= lo && group + 1 < hi ? 0xFFFF0000u : 0u);
+          half[h].y &= (group + 2 >= lo && group + 2 < hi ? 0xFFFFu : 0u) | (group + 3 >= lo && group + 3 < hi ? 0xFFFF0000u : 0u);
         }
       } else {
         uint32_t q[4];
@@ -436,6 +460,20 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
 template <typename A>
 __device__ __forceinline__ int clip_of(const A& a, bool full, uint64_t hi) {
   return full ? kWhole : hi + 3 <= (a.d | 3) ? kGroups : kElements;
+}
+
+// The same lane and range as elements of a tile that [lo, hi) cuts (the block it lies in is cut as well, so lanes keep their order).
+struct Cut {
+  uint32_t e, lo, hi;
+};
+template <int VEC, int U, bool STREAM>
+__device__ __forceinline__ Cut cut_of(uint64_t tbase, uint64_t lo, uint64_t hi, int lane) {
+  constexpr uint32_t N = kWave * VEC * U;
+  Cut c;
+  c.e = lane_in_order<VEC, U, STREAM>((uint32_t)lane);
+  c.lo = lo > tbase ? (uint32_t)(lo - tbase) : 0;
+  c.hi = hi - tbase < N ? (uint32_t)(hi - tbase) : N;
+  return c;
 }
 
 // Pointers of the bound buffers.  EXT = false: from the argument block (at most kInlineRows rows and
@@ -567,35 +605,62 @@ __device__ __forceinline__ float list_w(const RowList& r, int k) {
 // ---------------------------------------------------------------------------------------------
 // tile mode
 // ---------------------------------------------------------------------------------------------
+// Where a body works: elements of the buffers (origin 0), or, in tiles whose loads go by groups, elements of the tile from
+// `origin` on.  A kernel's registers are those of its largest body: with clamped 64-bit indexes the body for such tiles took 4 to
+// 20 more than that for whole ones, and a wavefront per SIMD from 119 kernels.  us, without that body / 64 / 32 bits: bfloat16 steps that
+// do not stream 145.0 / 146.5 / 144.4 (16 replicas), 76.9 / 77.5 / 76.6 (96 replicas); 25 MB buckets of a bfloat16 row 2252 / 2246 / 2177;
+// 8 replicas of 300 odd-sized tensors 68.8 / 60.0 / 58.8; mixing of 16 x 19 million elements 1464 / 1468 / 1452.  Mixing that does not
+// stream has registers to spare and keeps 64 (12 bfloat16 replicas of odd-sized tensors 32.0 / 33.8).
+template <int CLIP, bool NARROW = true>
+using Index = typename std::conditional<CLIP >= kGroups && NARROW, uint32_t, uint64_t>::type;
+template <int BYTES, typename P>
+__device__ __forceinline__ P* from(P* base, uint64_t origin) {
+  typedef typename std::conditional<std::is_const<P>::value, const char, char>::type Byte;
+  return reinterpret_cast<P*>(reinterpret_cast<Byte*>(base) + origin * BYTES);
+}
+
+// What is computed from an index of a cut tile (clamped, scaled for each element type) is computed again after this, and held
+// in no register from row to row or from a row's loads to its stores.
+template <typename E>
+__device__ __forceinline__ E afresh(E e) {
+  if constexpr (sizeof(E) == 4) asm volatile("" : "+v"(e));
+  return e;
+}
+template <int STEP, int U, typename E>
+__device__ __forceinline__ void vector_indexes(E start, E (&e)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) e[u] = start + u * STEP;
+}
+
 // The stream inputs of one row of a tile: gradient, moments, accumulator (whatever the phase needs).
-template <typename GT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void load_row_inputs(const A& a, int i, const uint64_t (&e)[UT], uint64_t lo,
-                                                uint64_t hi, float (&g)[UT][VEC], float (&mh)[UT][VEC],
+template <typename GT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void load_row_inputs(const A& a, int i, uint64_t origin, const E (&e)[UT], E lo,
+                                                E hi, float (&g)[UT][VEC], float (&mh)[UT][VEC],
                                                 float (&vh)[UT][VEC], float (&b)[UT][VEC]) {
   if constexpr (Needs<PHASE>::grad) {
-    const void* gp = a.grad[i];
+    const void* gp = from<GT::bytes>(a.grad[i], origin);
 #pragma unroll
     for (int u = 0; u < UT; ++u) load_vals<GT, VEC, kGroupStep<NT>, CLIP, NT>(gp, e[u], lo, hi, g[u]);
   }
   if constexpr (Needs<PHASE>::moments_in) {
-    const float* mp = m_hat_of<EXT>(a, i);
-    const float* vp = v_hat_of<EXT>(a, i);
+    const float* mp = from<4>(m_hat_of<EXT>(a, i), origin);
+    const float* vp = from<4>(v_hat_of<EXT>(a, i), origin);
 #pragma unroll
     for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(mp, e[u], lo, hi, mh[u]);
 #pragma unroll
     for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(vp, e[u], lo, hi, vh[u]);
   }
   if constexpr (Needs<PHASE>::acc_in) {
-    const float* bp = acc_of<EXT>(a, i);
+    const float* bp = from<4>(acc_of<EXT>(a, i), origin);
 #pragma unroll
     for (int u = 0; u < UT; ++u) load_vals<TF32, VEC, kGroupStep<NT>, CLIP, NT>(bp, e[u], lo, hi, b[u]);
   }
 }
 
 // Mixing from LDS, the update of Algorithm 3 and the stores of one row of a tile.
-template <typename XT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A>
+template <typename XT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A, typename E>
 __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, RowList rl,
-                                           const uint64_t (&e)[UT], uint64_t lo, uint64_t hi, float wd, int lane,
+                                           uint64_t origin, E start, E lo, E hi, float wd, int lane,
                                            float (&g)[UT][VEC], float (&mh)[UT][VEC], float (&vh)[UT][VEC],
                                            float (&b)[UT][VEC]) {
   // neighbour sum in the order the row lists its entries: first a product, then fused
@@ -653,21 +718,22 @@ __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, Row
     for (int j = 0; j < VEC; ++j)
       xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[u][j]);
 
-  store_vectors<XT, VEC, kGroupStep<NT>, CLIP, NT>(dst_of<EXT>(a, i), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(acc_of<EXT>(a, i), e, lo, hi, b);
+  E e[UT];
+  vector_indexes<kVectorStep<VEC, NT>>(VEC * UT > 4 ? afresh(start) : start, e);
+  store_vectors<XT, VEC, kGroupStep<NT>, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, i), origin), e, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(acc_of<EXT>(a, i), origin), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(m_hat_of<EXT>(a, i), e, lo, hi, mh);
-    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(v_hat_of<EXT>(a, i), e, lo, hi, vh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(m_hat_of<EXT>(a, i), origin), e, lo, hi, mh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(v_hat_of<EXT>(a, i), origin), e, lo, hi, vh);
   }
 }
 
-template <typename XT, typename GT, int PHASE, int W, int UT, int CLIP, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, uint64_t lo,
-                                          uint64_t hi, float wd, uint32_t tile_id, int lane, int wave) {
+template <typename XT, typename GT, int PHASE, int W, int UT, int CLIP, bool NT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, E start, E lo, E hi, float wd, uint32_t tile_id,
+                                          int lane, int wave) {
   constexpr int VEC = XT::vec;
-  uint64_t e[UT];
-#pragma unroll
-  for (int u = 0; u < UT; ++u) e[u] = start + u * kVectorStep<VEC, NT>;
+  E e[UT];
+  vector_indexes<kVectorStep<VEC, NT>>(start, e);
 
   const int n_rows = (int)a.n_rows;
   const RowPtrs<EXT> rp = load_row_ptrs<EXT>(a, lane);
@@ -685,7 +751,7 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
       for (int k = 0; k < KB; ++k) {
         const int c = c0 + k * W;
         if (c < n_cols) {
-          const void* src = src_of<EXT>(a, c);
+          const void* src = from<XT::bytes>(src_of<EXT>(a, c), origin);
 #pragma unroll
           for (int u = 0; u < UT; ++u) r[k][u] = load_raw<XT, kGroupStep<NT>, CLIP, NT>(src, e[u], lo, hi);
         }
@@ -701,7 +767,7 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
     }
   } else {
     for (int c = wave; c < n_cols; c += W) {
-      const void* src = src_of<EXT>(a, c);
+      const void* src = from<XT::bytes>(src_of<EXT>(a, c), origin);
       u4 r[UT];
 #pragma unroll
       for (int u = 0; u < UT; ++u) r[u] = load_raw<XT, kGroupStep<NT>, CLIP, NT>(src, e[u], lo, hi);
@@ -761,8 +827,10 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t start, u
     const RowList rl = rl_next;
     rl_next = load_row_list(a, rp, i + W < n_rows ? i + W : i, lane);
     float g[UT][VEC], mh[UT][VEC], vh[UT][VEC], b[UT][VEC];
-    load_row_inputs<GT, PHASE, VEC, UT, CLIP, NT, EXT>(a, i, e, lo, hi, g, mh, vh, b);
-    finish_row<XT, PHASE, VEC, UT, CLIP, NT, EXT>(a, lds, i, rl, e, lo, hi, wd, lane, g, mh, vh, b);
+    if (VEC * UT > 4) start = afresh(start);
+    vector_indexes<kVectorStep<VEC, NT>>(start, e);
+    load_row_inputs<GT, PHASE, VEC, UT, CLIP, NT, EXT>(a, i, origin, e, lo, hi, g, mh, vh, b);
+    finish_row<XT, PHASE, VEC, UT, CLIP, NT, EXT>(a, lds, i, rl, origin, start, lo, hi, wd, lane, g, mh, vh, b);
   }
 }
 
@@ -790,12 +858,15 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
   const uint64_t start = lane_start<VEC, UT, NT>(tile_index, lo, hi, lane);
+  const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
   // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
   constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
+  constexpr bool NARROW = Needs<PHASE>::grad || NT;  // see Index
   const int clip = clip_of(a, full, hi);
-  if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
-  else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
-  else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, start, lo, hi, wd, b, lane, wave);
+  if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
+  else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, wd, b, lane, wave);
+  else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
+  else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -839,18 +910,21 @@ struct OwnSource {
   bool found = false;
   float x[VEC];
 };
-template <typename XT, int N, bool FIRST, int U, int H, int CLIP, bool NT, bool EXT, typename A>  // NT: hint on the source loads
-__device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, const uint64_t (&e)[U], uint64_t lo,
-                                            uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
+template <typename XT, int N, bool FIRST, int U, int H, int CLIP, bool NT, bool EXT, typename A, typename E>  // NT: hint on the source loads
+__device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k, uint64_t origin, const E (&e)[U], E lo,
+                                            E hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
   constexpr int VEC = XT::vec;
   u4 r[N][U];
   float wk[N];
+  E f[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) f[u] = afresh(e[u]);
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    const void* src = src_of<EXT>(a, list_col(rl, k + q));
+    const void* src = from<XT::bytes>(src_of<EXT>(a, list_col(rl, k + q)), origin);
     wk[q] = list_w(rl, k + q);
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[q][u] = load_raw<XT, H, CLIP, NT>(src, e[u], lo, hi);
+    for (int u = 0; u < U; ++u) r[q][u] = load_raw<XT, H, CLIP, NT>(src, f[u], lo, hi);
   }
 #pragma unroll
   for (int q = 0; q < N; ++q)
@@ -873,10 +947,10 @@ __device__ __forceinline__ void mix_entries(const A& a, const RowList& rl, int k
 // with two bfloat16 vectors a lane (16 sums live) they are two sources after the first four: four more cost 76 registers
 // and with them the seventh wavefront (mixing in pairs, 24 to 64 rows, 0.96-0.98 -> 1.00-1.02 of the rate of workgroups of
 // 67 registers, 96 rows of three 1.07 -> 1.13, rows of seven the same).
-template <typename XT, int U, int H, int CLIP, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, const uint64_t (&e)[U], uint64_t lo,
-                                           uint64_t hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
-#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, U, H, CLIP, NT, EXT>(a, rl, K, e, lo, hi, mix, own)
+template <typename XT, int U, int H, int CLIP, bool NT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, uint64_t origin, const E (&e)[U], E lo,
+                                           E hi, float (&mix)[U][XT::vec], OwnSource<XT::vec>& own) {
+#define DADAM_MIX(N, FIRST, K) mix_entries<XT, N, FIRST, U, H, CLIP, NT, EXT>(a, rl, K, origin, e, lo, hi, mix, own)
   constexpr int FIRST_BATCH = U == 1 ? 8 : 4;
   if (rl.deg < FIRST_BATCH) {
     switch (rl.deg) {
@@ -921,9 +995,9 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, con
 
 // HINT: 0 no streaming hints, 1 on every vector access, 2 on all but the loads of sources (rows share
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
-template <typename XT, typename GT, int PHASE, int U, int CLIP, int HINT, bool EXT, typename A>
-__device__ __forceinline__ void direct_body(const A& a, int position, int row, const uint64_t (&e)[U], uint64_t lo,
-                                            uint64_t hi, float wd, int lane) {
+template <typename XT, typename GT, int PHASE, int U, int CLIP, int HINT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void direct_body(const A& a, int position, int row, uint64_t origin, const E (&e)[U], E lo,
+                                            E hi, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
   // The neighbour list sits one entry per lane and is handed out with readlane, which must find a
@@ -934,14 +1008,17 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_position_list(a, position, lane);
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
-  load_row_inputs<GT, PHASE, VEC, U, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+  load_row_inputs<GT, PHASE, VEC, U, CLIP, NT, EXT>(a, row, origin, e, lo, hi, g, mh, vh, b);
   // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
   // sum where the row lists itself (loading them again would be a second trip to memory after the first).
   const bool decays = !Needs<PHASE>::mixing_only && wd != 0.0f;
   OwnSource<VEC> own;
   own.col = decays ? row : -1;
   float mix[U][VEC];
-  mix_direct<XT, U, H, CLIP, NTSRC, EXT>(a, rl, lane, e, lo, hi, mix, own);
+  mix_direct<XT, U, H, CLIP, NTSRC, EXT>(a, rl, lane, origin, e, lo, hi, mix, own);
+  E f[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) f[u] = afresh(e[u]);
   float xo[U][VEC];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -949,7 +1026,7 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
 #pragma unroll
     for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
     if (decays) {
-      if (!own.found) unpack_raw<XT>(load_raw<XT, H, CLIP, false>(src_of<EXT>(a, row), e[u], lo, hi), own.x);
+      if (!own.found) unpack_raw<XT>(load_raw<XT, H, CLIP, false>(from<XT::bytes>(src_of<EXT>(a, row), origin), f[u], lo, hi), own.x);
 #pragma unroll
       for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
     }
@@ -957,11 +1034,11 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, c
     for (int j = 0; j < VEC; ++j)
       xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[j]);
   }
-  store_vectors<XT, VEC, H, CLIP, NT>(dst_of<EXT>(a, row), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  store_vectors<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), f, lo, hi, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), f, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), f, lo, hi, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), f, lo, hi, vh);
   }
 }
 
@@ -997,9 +1074,12 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   if (active && p.any) {  // uniform over the workgroup
     constexpr int CUT = HINT == 1 && EXT ? kElements : kGroups;  // see tile_entry
     const int clip = clip_of(a, p.full, p.hi);
-    if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
-    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
-    else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, e, p.lo, p.hi, p.wd, lane);
+    const uint64_t tbase = p.index * (kWave * XT::vec);
+    const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, p.lo, p.hi, lane);
+    const uint32_t c[1] = {cut.e};
+    if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
+    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.wd, lane);
+    else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
   }
 }
 
@@ -1032,10 +1112,10 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a
     float mix[2][VEC];
     void* to = dst_of<EXT>(a, row);
     if (tbase >= lo && tbase + ITEM <= hi) {
-      mix_direct<XT, 2, kGroupStep<HINT != 0>, kWhole, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      mix_direct<XT, 2, kGroupStep<HINT != 0>, kWhole, HINT == 1, EXT>(a, rl, lane, 0, e, lo, hi, mix, none);
       store_vectors<XT, VEC, kGroupStep<HINT != 0>, kWhole, HINT != 0>(to, e, lo, hi, mix);
     } else {
-      mix_direct<XT, 2, kGroupStep<HINT != 0>, kElements, HINT == 1, EXT>(a, rl, lane, e, lo, hi, mix, none);
+      mix_direct<XT, 2, kGroupStep<HINT != 0>, kElements, HINT == 1, EXT>(a, rl, lane, 0, e, lo, hi, mix, none);
       store_vectors<XT, VEC, kGroupStep<HINT != 0>, kElements, HINT != 0>(to, e, lo, hi, mix);
     }
   }
@@ -1058,8 +1138,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
   const uint64_t e0 = lane_start<VEC, 2, HINT != 0>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, HINT != 0>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, kWhole, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
-    else direct_body<XT, GT, PHASE, 2, kElements, HINT, EXT>(a, (int)position, row, e, lo, hi, wd, lane);
+    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, kWhole, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, wd, lane);
+    else direct_body<XT, GT, PHASE, 2, kElements, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, wd, lane);
   }
 }
 
@@ -1076,11 +1156,11 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
 template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A>
-__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t start, uint64_t lo, uint64_t hi,
-                                          float wd, int lane, int wave, int waves) {
+__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, Index<CLIP> start, Index<CLIP> lo,
+                                          Index<CLIP> hi, float wd, int lane, int wave, int waves) {
   constexpr bool NT = HINT != 0;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
-  const uint64_t e[1] = {start};
+  const Index<CLIP> e[1] = {start};
   const Loop l = a.loops[loop];
   // This wavefront's rows, every `waves`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
   // each).  A wavefront that sums has at least three sources, so that the sum is never less accurate than the listed
@@ -1098,12 +1178,12 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   const int row_v = a.row_order[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
   float g[1][VEC], mh[1][VEC], vh[1][VEC], b[1][VEC];
   int row = __builtin_amdgcn_readlane(row_v, 0);
-  if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+  if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, origin, e, lo, hi, g, mh, vh, b);
   if (rl.deg > 0) {
     float part[1][VEC];
     OwnSource<VEC> none;
     none.col = -1;
-    mix_direct<XT, 1, H, CLIP, HINT == 1, EXT>(a, rl, lane, e, lo, hi, part, none);
+    mix_direct<XT, 1, H, CLIP, HINT == 1, EXT>(a, rl, lane, origin, e, lo, hi, part, none);
 #pragma unroll
     for (int h = 0; h < VEC / 4; ++h) {
       f4 v = {part[0][4 * h], part[0][4 * h + 1], part[0][4 * h + 2], part[0][4 * h + 3]};
@@ -1125,21 +1205,21 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
     for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
     if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
       float own[VEC];
-      unpack_raw<XT>(load_raw<XT, H, CLIP, false>(src_of<EXT>(a, row), e[0], lo, hi), own);
+      unpack_raw<XT>(load_raw<XT, H, CLIP, false>(from<XT::bytes>(src_of<EXT>(a, row), origin), e[0], lo, hi), own);
 #pragma unroll
       for (int j = 0; j < VEC; ++j) decay[j] = wd * own[j];
     }
 #pragma unroll
     for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[0][j], mh[0][j], vh[0][j], b[0][j], decay[j]);
-    store_vals<XT, VEC, H, CLIP, NT>(dst_of<EXT>(a, row), e[0], lo, hi, xo);
-    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e[0], lo, hi, b[0]);
+    store_vals<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), e[0], lo, hi, xo);
+    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e[0], lo, hi, b[0]);
     if constexpr (Needs<PHASE>::moments_out) {
-      store_vals<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e[0], lo, hi, mh[0]);
-      store_vals<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e[0], lo, hi, vh[0]);
+      store_vals<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e[0], lo, hi, mh[0]);
+      store_vals<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e[0], lo, hi, vh[0]);
     }
     if (r + 1 < my_rows) {
       row = __builtin_amdgcn_readlane(row_v, r + 1);
-      load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, e, lo, hi, g, mh, vh, b);
+      load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, origin, e, lo, hi, g, mh, vh, b);
     }
   }
 }
@@ -1166,9 +1246,10 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   const uint64_t start = lane_start<XT::vec, 1, HINT != 0>(tile_index, lo, hi, lane);
   constexpr int CUT = HINT != 0 && EXT ? kElements : kGroups;  // see tile_entry
   const int clip = clip_of(a, full, hi);
-  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
-  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, start, lo, hi, wd, lane, wave, waves);
+  const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
+  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, wd, lane, wave, waves);
+  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1186,30 +1267,30 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
   }
 }
 
-template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi) {
+template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void acc_body(const A& a, int row, uint64_t origin, const E (&e)[U], E lo, E hi) {
   constexpr int H = kGroupStep<NT>;
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
 #pragma unroll
-  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(a.grad[row], e[u], lo, hi, g[u]);
+  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(from<GT::bytes>(a.grad[row], origin), e[u], lo, hi, g[u]);
   if constexpr (Needs<PHASE>::moments_out) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e[u], lo, hi, mh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e[u], lo, hi, mh[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e[u], lo, hi, vh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e[u], lo, hi, vh[u]);
   }
   if constexpr (Needs<PHASE>::acc_in) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e[u], lo, hi, b[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e[u], lo, hi, b[u]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e, lo, hi, vh);
   }
 }
 
@@ -1232,9 +1313,12 @@ __device__ __forceinline__ void acc_entry(const A& a) {
   if (active && p.any) {
     constexpr int CUT = NT && EXT ? kElements : kGroups;  // see tile_entry
     const int clip = clip_of(a, p.full, p.hi);
-    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi);
-    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi);
-    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi);
+    const uint64_t tbase = p.index * (kWave * VEC);
+    const Cut cut = cut_of<VEC, 1, NT>(tbase, p.lo, p.hi, (int)threadIdx.x);
+    const uint32_t c[1] = {cut.e};
+    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, 0, e, p.lo, p.hi);
+    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, tbase, c, cut.lo, cut.hi);
+    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, 0, e, p.lo, p.hi);
   }
 }
 
@@ -1254,8 +1338,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   const uint64_t e0 = lane_start<VEC, 2, NT>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, NT>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, e, lo, hi);
-    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, e, lo, hi);
+    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, 0, e, lo, hi);
+    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, 0, e, lo, hi);
   }
 }
 
