@@ -429,8 +429,10 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
     weight_decay = a.weight_decay;
   } else {
     typedef const Segment __attribute__((address_space(4))) * GlobalSegments;  // constant memory: scalar loads
+    typedef const uint32_t __attribute__((address_space(4))) * GlobalWork;
     const GlobalSegments seg = (GlobalSegments)a.seg;
     const uint32_t grid = a.grid;
+    const GlobalWork work0 = (GlobalWork)(a.seg_work + (uint64_t)grid * a.n_seg);
     uint32_t s = 0, n = a.n_seg;  // the segment is one of [s, s + n)
     if (a.wide_search) {
       const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -443,12 +445,12 @@ __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile
     } else {
       while (n > 1) {
         const uint32_t half = n >> 1;
-        const bool right = seg[s + half].work0[grid] <= work;
+        const bool right = work0[s + half] <= work;
         s = right ? s + half : s;
         n = right ? n - half : half;
       }
     }
-    tile_index = seg[s].first_tile[grid] + (work - seg[s].work0[grid]);
+    tile_index = seg[s].first_tile[grid] + (work - work0[s]);
     const uint64_t slo = seg[s].lo, shi = seg[s].hi;
     lo = slo > a.clip_lo ? slo : a.clip_lo;
     hi = shi < a.clip_hi ? shi : a.clip_hi;

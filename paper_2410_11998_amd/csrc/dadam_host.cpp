@@ -70,6 +70,7 @@ struct dadam_handle {
   std::vector<dadam_tensor_desc> tensors;
   std::vector<uint32_t> tensor_seg;  // segment of each non-empty tensor, UINT32_MAX for empty ones
   std::vector<Segment> segs;
+  std::vector<uint32_t> seg_work[kNumGrids];  // per Grid: number of work items (tiles; per row in direct mode) in earlier segments
   Segment* d_segs = nullptr;     // the segments, and behind them
   uint32_t* d_seg_work = nullptr;  // their first work items, per Grid (what the kernels search)
   double* d_partials = nullptr;  // kConsensusPartials doubles of scratch for the consensus error
@@ -192,10 +193,10 @@ int plan(dadam_handle* h) {
     s.first_tile[kGridMix] = s.lo / h->mix_tile_elems;
     s.first_tile[kGridVector] = s.lo / vector_elems(h);
     if (wv > 0x7fffffffull || wd > 0x7fffffffull) break;
-    s.work0[kGridTile] = (uint32_t)wt;
-    s.work0[kGridDirect] = (uint32_t)wd;
-    s.work0[kGridMix] = (uint32_t)wm;
-    s.work0[kGridVector] = (uint32_t)wv;
+    h->seg_work[kGridTile].push_back((uint32_t)wt);
+    h->seg_work[kGridDirect].push_back((uint32_t)wd);
+    h->seg_work[kGridMix].push_back((uint32_t)wm);
+    h->seg_work[kGridVector].push_back((uint32_t)wv);
     wt += (s.hi - 1) / h->tile_elems - s.first_tile[kGridTile] + 1;
     wd += (s.hi - 1) / h->direct_elems - s.first_tile[kGridDirect] + 1;
     wv += (s.hi - 1) / vector_elems(h) - s.first_tile[kGridVector] + 1;
@@ -217,8 +218,8 @@ void work_range(const dadam_handle* h, Grid grid, uint32_t s0, uint32_t s1, uint
   const uint64_t T = grid == kGridTile ? h->tile_elems : grid == kGridDirect ? h->direct_elems : grid == kGridMix ? h->mix_tile_elems : vector_elems(h);
   const Segment& a = h->segs[s0];
   const Segment& b = h->segs[s1];
-  *w0 = a.work0[grid] + (uint32_t)(lo / T - a.first_tile[grid]);
-  *w1 = b.work0[grid] + (uint32_t)((hi - 1) / T - b.first_tile[grid]) + 1;
+  *w0 = h->seg_work[grid][s0] + (uint32_t)(lo / T - a.first_tile[grid]);
+  *w1 = h->seg_work[grid][s1] + (uint32_t)((hi - 1) / T - b.first_tile[grid]) + 1;
 }
 
 int check_bound(const dadam_handle* h) {
@@ -935,8 +936,7 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
       std::vector<char> image(bytes + kNumGrids * n * sizeof(uint32_t));
       memcpy(image.data(), h->segs.data(), bytes);
       for (int g = 0; g < (int)kNumGrids; ++g)
-        for (size_t k = 0; k < n; ++k)
-          memcpy(image.data() + bytes + (g * n + k) * sizeof(uint32_t), &h->segs[k].work0[g], sizeof(uint32_t));
+        memcpy(image.data() + bytes + g * n * sizeof(uint32_t), h->seg_work[g].data(), n * sizeof(uint32_t));
       e = hipMalloc((void**)&h->d_segs, image.size());
       if (e == hipSuccess) e = hipMemcpy(h->d_segs, image.data(), image.size(), hipMemcpyHostToDevice);
       h->d_seg_work = reinterpret_cast<uint32_t*>(h->d_segs + n);

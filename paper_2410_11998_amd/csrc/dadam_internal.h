@@ -21,12 +21,12 @@ enum Grid : uint32_t { kGridTile = 0, kGridDirect = 1, kGridMix = 2, kGridVector
 // A maximal run of contiguous tensors with the same hyper-parameters: elements [lo, hi) of every buffer.  Work items are tiles of a
 // fixed grid anchored at element 0, so that vector accesses are 16-byte aligned whenever the
 // buffers are; a tile that sticks out of [lo, hi) is clipped element by element.
-struct Segment {
+struct alignas(64) Segment {
   uint64_t lo, hi;
   uint64_t first_tile[kNumGrids];  // per Grid: index of the first tile of that grid that intersects the segment
-  uint32_t work0[kNumGrids];       // per Grid: number of work items (tiles; per row in direct mode) in earlier segments
   float weight_decay;      // decoupled weight decay of the tensors in this segment
 };
+static_assert(sizeof(Segment) == 64, "a work item finds all of its segment in one line");
 
 // How the workgroups of a direct-kernel launch walk the (piece, row) pairs.
 enum Order : uint32_t { kOrderLinear = 0, kOrderDieGroups = 1, kOrderDieBlocks = 2 };
@@ -106,7 +106,7 @@ struct StepArgsFor {
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
   uint32_t reserve_lds;  // direct kernels: LDS a workgroup reserves (see bounded_occupancy_lds)
   const Segment* seg;        // device
-  const uint32_t* seg_work;  // device: per Grid, the first work item of every segment
+  const uint32_t* seg_work;  // device: per Grid, the first work item of every segment (tiles; per row in direct mode)
   uint32_t wide_search;      // small launch: all lanes search the segments (see locate)
   uint64_t first_tile;       // one segment: its first tile of this launch's grid ...
   float weight_decay;        // ... and its decay
