@@ -185,7 +185,7 @@ __device__ __forceinline__ void store_elem(void* base, uint64_t e, float v) {
   }
 }
 
-// Element e of type T (float or uint16_t).  An index of 32 bits counts from the tile's first element (see Index): the distance in
+// Element e of type T (float or uint16_t).  An index of 32 bits counts from the tile's first element (see from): the distance in
 // bytes then is 32 bits beside a uniform address.
 template <typename T>
 __device__ __forceinline__ const T* at(const void* base, uint64_t e) { return reinterpret_cast<const T*>(base) + e; }
@@ -611,10 +611,9 @@ __device__ __forceinline__ float list_w(const RowList& r, int k) {
 // `origin` on.  A kernel's registers are those of its largest body: with clamped 64-bit indexes the body for such tiles took 4 to
 // 20 more than that for whole ones, and a wavefront per SIMD from 119 kernels.  us, without that body / 64 / 32 bits: bfloat16 steps that
 // do not stream 145.0 / 146.5 / 144.4 (16 replicas), 76.9 / 77.5 / 76.6 (96 replicas); 25 MB buckets of a bfloat16 row 2252 / 2246 / 2177;
-// 8 replicas of 300 odd-sized tensors 68.8 / 60.0 / 58.8; mixing of 16 x 19 million elements 1464 / 1468 / 1452.  Mixing that does not
-// stream has registers to spare and keeps 64 (12 bfloat16 replicas of odd-sized tensors 32.0 / 33.8).
-template <int CLIP, bool NARROW = true>
-using Index = typename std::conditional<CLIP >= kGroups && NARROW, uint32_t, uint64_t>::type;
+// 8 replicas of 300 odd-sized tensors 68.8 / 60.0 / 58.8; mixing of 16 x 19 million elements 1464 / 1468 / 1452.  Mixing by tiles that
+// do not stream, direct mixing, mixing of loops and accumulation have registers to spare and keep 64: tiles of 12 bfloat16 replicas of
+// odd-sized tensors 32.0 / 33.8, direct mixing of 48 rows of 250 thousand elements 102 / 115, accumulation of 16 rows 1843 / 2134.
 template <int BYTES, typename P>
 __device__ __forceinline__ P* from(P* base, uint64_t origin) {
   typedef typename std::conditional<std::is_const<P>::value, const char, char>::type Byte;
@@ -863,7 +862,7 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
   // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
   constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
-  constexpr bool NARROW = Needs<PHASE>::grad || NT;  // see Index
+  constexpr bool NARROW = Needs<PHASE>::grad || NT;  // see `from`
   const int clip = clip_of(a, full, hi);
   if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
   else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, wd, b, lane, wave);
@@ -1080,7 +1079,8 @@ __device__ __forceinline__ void direct_entry(const A& a) {
     const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, p.lo, p.hi, lane);
     const uint32_t c[1] = {cut.e};
     if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
-    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.wd, lane);
+    else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.wd, lane);
+    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
     else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
   }
 }
@@ -1157,12 +1157,12 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM: the bytes moved are
 // those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
-template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A>
-__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, Index<CLIP> start, Index<CLIP> lo,
-                                          Index<CLIP> hi, float wd, int lane, int wave, int waves) {
+template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A, typename E>
+__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, E start, E lo, E hi, float wd, int lane,
+                                          int wave, int waves) {
   constexpr bool NT = HINT != 0;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
-  const Index<CLIP> e[1] = {start};
+  const E e[1] = {start};
   const Loop l = a.loops[loop];
   // This wavefront's rows, every `waves`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
   // each).  A wavefront that sums has at least three sources, so that the sum is never less accurate than the listed
@@ -1250,7 +1250,8 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   const int clip = clip_of(a, full, hi);
   const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
   if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
   else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
 }
 
@@ -1269,30 +1270,30 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
   }
 }
 
-template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A, typename E>
-__device__ __forceinline__ void acc_body(const A& a, int row, uint64_t origin, const E (&e)[U], E lo, E hi) {
+template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A>
+__device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi) {
   constexpr int H = kGroupStep<NT>;
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
 #pragma unroll
-  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(from<GT::bytes>(a.grad[row], origin), e[u], lo, hi, g[u]);
+  for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(a.grad[row], e[u], lo, hi, g[u]);
   if constexpr (Needs<PHASE>::moments_out) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e[u], lo, hi, mh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e[u], lo, hi, mh[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e[u], lo, hi, vh[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e[u], lo, hi, vh[u]);
   }
   if constexpr (Needs<PHASE>::acc_in) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e[u], lo, hi, b[u]);
+    for (int u = 0; u < U; ++u) load_vals<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e[u], lo, hi, b[u]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e, lo, hi, b);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
   }
 }
 
@@ -1315,12 +1316,9 @@ __device__ __forceinline__ void acc_entry(const A& a) {
   if (active && p.any) {
     constexpr int CUT = NT && EXT ? kElements : kGroups;  // see tile_entry
     const int clip = clip_of(a, p.full, p.hi);
-    const uint64_t tbase = p.index * (kWave * VEC);
-    const Cut cut = cut_of<VEC, 1, NT>(tbase, p.lo, p.hi, (int)threadIdx.x);
-    const uint32_t c[1] = {cut.e};
-    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, 0, e, p.lo, p.hi);
-    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, tbase, c, cut.lo, cut.hi);
-    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, 0, e, p.lo, p.hi);
+    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi);
+    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi);
+    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi);
   }
 }
 
@@ -1340,8 +1338,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   const uint64_t e0 = lane_start<VEC, 2, NT>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, NT>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, 0, e, lo, hi);
-    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, 0, e, lo, hi);
+    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, e, lo, hi);
+    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, e, lo, hi);
   }
 }
 
