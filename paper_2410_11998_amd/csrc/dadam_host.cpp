@@ -90,8 +90,9 @@ struct dadam_handle {
   uint64_t n_work_m = 0;
   bool nontemporal = false;
   bool decays = false;  // some tensor carries weight decay
-  // Few blocks of elements lie in one segment: lanes are hardly ever spread and every tile needs its segment searched, so
-  // streaming launches keep the shapes and orders of contiguous lanes.  Fraction of 8 TB/s, contiguous / spread choices, segments of
+  // Segments of fewer than 65536 elements on average: lanes are hardly ever spread and most tiles need their segment searched, so
+  // streaming launches keep the shapes and orders of contiguous lanes.  (By the share of elements in whole blocks, which takes a long tensor
+  // beside many short ones for long, steps of GPT-2 shapes with decay gain nothing and unfused steps lose up to 7 % at 16 rows.)  Fraction of 8 TB/s, contiguous / spread choices, segments of
   // 1100 elements: exp. graph of 16 0.74 / 0.70, of 64 0.68 / 0.66, pairs of 64 0.53 / 0.51.
   bool short_segments = false;
   int vec = 4;
@@ -880,10 +881,6 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   shape.nontemporal = h->nontemporal;
   shape.ut = env_int("DADAM_TILE_UT", shape.ut);
   shape.waves = env_int("DADAM_TILE_WAVES", shape.waves);
-  if (!tile_shape_supported(shape)) {
-    delete h;
-    return fail(nullptr, DADAM_EINVAL, "unsupported tile shape (waves %d, ut %d)", shape.waves, shape.ut);
-  }
   // Streaming float32 steps: two vectors a lane, which lie the way the memory serves best (see lane_start), up to the
   // sources whose tile fits; sixteen wavefronts from 16 rows on.  Fraction of 8 TB/s, one vector by eight wavefronts / two by
   // eight / two by sixteen, 3e8 to 2e9 elements: 16 rows 0.710 / 0.802 / 0.814, 24 rows 0.801 / 0.802 / 0.809, 48 rows 0.783 / 0.806 /
@@ -898,6 +895,10 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
     // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
     shape.waves = env_int("DADAM_TILE_WAVES", 16);
+  }
+  if (!tile_shape_supported(shape)) {
+    delete h;
+    return fail(nullptr, DADAM_EINVAL, "unsupported tile shape (waves %d, ut %d)", shape.waves, shape.ut);
   }
   h->shape = shape;
   h->tile_elems = (uint32_t)(kWave * h->vec * shape.ut);

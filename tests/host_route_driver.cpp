@@ -17,7 +17,7 @@
 static bool capturing = false;
 static std::vector<std::function<void()>> recorded;
 static const char* fail_launch = nullptr;  // name of the launcher whose next call fails
-static std::string route;
+static std::string route, how;  // how: the shape of the tile's workgroup, the order of a row launch
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -43,16 +43,21 @@ static int enqueue(const char* name, std::function<void()> work) {
 namespace dadam {
 static double static_scratch[kConsensusPartials];
 int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint32_t, uint32_t, void*) {
+  how = std::to_string(shape.waves) + "x" + std::to_string(shape.ut) + (shape.nontemporal ? " streaming" : "") + " block " +
+        std::to_string(a.xcd_block) + (a.d == 0 ? " cut by elements" : "");
   route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
   double* p = a.partials;
   return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
 }
 int launch_direct(int, int, Phase, bool, bool, bool whole_items, const StepArgs& a, uint32_t, void*) {
+  how = std::string(a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : a.order == kOrderDieGroups ? "groups" : "linear") +
+        (whole_items ? ", whole items" : "") + (a.d == 0 ? " cut by elements" : "");
   route = a.order == kOrderDieBlocks ? "direct-blocks" : a.order == kOrderDieGroups ? "direct-groups" : "direct";
   if (whole_items) route += " whole";
   return enqueue("direct", [] {});
 }
-int launch_accumulate(int, Phase, bool, bool whole_items, const StepArgs&, uint32_t, void*, int) {
+int launch_accumulate(int, Phase, bool, bool whole_items, const StepArgs& a, uint32_t, void*, int) {
+  how = (a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : std::string("linear")) + (whole_items ? ", whole items" : "");
   route = whole_items ? "whole" : "pieces";
   return enqueue("accumulate", [] {});
 }
@@ -68,7 +73,11 @@ int launch_consensus_sum(double* p, double* out, void*) {
 }
 int static_partials(double** out, uint32_t* capacity) { *out = static_scratch; *capacity = kConsensusPartials; return 0; }
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? 8 : 4; }
-bool tile_shape_supported(TileShape s) { return (s.waves == 4 || s.waves == 8) && (s.ut == 1 || s.ut == 2); }
+bool tile_shape_supported(TileShape s) {
+  if (s.ut == 2 && (s.waves == 8 || s.waves == 16)) return s.nontemporal;
+  if (s.ut == 1 && s.waves == 16) return true;
+  return (s.waves == 4 && s.ut == 2) || ((s.waves == 4 || s.waves == 8) && s.ut == 1);
+}
 }  // namespace dadam
 
 // ---- a handle and its buffers (addresses only: nothing reads or writes through them) ----
@@ -323,6 +332,33 @@ static void accumulation() {
   }
 }
 
+// Large layouts of one long segment, or of segments of `each` elements: which kernel, in which shape and order.
+static void large(uint64_t each, uint64_t total) {
+  struct { int rows, degree; } cases[] = {{4, 3}, {8, 3}, {16, 3}, {18, 2}, {24, 3}, {32, 2}, {33, 2}, {32, 3}, {32, 6}, {40, 2}, {64, 3}, {96, 2}, {96, 3}, {96, 4}, {96, 5}, {96, 6}, {96, 7}};
+  for (uint32_t dtype : {DADAM_F32, DADAM_BF16})
+    for (const auto& c : cases) {
+      Rows r;
+      for (int i = 0; i < c.rows; ++i) {
+        std::vector<int32_t> cols;
+        for (int k = 0; k < c.degree; ++k) cols.push_back((i + k) % c.rows);
+        add_row(r, cols);
+      }
+      const uint64_t d = total / c.rows;
+      std::vector<dadam_tensor_desc> ts;
+      for (uint64_t at = 0; at < d; at += each + 8) ts.push_back({at, at + each < d ? each : d - at, 0.f, 0});
+      Sim s(c.rows, c.rows, ts, r, dtype);
+      s.bind();
+      auto told = [&](const std::string& kind) { return (kind.substr(0, 6) == "direct" ? "direct " : kind + " ") + how; };
+      const std::string step = told(s.step(DADAM_FUSE_ACCUM)), mix = told(s.mix(0));
+      double out = 0.0;
+      if (dadam_mix_consensus(s.h, 0, 0, &out, nullptr) != DADAM_OK) { printf("refused\n"); exit(1); }
+      const std::string error = how;
+      if (dadam_accumulate(s.h, s.g.data(), 1, nullptr) != DADAM_OK) { printf("refused\n"); exit(1); }
+      say(((dtype == DADAM_BF16 ? "bf16 " : "f32 ") + std::to_string(c.rows) + " of " + std::to_string(c.degree)).c_str(),
+          step + "; mix " + mix + "; error " + error + "; accumulate " + how);
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "foreign_in_place") foreign_in_place();
@@ -331,6 +367,10 @@ int main(int argc, char** argv) {
   else if (what == "few") few();
   else if (what == "die_order") die_order();
   else if (what == "accumulation") accumulation();
+  else if (what == "long") large(1ull << 40, 120000000);       // streams
+  else if (what == "short") large(1100, 120000000);            // streams
+  else if (what == "ordinary11") large(1ull << 40, 11000000);  // does not
+  else if (what == "ordinary20") large(1ull << 40, 20000000);
   else { printf("unknown question\n"); return 2; }
   return 0;
 }

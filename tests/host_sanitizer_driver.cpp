@@ -19,7 +19,11 @@ int launch_consensus_sum(double*, double*, void*) { return 0; }
 int launch_probe(const void* const*, void* const*, uint64_t, uint32_t, void*) { return 0; }
 int static_partials(double** out, uint32_t* capacity) { *out = nullptr; *capacity = kConsensusPartials; return 0; }
 int vec_elems(int xdt) { return xdt == DADAM_BF16 ? 8 : 4; }
-bool tile_shape_supported(TileShape s) { return (s.waves == 4 || s.waves == 8) && (s.ut == 1 || s.ut == 2); }
+bool tile_shape_supported(TileShape s) {
+  if (s.ut == 2 && (s.waves == 8 || s.waves == 16)) return s.nontemporal;
+  if (s.ut == 1 && s.waves == 16) return true;
+  return (s.waves == 4 && s.ut == 2) || ((s.waves == 4 || s.waves == 8) && s.ut == 1);
+}
 }
 int main() {
   std::mt19937_64 rng(1);
