@@ -1329,7 +1329,13 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t item, row_at;
-  const bool active = die_block_piece(blockIdx.x, a.n_rows, a.n_xcd, a.n_pieces, a.xcd_block, item, row_at, a.die_run);
+  bool active = true;
+  if (a.order == kOrderDieBlocks) {
+    active = die_block_piece(blockIdx.x, a.n_rows, a.n_xcd, a.n_pieces, a.xcd_block, item, row_at, a.die_run);
+  } else {
+    item = blockIdx.x / a.n_rows;
+    row_at = blockIdx.x - item * a.n_rows;
+  }
   const int row = (int)row_at;
   uint64_t tile_index, lo, hi;
   float wd;

@@ -493,8 +493,11 @@ bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t 
 // The same question for accumulation.  Time of one-wavefront pieces over whole items, 3e8 elements: 1 row 0.90, 16 rows 0.96,
 // 24 rows 0.98, 32 rows 0.98, 40 rows 1.03, 48 rows 1.02, 64 rows 1.01, 72 rows 0.99, 96 rows 1.03, 128 rows 1.00, 160 rows
 // 1.00 (bfloat16 0.96, 0.93, 0.97, 0.97, 1.00, 1.00, 1.01, 0.98, 1.01, 0.99, 0.99); 3e7 elements 0.92 to 1.01.
+// Segments of 1100 elements, us, pieces / whole items, 2e8 elements: 40 rows 2300 / 1804, 64 rows 2352 / 1894, 90 rows 2250 / 1960, 110 rows
+// 2222 / 1996, with bfloat16 parameters (eight elements a lane) 1789 / 1975, 1847 / 2007, 1966 / 2558, 2018 / 2566.
 bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
   const uint32_t R = h->cfg.n_rows;
+  if (h->short_segments && h->vec == 8) return false;
   return h->nontemporal && elems >= kManyElems && ((R > 32 && R <= 64) || (R > 80 && R < 128));
 }
 
@@ -1182,11 +1185,11 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
-  const bool whole_items = !h->short_segments && accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
+  const bool whole_items = accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
   // Rows share nothing here, but a die that walks run after run row by row has few arrays in use at a time.  Fraction of 8 TB/s of
   // the bytes moved, one row of a piece after the other / runs, 3e8 elements: 2 rows 0.80 / 0.79, 4 rows 0.80 / 0.82, 16 rows
   // 0.75 / 0.80, 40 rows 0.61 / 0.81, 64 rows 0.67 / 0.81, 100 rows 0.63 / 0.80, bfloat16 parameters 24 rows 0.66 / 0.73, 128 rows 0.56 / 0.75.
-  if (h->nontemporal && !h->short_segments && h->cfg.n_rows >= 4) {  // whole items always go this way
+  if (h->nontemporal && !h->short_segments && h->cfg.n_rows >= 4) {
     a.order = kOrderDieBlocks;
     set_die_run(whole_items ? kDieRunPieces / kDirectItem : kDieRunPieces, &a);
   }
