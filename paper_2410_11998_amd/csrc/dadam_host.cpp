@@ -511,13 +511,16 @@ bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
 //   0.64, seven 0.70 / 0.60 (bfloat16 four 0.73 / 0.75, five 0.73 / 0.74, six 0.74 / 0.73, seven 0.73 / 0.68), mixing with
 //   three (128 rows) 0.63 / 0.66, four 0.59 / 0.48, seven 0.51 / 0.36 (bfloat16 four 0.46 / 0.48, six 0.41 / 0.39).
 // Launches that do not stream stay: 128 rows of seven, 1e7 elements, 0.48 / 0.60.
+// Segments of 1100 elements, us, tile / direct: steps of bfloat16 rows of seven, 96 of them 1263 / 1091, 128 rows 1292 / 1107 (float32 1352 / 1503, 1376 /
+// 1577); mixing in pairs 24 rows 898 / 1673, 32 rows 910 / 1606, 48 rows 1088 / 1902, 64 rows 1068 / 1891 (bfloat16 545 / 1801, 514 / 1797, 655 / 2123, 717 / 2120), 96 and
+// 160 rows 1712 / 2405, 1791 / 2808 (1321 / 2578, 1555 / 2957), with three sources 504 / 791, 468 / 812 (398 / 881, 409 / 884).
 bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles, bool usual) {
   if (n_tiles < kManyTiles) return usual;
   const uint32_t C = h->cfg.n_cols;
-  if (usual && h->short_segments) return true;
+  if (h->short_segments && (usual || mix_only)) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
-  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5);
-  return mix_only && C < 32 && !h->short_segments;
+  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
+  return mix_only && C < 32;
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
