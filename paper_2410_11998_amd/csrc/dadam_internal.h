@@ -116,7 +116,7 @@ struct StepArgsFor {
   uint32_t work_begin;  // first work item (in tiles) of this launch
   uint32_t n_xcd;       // dies that consecutive workgroup ids are dealt over (tile order)
   uint32_t xcd_block;   // tile mode: tiles per block; blocks go to the dies in turn (0: one contiguous share each)
-  uint64_t d;                 // elements of a buffer
+  uint64_t d;                 // elements of a buffer (0: cut tiles load element by element, see cut_by_elements)
   uint64_t clip_lo, clip_hi;  // element range of this launch (whole layout or a tensor range)
   double* partials;           // kConsensusPartials doubles (device), used by kMixConsensus only
   Scalars s;
