@@ -483,7 +483,10 @@ bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only
   if (n_tiles < kManyTiles) return true;
   const uint32_t R = h->cfg.n_rows;
   if (mix_only) return false;
-  if (!h->nontemporal) return true;
+  if (!h->nontemporal) {
+    const bool even = R >= 32 && R < 64 && R % h->n_xcds == 0 && slot.max_degree <= 2;
+    return !(even && (h->vec == 8 || (uint64_t)n_tiles * vector_elems(h) * R < kPairElems));
+  }
   if (R < 64) return !h->short_segments && (R < 32 || slot.max_degree > 2);
   const bool wide = h->vec == 8;
   if (wide && R >= 72 && (R < 80 || R > 128)) return false;

@@ -137,6 +137,7 @@ constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launche
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
 constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there, whole_items, accumulate_whole_items
+constexpr uint64_t kPairElems = 13000000;   // the same, of launches that do not stream; measured, see rows_stay_on_one_die
 constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
 constexpr uint32_t kBoundedPieces = 65536, kInFlightBytes = 90 * 1024;  // measured, see bounded_occupancy_lds
 constexpr uint32_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;        // LDS of a compute unit; it is given out in granules
