@@ -262,8 +262,8 @@ int dadam_set_lr(dadam_handle* h, float lr);
 int dadam_get_plan_info(const dadam_handle* h, dadam_plan_info* out);
 
 /* The choice between tile and direct mode for a step with this slot when no FORCE flag is given, as described at the
- * flags above: 1 tile, 0 direct, negative status on error.  Launches of rows that share whole neighbour lists and launches
- * of few tiles may then run in other kernels all the same. */
+ * flags above: 1 tile, 0 direct, negative status on error.  Launches of rows that share whole neighbour lists, launches
+ * of few tiles and very large ones may then run in other kernels all the same. */
 int dadam_slot_uses_tile_mode(const dadam_handle* h, uint32_t slot);
 
 /* The order in which direct mode takes the rows of this slot (order_out: n_rows entries, a permutation of

@@ -21,8 +21,8 @@
 //
 // Every access of a full tile is a 128-bit (float32) or 64-bit (bfloat16) load or store per lane,
 // laid out so that each instruction of a wavefront covers whole lines: one contiguous run of memory, or in kernels that
-// stream two or four of them (see lane_start); lanes at
-// the ragged edge of a segment fall back to element accesses.  Neighbour lists are read once per
+// stream two or four of them (see lane_start).  Tiles that a segment's edge cuts load whole groups of four and store single elements
+// at the edge, or load element by element too (see Clip).  Neighbour lists are read once per
 // row as one coalesced load (one entry per lane) and handed out with readlane, so the inner loop
 // has no dependent scalar memory traffic - which also means that no lane may leave a wavefront
 // before the last readlane (see direct_body).
@@ -103,9 +103,9 @@ __device__ __forceinline__ bool die_block_piece(uint32_t b, uint32_t R, uint32_t
 // Where a lane's first group of four elements lies, for tile `index` of N = 64 VEC U elements of a launch over [lo, hi).
 //
 // In streaming kernels the two halves of a wavefront work 8192 or 16384 elements apart: the tiles of a block of twice that
-// many elements take its two halves side by side.  Address bits seven apart (8 and 15, 9 and 16) select the same channel
-// of the memory, and what an instruction touches in one channel is served from one open row where it differs in both.
-// Found by trying which address bits the sixteen-lane groups, the lane's vectors, the dies and time should have: two
+// many elements take its two halves side by side.  Why that helps is not known (timings alone show that address bits seven apart,
+// 8 and 15, 9 and 16, are to differ together within an instruction, as if such bits chose a channel of the memory and an open row
+// served both places; no counter shows either).  Found by trying which address bits the sixteen-lane groups, the lane's vectors, the dies and time should have: two
 // placements of a wavefront's four runs of 256 bytes stand out, {0, 256, 32 K, 32 K + 256} and {0, 512, 64 K, 64 K + 512}
 // with the lane's second group between; all others lie with or below the contiguous kilobyte.  Fraction of 8 TB/s,
 // contiguous / spread: 7 reads and 2 writes 0.79 / 0.85, 80 reads and 32 writes of a tile of 16 rows with two vectors a lane 0.67 / 0.82
@@ -1003,8 +1003,8 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
   // The neighbour list sits one entry per lane and is handed out with readlane, which must find a
   // loaded value in whichever lane it asks.  So no lane may leave before the last readlane: a
-  // thread of a clipped tile whose vectors all lie outside the range runs through the body with
-  // every access masked off instead of returning early.  (With an early return the compiler is
+  // thread of a cut tile whose vectors all lie outside the range runs through the body with its stores (and loads, where
+  // they go by elements) masked off instead of returning early.  (With an early return the compiler is
   // free to sink the list's load below it, into the lanes that stay - and a row whose leading
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_position_list(a, position, lane);
@@ -1091,6 +1091,8 @@ __device__ __forceinline__ void direct_entry(const A& a) {
 // read, 1.20 written in 449 us); longer rows fetch a source once for every die that has a reader, and those bytes bound them
 // (96 rows of seven sources: 4.84 GB read for 1.20 of sources, 897 us, 6.7 TB/s).  us, two rounds, one-wavefront pieces / this: 72 rows
 // in pairs 631 / 465, 96 rows of three sources 608 / 500, 96 replicas of a one-peer graph, one round of each hop, 2030 / 1640.
+// Cut items load element by element, here and in k_rows and k_acc_rows: only large launches come here, and those over short
+// segments, where cut items are many, mix by the tile (see staging_is_faster).
 constexpr int kWideWaves = kDirectItem / 2;
 template <typename XT, int HINT, bool EXT>
 __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a) {

@@ -397,7 +397,8 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool de
     // one-peer graph: mixing 0.77 against 0.75 of peak, the whole step 0.792 against 0.788; with three
     // sources a row, a ring, the tile is as fast or faster);
     // (2) a tile so large that a CU holds one workgroup of it (more than 80 sources on 160 KB), with rows of
-    // at most eight sources (128 replicas: the step 0.76-0.79 against 0.48-0.49, mixing 0.50-0.74 against 0.40).
+    // at most eight sources (128 replicas, launches that do not stream: the step of seven sources 0.60 against 0.48; launches that stream
+    // are decided in staging_is_faster).
     const bool ordered = slot.reuse && direct_legal && h->n_xcds > 1;
     const bool pairs_stream = ordered && slot.max_degree <= 2 && h->cfg.n_cols > 16;
     const bool alone_streams = ordered && slot.max_degree <= 8 && lone_tile(h);
@@ -470,15 +471,21 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
 //   128 rows   1.00  1.03   0.98  0.98         128 rows   0.95  1.04   1.02  1.01     (3e8: 1.08)
 //   160 rows   0.98  0.99   1.04  0.99         160 rows   0.88  0.99   0.98  0.98
 // That was with all rows of a piece one after the other.  Since large launches walk runs of 256 pieces a die row after row,
-// blocks are ahead of groups nearly everywhere: a die has the arrays of few rows in use at a time instead of those of all
-// (64 rows of 6 arrays are more pages than a compute unit's address translation holds), and rows that do not divide among the dies leave none
-// waiting.  Fraction of 8 TB/s, groups / piece by piece / runs of 64 / 256 / 512, two rows to a source: 64 rows of 26 million elements
+// blocks are ahead of groups in every streaming launch of at least 1024 tiles: a die has the arrays of few rows in use at a time
+// instead of those of all, and rows that do not divide among the dies leave none waiting.  Fraction of 8 TB/s, groups / piece by piece / runs of 64 / 256 / 512, two rows to a source: 64 rows of 26 million elements
 // 0.83 / 0.78 / 0.83 / 0.84 / 0.84, 18 rows 0.67 / - / 0.81 / 0.80 / 0.81, 32 rows 0.82 / 0.82 / 0.83 / 0.83 / 0.84, 40 rows 0.79 / - / 0.79 / 0.82 /
 // 0.82, bfloat16 18 rows 0.67 / - / 0.78 / 0.80 / 0.80; rings of 48 in bfloat16 0.79 / - / 0.80 / 0.80 / 0.80, of 64 0.80 / 0.72 / 0.80 /
 // 0.80 / 0.80, of 128 0.80 / 0.76 / 0.79 / 0.78 / 0.79 (bfloat16 0.76 / 0.78 / 0.79 / 0.79 / 0.79).  Launches that do not stream, groups' time
 // over that of runs of 256: 18 rows 1.24, 26 rows (bfloat16) 1.04, 64 rows 1.03-1.07, ring of 100 1.03-1.07, 20 rows of 250 thousand
-// elements 1.02, 32 rows 1.03 and 0.96.  Pairs of 32 to 63 rows and the larger numbers of rows below the sizes of the table have stayed
-// with groups, 1 to 4 % behind.
+// elements 1.02, 32 rows 1.03 and 0.96.
+// Pairs of 32 to 63 rows and the larger numbers of rows below the sizes of the table have stayed with groups.  us of a loop of two,
+// groups / runs, float32 of 4e7, 1.2e8, 4e8 elements of all rows: 32 rows 372 / 366, 1104 / 1081, 3620 / 3586, 33 rows 415 / 370, 1240 / 1086, 4111 / 3583,
+// 36 rows 390 / 371, 1152 / 1084, 3849 / 3597, 48 rows 380 / 371, 1101 / 1082, 3642 / 3606, 63 rows 375 / 370, 1114 / 1078, 3666 / 3577, 72 rows 385 / 372,
+// 1115 / 1086, 3773 / 3605, 80 rows 381 / 371, 1103 / 1085, 3693 / 3596 (bfloat16 33 rows 341 / 305, 1004 / 884, 3336 / 2911, 48 rows 308 / 303, 912 / 881, 2978 /
+// 2947, 160 rows of 1.2e8, 4e8 931 / 882, 3043 / 2918).  Streaming launches of fewer tiles go piece by piece and would be faster by groups from 80
+// rows on (bfloat16, 4e7 elements: 96 rows 375 / 318, 128 rows 330 / 321).
+// Launches that do not stream, us, groups / runs, 1.1e7 and 1.6e7 elements: float32 32 rows 106 / 112, 170 / 163, 33 rows 120 / 107, 182 / 159, 40 rows 107 /
+// 107, 171 / 164, 48 rows 108 / 109, 168 / 155; bfloat16 of 1.6e7 32 rows 121 / 125, 40 rows 132 / 141, 48 rows 124 / 132, 56 rows 124 / 129, 33 rows 140 / 126.
 bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles) {
   if (n_tiles < kManyTiles) return true;
   const uint32_t R = h->cfg.n_rows;
@@ -928,8 +935,8 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // The mixing-only launch moves few bytes per row, so it wants more of them in flight per
   // wavefront: two vectors per lane and four wavefronts, as long as that tile stays small enough
   // (32 KB) for five workgroups to share a CU's LDS.  Measured: 16 sources (32 KB) +3 % over the
-  // step's shape; 64 sources (128 KB, one workgroup per CU) 0.68-0.75 of peak against 0.76 with the
-  // step's one-vector tile, so large source counts keep that.  Streaming float32 passes spread the lanes and take eight
+  // step's shape; with 64 sources (128 KB, one workgroup per CU) and contiguous lanes 0.68-0.75 of peak against 0.76 with the
+  // step's one-vector tile, so larger source counts keep the step's shape.  Streaming float32 passes spread the lanes and take eight
   // wavefronts up to 32 sources, then the step's sixteen (four / eight / sixteen: 12 sources 0.815 / 0.814, 16 sources 0.810 / 0.819, with
   // the error 0.750 / 0.778, 24 sources 0.797 / 0.812 / 0.809, with the error 0.73 / 0.80 / 0.74, 48 sources 0.63 / 0.745 / 0.780).
   h->mix_shape = shape;

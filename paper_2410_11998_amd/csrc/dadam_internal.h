@@ -20,7 +20,7 @@ enum Grid : uint32_t { kGridTile = 0, kGridDirect = 1, kGridMix = 2, kGridVector
 
 // A maximal run of contiguous tensors with the same hyper-parameters: elements [lo, hi) of every buffer.  Work items are tiles of a
 // fixed grid anchored at element 0, so that vector accesses are 16-byte aligned whenever the
-// buffers are; a tile that sticks out of [lo, hi) is clipped element by element.
+// buffers are; a tile that sticks out of [lo, hi) is stored, and at the end of a buffer loaded, element by element.
 struct alignas(64) Segment {
   uint64_t lo, hi;
   uint64_t first_tile[kNumGrids];  // per Grid: index of the first tile of that grid that intersects the segment
