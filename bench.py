@@ -10,8 +10,9 @@ zero moments) are resident in HBM before the timed region starts.  Prints ONE JS
 The headline workload is the benchmark's configuration 2 (16 replicas, static exponential graph,
 GPT-2-small tensor shapes, float32, s = 4); --config selects 1..5.  Without --config the same line
 also carries, under "per_config", the same measurement of configurations 3, 4 and 5 (each with its
-own step count, buffers freed in between) and, under "packed_frac", configuration 2 again with one
-ordinary allocation per buffer instead of the placed arena.
+own step count, buffers freed in between) and, under "placed_frac", configuration 2 again with its
+buffers placed in one arena instead of one ordinary allocation each (which is the faster layout of
+configurations 2 to 4 by 1 to 2.5 %, and the slower one of configuration 5 by 2.5 %).
 
 Other measurements share the set-up (none of them is the benchmark's value): --path selects another
 call sequence (unfused, mix, mix_consensus, accumulate, buckets), --bucket-streams and
@@ -239,6 +240,8 @@ def measure(args, want_cpu_sample: bool):
         B.dadam_set_topology(h, k, rp, col, w)
     B.dadam_bind(h, x_src, x_dst, m_hat, v_hat, acc)
     flags = B.DADAM_FUSE_ACCUM | {"auto": 0, "tile": B.DADAM_FORCE_TILE, "direct": B.DADAM_FORCE_DIRECT}[args.mode]
+    # (the choice by topology; very large launches and those of few tiles may be rerouted by size, which none of the five
+    # configurations' steps is)
     tile_mode = (args.mode == "tile") or (args.mode == "auto" and B.dadam_slot_uses_tile_mode(h, 0))
     info = B.dadam_get_plan_info(h)
     if args.path == "mix_consensus" and args.mode != "direct" and info.tile_mode_possible:
@@ -504,7 +507,7 @@ def main() -> int:
     ap.add_argument("--steps", type=int, default=None)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--config", type=int, default=None,
-                    help="1..5; default: 2 as the headline plus configurations 3, 4, 5 and the packed layout on the side")
+                    help="1..5; default: 2 as the headline plus configurations 3, 4, 5 and the placed layout on the side")
     ap.add_argument("--mode", choices=["auto", "tile", "direct"], default="auto")
     ap.add_argument("--inplace", action="store_true", help="update parameters in place instead of ping-pong")
     ap.add_argument("--pool", type=int, default=2, help="number of pre-generated gradient sets cycled through")
@@ -520,17 +523,17 @@ def main() -> int:
                          "stand-in for that bucket's backward pass; with --bucket-streams >= 2 the updates go to side "
                          "streams and overlap the next stand-in (the value then is not the benchmark's metric)")
     ap.add_argument("--standin-only", action="store_true", help="with --standin-backward: skip the updates (the stand-in alone)")
-    ap.add_argument("--layout", choices=["spread", "rule", "whole", "packed"], default="spread",
-                    help="spread: one arena over most of the free HBM, buffers dealt alternately over two stretches of it "
+    ap.add_argument("--layout", choices=["spread", "rule", "whole", "packed"], default="packed",
+                    help="packed: one ordinary allocation per buffer; spread: one arena over most of the free HBM, buffers dealt alternately over two stretches of it "
                          "that a timing probe finds to lie in different thirds of the memory (see "
                          "paper_2410_11998_amd/arena.py); rule: no probe, the two regions either side of the arena's 96 GiB "
                          "mark when the arena covers the device, equal distances otherwise; whole: the same arena, always "
-                         "equal distances; packed: one ordinary allocation per buffer")
+                         "equal distances")
     ap.add_argument("--prealloc-gib", type=int, default=0,
                     help="allocate that much device memory first and keep it (stands for a job's weights and activations)")
     ap.add_argument("--scale-div", type=int, default=1, help="divide tensor dimensions (debugging only)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
-    ap.add_argument("--no-side-configs", action="store_true", help="headline only: skip per_config and packed_frac")
+    ap.add_argument("--no-side-configs", action="store_true", help="headline only: skip per_config and placed_frac")
     ap.add_argument("--graph", action="store_true",
                     help="record a whole number of accumulation loops in a HIP graph once and time its replays "
                          "(launch gaps of --path buckets); per-launch times then are replay averages")
@@ -561,7 +564,7 @@ def main() -> int:
 
     if side_configs:
         # the other configurations of the benchmark, each over its own step count, and configuration 2 again
-        # with ordinary allocations; shorter runs of regions (the headline's regions carry the statistics)
+        # with placed buffers; shorter runs of regions (the headline's regions carry the statistics)
         import copy
         per = {}
         for cfg in (3, 4, 5):
@@ -571,10 +574,10 @@ def main() -> int:
             per[f"cfg{cfg}"] = brief(res)
         out["per_config"] = per
         a = copy.copy(args)
-        a.layout, a.repeats, a.copy_calibration = "packed", min(args.repeats, 5), False
+        a.layout, a.repeats, a.copy_calibration = "spread", min(args.repeats, 5), False
         res, _ = measure_and_release(a, want_cpu_sample=False)
-        out["packed_frac"] = res["roofline"]["frac"]
-        out["packed"] = brief(res)
+        out["placed_frac"] = res["roofline"]["frac"]
+        out["placed"] = brief(res)
 
     if sample is not None:
         wl, ns, x0_sample, g_samples, csrs = sample

@@ -138,8 +138,8 @@ def cmd_fused(a) -> int:
              f"  rocprofv3 --kernel-trace --stats --output-format csv -d OUT/kt -- {bench_command(a.kt)}",
              f"  rocprofv3 --pmc FETCH_SIZE --output-format csv -d OUT/fetch -- {bench_command(a.fetch)}",
              f"  rocprofv3 --pmc WRITE_SIZE --output-format csv -d OUT/write -- {bench_command(a.write)}", "",
-             "bench.py line of the kernel-trace run (per_config / packed / cpu_baseline left out):",
-             "  " + json.dumps({k: v for k, v in j.items() if k not in ("per_config", "packed", "cpu_baseline")}), "",
+             "bench.py line of the kernel-trace run (per_config / placed / cpu_baseline left out):",
+             "  " + json.dumps({k: v for k, v in j.items() if k not in ("per_config", "placed", "cpu_baseline")}), "",
              "Kernel statistics (from *_kernel_trace.csv, per dispatch), the library's kernels; shape = <param type, grad type,",
              "[waves, vectors per lane,] non-temporal>; k_probe: the placement probe's passes over 2 GiB:",
              f"  {'kernel':34s} {'phase':17s} {'calls':>5s} {'avg ms':>9s} {'min ms':>9s} {'max ms':>9s}"]
