@@ -1210,10 +1210,12 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   DeviceGuard guard(h->cfg.device);
   if (guard.err != hipSuccess) return fail(h, DADAM_EHIP, "hipSetDevice: %s", hipGetErrorString(guard.err));
   const bool whole_items = accumulate_whole_items(h, (uint64_t)(w1 - w0) * h->direct_elems * h->cfg.n_rows);
-  // Rows share nothing here, but a die that walks run after run row by row has few arrays in use at a time.  Fraction of 8 TB/s of
-  // the bytes moved, one row of a piece after the other / runs, 3e8 elements: 2 rows 0.80 / 0.79, 4 rows 0.80 / 0.82, 16 rows
-  // 0.75 / 0.80, 40 rows 0.61 / 0.81, 64 rows 0.67 / 0.81, 100 rows 0.63 / 0.80, bfloat16 parameters 24 rows 0.66 / 0.73, 128 rows 0.56 / 0.75.
-  if (h->nontemporal && !h->short_segments && h->cfg.n_rows >= 4) {
+  // Rows share nothing here, but with many of them a die that walks run after run row by row has few arrays in use at a time.  us of a
+  // loop of four, one row of a piece after the other / runs, 5e8 elements: float32 4 rows 4790 / 5136, 8 rows 4752 / 4984, 16 rows 4712 / 4853,
+  // 24 rows 4649 / 4773, 32 rows 4869 / 4901, 40 rows 4581 / 4606 (2e9 elements 4 rows 18602 / 19346, 16 rows 19031 / 19612, 32 rows 19324 / 19491, but with arrays that lie badly 11040 / 10966 of a whole loop);
+  // bfloat16 8 rows 4092 / 4096, 16 rows 4048 / 3984, 24 rows 4013 / 3979, 32 rows 4167 / 4034.  Where the arrays lie badly runs gain more (fraction of
+  // 8 TB/s, 40 rows 0.61 / 0.81, 64 rows 0.67 / 0.81, 100 rows 0.63 / 0.80, bfloat16 parameters 24 rows 0.66 / 0.73, 128 rows 0.56 / 0.75).
+  if (h->nontemporal && !h->short_segments && h->cfg.n_rows >= (h->vec == 8 ? 16u : 32u)) {
     a.order = kOrderDieBlocks;
     set_die_run(whole_items ? kDieRunPieces / kDirectItem : kDieRunPieces, &a);
   }
