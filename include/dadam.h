@@ -296,7 +296,8 @@ int dadam_spread_offsets(const uint64_t* nbytes, uint32_t n, uint64_t arena_byte
  * in one third and half in another.  The library's own streaming kernels have their lanes apart (two places 32 or 64 KB
  * from each other) and depend on it little: placed / ordinary allocations 0.795 / 0.806 (16 float32 replicas of 124
  * million elements), 0.795 / 0.815 (one row of 355 million), 0.813 / 0.833 (64 replicas of 26 million), 0.801 / 0.780 (8
- * bfloat16 replicas of 774 million).  Placement is for the last kind, and for a caller's own passes over the same buffers.  Nobody outside the driver sees physical addresses, and where the
+ * bfloat16 replicas of 774 million); the first after 100, 160, 200 GiB of other allocations 0.792 / 0.781, 0.796 / 0.779,
+ * 0.801 / 0.778.  Placement is for the last kind and for such cards, and for a caller's own passes over the same buffers.  Nobody outside the driver sees physical addresses, and where the
  * driver puts one allocation relative to another is not predictable (measured: an arena pushed into
  * place by an allocation made before it, or placed by the amount of memory in use, lands elsewhere and
  * runs at 0.64-0.72).  What does hold is that ONE allocation of nearly the whole device (within 16 GiB of
@@ -313,8 +314,8 @@ int dadam_spread_offsets(const uint64_t* nbytes, uint32_t n, uint64_t arena_byte
  *   DADAM_PLACE_TWO_REGIONS     the rule above was applied;
  *   DADAM_PLACE_ARENA_ELSEWHERE the arena does not cover the device: offsets in it say nothing about
  *                               physical positions, and the buffers are placed at equal distances over
- *                               the whole arena instead (0.70-0.77 measured for arenas of 230-275 GiB,
- *                               the packed level if the arena happens to lie inside one third);
+ *                               the whole arena instead (0.774 measured for an arena of 235 GiB; with contiguous
+ *                               lanes 0.70-0.77, the packed level if the arena happens to lie inside one third);
  *   DADAM_PLACE_TOO_LARGE       half of the buffers do not fit below the boundary or the other half
  *                               between it and the next one: equal distances over the whole arena.
  * The caller hands `arena + offsets[k]` to dadam_bind and may use the space between the buffers for

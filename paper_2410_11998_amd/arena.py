@@ -6,9 +6,9 @@ where a fresh process's consecutive allocations land - and 0.78-0.79 when half o
 third and half in another.  The library finds the thirds inside an allocation by timing such a
 pass over pairs of chunks and deals the buffers over two stretches that lie in different
 thirds (``dadam_place_by_timing`` in include/dadam.h, which also says what is measured and why).
-The library's own streaming kernels have their lanes apart and no longer need it: steps in float32
-run 1-2 % faster from ordinary allocations, 8 bfloat16 replicas of 774 million elements 3 % faster
-from an arena.
+The library's own streaming kernels have their lanes apart and need it little: on a free card steps
+in float32 run 1-2 % faster from ordinary allocations and 8 bfloat16 replicas of 774 million
+elements 3 % faster from an arena; among 100 to 200 GiB of other allocations an arena is 1-3 % ahead.
 
 ``SpreadArena`` is the PyTorch side of that: it makes ONE allocation (by default: free memory
 minus ``keep_free_bytes``), hands it to the library before anything is stored in it, and gives out
