@@ -614,6 +614,9 @@ __device__ __forceinline__ float list_w(const RowList& r, int k) {
 // 8 replicas of 300 odd-sized tensors 68.8 / 60.0 / 58.8; mixing of 16 x 19 million elements 1464 / 1468 / 1452.  Mixing by tiles that
 // do not stream, direct mixing, mixing of loops and accumulation have registers to spare and keep 64: tiles of 12 bfloat16 replicas of
 // odd-sized tensors 32.0 / 33.8, direct mixing of 48 rows of 250 thousand elements 102 / 115, accumulation of 16 rows 1843 / 2134.
+// Steps of bfloat16 rows with float32 gradients by tiles that do not stream keep 64 too, but for the fold (74 registers, 71 with 32):
+// 8 replicas of 1 million elements in 200 odd-sized tensors 43.2 / 44.9, 5 replicas of 530 thousand 75.2 / 78.3, 16 replicas of 10 million
+// 166.4 / 166.7.  With bfloat16 gradients the same layouts give 42.4 / 44.1 and 147.8 / 146.1 (69 registers, 63 with 32).
 template <int BYTES, typename P>
 __device__ __forceinline__ P* from(P* base, uint64_t origin) {
   typedef typename std::conditional<std::is_const<P>::value, const char, char>::type Byte;
@@ -862,7 +865,8 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
   // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
   constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
-  constexpr bool NARROW = Needs<PHASE>::grad || NT;  // see `from`
+  // see `from`; bfloat16 rows with float32 gradients keep their wavefronts with 64 bits where nothing is folded
+  constexpr bool NARROW = NT || (Needs<PHASE>::grad && (XT::bytes == 4 || GT::bytes == 2 || PHASE == kFold));
   const int clip = clip_of(a, full, hi);
   if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
   else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, wd, b, lane, wave);
