@@ -352,11 +352,12 @@ bool range_decays(const dadam_handle* h, bool whole, uint32_t tb, uint32_t te) {
 // Streaming float32 steps over short segments: cut tiles load element by element where that is faster.  (Where every row's loads are
 // few lines, groups that lie outside a segment cost more than waiting does.)  us, elements / groups, 2e8 elements in segments of 1100, by the tile
 // kernel: 4 rows 1876 / 1926, 6 rows 1905 / 1962, 8 rows 2013 / 1982, 12 rows 1942 / 1943, 16 rows 1969 / 2000, 24 rows 1957 / 2010, 32 rows 1992 / 2031,
-// 48 rows 2069 / 2092, 64 rows 2102 / 2091; by the loop kernel: 16 rows 3877 / 3780, 24 rows 3795 / 3845, 32 rows 3802 / 3882, 48 rows 3997 / 4044.  In
+// 48 rows 2069 / 2092, 64 rows 2102 / 2091; 1.5e8 elements in segments of 1000: 50 rows 3937 / 3974, 56 rows 4415 / 4372, 60 rows 4780 / 4746;
+// by the loop kernel: 16 rows 3877 / 3780, 24 rows 3795 / 3845, 32 rows 3802 / 3882, 48 rows 3997 / 4044.  In
 // bfloat16, mixing and by the direct kernel groups are ahead, by 1 to 20 %.
 bool cut_by_elements(const dadam_handle* h, bool mix_only, bool by_loops) {
   const uint32_t R = h->cfg.n_rows;
-  return h->nontemporal && h->short_segments && h->vec == 4 && !mix_only && R < 64 && (by_loops ? R >= 24 : R < 8 || R >= 16);
+  return h->nontemporal && h->short_segments && h->vec == 4 && !mix_only && (by_loops ? R >= 24 && R < 64 : R < 8 || (R >= 16 && R < 56));
 }
 
 // Large launches in die blocks: a die takes runs of `run` pieces (or items), row after row (see rows_stay_on_one_die).
