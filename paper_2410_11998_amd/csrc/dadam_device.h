@@ -115,13 +115,15 @@ template <int VEC, int U, bool STREAM>
 __device__ __forceinline__ uint32_t lane_in_order(uint32_t l) {
   return STREAM && VEC * U > 4 ? 4 * (l & 15) + 8 * (l & 16) + (l >> 5) * 256 : 4 * l;
 }
+template <int VEC, int U>
+constexpr uint32_t spread_distance = kWave * VEC * U == 256 ? 8192 : 16384;  // elements between the halves
 template <int VEC, int U, bool STREAM>
 __device__ __forceinline__ uint64_t lane_start(uint64_t index, uint64_t lo, uint64_t hi, int lane) {
   constexpr uint32_t N = kWave * VEC * U;
   const uint64_t first = index * N;
   const uint32_t l = (uint32_t)lane;
   if constexpr (!STREAM) return first + 4 * l;
-  constexpr uint32_t NEAR = N == 256 ? 128 : 256, FAR = N == 256 ? 8192 : 16384, BLOCK = 2 * FAR;
+  constexpr uint32_t NEAR = N == 256 ? 128 : 256, FAR = spread_distance<VEC, U>, BLOCK = 2 * FAR;
   static_assert(N == 256 || N == 512 || N == 1024, "one or two vectors a lane");
   const uint64_t block = first & ~(uint64_t)(BLOCK - 1);
   const bool whole = block >= lo && block + BLOCK <= hi;
@@ -233,7 +235,7 @@ __device__ __forceinline__ void vstore(V* p, V v) {
   else *p = v;
 }
 
-enum Clip : int { kWhole = 0, kElements = 1, kGroups = 2, kGroupsZeroed = 3 };
+enum Clip : int { kWhole = 0, kElements = 1, kGroups = 2, kGroupsZeroed = 3, kMapped = 4 };  // kMapped: all tiles of a layout with a map
 template <typename E>
 __device__ __forceinline__ E nearest_group(E e, E lo, E hi) {
   const E first = lo & ~(E)3, last = (hi - 1) & ~(E)3;
@@ -247,7 +249,7 @@ __device__ __forceinline__ void load_vals(const void* base, E e, E lo, E hi, flo
   static_assert(CLIP != kGroupsZeroed, "only sources are cleared outside the range");
 #pragma unroll
   for (int h = 0; h < VEC / 4; ++h) {
-    const E group = e + (E)h * H, eh = CLIP == kGroups ? nearest_group(group, lo, hi) : group;
+    const E group = e + (E)h * H, eh = CLIP >= kGroups ? nearest_group(group, lo, hi) : group;
     if (CLIP != kElements || (eh >= lo && eh + 4 <= hi)) {
       if constexpr (T::bytes == 4) {
         f4 v = vload<NT && kNtStream>(reinterpret_cast<const f4*>(at<float>(base, eh)));
@@ -297,13 +299,44 @@ __device__ __forceinline__ void store_vals(void* base, E e, E lo, E hi, const fl
   }
 }
 
+// What a launch may do to the elements of a lane's vector where the layout has a map: for group h, in bits 8 h to 8 h + 3, which
+// elements it stores, and in bit 8 h + 4 whether they decay.
+constexpr uint32_t kStoreBits = 0x0F, kDecayBit = 0x10;
+template <typename E>
+__device__ __forceinline__ uint32_t bits_inside(E group, E lo, E hi) {
+  const uint32_t before = lo > group ? (lo - group < 4 ? (uint32_t)(lo - group) : 4u) : 0u;
+  const uint32_t end = hi > group ? (hi - group < 4 ? (uint32_t)(hi - group) : 4u) : 0u;
+  return (kStoreBits << before) & ((1u << end) - 1u);
+}
+template <typename T, int VEC, int H, bool NT, typename E>
+__device__ __forceinline__ void store_bits(void* base, E e, uint32_t bits, const float (&in)[VEC]) {
+#pragma unroll
+  for (int h = 0; h < VEC / 4; ++h) {
+    const E eh = e + (E)h * H;
+    const uint32_t b = (bits >> (8 * h)) & kStoreBits;
+    const float group[4] = {in[4 * h], in[4 * h + 1], in[4 * h + 2], in[4 * h + 3]};
+    if (b == kStoreBits) {
+      store_vals<T, 4, H, kWhole, NT>(base, eh, (E)0, (E)0, group);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (b >> j & 1) store_elem<T>(at<typename T::elem>(base, eh), j, group[j]);
+    }
+  }
+}
+
 // The stores of a row's UT vectors.  With one vector per lane there must be no loop around the store: a loop
 // that runs once has a loop-invariant address, the compiler's loop-invariant code motion then "promotes" the
 // location to a register and re-creates the store behind the loop - without the non-temporal hint (seen with
 // the bfloat16 one-vector tile kernels: 1.2 % slower on the ring of 8; the compile test counts the hints).
+// Where the layout has a map they follow `bits`.
 template <typename T, int VEC, int H, int CLIP, bool NT, int UT, typename E>
-__device__ __forceinline__ void store_vectors(void* base, const E (&e)[UT], E lo, E hi, const float (&in)[UT][VEC]) {
-  if constexpr (UT == 1) {
+__device__ __forceinline__ void store_vectors(void* base, const E (&e)[UT], E lo, E hi, const uint32_t (&bits)[UT],
+                                              const float (&in)[UT][VEC]) {
+  if constexpr (CLIP == kMapped) {
+#pragma unroll
+    for (int u = 0; u < UT; ++u) store_bits<T, VEC, H, NT>(base, e[u], bits[u], in[u]);
+  } else if constexpr (UT == 1) {
     store_vals<T, VEC, H, CLIP, NT>(base, e[0], lo, hi, in[0]);
   } else {
 #pragma unroll
@@ -358,6 +391,32 @@ __device__ __forceinline__ u4 load_raw(const void* base, E e, E lo, E hi) {
     u4 r = {half[0].x, half[0].y, half[1].x, half[1].y};
     return r;
   }
+}
+
+// What is computed from an index of a cut tile (clamped, scaled for each element type) is computed again after this, and held
+// in no register from row to row or from a row's loads to its stores.
+template <typename E>
+__device__ __forceinline__ E afresh(E e) {
+  if constexpr (sizeof(E) == 4) asm volatile("" : "+v"(e));
+  return e;
+}
+// Clears the elements of a vector that the map leaves out (group: its bytes of the vector's groups, see load_map).
+template <typename XT>
+__device__ __forceinline__ u4 cleared(u4 r, const uint32_t (&group)[XT::vec / 4]) {
+  if constexpr (XT::bytes == 4) {
+    r.x = group[0] & 1 ? r.x : 0u;
+    r.y = group[0] & 2 ? r.y : 0u;
+    r.z = group[0] & 4 ? r.z : 0u;
+    r.w = group[0] & 8 ? r.w : 0u;
+  } else {
+    auto halves = [](uint32_t b) { return (b & 1 ? 0xFFFFu : 0u) | (b & 2 ? 0xFFFF0000u : 0u); };
+    const uint32_t g0 = afresh(group[0]), g1 = afresh(group[1]);
+    r.x &= halves(g0);
+    r.y &= halves(g0 >> 2);
+    r.z &= halves(g1);
+    r.w &= halves(g1 >> 2);
+  }
+  return r;
 }
 
 template <typename XT>
@@ -419,10 +478,10 @@ struct Needs {
 // (Fields are read one by one through the pointer: copying the struct would put it in scratch.  The cast names global
 // memory: the compiler would otherwise merge a read of a segment with the same read of the argument block into one
 // through a generic pointer.)
-template <typename A>
+template <bool MAP = false, typename A>
 __device__ __forceinline__ void locate(const A& a, uint32_t work, uint64_t& tile_index,
                                        uint64_t& lo, uint64_t& hi, float& weight_decay) {
-  if (a.n_seg == 1) {  // the launch's range lies inside the only segment
+  if (MAP || a.n_seg == 1) {  // the launch's range lies inside the only segment, or the layout has a map
     tile_index = a.first_tile + work;
     lo = a.clip_lo;
     hi = a.clip_hi;
@@ -476,6 +535,69 @@ __device__ __forceinline__ Cut cut_of(uint64_t tbase, uint64_t lo, uint64_t hi, 
   c.lo = lo > tbase ? (uint32_t)(lo - tbase) : 0;
   c.hi = hi - tbase < N ? (uint32_t)(hi - tbase) : N;
   return c;
+}
+
+// Layouts with a map (many short tensors side by side): one dense grid of tiles over the whole vector.  A lane loads whole groups
+// of four as if the vector were one tensor, padding included, and the map's byte for each group, in flight beside the data, says which
+// elements it stores and whether they decay.  So no work item waits for a search (two trips to memory before the first load), a tile that
+// several tensors cross is launched once instead of once for each, lanes are spread and tiles as wide as in layouts of one segment.
+// Bound as those are, by HBM or by the launch; the map is a byte for every four elements of ONE row.  us, by segments / by the map, tensors of 1100 elements on
+// average: 8 replicas of 300 tensors, bfloat16, decay, four steps 63.3 / 53.8; one row of 3000 tensors, bfloat16, four steps 104 / 77 (float32 103 / 90); 16
+// replicas of 3000, four steps 1209 / 1005; 48 in pairs of 3000 1132 / 707; 96 in loops of 1000 2631 / 1988; mixing of 70 by threes of 1940, bfloat16
+// 566 / 302; accumulation apart, 100 rows of 1000 4386 / 2623; the consensus error of 100 rows of 400 282 / 226.  In kernels of their own (_map): as a
+// fourth body of the others it took a wavefront per SIMD from some and 0.5 to 3 % from mixing of layouts without a map.
+// A tile of such a layout: its elements counted from `origin`, its first one or that of its block where lanes are spread.
+struct MapTile {
+  uint64_t origin;
+  uint32_t e, lo, hi;
+};
+template <int VEC, int U, bool STREAM>
+__device__ __forceinline__ MapTile map_tile(uint64_t tbase, uint64_t lo, uint64_t hi, int lane) {
+  constexpr uint64_t BLOCK = 2 * spread_distance<VEC, U>;
+  const uint64_t block = tbase & ~(BLOCK - 1);
+  MapTile t;
+  t.origin = STREAM && block >= lo && block + BLOCK <= hi ? block : tbase;
+  t.e = (uint32_t)(lane_start<VEC, U, STREAM>(tbase / (kWave * VEC * U), lo, hi, lane) - t.origin);
+  t.lo = lo > t.origin ? (uint32_t)(lo - t.origin) : 0;
+  t.hi = hi - t.origin < BLOCK ? (uint32_t)(hi - t.origin) : (uint32_t)BLOCK;
+  return t;
+}
+
+// What the map has for a lane's vectors at e (counted from origin): loaded before the data and first looked at behind it.
+template <int VEC, int U>
+struct MapBytes {
+  uint32_t group[U][VEC / 4];
+};
+template <int VEC, int U, int H, typename A, typename E>
+__device__ __forceinline__ MapBytes<VEC, U> load_map(const A& a, uint64_t origin, const E (&e)[U]) {
+  const uint8_t* map = a.map + (origin >> 2);
+  MapBytes<VEC, U> m;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int h = 0; h < VEC / 4; ++h) m.group[u][h] = *at<uint8_t>(map, (E)((e[u] + h * H) >> 2));
+  return m;
+}
+// What the launch may do to them: what lies in [lo, hi) (full: all of the tile), and of that what the map has.
+template <int VEC, int U, int H, typename E>
+__device__ __forceinline__ void group_bits(const MapBytes<VEC, U>& m, bool full, const E (&e)[U], E lo, E hi, uint32_t (&bits)[U]) {
+  uint32_t inside[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) inside[u] = ~0u;
+  if (!full) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      inside[u] = 0;
+#pragma unroll
+      for (int h = 0; h < VEC / 4; ++h) inside[u] |= (bits_inside<E>(e[u] + h * H, lo, hi) | kDecayBit) << (8 * h);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    bits[u] = m.group[u][0];
+    if constexpr (VEC == 8) bits[u] |= m.group[u][1] << 8;
+    bits[u] &= inside[u];
+  }
 }
 
 // Pointers of the bound buffers.  EXT = false: from the argument block (at most kInlineRows rows and
@@ -623,17 +745,16 @@ __device__ __forceinline__ P* from(P* base, uint64_t origin) {
   return reinterpret_cast<P*>(reinterpret_cast<Byte*>(base) + origin * BYTES);
 }
 
-// What is computed from an index of a cut tile (clamped, scaled for each element type) is computed again after this, and held
-// in no register from row to row or from a row's loads to its stores.
-template <typename E>
-__device__ __forceinline__ E afresh(E e) {
-  if constexpr (sizeof(E) == 4) asm volatile("" : "+v"(e));
-  return e;
-}
 template <int STEP, int U, typename E>
 __device__ __forceinline__ void vector_indexes(E start, E (&e)[U]) {
 #pragma unroll
   for (int u = 0; u < U; ++u) e[u] = start + u * STEP;
+}
+
+// Weight decay of element j of a vector: where the layout has a map only if the bits say so.
+template <int CLIP>
+__device__ __forceinline__ float decay_of(uint32_t bits, int j, float wd, float x) {
+  return CLIP != kMapped || (bits & (kDecayBit << (8 * (j / 4)))) ? wd * x : 0.0f;
 }
 
 // The stream inputs of one row of a tile: gradient, moments, accumulator (whatever the phase needs).
@@ -664,7 +785,7 @@ __device__ __forceinline__ void load_row_inputs(const A& a, int i, uint64_t orig
 // Mixing from LDS, the update of Algorithm 3 and the stores of one row of a tile.
 template <typename XT, int PHASE, int VEC, int UT, int CLIP, bool NT, bool EXT, typename A, typename E>
 __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, RowList rl,
-                                           uint64_t origin, E start, E lo, E hi, float wd, int lane,
+                                           uint64_t origin, E start, E lo, E hi, const uint32_t (&bits)[UT], float wd, int lane,
                                            float (&g)[UT][VEC], float (&mh)[UT][VEC], float (&vh)[UT][VEC],
                                            float (&b)[UT][VEC]) {
   // neighbour sum in the order the row lists its entries: first a product, then fused
@@ -711,7 +832,7 @@ __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, Row
       float xs[VEC];
       unpack_raw<XT>(lds[(i * UT + u) * kWave + lane], xs);
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) decay[u][j] = wd * xs[j];
+      for (int j = 0; j < VEC; ++j) decay[u][j] = decay_of<CLIP>(bits[u], j, wd, xs[j]);
     }
   }
 
@@ -724,20 +845,25 @@ __device__ __forceinline__ void finish_row(const A& a, const u4* lds, int i, Row
 
   E e[UT];
   vector_indexes<kVectorStep<VEC, NT>>(VEC * UT > 4 ? afresh(start) : start, e);
-  store_vectors<XT, VEC, kGroupStep<NT>, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, i), origin), e, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(acc_of<EXT>(a, i), origin), e, lo, hi, b);
+  store_vectors<XT, VEC, kGroupStep<NT>, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, i), origin), e, lo, hi, bits, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(acc_of<EXT>(a, i), origin), e, lo, hi, bits, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(m_hat_of<EXT>(a, i), origin), e, lo, hi, mh);
-    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(v_hat_of<EXT>(a, i), origin), e, lo, hi, vh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(m_hat_of<EXT>(a, i), origin), e, lo, hi, bits, mh);
+    store_vectors<TF32, VEC, kGroupStep<NT>, CLIP, NT>(from<4>(v_hat_of<EXT>(a, i), origin), e, lo, hi, bits, vh);
   }
 }
 
 template <typename XT, typename GT, int PHASE, int W, int UT, int CLIP, bool NT, bool EXT, typename A, typename E>
-__device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, E start, E lo, E hi, float wd, uint32_t tile_id,
+__device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, E start, E lo, E hi, bool full, float wd, uint32_t tile_id,
                                           int lane, int wave) {
   constexpr int VEC = XT::vec;
   E e[UT];
   vector_indexes<kVectorStep<VEC, NT>>(start, e);
+  MapBytes<VEC, UT> map;
+  if constexpr (CLIP == kMapped) map = load_map<VEC, UT, kGroupStep<NT>>(a, origin, e);
+  uint32_t bits[UT];
+  // the consensus error counts on zeros outside the tensors
+  constexpr bool CLEAR = CLIP == kMapped && PHASE == kMixConsensus;
 
   const int n_rows = (int)a.n_rows;
   const RowPtrs<EXT> rp = load_row_ptrs<EXT>(a, lane);
@@ -765,7 +891,7 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, 
         const int c = c0 + k * W;
         if (c < n_cols) {
 #pragma unroll
-          for (int u = 0; u < UT; ++u) lds[(c * UT + u) * kWave + lane] = r[k][u];
+          for (int u = 0; u < UT; ++u) lds[(c * UT + u) * kWave + lane] = CLEAR ? cleared<XT>(r[k][u], map.group[u]) : r[k][u];
         }
       }
     }
@@ -776,12 +902,13 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, 
 #pragma unroll
       for (int u = 0; u < UT; ++u) r[u] = load_raw<XT, kGroupStep<NT>, CLIP, NT>(src, e[u], lo, hi);
 #pragma unroll
-      for (int u = 0; u < UT; ++u) lds[(c * UT + u) * kWave + lane] = r[u];
+      for (int u = 0; u < UT; ++u) lds[(c * UT + u) * kWave + lane] = CLEAR ? cleared<XT>(r[u], map.group[u]) : r[u];
     }
   }
   // the first row's neighbour list travels while the group meets at the barrier
   RowList rl_next = load_row_list(a, rp, wave < n_rows ? wave : 0, lane);
   __syncthreads();
+  if constexpr (CLIP == kMapped) group_bits<VEC, UT, kGroupStep<NT>>(map, full, e, lo, hi, bits);
 
   if constexpr (PHASE == kMixConsensus) {
     // Consensus error of the sources, sum_c (x_c - mean)^2 per element, as a by-product: the whole
@@ -834,11 +961,11 @@ __device__ __forceinline__ void tile_body(const A& a, u4* lds, uint64_t origin, 
     if (VEC * UT > 4) start = afresh(start);
     vector_indexes<kVectorStep<VEC, NT>>(start, e);
     load_row_inputs<GT, PHASE, VEC, UT, CLIP, NT, EXT>(a, i, origin, e, lo, hi, g, mh, vh, b);
-    finish_row<XT, PHASE, VEC, UT, CLIP, NT, EXT>(a, lds, i, rl, origin, start, lo, hi, wd, lane, g, mh, vh, b);
+    finish_row<XT, PHASE, VEC, UT, CLIP, NT, EXT>(a, lds, i, rl, origin, start, lo, hi, bits, wd, lane, g, mh, vh, b);
   }
 }
 
-template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT, typename A>
+template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT, bool MAP, typename A>
 __device__ __forceinline__ void tile_entry(const A& a) {
   constexpr int VEC = XT::vec;
   constexpr uint64_t TILE = (uint64_t)kWave * VEC * UT;
@@ -858,20 +985,25 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block);
   uint64_t tile_index, lo, hi;
   float wd;
-  locate(a, a.work_begin + b, tile_index, lo, hi, wd);
+  locate<MAP>(a, a.work_begin + b, tile_index, lo, hi, wd);
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
-  const uint64_t start = lane_start<VEC, UT, NT>(tile_index, lo, hi, lane);
-  const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
-  // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
-  constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
-  // see `from`; bfloat16 rows with float32 gradients keep their wavefronts with 64 bits where nothing is folded
-  constexpr bool NARROW = NT || (Needs<PHASE>::grad && (XT::bytes == 4 || GT::bytes == 2 || PHASE == kFold));
-  const int clip = clip_of(a, full, hi);
-  if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
-  else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, wd, b, lane, wave);
-  else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
-  else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, 0, start, lo, hi, wd, b, lane, wave);
+  if constexpr (MAP) {
+    const MapTile t = map_tile<VEC, UT, NT>(tbase, lo, hi, lane);
+    tile_body<XT, GT, PHASE, W, UT, kMapped, NT, EXT>(a, lds, t.origin, t.e, t.lo, t.hi, full, wd, b, lane, wave);
+  } else {
+    const uint64_t start = lane_start<VEC, UT, NT>(tile_index, lo, hi, lane);
+    const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
+    // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
+    constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
+    // see `from`; bfloat16 rows with float32 gradients keep their wavefronts with 64 bits where nothing is folded
+    constexpr bool NARROW = NT || (Needs<PHASE>::grad && (XT::bytes == 4 || GT::bytes == 2 || PHASE == kFold));
+    const int clip = clip_of(a, full, hi);
+    if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
+    else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, full, wd, b, lane, wave);
+    else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
+    else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -893,12 +1025,12 @@ struct PieceAt {
   float wd;
   bool any, full;  // some / all elements of the piece lie in [lo, hi)
 };
-template <int VEC, typename A>
+template <int VEC, bool MAP, typename A>
 __device__ __forceinline__ PieceAt locate_piece(const A& a, uint32_t tile) {
   constexpr uint64_t PIECE = (uint64_t)kWave * VEC;
   PieceAt p;
   uint64_t tile_index;
-  locate(a, a.work_begin + tile / kPieces, tile_index, p.lo, p.hi, p.wd);
+  locate<MAP>(a, a.work_begin + tile / kPieces, tile_index, p.lo, p.hi, p.wd);
   p.index = tile_index * kPieces + tile % kPieces;
   const uint64_t tbase = p.index * PIECE;
   p.any = tbase < p.hi && tbase + PIECE > p.lo;
@@ -1002,7 +1134,7 @@ __device__ __forceinline__ void mix_direct(const A& a, RowList rl, int lane, uin
 // sources: the second reader must find them in the cache, while gradients, state and all stores still stream).
 template <typename XT, typename GT, int PHASE, int U, int CLIP, int HINT, bool EXT, typename A, typename E>
 __device__ __forceinline__ void direct_body(const A& a, int position, int row, uint64_t origin, const E (&e)[U], E lo,
-                                            E hi, float wd, int lane) {
+                                            E hi, bool full, float wd, int lane) {
   constexpr bool NT = HINT != 0, NTSRC = HINT == 1;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
   // The neighbour list sits one entry per lane and is handed out with readlane, which must find a
@@ -1012,6 +1144,8 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
   // free to sink the list's load below it, into the lanes that stay - and a row whose leading
   // lanes lie before the segment then reads its neighbours' indices from lanes that never loaded.)
   RowList rl = load_position_list(a, position, lane);
+  MapBytes<VEC, U> map;
+  if constexpr (CLIP == kMapped) map = load_map<VEC, U, H>(a, origin, e);
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
   load_row_inputs<GT, PHASE, VEC, U, CLIP, NT, EXT>(a, row, origin, e, lo, hi, g, mh, vh, b);
   // Decoupled weight decay acts on the row's own previous parameters, source buffer `row`: kept from the mixing
@@ -1024,6 +1158,8 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
   E f[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) f[u] = afresh(e[u]);
+  uint32_t bits[U];
+  if constexpr (CLIP == kMapped) group_bits<VEC, U, H>(map, full, f, lo, hi, bits);
   float xo[U][VEC];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -1033,22 +1169,22 @@ __device__ __forceinline__ void direct_body(const A& a, int position, int row, u
     if (decays) {
       if (!own.found) unpack_raw<XT>(load_raw<XT, H, CLIP, false>(from<XT::bytes>(src_of<EXT>(a, row), origin), f[u], lo, hi), own.x);
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) decay[j] = wd * own.x[j];
+      for (int j = 0; j < VEC; ++j) decay[j] = decay_of<CLIP>(bits[u], j, wd, own.x[j]);
     }
 #pragma unroll
     for (int j = 0; j < VEC; ++j)
       xo[u][j] = element_step<PHASE>(a.s, mix[u][j], g[u][j], mh[u][j], vh[u][j], b[u][j], decay[j]);
   }
-  store_vectors<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), f, lo, hi, xo);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), f, lo, hi, b);
+  store_vectors<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), f, lo, hi, bits, xo);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), f, lo, hi, bits, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), f, lo, hi, mh);
-    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), f, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), f, lo, hi, bits, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), f, lo, hi, bits, vh);
   }
 }
 
 // Which piece and row a workgroup takes is the launch's order (see rows_stay_on_one_die).
-template <typename XT, typename GT, int PHASE, int HINT, bool EXT, typename A>
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT, bool MAP, typename A>
 __device__ __forceinline__ void direct_entry(const A& a) {
   const int lane = threadIdx.x;
   const uint32_t n_rows = a.n_rows;
@@ -1074,18 +1210,26 @@ __device__ __forceinline__ void direct_entry(const A& a) {
     position = blockIdx.x - t * n_rows;
   }
   const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
-  const PieceAt p = locate_piece<XT::vec>(a, t);
-  const uint64_t e[1] = {lane_start<XT::vec, 1, HINT != 0>(p.index, p.lo, p.hi, lane)};
-  if (active && p.any) {  // uniform over the workgroup
-    constexpr int CUT = HINT == 1 && EXT ? kElements : kGroups;  // see tile_entry
-    const int clip = clip_of(a, p.full, p.hi);
-    const uint64_t tbase = p.index * (kWave * XT::vec);
-    const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, p.lo, p.hi, lane);
-    const uint32_t c[1] = {cut.e};
-    if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
-    else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.wd, lane);
-    else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
-    else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.wd, lane);
+  const PieceAt p = locate_piece<XT::vec, MAP>(a, t);
+  if constexpr (MAP) {
+    if (active && p.any) {  // uniform over the workgroup
+      const MapTile m = map_tile<XT::vec, 1, HINT != 0>(p.index * (kWave * XT::vec), p.lo, p.hi, lane);
+      const uint32_t c[1] = {m.e};
+      direct_body<XT, GT, PHASE, 1, kMapped, HINT, EXT>(a, (int)position, row, m.origin, c, m.lo, m.hi, p.full, p.wd, lane);
+    }
+  } else {
+    const uint64_t e[1] = {lane_start<XT::vec, 1, HINT != 0>(p.index, p.lo, p.hi, lane)};
+    if (active && p.any) {  // uniform over the workgroup
+      constexpr int CUT = HINT == 1 && EXT ? kElements : kGroups;  // see tile_entry
+      const int clip = clip_of(a, p.full, p.hi);
+      const uint64_t tbase = p.index * (kWave * XT::vec);
+      const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, p.lo, p.hi, lane);
+      const uint32_t c[1] = {cut.e};
+      if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
+      else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.full, p.wd, lane);
+      else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
+      else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
+    }
   }
 }
 
@@ -1119,13 +1263,43 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows(const StepArgs a
     none.col = -1;
     float mix[2][VEC];
     void* to = dst_of<EXT>(a, row);
+    const uint32_t bits[2] = {};  // of layouts with a map only
     if (tbase >= lo && tbase + ITEM <= hi) {
       mix_direct<XT, 2, kGroupStep<HINT != 0>, kWhole, HINT == 1, EXT>(a, rl, lane, 0, e, lo, hi, mix, none);
-      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kWhole, HINT != 0>(to, e, lo, hi, mix);
+      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kWhole, HINT != 0>(to, e, lo, hi, bits, mix);
     } else {
       mix_direct<XT, 2, kGroupStep<HINT != 0>, kElements, HINT == 1, EXT>(a, rl, lane, 0, e, lo, hi, mix, none);
-      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kElements, HINT != 0>(to, e, lo, hi, mix);
+      store_vectors<XT, VEC, kGroupStep<HINT != 0>, kElements, HINT != 0>(to, e, lo, hi, bits, mix);
     }
+  }
+}
+
+template <typename XT, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave* kWideWaves) void k_mix_rows_map(const StepArgs a) {
+  constexpr int VEC = XT::vec, H = kGroupStep<HINT != 0>;
+  constexpr uint64_t TILE = (uint64_t)kWave * VEC * 2;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t item, position;
+  const bool active = die_group_order(blockIdx.x, a.n_rows, a.n_xcd, a.order_group, item, position);
+  const int row = __builtin_amdgcn_readfirstlane(a.row_order[position]);
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate<true>(a, a.work_begin + item, tile_index, lo, hi, wd);
+  const uint64_t tbase = (tile_index * kWideWaves + wave) * TILE;
+  if (active && tbase < hi && tbase + TILE > lo) {  // uniform over the wavefront
+    const RowList rl = load_position_list(a, (int)position, lane);
+    const MapTile t = map_tile<VEC, 2, HINT != 0>(tbase, lo, hi, lane);
+    const uint32_t e[2] = {t.e, t.e + kVectorStep<VEC, HINT != 0>};
+    const MapBytes<VEC, 2> map = load_map<VEC, 2, H>(a, t.origin, e);
+    OwnSource<VEC> none;
+    none.col = -1;
+    float mix[2][VEC];
+    mix_direct<XT, 2, H, kMapped, HINT == 1, EXT>(a, rl, lane, t.origin, e, t.lo, t.hi, mix, none);
+    const uint32_t f[2] = {afresh(e[0]), afresh(e[1])};
+    uint32_t bits[2];
+    group_bits<VEC, 2, H>(map, tbase >= lo && tbase + TILE <= hi, f, t.lo, t.hi, bits);
+    store_vectors<XT, VEC, H, kMapped, HINT != 0>(from<XT::bytes>(dst_of<EXT>(a, row), t.origin), f, t.lo, t.hi, bits, mix);
   }
 }
 
@@ -1146,8 +1320,8 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
   const uint64_t e0 = lane_start<VEC, 2, HINT != 0>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, HINT != 0>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, kWhole, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, wd, lane);
-    else direct_body<XT, GT, PHASE, 2, kElements, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, wd, lane);
+    if (tbase >= lo && tbase + ITEM <= hi) direct_body<XT, GT, PHASE, 2, kWhole, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, true, wd, lane);
+    else direct_body<XT, GT, PHASE, 2, kElements, HINT, EXT>(a, (int)position, row, 0, e, lo, hi, true, wd, lane);
   }
 }
 
@@ -1164,11 +1338,13 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
 template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A, typename E>
-__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, E start, E lo, E hi, float wd, int lane,
+__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, E start, E lo, E hi, bool full, float wd, int lane,
                                           int wave, int waves) {
   constexpr bool NT = HINT != 0;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
   const E e[1] = {start};
+  MapBytes<VEC, 1> map;
+  if constexpr (CLIP == kMapped) map = load_map<VEC, 1, H>(a, origin, e);
   const Loop l = a.loops[loop];
   // This wavefront's rows, every `waves`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
   // each).  A wavefront that sums has at least three sources, so that the sum is never less accurate than the listed
@@ -1199,6 +1375,8 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
     }
   }
   __syncthreads();
+  uint32_t bits[1];
+  if constexpr (CLIP == kMapped) group_bits<VEC, 1, H>(map, full, e, lo, hi, bits);
   float mix[VEC];
   for (int p = 0; p < parts; ++p)
 #pragma unroll
@@ -1208,22 +1386,22 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
       for (int j = 0; j < 4; ++j) mix[4 * h + j] = p == 0 ? v[j] : mix[4 * h + j] + v[j];
     }
   for (int r = 0; r < my_rows; ++r) {
-    float decay[VEC], xo[VEC];
+    float decay[VEC], xo[1][VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) decay[j] = 0.0f;
     if (!Needs<PHASE>::mixing_only && wd != 0.0f) {
       float own[VEC];
       unpack_raw<XT>(load_raw<XT, H, CLIP, false>(from<XT::bytes>(src_of<EXT>(a, row), origin), e[0], lo, hi), own);
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) decay[j] = wd * own[j];
+      for (int j = 0; j < VEC; ++j) decay[j] = decay_of<CLIP>(bits[0], j, wd, own[j]);
     }
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) xo[j] = element_step<PHASE>(a.s, mix[j], g[0][j], mh[0][j], vh[0][j], b[0][j], decay[j]);
-    store_vals<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), e[0], lo, hi, xo);
-    if constexpr (Needs<PHASE>::acc_out) store_vals<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e[0], lo, hi, b[0]);
+    for (int j = 0; j < VEC; ++j) xo[0][j] = element_step<PHASE>(a.s, mix[j], g[0][j], mh[0][j], vh[0][j], b[0][j], decay[j]);
+    store_vectors<XT, VEC, H, CLIP, NT>(from<XT::bytes>(dst_of<EXT>(a, row), origin), e, lo, hi, bits, xo);
+    if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(acc_of<EXT>(a, row), origin), e, lo, hi, bits, b);
     if constexpr (Needs<PHASE>::moments_out) {
-      store_vals<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e[0], lo, hi, mh[0]);
-      store_vals<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e[0], lo, hi, vh[0]);
+      store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(m_hat_of<EXT>(a, row), origin), e, lo, hi, bits, mh);
+      store_vectors<TF32, VEC, H, CLIP, NT>(from<4>(v_hat_of<EXT>(a, row), origin), e, lo, hi, bits, vh);
     }
     if (r + 1 < my_rows) {
       row = __builtin_amdgcn_readlane(row_v, r + 1);
@@ -1255,10 +1433,27 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   constexpr int CUT = HINT != 0 && EXT ? kElements : kGroups;  // see tile_entry
   const int clip = clip_of(a, full, hi);
   const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
-  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
-  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, 0, start, lo, hi, wd, lane, wave, waves);
+  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
+  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
+}
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop_map(const StepArgs a) {
+  constexpr uint64_t TILE = (uint64_t)kWave * XT::vec;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * a.n_loops);
+  const uint32_t tile = b / a.n_loops;
+  uint64_t tile_index, lo, hi;
+  float wd;
+  locate<true>(a, a.work_begin + tile, tile_index, lo, hi, wd);
+  const uint64_t tbase = tile_index * TILE;
+  const bool full = tbase >= lo && tbase + TILE <= hi;
+  const MapTile t = map_tile<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
+  loop_body<XT, GT, PHASE, kMapped, HINT, EXT>(a, reinterpret_cast<f4*>(lds_bytes), (int)(b - tile * a.n_loops), t.origin, t.e, t.lo, t.hi,
+                                               full, wd, lane, wave, (int)(blockDim.x / kWave));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1277,8 +1472,10 @@ __device__ __forceinline__ void acc_step(const Scalars& s, float g, float& mh, f
 }
 
 template <typename GT, int VEC, int PHASE, int U, int CLIP, bool NT, bool EXT, typename A>
-__device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi) {
+__device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e)[U], uint64_t lo, uint64_t hi, bool full) {
   constexpr int H = kGroupStep<NT>;
+  MapBytes<VEC, U> map;
+  if constexpr (CLIP == kMapped) map = load_map<VEC, U, H>(a, 0, e);
   float g[U][VEC], mh[U][VEC], vh[U][VEC], b[U][VEC];
 #pragma unroll
   for (int u = 0; u < U; ++u) load_vals<GT, VEC, H, CLIP, NT>(a.grad[row], e[u], lo, hi, g[u]);
@@ -1296,16 +1493,18 @@ __device__ __forceinline__ void acc_body(const A& a, int row, const uint64_t (&e
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc_step<PHASE>(a.s, g[u][j], mh[u][j], vh[u][j], b[u][j]);
-  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, b);
+  uint32_t bits[U];
+  if constexpr (CLIP == kMapped) group_bits<VEC, U, H>(map, full, e, lo, hi, bits);
+  if constexpr (Needs<PHASE>::acc_out) store_vectors<TF32, VEC, H, CLIP, NT>(acc_of<EXT>(a, row), e, lo, hi, bits, b);
   if constexpr (Needs<PHASE>::moments_out) {
-    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, mh);
-    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, vh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(m_hat_of<EXT>(a, row), e, lo, hi, bits, mh);
+    store_vectors<TF32, VEC, H, CLIP, NT>(v_hat_of<EXT>(a, row), e, lo, hi, bits, vh);
   }
 }
 
 // VEC is the element count of a parameter vector of this handle, so that the accumulate kernel walks the
 // same grid as the direct kernel.
-template <typename GT, int VEC, int PHASE, bool NT, bool EXT, typename A>
+template <typename GT, int VEC, int PHASE, bool NT, bool EXT, bool MAP, typename A>
 __device__ __forceinline__ void acc_entry(const A& a) {
   const uint32_t n_rows = a.n_rows;
   uint32_t t, row_at;
@@ -1317,14 +1516,15 @@ __device__ __forceinline__ void acc_entry(const A& a) {
     row_at = blockIdx.x - t * n_rows;
   }
   const int row = (int)row_at;
-  const PieceAt p = locate_piece<VEC>(a, t);
+  const PieceAt p = locate_piece<VEC, MAP>(a, t);
   const uint64_t e[1] = {lane_start<VEC, 1, NT>(p.index, p.lo, p.hi, (int)threadIdx.x)};
   if (active && p.any) {
     constexpr int CUT = NT && EXT ? kElements : kGroups;  // see tile_entry
     const int clip = clip_of(a, p.full, p.hi);
-    if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi);
-    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi);
-    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi);
+    if constexpr (MAP) acc_body<GT, VEC, PHASE, 1, kMapped, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
+    else if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
+    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
+    else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
   }
 }
 
@@ -1350,38 +1550,63 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_acc_rows(const StepArgs a
   const uint64_t e0 = lane_start<VEC, 2, NT>(tile_index * kWideWaves + wave, lo, hi, lane);
   const uint64_t e[2] = {e0, e0 + kVectorStep<VEC, NT>};
   if (active) {  // uniform over the workgroup
-    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, e, lo, hi);
-    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, e, lo, hi);
+    if (tbase >= lo && tbase + ITEM <= hi) acc_body<GT, VEC, PHASE, 2, kWhole, NT, EXT>(a, row, e, lo, hi, true);
+    else acc_body<GT, VEC, PHASE, 2, kElements, NT, EXT>(a, row, e, lo, hi, true);
   }
 }
 
 // ---------------------------------------------------------------------------------------------
 // the kernels
 // ---------------------------------------------------------------------------------------------
+// Of each a second one, _map, for layouts with a map (see StepArgsFor::map): one body instead of three.
 template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT>
 __global__ __launch_bounds__(kWave* W) void k_tile(const StepArgs a) {
-  tile_entry<XT, GT, PHASE, W, UT, NT, EXT>(a);
+  tile_entry<XT, GT, PHASE, W, UT, NT, EXT, false>(a);
+}
+template <typename XT, typename GT, int PHASE, int W, int UT, bool NT, bool EXT>
+__global__ __launch_bounds__(kWave* W) void k_tile_map(const StepArgs a) {
+  tile_entry<XT, GT, PHASE, W, UT, NT, EXT, true>(a);
 }
 template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
 __global__ __launch_bounds__(kWave) void k_direct(const StepArgs a) {
-  direct_entry<XT, GT, PHASE, HINT, EXT>(a);
+  direct_entry<XT, GT, PHASE, HINT, EXT, false>(a);
+}
+template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
+__global__ __launch_bounds__(kWave) void k_direct_map(const StepArgs a) {
+  direct_entry<XT, GT, PHASE, HINT, EXT, true>(a);
 }
 template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
 __global__ __launch_bounds__(kWave) void k_acc(const StepArgs a) {
-  acc_entry<GT, VEC, PHASE, NT, EXT>(a);
+  acc_entry<GT, VEC, PHASE, NT, EXT, false>(a);
+}
+template <typename GT, int VEC, int PHASE, bool NT, bool EXT>
+__global__ __launch_bounds__(kWave) void k_acc_map(const StepArgs a) {
+  acc_entry<GT, VEC, PHASE, NT, EXT, true>(a);
 }
 // The same on the short argument block (small handles: no streaming hints, tables in the block).
 template <typename XT, typename GT, int PHASE, int W, int UT>
 __global__ __launch_bounds__(kWave* W) void k_tile_few(const StepArgsFew a) {
-  tile_entry<XT, GT, PHASE, W, UT, false, false>(a);
+  tile_entry<XT, GT, PHASE, W, UT, false, false, false>(a);
+}
+template <typename XT, typename GT, int PHASE, int W, int UT>
+__global__ __launch_bounds__(kWave* W) void k_tile_few_map(const StepArgsFew a) {
+  tile_entry<XT, GT, PHASE, W, UT, false, false, true>(a);
 }
 template <typename XT, typename GT, int PHASE>
 __global__ __launch_bounds__(kWave) void k_direct_few(const StepArgsFew a) {
-  direct_entry<XT, GT, PHASE, 0, false>(a);
+  direct_entry<XT, GT, PHASE, 0, false, false>(a);
+}
+template <typename XT, typename GT, int PHASE>
+__global__ __launch_bounds__(kWave) void k_direct_few_map(const StepArgsFew a) {
+  direct_entry<XT, GT, PHASE, 0, false, true>(a);
 }
 template <typename GT, int VEC, int PHASE>
 __global__ __launch_bounds__(kWave) void k_acc_few(const StepArgsFew a) {
-  acc_entry<GT, VEC, PHASE, false, false>(a);
+  acc_entry<GT, VEC, PHASE, false, false, false>(a);
+}
+template <typename GT, int VEC, int PHASE>
+__global__ __launch_bounds__(kWave) void k_acc_few_map(const StepArgsFew a) {
+  acc_entry<GT, VEC, PHASE, false, false, true>(a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1389,95 +1614,95 @@ __global__ __launch_bounds__(kWave) void k_acc_few(const StepArgsFew a) {
 // ---------------------------------------------------------------------------------------------
 
 template <typename XT, typename GT, int W, int UT, bool NT, bool EXT>
-KernelFn tile_kernel_for_phase(int phase) {
+KernelFn tile_kernel_for_phase(int phase, bool map) {
   switch (phase) {
-    case kMixOnly: return (KernelFn)k_tile<XT, GT, kMixOnly, W, UT, NT, EXT>;
-    case kMixConsensus: return (KernelFn)k_tile<XT, GT, kMixConsensus, W, UT, NT, EXT>;
-    case kUpdateOnly: return (KernelFn)k_tile<XT, GT, kUpdateOnly, W, UT, NT, EXT>;
-    case kPlain: return (KernelFn)k_tile<XT, GT, kPlain, W, UT, NT, EXT>;
-    case kLoopStart: return (KernelFn)k_tile<XT, GT, kLoopStart, W, UT, NT, EXT>;
-    case kFold: return (KernelFn)k_tile<XT, GT, kFold, W, UT, NT, EXT>;
-    case kAlg1: return (KernelFn)k_tile<XT, GT, kAlg1, W, UT, NT, EXT>;
+    case kMixOnly: return map ? (KernelFn)k_tile_map<XT, GT, kMixOnly, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kMixOnly, W, UT, NT, EXT>;
+    case kMixConsensus: return map ? (KernelFn)k_tile_map<XT, GT, kMixConsensus, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kMixConsensus, W, UT, NT, EXT>;
+    case kUpdateOnly: return map ? (KernelFn)k_tile_map<XT, GT, kUpdateOnly, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kUpdateOnly, W, UT, NT, EXT>;
+    case kPlain: return map ? (KernelFn)k_tile_map<XT, GT, kPlain, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kPlain, W, UT, NT, EXT>;
+    case kLoopStart: return map ? (KernelFn)k_tile_map<XT, GT, kLoopStart, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kLoopStart, W, UT, NT, EXT>;
+    case kFold: return map ? (KernelFn)k_tile_map<XT, GT, kFold, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kFold, W, UT, NT, EXT>;
+    case kAlg1: return map ? (KernelFn)k_tile_map<XT, GT, kAlg1, W, UT, NT, EXT> : (KernelFn)k_tile<XT, GT, kAlg1, W, UT, NT, EXT>;
   }
   return nullptr;
 }
 
 template <typename XT, typename GT, int W, int UT>
-KernelFn few_tile_kernel_for_phase(int phase) {
+KernelFn few_tile_kernel_for_phase(int phase, bool map) {
   switch (phase) {
-    case kMixOnly: return (KernelFn)k_tile_few<XT, GT, kMixOnly, W, UT>;
-    case kMixConsensus: return (KernelFn)k_tile_few<XT, GT, kMixConsensus, W, UT>;
-    case kUpdateOnly: return (KernelFn)k_tile_few<XT, GT, kUpdateOnly, W, UT>;
-    case kPlain: return (KernelFn)k_tile_few<XT, GT, kPlain, W, UT>;
-    case kLoopStart: return (KernelFn)k_tile_few<XT, GT, kLoopStart, W, UT>;
-    case kFold: return (KernelFn)k_tile_few<XT, GT, kFold, W, UT>;
-    case kAlg1: return (KernelFn)k_tile_few<XT, GT, kAlg1, W, UT>;
+    case kMixOnly: return map ? (KernelFn)k_tile_few_map<XT, GT, kMixOnly, W, UT> : (KernelFn)k_tile_few<XT, GT, kMixOnly, W, UT>;
+    case kMixConsensus: return map ? (KernelFn)k_tile_few_map<XT, GT, kMixConsensus, W, UT> : (KernelFn)k_tile_few<XT, GT, kMixConsensus, W, UT>;
+    case kUpdateOnly: return map ? (KernelFn)k_tile_few_map<XT, GT, kUpdateOnly, W, UT> : (KernelFn)k_tile_few<XT, GT, kUpdateOnly, W, UT>;
+    case kPlain: return map ? (KernelFn)k_tile_few_map<XT, GT, kPlain, W, UT> : (KernelFn)k_tile_few<XT, GT, kPlain, W, UT>;
+    case kLoopStart: return map ? (KernelFn)k_tile_few_map<XT, GT, kLoopStart, W, UT> : (KernelFn)k_tile_few<XT, GT, kLoopStart, W, UT>;
+    case kFold: return map ? (KernelFn)k_tile_few_map<XT, GT, kFold, W, UT> : (KernelFn)k_tile_few<XT, GT, kFold, W, UT>;
+    case kAlg1: return map ? (KernelFn)k_tile_few_map<XT, GT, kAlg1, W, UT> : (KernelFn)k_tile_few<XT, GT, kAlg1, W, UT>;
   }
   return nullptr;
 }
 template <typename XT, typename GT>
-KernelFn few_tile_kernel(int phase, TileShape s) {
-  if (s.waves == 4 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 4, 1>(phase);
-  if (s.waves == 4 && s.ut == 2) return few_tile_kernel_for_phase<XT, GT, 4, 2>(phase);
-  if (s.waves == 8 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 8, 1>(phase);
+KernelFn few_tile_kernel(int phase, TileShape s, bool map) {
+  if (s.waves == 4 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 4, 1>(phase, map);
+  if (s.waves == 4 && s.ut == 2) return few_tile_kernel_for_phase<XT, GT, 4, 2>(phase, map);
+  if (s.waves == 8 && s.ut == 1) return few_tile_kernel_for_phase<XT, GT, 8, 1>(phase, map);
   return nullptr;  // no handle of few rows has another shape
 }
 template <typename XT, typename GT>
-KernelFn few_direct_kernel(int phase) {
+KernelFn few_direct_kernel(int phase, bool map) {
   switch (phase) {
-    case kMixOnly: return (KernelFn)k_direct_few<XT, GT, kMixOnly>;
-    case kUpdateOnly: return (KernelFn)k_direct_few<XT, GT, kUpdateOnly>;
-    case kPlain: return (KernelFn)k_direct_few<XT, GT, kPlain>;
-    case kLoopStart: return (KernelFn)k_direct_few<XT, GT, kLoopStart>;
-    case kFold: return (KernelFn)k_direct_few<XT, GT, kFold>;
-    case kAlg1: return (KernelFn)k_direct_few<XT, GT, kAlg1>;
+    case kMixOnly: return map ? (KernelFn)k_direct_few_map<XT, GT, kMixOnly> : (KernelFn)k_direct_few<XT, GT, kMixOnly>;
+    case kUpdateOnly: return map ? (KernelFn)k_direct_few_map<XT, GT, kUpdateOnly> : (KernelFn)k_direct_few<XT, GT, kUpdateOnly>;
+    case kPlain: return map ? (KernelFn)k_direct_few_map<XT, GT, kPlain> : (KernelFn)k_direct_few<XT, GT, kPlain>;
+    case kLoopStart: return map ? (KernelFn)k_direct_few_map<XT, GT, kLoopStart> : (KernelFn)k_direct_few<XT, GT, kLoopStart>;
+    case kFold: return map ? (KernelFn)k_direct_few_map<XT, GT, kFold> : (KernelFn)k_direct_few<XT, GT, kFold>;
+    case kAlg1: return map ? (KernelFn)k_direct_few_map<XT, GT, kAlg1> : (KernelFn)k_direct_few<XT, GT, kAlg1>;
   }
   return nullptr;
 }
 
 template <typename XT, typename GT, bool NT, bool EXT>
-KernelFn tile_kernel_for_shape_nt(int phase, TileShape s) {
-  if (s.waves == 4 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 4, 1, NT, EXT>(phase);
-  if (s.waves == 4 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 4, 2, NT, EXT>(phase);
-  if (s.waves == 8 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 8, 1, NT, EXT>(phase);
+KernelFn tile_kernel_for_shape_nt(int phase, TileShape s, bool map) {
+  if (s.waves == 4 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 4, 1, NT, EXT>(phase, map);
+  if (s.waves == 4 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 4, 2, NT, EXT>(phase, map);
+  if (s.waves == 8 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 8, 1, NT, EXT>(phase, map);
   if constexpr (NT && XT::vec == 4) {
-    if (s.waves == 8 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 8, 2, NT, EXT>(phase);
-    if (s.waves == 16 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 16, 2, NT, EXT>(phase);
+    if (s.waves == 8 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 8, 2, NT, EXT>(phase, map);
+    if (s.waves == 16 && s.ut == 2) return tile_kernel_for_phase<XT, GT, 16, 2, NT, EXT>(phase, map);
   }
   if constexpr (EXT)
-    if (s.waves == 16 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 16, 1, NT, EXT>(phase);
+    if (s.waves == 16 && s.ut == 1) return tile_kernel_for_phase<XT, GT, 16, 1, NT, EXT>(phase, map);
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>
-KernelFn loop_kernel_for_phase(int phase) {
+KernelFn loop_kernel_for_phase(int phase, bool map) {
   switch (phase) {
-    case kMixOnly: return (KernelFn)k_loop<XT, GT, kMixOnly, HINT, EXT>;
-    case kUpdateOnly: return (KernelFn)k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
-    case kPlain: return (KernelFn)k_loop<XT, GT, kPlain, HINT, EXT>;
-    case kLoopStart: return (KernelFn)k_loop<XT, GT, kLoopStart, HINT, EXT>;
-    case kFold: return (KernelFn)k_loop<XT, GT, kFold, HINT, EXT>;
-    case kAlg1: return (KernelFn)k_loop<XT, GT, kAlg1, HINT, EXT>;
+    case kMixOnly: return map ? (KernelFn)k_loop_map<XT, GT, kMixOnly, HINT, EXT> : (KernelFn)k_loop<XT, GT, kMixOnly, HINT, EXT>;
+    case kUpdateOnly: return map ? (KernelFn)k_loop_map<XT, GT, kUpdateOnly, HINT, EXT> : (KernelFn)k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return map ? (KernelFn)k_loop_map<XT, GT, kPlain, HINT, EXT> : (KernelFn)k_loop<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return map ? (KernelFn)k_loop_map<XT, GT, kLoopStart, HINT, EXT> : (KernelFn)k_loop<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return map ? (KernelFn)k_loop_map<XT, GT, kFold, HINT, EXT> : (KernelFn)k_loop<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return map ? (KernelFn)k_loop_map<XT, GT, kAlg1, HINT, EXT> : (KernelFn)k_loop<XT, GT, kAlg1, HINT, EXT>;
   }
   return nullptr;
 }
 template <typename XT, typename GT, int HINT, bool EXT>
-KernelFn direct_kernel_for_phase(int phase) {
+KernelFn direct_kernel_for_phase(int phase, bool map) {
   switch (phase) {
-    case kMixOnly: return (KernelFn)k_direct<XT, GT, kMixOnly, HINT, EXT>;
-    case kUpdateOnly: return (KernelFn)k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
-    case kPlain: return (KernelFn)k_direct<XT, GT, kPlain, HINT, EXT>;
-    case kLoopStart: return (KernelFn)k_direct<XT, GT, kLoopStart, HINT, EXT>;
-    case kFold: return (KernelFn)k_direct<XT, GT, kFold, HINT, EXT>;
-    case kAlg1: return (KernelFn)k_direct<XT, GT, kAlg1, HINT, EXT>;
+    case kMixOnly: return map ? (KernelFn)k_direct_map<XT, GT, kMixOnly, HINT, EXT> : (KernelFn)k_direct<XT, GT, kMixOnly, HINT, EXT>;
+    case kUpdateOnly: return map ? (KernelFn)k_direct_map<XT, GT, kUpdateOnly, HINT, EXT> : (KernelFn)k_direct<XT, GT, kUpdateOnly, HINT, EXT>;
+    case kPlain: return map ? (KernelFn)k_direct_map<XT, GT, kPlain, HINT, EXT> : (KernelFn)k_direct<XT, GT, kPlain, HINT, EXT>;
+    case kLoopStart: return map ? (KernelFn)k_direct_map<XT, GT, kLoopStart, HINT, EXT> : (KernelFn)k_direct<XT, GT, kLoopStart, HINT, EXT>;
+    case kFold: return map ? (KernelFn)k_direct_map<XT, GT, kFold, HINT, EXT> : (KernelFn)k_direct<XT, GT, kFold, HINT, EXT>;
+    case kAlg1: return map ? (KernelFn)k_direct_map<XT, GT, kAlg1, HINT, EXT> : (KernelFn)k_direct<XT, GT, kAlg1, HINT, EXT>;
   }
   return nullptr;
 }
 // Whole items by four wavefronts: mixing (no gradient: built once per parameter type), and the large float32 steps that
 // the host gives it (streaming, tables in the argument block).
 template <typename XT, typename GT, int HINT, bool EXT>
-KernelFn rows_kernel_for_phase(int phase) {
+KernelFn rows_kernel_for_phase(int phase, bool map) {
   if constexpr (XT::bytes == GT::bytes)
-    if (phase == kMixOnly) return (KernelFn)k_mix_rows<XT, HINT, EXT>;
+    if (phase == kMixOnly) return map ? (KernelFn)k_mix_rows_map<XT, HINT, EXT> : (KernelFn)k_mix_rows<XT, HINT, EXT>;
   if constexpr (XT::bytes == 4 && HINT == 2 && !EXT) switch (phase) {
     case kUpdateOnly: return (KernelFn)k_rows<XT, GT, kUpdateOnly, HINT, EXT>;
     case kPlain: return (KernelFn)k_rows<XT, GT, kPlain, HINT, EXT>;

@@ -71,6 +71,11 @@ struct dadam_handle {
   std::vector<uint32_t> tensor_seg;  // segment of each non-empty tensor, UINT32_MAX for empty ones
   std::vector<Segment> segs;
   std::vector<uint32_t> seg_work[kNumGrids];  // per Grid: number of work items (tiles; per row in direct mode) in earlier segments
+  // Layouts of many short tensors side by side: no search and no tile launched twice, but one dense grid over the whole vector and a byte
+  // for every four elements that says which are stored and decay (build_map).
+  bool mapped = false;
+  float map_decay = 0.f;      // of the tensors that decay
+  uint8_t* d_map = nullptr;
   Segment* d_segs = nullptr;     // the segments, and behind them
   uint32_t* d_seg_work = nullptr;  // their first work items, per Grid (what the kernels search)
   double* d_partials = nullptr;  // kConsensusPartials doubles of scratch for the consensus error
@@ -184,6 +189,39 @@ void find_segments(dadam_handle* h) {
   h->short_segments = h->segs.size() * (uint64_t)kLongSegment > h->cfg.d;
 }
 
+// Does the layout get a map?  Segments of 65536 elements on average or fewer, a gap of at most 7 elements between two (what packing to
+// multiples of 8 leaves), one value of decay beside 0, four elements never with and without it, d a multiple of 4 (the last group of a
+// buffer is whole), and at most 2^28 elements (64 MB of map).  Such layouts then count as one segment everywhere.  What it gives stands at
+// MapTile.  Where segments are long, a byte for every four elements costs a step of one row 1 % and there are few cut tiles to save; wider gaps
+// keep the walk by segments, whose routes tests/golden/large_routes.txt holds (segments of 1100 elements 8 apart).
+bool can_map(const dadam_handle* h, float* decay) {
+  if (!h->short_segments || h->segs.size() < 2 || h->cfg.d % 4 != 0 || h->cfg.d > kMostMapped) return false;
+  *decay = 0.f;
+  for (size_t k = 0; k < h->segs.size(); ++k) {
+    const Segment& s = h->segs[k];
+    if (s.weight_decay != 0.f && *decay != 0.f && s.weight_decay != *decay) return false;
+    if (s.weight_decay != 0.f) *decay = s.weight_decay;
+    if (k == 0) continue;
+    const Segment& before = h->segs[k - 1];
+    if (s.lo - before.hi > kWidestGap) return false;
+    if (s.lo / 4 == (before.hi - 1) / 4 && (s.weight_decay != 0.f) != (before.weight_decay != 0.f)) return false;
+  }
+  return true;
+}
+
+// The map (see StepArgs::map), zero behind the layout up to the end of the last tile of any grid.
+std::vector<uint8_t> build_map(const dadam_handle* h) {
+  std::vector<uint8_t> map((h->cfg.d + kLongSegment) / 4, 0);
+  for (const Segment& s : h->segs) {
+    const uint8_t decays = s.weight_decay != 0.f ? 0x10 : 0;
+    const uint64_t first = (s.lo + 3) / 4, last = s.hi / 4;  // whole groups [first, last)
+    if (first < last) memset(map.data() + first, 0x0F | decays, last - first);
+    for (uint64_t e = s.lo; e < std::min(s.hi, 4 * first); ++e) map[e / 4] |= (uint8_t)(1u << e % 4) | decays;
+    for (uint64_t e = std::max(s.lo, 4 * std::max(first, last)); e < s.hi; ++e) map[e / 4] |= (uint8_t)(1u << e % 4) | decays;
+  }
+  return map;
+}
+
 // Number the tiles of every tile grid.
 int plan(dadam_handle* h) {
   uint64_t wt = 0, wd = 0, wm = 0, wv = 0;
@@ -217,6 +255,11 @@ int plan(dadam_handle* h) {
 void work_range(const dadam_handle* h, Grid grid, uint32_t s0, uint32_t s1, uint64_t lo,
                 uint64_t hi, uint32_t* w0, uint32_t* w1) {
   const uint64_t T = grid == kGridTile ? h->tile_elems : grid == kGridDirect ? h->direct_elems : grid == kGridMix ? h->mix_tile_elems : vector_elems(h);
+  if (h->mapped) {
+    *w0 = (uint32_t)(lo / T);
+    *w1 = (uint32_t)((hi - 1) / T) + 1;
+    return;
+  }
   const Segment& a = h->segs[s0];
   const Segment& b = h->segs[s1];
   *w0 = h->seg_work[grid][s0] + (uint32_t)(lo / T - a.first_tile[grid]);
@@ -293,7 +336,8 @@ void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
   for (uint32_t i = 0; i < R; ++i) a->grad[i] = grads ? grads[i] : nullptr;
   a->seg = h->d_segs;
   a->seg_work = h->d_seg_work;
-  a->n_seg = (uint32_t)h->segs.size();
+  a->map = h->d_map;
+  a->n_seg = h->mapped ? 1u : (uint32_t)h->segs.size();
   a->n_rows = R;
   a->n_cols = C;
   a->n_xcd = h->n_xcds;
@@ -371,8 +415,8 @@ void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t l
   a->work_begin = work_begin;
   a->clip_lo = lo;
   a->clip_hi = hi;
-  a->first_tile = h->segs.front().first_tile[grid];
-  a->weight_decay = h->segs.front().weight_decay;
+  a->first_tile = h->mapped ? 0 : h->segs.front().first_tile[grid];
+  a->weight_decay = h->mapped ? h->map_decay : h->segs.front().weight_decay;
 }
 
 // Does a compute unit hold one workgroup of the tile, even with one vector a lane?
@@ -412,6 +456,13 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool de
 
 uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(waves * kWave * h->vec * 4); }
 
+// Tiles of one vector a lane of a launch over the whole layout.
+uint64_t vector_tiles(const dadam_handle* h) {
+  if (!h->mapped) return h->n_work_v;
+  const uint64_t T = vector_elems(h);
+  return (h->segs.back().hi - 1) / T - h->segs.front().lo / T + 1;
+}
+
 // Wavefronts of a loop kernel's workgroup, 0: another kernel takes the launch.  Depends on the slot and on the whole
 // layout, never on the range of a launch: the order in which a loop is summed follows from it, and a step issued
 // range by range has the bits of the whole one.
@@ -437,12 +488,12 @@ uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(wa
 // 1.21, 1.13, 64 in loops of 32, 16, 16 1.14, 1.02, 1.08, 0.92, 0.83.
 int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   const uint64_t R = h->cfg.n_rows, G = slot.loops.size();
-  if (G == 0 || (R < 16 * G && (R < 8 * G || h->n_work_v > kFewTiles))) return 0;
-  if (!mix_only && h->decays && h->n_work_v * G > 32 * R && R < 56 * G && h->cfg.n_cols <= (uint32_t)kInlineRows) return 0;
+  if (G == 0 || (R < 16 * G && (R < 8 * G || vector_tiles(h) > kFewTiles))) return 0;
+  if (!mix_only && h->decays && vector_tiles(h) * G > 32 * R && R < 56 * G && h->cfg.n_cols <= (uint32_t)kInlineRows) return 0;
   for (uint32_t i = 0; i < R; ++i)
     for (int32_t c : h->inplace_cols[i])
       if ((slot.loop_of_source[c] != -1 && slot.loop_of_source[c] != slot.loop_of_row[i]) || h->decays) return 0;
-  const int waves = h->n_work_v * G <= (G == 1 && R < 28 ? 1 : 2) * kFewTiles ? 16 : 8;
+  const int waves = vector_tiles(h) * G <= (G == 1 && R < 28 ? 1 : 2) * kFewTiles ? 16 : 8;
   return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 
@@ -508,6 +559,7 @@ bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only
 // 48 rows 1.01 / 1.01, 56 rows 1.00 / 1.01, 72 rows 1.00 / 0.98; 3e7 elements 0.98 to 1.00; bfloat16 0.98 to 1.01, 3e7 0.95 to 0.98.
 bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t elems) {
   if (order != kOrderDieGroups) return false;
+  if (h->mapped && !mix_only) return false;  // (k_rows has no body for maps: with it 74 registers became 87, a wavefront per SIMD)
   return mix_only || (h->cfg.n_rows > 32 && h->cfg.n_rows < 64 && h->vec == 4 && h->d_tables == nullptr && h->nontemporal && elems >= kManyElems);
 }
 
@@ -518,7 +570,7 @@ bool whole_items(const dadam_handle* h, bool mix_only, uint32_t order, uint64_t 
 // 2222 / 1996, with bfloat16 parameters (eight elements a lane) 1789 / 1975, 1847 / 2007, 1966 / 2558, 2018 / 2566.
 bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
   const uint32_t R = h->cfg.n_rows;
-  if (h->short_segments && h->vec == 8) return false;
+  if (h->mapped || (h->short_segments && h->vec == 8)) return false;  // (as in whole_items)
   return h->nontemporal && elems >= kManyElems && ((R > 32 && R <= 64) || (R > 80 && R < 128));
 }
 
@@ -669,6 +721,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
   if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
+  if (h->mapped && !decays) a.weight_decay = 0.f;
   if (tile_mode && cut_by_elements(h, mix_only, by_loops)) a.d = 0;
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
@@ -915,6 +968,8 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // 0.805, 72 rows 0.72 / 0.725 / 0.779; 8 rows 0.817 / 0.825 / 0.802, 4 rows by four wavefronts 0.816 / 0.820, by sixteen 0.794.
   // In bfloat16 one vector has that layout already, and sixteen wavefronts lose (8 rows 0.813 / 0.783, 16 rows 0.780 / 0.770).
   find_segments(h);
+  h->mapped = env_int("DADAM_MAP", 1) && can_map(h, &h->map_decay);
+  if (h->mapped) h->short_segments = false;
   if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
     shape.ut = 2;
     if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
@@ -970,6 +1025,11 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
       if (e == hipSuccess) e = hipMemcpy(h->d_segs, image.data(), image.size(), hipMemcpyHostToDevice);
       h->d_seg_work = reinterpret_cast<uint32_t*>(h->d_segs + n);
     }
+    if (e == hipSuccess && h->mapped) {
+      const std::vector<uint8_t> map = build_map(h);
+      e = hipMalloc((void**)&h->d_map, map.size());
+      if (e == hipSuccess) e = hipMemcpy(h->d_map, map.data(), map.size(), hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess && (cfg->n_rows > (uint32_t)kInlineRows || cfg->n_cols > (uint32_t)kInlineRows))
       e = hipMalloc((void**)&h->d_tables, 2 * DADAM_BINDINGS_KEPT * sizeof(BoundTables));
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_partials, kConsensusPartials * sizeof(double));
@@ -981,6 +1041,7 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
     if (e == hipSuccess) e = (hipError_t)static_partials(&h->d_static_partials, &h->static_capacity);
     if (e != hipSuccess) {
       if (h->d_segs) (void)hipFree(h->d_segs);
+      if (h->d_map) (void)hipFree(h->d_map);
       if (h->d_partials) (void)hipFree(h->d_partials);
       if (h->d_tables) (void)hipFree(h->d_tables);
       delete h;
@@ -1403,6 +1464,7 @@ void dadam_destroy(dadam_handle* h) {
     DeviceGuard guard(h->cfg.device);
     for (Slot& s : h->slots) free_slot(s);
     if (h->d_segs) (void)hipFree(h->d_segs);
+    if (h->d_map) (void)hipFree(h->d_map);
     if (h->d_partials) (void)hipFree(h->d_partials);
     if (h->d_tables) (void)hipFree(h->d_tables);
   }

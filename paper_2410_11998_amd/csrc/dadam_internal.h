@@ -105,6 +105,9 @@ struct StepArgsFor {
   uint32_t order_group;  // kOrderDieGroups: rows per die, ceil(n_rows / n_xcd); the launch has n_xcd * order_group
                          // workgroups per tile, of which those beyond a die's share of the rows have nothing to do
   uint32_t reserve_lds;  // direct kernels: LDS a workgroup reserves (see bounded_occupancy_lds)
+  // Device, null where the launch walks segments: a byte for every four elements of the packed vector, kept by layouts of
+  // short segments side by side (see build_map).  Bits 0 to 3: which of them belong to a tensor; bit 4: they decay.
+  const uint8_t* map;
   const Segment* seg;        // device
   const uint32_t* seg_work;  // device: per Grid, the first work item of every segment (tiles; per row in direct mode)
   uint32_t wide_search;      // small launch: all lanes search the segments (see locate)
@@ -132,6 +135,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kLongSegment = 65536;  // elements of two blocks of spread lanes; measured, see dadam_handle::short_segments
+constexpr uint64_t kMostMapped = 1ull << 28, kWidestGap = 7;  // elements; see can_map
 constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks; measured, see rows_stay_on_one_die
 constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves

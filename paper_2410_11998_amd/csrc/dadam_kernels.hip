@@ -24,14 +24,14 @@ namespace dadam {
 
 // what the parts define
 #define DADAM_PART(name)                                       \
-  KernelFn tile_kernel_##name(int phase, TileShape s);         \
-  KernelFn direct_kernel_##name(int phase, bool shared);       \
-  KernelFn rows_kernel_##name(int phase);                      \
-  KernelFn rows_kernel_##name##_ext(int phase);                \
-  KernelFn loop_kernel_##name(int phase);                      \
-  KernelFn loop_kernel_##name##_ext(int phase);                \
-  KernelFn tile_kernel_##name##_ext(int phase, TileShape s);   \
-  KernelFn direct_kernel_##name##_ext(int phase, bool shared)
+  KernelFn tile_kernel_##name(int phase, TileShape s, bool map);         \
+  KernelFn direct_kernel_##name(int phase, bool shared, bool map);       \
+  KernelFn rows_kernel_##name(int phase, bool map);                      \
+  KernelFn rows_kernel_##name##_ext(int phase, bool map);                \
+  KernelFn loop_kernel_##name(int phase, bool map);                      \
+  KernelFn loop_kernel_##name##_ext(int phase, bool map);                \
+  KernelFn tile_kernel_##name##_ext(int phase, TileShape s, bool map);   \
+  KernelFn direct_kernel_##name##_ext(int phase, bool shared, bool map)
 DADAM_PART(f32_f32_nt);
 DADAM_PART(f32_f32);
 DADAM_PART(bf16_bf16_nt);
@@ -42,8 +42,8 @@ DADAM_PART(f32_bf16_nt);
 DADAM_PART(f32_bf16);
 #undef DADAM_PART
 #define DADAM_PART(name)                                   \
-  KernelFn tile_kernel_##name##_few(int phase, TileShape s); \
-  KernelFn direct_kernel_##name##_few(int phase)
+  KernelFn tile_kernel_##name##_few(int phase, TileShape s, bool map); \
+  KernelFn direct_kernel_##name##_few(int phase, bool map)
 DADAM_PART(f32_f32);
 DADAM_PART(bf16_bf16);
 DADAM_PART(bf16_f32);
@@ -117,12 +117,12 @@ __global__ __launch_bounds__(256) void k_probe(const ProbeArgs a) {
 // dispatch tables
 // ---------------------------------------------------------------------------------------------
 template <typename GT, int VEC, bool NT, bool EXT>
-KernelFn acc_kernel_for_phase(int phase) {
+KernelFn acc_kernel_for_phase(int phase, bool map) {
   switch (phase) {
-    case kPlain: return (KernelFn)k_acc<GT, VEC, kPlain, NT, EXT>;
-    case kLoopStart: return (KernelFn)k_acc<GT, VEC, kLoopStart, NT, EXT>;
-    case kFold: return (KernelFn)k_acc<GT, VEC, kFold, NT, EXT>;
-    case kAlg1: return (KernelFn)k_acc<GT, VEC, kAlg1, NT, EXT>;
+    case kPlain: return map ? (KernelFn)k_acc_map<GT, VEC, kPlain, NT, EXT> : (KernelFn)k_acc<GT, VEC, kPlain, NT, EXT>;
+    case kLoopStart: return map ? (KernelFn)k_acc_map<GT, VEC, kLoopStart, NT, EXT> : (KernelFn)k_acc<GT, VEC, kLoopStart, NT, EXT>;
+    case kFold: return map ? (KernelFn)k_acc_map<GT, VEC, kFold, NT, EXT> : (KernelFn)k_acc<GT, VEC, kFold, NT, EXT>;
+    case kAlg1: return map ? (KernelFn)k_acc_map<GT, VEC, kAlg1, NT, EXT> : (KernelFn)k_acc<GT, VEC, kAlg1, NT, EXT>;
   }
   return nullptr;
 }
@@ -139,12 +139,12 @@ KernelFn acc_rows_kernel(int phase) {
 }
 
 template <typename GT, int VEC>
-KernelFn few_acc_kernel(int phase) {
+KernelFn few_acc_kernel(int phase, bool map) {
   switch (phase) {
-    case kPlain: return (KernelFn)k_acc_few<GT, VEC, kPlain>;
-    case kLoopStart: return (KernelFn)k_acc_few<GT, VEC, kLoopStart>;
-    case kFold: return (KernelFn)k_acc_few<GT, VEC, kFold>;
-    case kAlg1: return (KernelFn)k_acc_few<GT, VEC, kAlg1>;
+    case kPlain: return map ? (KernelFn)k_acc_few_map<GT, VEC, kPlain> : (KernelFn)k_acc_few<GT, VEC, kPlain>;
+    case kLoopStart: return map ? (KernelFn)k_acc_few_map<GT, VEC, kLoopStart> : (KernelFn)k_acc_few<GT, VEC, kLoopStart>;
+    case kFold: return map ? (KernelFn)k_acc_few_map<GT, VEC, kFold> : (KernelFn)k_acc_few<GT, VEC, kFold>;
+    case kAlg1: return map ? (KernelFn)k_acc_few_map<GT, VEC, kAlg1> : (KernelFn)k_acc_few<GT, VEC, kAlg1>;
   }
   return nullptr;
 }
@@ -287,9 +287,9 @@ bool tile_shape_supported(TileShape s) {
 static int launch_loops(int xdt, int gdt, Phase phase, TileShape shape, StepArgs a, uint32_t n_tiles, uint32_t lds_bytes,
                         void* stream) {
   KernelFn fn = nullptr;
-  const bool nt = shape.nontemporal, ext = a.ext != nullptr;
-#define DADAM_PICK(name) (ext ? (nt ? loop_kernel_##name##_nt_ext(phase) : loop_kernel_##name##_ext(phase)) \
-                              : (nt ? loop_kernel_##name##_nt(phase) : loop_kernel_##name(phase)))
+  const bool nt = shape.nontemporal, ext = a.ext != nullptr, map = a.map != nullptr;
+#define DADAM_PICK(name) (ext ? (nt ? loop_kernel_##name##_nt_ext(phase, map) : loop_kernel_##name##_ext(phase, map)) \
+                              : (nt ? loop_kernel_##name##_nt(phase, map) : loop_kernel_##name(phase, map)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
@@ -313,10 +313,10 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
   // A handle with more than 64 rows or sources keeps its pointer tables in device memory and runs kernels
   // compiled for that (kernels of their own, so that the small handles' register budget is not theirs).
   KernelFn fn = nullptr;
-  const bool nt = shape.nontemporal, ext = a.ext != nullptr;
+  const bool nt = shape.nontemporal, ext = a.ext != nullptr, map = a.map != nullptr;
   const bool short_block = few(a, nt);
-#define DADAM_PICK(name) (short_block ? tile_kernel_##name##_few(phase, shape) : ext ? (nt ? tile_kernel_##name##_nt_ext(phase, shape) : tile_kernel_##name##_ext(phase, shape)) \
-                              : (nt ? tile_kernel_##name##_nt(phase, shape) : tile_kernel_##name(phase, shape)))
+#define DADAM_PICK(name) (short_block ? tile_kernel_##name##_few(phase, shape, map) : ext ? (nt ? tile_kernel_##name##_nt_ext(phase, shape, map) : tile_kernel_##name##_ext(phase, shape, map)) \
+                              : (nt ? tile_kernel_##name##_nt(phase, shape, map) : tile_kernel_##name(phase, shape, map)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
@@ -328,11 +328,11 @@ int launch_tile(int xdt, int gdt, Phase phase, TileShape shape, const StepArgs& 
 int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, bool whole_items, const StepArgs& a,
                   uint32_t n_work_tiles, void* stream) {
   KernelFn fn = nullptr;
-  const bool ext = a.ext != nullptr;
+  const bool ext = a.ext != nullptr, map = a.map != nullptr;
   if (whole_items) {
     if (phase == kMixOnly) gdt = xdt;  // no gradient: one kernel per parameter type
-#define DADAM_PICK(name) (ext ? (nt ? rows_kernel_##name##_nt_ext(phase) : rows_kernel_##name##_ext(phase)) \
-                              : (nt ? rows_kernel_##name##_nt(phase) : rows_kernel_##name(phase)))
+#define DADAM_PICK(name) (ext ? (nt ? rows_kernel_##name##_nt_ext(phase, map) : rows_kernel_##name##_ext(phase, map)) \
+                              : (nt ? rows_kernel_##name##_nt(phase, map) : rows_kernel_##name(phase, map)))
     if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
     if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
     if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
@@ -340,8 +340,8 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, bool whol
     return launch_pieces(fn, false, a, n_work_tiles, stream, true);
   }
   const bool short_block = few(a, nt);
-#define DADAM_PICK(name) (short_block ? direct_kernel_##name##_few(phase) : ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared) : direct_kernel_##name##_ext(phase, shared)) \
-                              : (nt ? direct_kernel_##name##_nt(phase, shared) : direct_kernel_##name(phase, shared)))
+#define DADAM_PICK(name) (short_block ? direct_kernel_##name##_few(phase, map) : ext ? (nt ? direct_kernel_##name##_nt_ext(phase, shared, map) : direct_kernel_##name##_ext(phase, shared, map)) \
+                              : (nt ? direct_kernel_##name##_nt(phase, shared, map) : direct_kernel_##name(phase, shared, map)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
@@ -353,12 +353,12 @@ int launch_direct(int xdt, int gdt, Phase phase, bool nt, bool shared, bool whol
 int launch_accumulate(int gdt, Phase phase, bool nt, bool whole_items, const StepArgs& a, uint32_t n_work_tiles, void* stream,
                       int vec) {
   KernelFn fn = nullptr;
-  const bool ext = a.ext != nullptr;
+  const bool ext = a.ext != nullptr, map = a.map != nullptr;
   const bool short_block = !whole_items && few(a, nt);
 #define DADAM_PICK(GT, VEC)                                                                                      \
   (whole_items ? (ext ? acc_rows_kernel<GT, VEC, true>(phase) : acc_rows_kernel<GT, VEC, false>(phase))             \
-   : short_block ? few_acc_kernel<GT, VEC>(phase) : ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase) : acc_kernel_for_phase<GT, VEC, false, true>(phase)) \
-       : (nt ? acc_kernel_for_phase<GT, VEC, true, false>(phase) : acc_kernel_for_phase<GT, VEC, false, false>(phase)))
+   : short_block ? few_acc_kernel<GT, VEC>(phase, map) : ext ? (nt ? acc_kernel_for_phase<GT, VEC, true, true>(phase, map) : acc_kernel_for_phase<GT, VEC, false, true>(phase, map)) \
+       : (nt ? acc_kernel_for_phase<GT, VEC, true, false>(phase, map) : acc_kernel_for_phase<GT, VEC, false, false>(phase, map)))
   if (gdt == DADAM_F32 && vec == 4) fn = DADAM_PICK(TF32, 4);
   if (gdt == DADAM_F32 && vec == 8) fn = DADAM_PICK(TF32, 8);
   if (gdt == DADAM_BF16 && vec == 4) fn = DADAM_PICK(TBF16, 4);

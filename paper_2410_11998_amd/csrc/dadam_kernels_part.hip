@@ -14,32 +14,32 @@
 
 namespace dadam {
 
-KernelFn DADAM_JOIN(tile_kernel_, DADAM_PART_NAME)(int phase, TileShape s) {
-  return tile_kernel_for_shape_nt<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT, DADAM_PART_EXT>(phase, s);
+KernelFn DADAM_JOIN(tile_kernel_, DADAM_PART_NAME)(int phase, TileShape s, bool map) {
+  return tile_kernel_for_shape_nt<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT, DADAM_PART_EXT>(phase, s, map);
 }
 
 // shared: rows share sources (a streaming part then keeps the hint off the source loads)
-KernelFn DADAM_JOIN(direct_kernel_, DADAM_PART_NAME)(int phase, bool shared) {
-  if (!DADAM_PART_NT) return direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, 0, DADAM_PART_EXT>(phase);
-  return shared ? direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase)
-                : direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
+KernelFn DADAM_JOIN(direct_kernel_, DADAM_PART_NAME)(int phase, bool shared, bool map) {
+  if (!DADAM_PART_NT) return direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, 0, DADAM_PART_EXT>(phase, map);
+  return shared ? direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase, map)
+                : direct_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase, map);
 }
 
 #if DADAM_PART_FEW
-KernelFn DADAM_JOIN(DADAM_JOIN(tile_kernel_, DADAM_PART_NAME), _few)(int phase, TileShape s) {
-  return few_tile_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase, s);
+KernelFn DADAM_JOIN(DADAM_JOIN(tile_kernel_, DADAM_PART_NAME), _few)(int phase, TileShape s, bool map) {
+  return few_tile_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase, s, map);
 }
-KernelFn DADAM_JOIN(DADAM_JOIN(direct_kernel_, DADAM_PART_NAME), _few)(int phase) {
-  return few_direct_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase);
+KernelFn DADAM_JOIN(DADAM_JOIN(direct_kernel_, DADAM_PART_NAME), _few)(int phase, bool map) {
+  return few_direct_kernel<DADAM_PART_XT, DADAM_PART_GT>(phase, map);
 }
 #endif
 
-KernelFn DADAM_JOIN(rows_kernel_, DADAM_PART_NAME)(int phase) {
-  return rows_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase);
+KernelFn DADAM_JOIN(rows_kernel_, DADAM_PART_NAME)(int phase, bool map) {
+  return rows_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase, map);
 }
 
-KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase) {
-  return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase);
+KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase, bool map) {
+  return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase, map);
 }
 
 }  // namespace dadam

@@ -39,7 +39,8 @@ PHASES = {0: "mix", 1: "updateonly", 2: "plain", 3: "loopstart", 4: "fold", 5: "
 
 
 PROBE_PHASE = "placement probe"      # the passes with which the arena finds the thirds of the memory before a workload is set up
-KERNELS = "k_probe|k_tile_few|k_direct_few|k_acc_few|k_mix_rows|k_acc_rows|k_tile|k_direct|k_rows|k_loop|k_acc"
+KERNELS = ("k_probe|k_tile_few|k_direct_few|k_acc_few|k_mix_rows|k_acc_rows|k_tile|k_direct|k_rows|k_loop|k_acc|k_tile_few_map|"
+           "k_direct_few_map|k_acc_few_map|k_mix_rows_map|k_tile_map|k_direct_map|k_loop_map|k_acc_map")      # _map: layouts with a map
 
 
 def parse_kernel(name: str):
@@ -50,22 +51,23 @@ def parse_kernel(name: str):
     if not m:
         return None, None
     args = [a.strip().split("::")[-1] for a in m.group(2).split(",")]
-    kind = m.group(1)
+    name = m.group(1)
+    kind = name[:-4] if name.endswith("_map") else name
     hint = lambda a: {"0": "false", "1": "true", "2": "shared"}.get(a, a)    # 0 none, 1 all, 2 all but the sources'
     try:
         if kind == "k_tile":          # <param type, grad type, phase, waves, vectors, non-temporal>
-            return f"k_tile<{args[0]},{args[1]},{args[3]},{args[4]},{args[5]}>", PHASES[int(args[2])]
+            return f"{name}<{args[0]},{args[1]},{args[3]},{args[4]},{args[5]}>", PHASES[int(args[2])]
         if kind == "k_tile_few":      # the kernels on the short argument block never stream
-            return f"k_tile_few<{args[0]},{args[1]},{args[3]},{args[4]}>", PHASES[int(args[2])]
+            return f"{name}<{args[0]},{args[1]},{args[3]},{args[4]}>", PHASES[int(args[2])]
         if kind == "k_direct_few":
-            return f"k_direct_few<{args[0]},{args[1]}>", PHASES[int(args[2])]
+            return f"{name}<{args[0]},{args[1]}>", PHASES[int(args[2])]
         if kind == "k_mix_rows":      # <param type, hints>: mixing only
-            return f"k_mix_rows<{args[0]},{hint(args[1])}>", PHASES[0]
+            return f"{name}<{args[0]},{hint(args[1])}>", PHASES[0]
         if kind in ("k_direct", "k_rows", "k_loop"):        # <param type, grad type, phase, hints>
-            return f"{kind}<{args[0]},{args[1]},{hint(args[3])}>", PHASES[int(args[2])]
+            return f"{name}<{args[0]},{args[1]},{hint(args[3])}>", PHASES[int(args[2])]
         if kind == "k_acc_few":       # <grad type, elements per vector, phase>
-            return f"k_acc_few<{args[0]},{args[1]}>", PHASES[int(args[2])]
-        return f"{kind}<{args[0]},{args[1]},{args[3]}>", PHASES[int(args[2])]     # k_acc, k_acc_rows: <grad type, elements per vector, phase, nt>
+            return f"{name}<{args[0]},{args[1]}>", PHASES[int(args[2])]
+        return f"{name}<{args[0]},{args[1]},{args[3]}>", PHASES[int(args[2])]     # k_acc, k_acc_rows: <grad type, elements per vector, phase, nt>
     except (IndexError, KeyError, ValueError):
         return None, None
 
