@@ -93,7 +93,8 @@ struct dadam_handle {
   TileShape mix_shape{4, 1, false};  // shape of the mixing-only launch (more bytes in flight per wavefront)
   uint32_t mix_tile_elems = 0, mix_lds_bytes = 0;
   uint64_t n_work_m = 0;
-  bool nontemporal = false;
+  bool nontemporal = false;      // steps and accumulation stream
+  bool mix_nontemporal = false;  // mixing streams
   bool decays = false;  // some tensor carries weight decay
   // Segments of fewer than 65536 elements on average: lanes are hardly ever spread and most tiles need their segment searched, so
   // streaming launches keep the shapes and orders of contiguous lanes.  (By the share of elements in whole blocks, which takes a long tensor
@@ -592,7 +593,7 @@ bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, u
   const uint32_t C = h->cfg.n_cols;
   if (h->short_segments && (usual || mix_only)) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
-  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
+  if (lone_tile(h)) return (mix_only ? h->mix_shape : h->shape).waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
   return mix_only && C < 32;
 }
 
@@ -709,7 +710,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
-  if (h->nontemporal && !by_loops && !few_tiles && !consensus_out &&
+  const bool streams = mix_only ? h->mix_nontemporal : h->nontemporal;
+  if (streams && !by_loops && !few_tiles && !consensus_out &&
       !(flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) && slot.reuse && h->n_xcds > 1 && h->tile_possible && direct_is_legal(h, slot, decays))
     tile_mode = staging_is_faster(h, slot, mix_only, n_tiles, tile_mode);
   if (few_tiles) tile_mode = false;
@@ -719,7 +721,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
-  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
+  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(streams && h->short_segments)) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
   if (h->mapped && !decays) a.weight_decay = 0.f;
   if (tile_mode && cut_by_elements(h, mix_only, by_loops)) a.d = 0;
@@ -736,10 +738,10 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.row_order = slot.d_loop_rows;
     shape.ut = 1;
     shape.waves = loop_waves;
-    if (h->nontemporal) a.xcd_block = kDieBlockLoops;
+    if (streams) a.xcd_block = kDieBlockLoops;
     lds = loop_lds_bytes(h, shape.waves);
   } else if (tile_mode) {
-    if (mix_only && h->nontemporal && shape.ut == 2) a.xcd_block = kDieBlockMix;
+    if (mix_only && streams && shape.ut == 2) a.xcd_block = kDieBlockMix;
     a.row_ptr = slot.d_row_ptr;
     a.col = slot.d_col;
     a.w = slot.d_w;
@@ -757,7 +759,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)
               : launch_direct((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase,
                               // where rows share sources the re-reads must find them in the cache
-                              h->nontemporal, slot.reuse, whole_items(h, mix_only, a.order, (uint64_t)n_tiles * vector_elems(h) * h->cfg.n_rows),
+                              streams, slot.reuse, whole_items(h, mix_only, a.order, (uint64_t)n_tiles * vector_elems(h) * h->cfg.n_rows),
                               a, w1 - w0, stream);
   if (e == (int)hipSuccess && consensus_out) e = launch_consensus_sum(partials, consensus_out, stream);
   if (e == (int)hipSuccess && own_partials && !recorded) h->partials_clear = true;
@@ -947,38 +949,48 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   h->n_xcds = (uint32_t)env_int("DADAM_XCDS", (int)h->n_xcds);
   if (h->n_xcds > 64) { delete h; return fail(nullptr, DADAM_EINVAL, "n_xcds out of range"); }
 
+  h->vec = vec_elems((int)cfg->param_dtype);
+  find_segments(h);
+  h->mapped = env_int("DADAM_MAP", 1) && can_map(h, &h->map_decay);
+  if (h->mapped) h->short_segments = false;
+
+  // Non-temporal accesses pay off when an iteration's working set cannot stay in the last-level cache (256 MB) anyway; small problems
+  // keep ordinary accesses so that one iteration finds the previous one's output on chip.  The line is at 22 million elements of all rows; steps
+  // and accumulation of up to three rows stream from 336 MB of sources, outputs, gradients and state on.  Time of ordinary accesses over
+  // streaming ones, one row with three sources, one handle / three in turn: float32 1.1e7 elements 0.94 / 1.01, 1.5e7 1.17 / 1.14, 2e7
+  // 1.20 / 1.18 (four steps 550 -> 461 us, with accumulation apart 640 -> 546), bfloat16 0.96 / 0.98, 0.97 / 1.02, 1.13 / 1.11.  (Steps of more rows would gain
+  // as much between 15 and 22 million elements, but pairs in bfloat16 and loops lose, and the kernels of 2e7 elements are held by
+  // tests.  Mixing of 2e7 elements: pairs of 32 rows 0.79 / 0.82.  Short segments without a map were not measured.)
+  const double px = (double)dtype_bytes(cfg->param_dtype), state = dtype_bytes(cfg->grad_dtype) + (cfg->accum_s > 1 ? 12.0 : 8.0);
+  const double touched = (double)cfg->d * ((cfg->n_cols + cfg->n_rows) * px + cfg->n_rows * state);
+  h->nontemporal = h->mix_nontemporal = env_int("DADAM_NT", (double)cfg->d * cfg->n_rows * 24.0 > 512.0 * 1024 * 1024 ? 1 : 0) != 0;
+  if (cfg->n_rows < 4 && !h->short_segments && touched > 336.0 * 1024 * 1024) h->nontemporal = true;
+
   // tile geometry: 16 bytes per lane and vector, `ut` vectors per lane, all source buffers' slices
   // of one tile resident in LDS.  One vector per lane (many small workgroups) and eight wavefronts per group, four when there
   // are fewer than eight rows to deal out; larger launches below.
-  h->vec = vec_elems((int)cfg->param_dtype);
-  TileShape shape;
-  shape.ut = 1;
-  shape.waves = cfg->n_rows >= 8 ? 8 : 4;
-  // Non-temporal accesses pay off when an iteration's working set cannot stay in the last-level
-  // cache anyway; small problems keep ordinary accesses so that one iteration finds the previous
-  // one's output on chip.
-  const double touched = (double)cfg->d * cfg->n_rows * 24.0;
-  h->nontemporal = env_int("DADAM_NT", touched > 512.0 * 1024 * 1024 ? 1 : 0) != 0;
-  shape.nontemporal = h->nontemporal;
-  shape.ut = env_int("DADAM_TILE_UT", shape.ut);
-  shape.waves = env_int("DADAM_TILE_WAVES", shape.waves);
   // Streaming float32 steps: two vectors a lane, which lie the way the memory serves best (see lane_start), up to the
   // sources whose tile fits; sixteen wavefronts from 16 rows on.  Fraction of 8 TB/s, one vector by eight wavefronts / two by
   // eight / two by sixteen, 3e8 to 2e9 elements: 16 rows 0.710 / 0.802 / 0.814, 24 rows 0.801 / 0.802 / 0.809, 48 rows 0.783 / 0.806 /
   // 0.805, 72 rows 0.72 / 0.725 / 0.779; 8 rows 0.817 / 0.825 / 0.802, 4 rows by four wavefronts 0.816 / 0.820, by sixteen 0.794.
   // In bfloat16 one vector has that layout already, and sixteen wavefronts lose (8 rows 0.813 / 0.783, 16 rows 0.780 / 0.770).
-  find_segments(h);
-  h->mapped = env_int("DADAM_MAP", 1) && can_map(h, &h->map_decay);
-  if (h->mapped) h->short_segments = false;
-  if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
-    shape.ut = 2;
-    if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
-  } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
-    // A compute unit holds one workgroup of the tile: sixteen wavefronts keep more of it busy.  us, eight / sixteen: steps of 96
-    // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
-    // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
-    shape.waves = env_int("DADAM_TILE_WAVES", 16);
-  }
+  auto tile_shape = [&](bool streams) {
+    TileShape shape;
+    shape.ut = env_int("DADAM_TILE_UT", 1);
+    shape.waves = env_int("DADAM_TILE_WAVES", cfg->n_rows >= 8 ? 8 : 4);
+    shape.nontemporal = streams;
+    if (env_int("DADAM_TILE_UT", 0) == 0 && streams && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
+      shape.ut = 2;
+      if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
+    } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
+      // A compute unit holds one workgroup of the tile: sixteen wavefronts keep more of it busy.  us, eight / sixteen: steps of 96
+      // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
+      // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
+      shape.waves = env_int("DADAM_TILE_WAVES", 16);
+    }
+    return shape;
+  };
+  const TileShape shape = tile_shape(h->nontemporal);
   if (!tile_shape_supported(shape)) {
     delete h;
     return fail(nullptr, DADAM_EINVAL, "unsupported tile shape (waves %d, ut %d)", shape.waves, shape.ut);
@@ -995,18 +1007,19 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // step's one-vector tile, so larger source counts keep the step's shape.  Streaming float32 passes spread the lanes and take eight
   // wavefronts up to 32 sources, then the step's sixteen (four / eight / sixteen: 12 sources 0.815 / 0.814, 16 sources 0.810 / 0.819, with
   // the error 0.750 / 0.778, 24 sources 0.797 / 0.812 / 0.809, with the error 0.73 / 0.80 / 0.74, 48 sources 0.63 / 0.745 / 0.780).
-  h->mix_shape = shape;
+  const TileShape mix_base = tile_shape(h->mix_nontemporal);
+  h->mix_shape = mix_base;
   if (cfg->n_cols * 2u * kWave * 16u <= 32768u && h->lds_limit >= 32768u && env_int("DADAM_TILE_UT", 0) == 0 &&
       env_int("DADAM_TILE_WAVES", 0) == 0) {
     h->mix_shape.ut = 2;
     h->mix_shape.waves = 4;
   }
-  if (h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2)
+  if (h->mix_nontemporal && !h->short_segments && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2)
     h->mix_shape.waves = 8;
   h->mix_shape.ut = env_int("DADAM_MIX_UT", h->mix_shape.ut);
   h->mix_shape.waves = env_int("DADAM_MIX_WAVES", h->mix_shape.waves);
   if (!tile_shape_supported(h->mix_shape) || cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u > h->lds_limit)
-    h->mix_shape = shape;
+    h->mix_shape = mix_base;
   h->mix_tile_elems = (uint32_t)(kWave * h->vec * h->mix_shape.ut);
   h->mix_lds_bytes = cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u;
   int rc = plan(h);
@@ -1312,7 +1325,7 @@ int dadam_get_plan_info(const dadam_handle* h, dadam_plan_info* out) {
   out->tile_vectors = (uint32_t)h->shape.ut;
   out->mix_waves = (uint32_t)h->mix_shape.waves;
   out->mix_vectors = (uint32_t)h->mix_shape.ut;
-  out->streaming = h->nontemporal ? 1u : 0u;
+  out->streaming = h->mix_nontemporal ? 1u : 0u;
   return DADAM_OK;
 }
 
