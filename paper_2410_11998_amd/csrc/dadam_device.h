@@ -1334,11 +1334,13 @@ __global__ __launch_bounds__(kWave* kWideWaves) void k_rows(const StepArgs a) {
 // barrier the wavefronts deal the loop's rows among themselves.  Every source is read once and summed once, where
 // the tile kernel sums it once per row from a staged copy.  What that costs there: 64 rows of 64 sources read 64 x
 // the tile from LDS, and beyond 80 sources a CU holds one workgroup of the tile, whose phases nothing overlaps.
+// Where loops have many rows, a.loop_shares workgroups take the rows of one tile between them (see loop_shares): each sums the sources
+// for itself, in the same order, and in streaming launches the loads of sources carry no hint, so that the second finds them in its die's L2.
 // All sources of the loop are read before the barrier and its rows written after it.  Bound by HBM: the bytes moved are
 // those needed (96 rows in loops of 48 and 24, 2e8 elements: 4.0 GB read and 1.6 written in 1062 us, 5.3 TB/s); measured against the other kernels in loop_kernel_waves (mixing 64 sources 0.19 -> 0.69 of 8 TB/s, 96 in loops
 // of 48 and 24 0.14 -> 0.69, the step on those 0.34 -> 0.71).
 template <typename XT, typename GT, int PHASE, int CLIP, int HINT, bool EXT, typename A, typename E>
-__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_t origin, E start, E lo, E hi, bool full, float wd, int lane,
+__device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, int share, uint64_t origin, E start, E lo, E hi, bool full, float wd, int lane,
                                           int wave, int waves) {
   constexpr bool NT = HINT != 0;
   constexpr int VEC = XT::vec, H = kGroupStep<NT>;
@@ -1346,7 +1348,7 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   MapBytes<VEC, 1> map;
   if constexpr (CLIP == kMapped) map = load_map<VEC, 1, H>(a, origin, e);
   const Loop l = a.loops[loop];
-  // This wavefront's rows, every `waves`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
+  // This wavefront's rows, every `row_step`-th of the loop's, and sources, every `parts`-th, one per lane (at most 160 / 8 of
   // each).  A wavefront that sums has at least three sources, so that the sum is never less accurate than the listed
   // order: a partial sum starts with a rounded product and is added with a rounded sum, where the chain of fused
   // multiply-adds rounds once.  Mean error against 64 bits, relative to that chain, 3 / 9 / 13 / 20 sources of
@@ -1355,11 +1357,12 @@ __device__ __forceinline__ void loop_body(const A& a, f4* lds, int loop, uint64_
   RowList rl;
   rl.k0 = 0;
   rl.deg = wave < parts ? (l.n_entries - wave + parts - 1) / parts : 0;
-  const int my_rows = wave < l.n_rows ? (l.n_rows - wave + waves - 1) / waves : 0;
+  const int first_row = share * waves + wave, row_step = (int)a.loop_shares * waves;
+  const int my_rows = first_row < l.n_rows ? (l.n_rows - first_row + row_step - 1) / row_step : 0;
   const int entry = l.first_entry + (lane < rl.deg ? wave + lane * parts : 0);
   rl.col_v = a.col[entry];
   rl.w_v = a.w[entry];
-  const int row_v = a.row_order[l.first_row + (lane < my_rows ? wave + lane * waves : 0)];
+  const int row_v = a.row_order[l.first_row + (lane < my_rows ? first_row + lane * row_step : 0)];
   float g[1][VEC], mh[1][VEC], vh[1][VEC], b[1][VEC];
   int row = __builtin_amdgcn_readlane(row_v, 0);
   if (my_rows > 0) load_row_inputs<GT, PHASE, VEC, 1, CLIP, NT, EXT>(a, row, origin, e, lo, hi, g, mh, vh, b);
@@ -1420,9 +1423,9 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   // the dies take runs of tiles in turn, all loops of a tile one after the other (see k_tile).  Streaming launches: runs of two
   // tiles (kDieBlockLoops), because every tile of several loops is many streams: 96 rows in loops of 48 and 24, runs of
   // 1, 2, 4, 8, 32, 256 tiles 0.80, 0.81, 0.80, 0.80, 0.76, 0.76 of 8 TB/s; one loop of 64 rows the same with all of them.
-  const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * a.n_loops);
-  const uint32_t tile = b / a.n_loops;
-  const int loop = (int)(b - tile * a.n_loops);
+  const uint32_t units = a.n_loops * a.loop_shares, b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * units);
+  const uint32_t tile = b / units, unit = b - tile * units;
+  const int loop = (int)(unit / a.loop_shares), share = (int)unit - loop * (int)a.loop_shares;
   uint64_t tile_index, lo, hi;
   float wd;
   locate(a, a.work_begin + tile, tile_index, lo, hi, wd);
@@ -1433,10 +1436,10 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   constexpr int CUT = HINT != 0 && EXT ? kElements : kGroups;  // see tile_entry
   const int clip = clip_of(a, full, hi);
   const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
-  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, tbase, cut.e, cut.lo, cut.hi, full, wd, lane, wave, waves);
-  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
-  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, 0, start, lo, hi, full, wd, lane, wave, waves);
+  if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, share, tbase, cut.e, cut.lo, cut.hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
+  else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
 }
 template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
 __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop_map(const StepArgs a) {
@@ -1444,15 +1447,16 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop_map(const StepArg
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * a.n_loops);
-  const uint32_t tile = b / a.n_loops;
+  const uint32_t units = a.n_loops * a.loop_shares, b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block * units);
+  const uint32_t tile = b / units, unit = b - tile * units;
+  const int loop = (int)(unit / a.loop_shares), share = (int)unit - loop * (int)a.loop_shares;
   uint64_t tile_index, lo, hi;
   float wd;
   locate<true>(a, a.work_begin + tile, tile_index, lo, hi, wd);
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
   const MapTile t = map_tile<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
-  loop_body<XT, GT, PHASE, kMapped, HINT, EXT>(a, reinterpret_cast<f4*>(lds_bytes), (int)(b - tile * a.n_loops), t.origin, t.e, t.lo, t.hi,
+  loop_body<XT, GT, PHASE, kMapped, HINT, EXT>(a, reinterpret_cast<f4*>(lds_bytes), loop, share, t.origin, t.e, t.lo, t.hi,
                                                full, wd, lane, wave, (int)(blockDim.x / kWave));
 }
 
@@ -1675,8 +1679,9 @@ KernelFn tile_kernel_for_shape_nt(int phase, TileShape s, bool map) {
 }
 template <typename XT, typename GT, int HINT, bool EXT>
 KernelFn loop_kernel_for_phase(int phase, bool map) {
+  if constexpr (HINT != 2)  // streaming mixing has no shares
+    if (phase == kMixOnly) return map ? (KernelFn)k_loop_map<XT, GT, kMixOnly, HINT, EXT> : (KernelFn)k_loop<XT, GT, kMixOnly, HINT, EXT>;
   switch (phase) {
-    case kMixOnly: return map ? (KernelFn)k_loop_map<XT, GT, kMixOnly, HINT, EXT> : (KernelFn)k_loop<XT, GT, kMixOnly, HINT, EXT>;
     case kUpdateOnly: return map ? (KernelFn)k_loop_map<XT, GT, kUpdateOnly, HINT, EXT> : (KernelFn)k_loop<XT, GT, kUpdateOnly, HINT, EXT>;
     case kPlain: return map ? (KernelFn)k_loop_map<XT, GT, kPlain, HINT, EXT> : (KernelFn)k_loop<XT, GT, kPlain, HINT, EXT>;
     case kLoopStart: return map ? (KernelFn)k_loop_map<XT, GT, kLoopStart, HINT, EXT> : (KernelFn)k_loop<XT, GT, kLoopStart, HINT, EXT>;

@@ -498,6 +498,30 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
   return loop_lds_bytes(h, waves) <= h->lds_limit ? waves : 0;
 }
 
+// How many workgroups share the rows of one tile of a loop.  The order of the sums does not depend on it.  A row updated in place
+// overwrites a source that the other workgroups may still read, so there it is one.
+// Launches that leave compute units idle: as many as keep it at one workgroup a unit (sixteen wavefronts then walk 6 rows of 96 in turn
+// otherwise).  us of four steps, one / two / four / eight workgroups: 32 rows of 4e5 elements in all 28.2 / 23.5, 64 rows 42.9 / 32.6 / 27.4, 96 rows
+// 65 / 45 / 38 / 32, 1.5e6 elements 73 / 51 / 46 / 57 (62 tiles), 5e6 119 / 130 (204 tiles); bfloat16 96 rows 98 / 64 / 52 / 40, 5e6 125 / 98 / 130
+// (102 tiles); 96 rows in loops of 48, 24, 24, 4e5 elements 45 / 37 / 31, 1.5e6 50 / 59 (186 tiles of a loop); mixing of 96 rows, 1.5e6
+// 17.0 / 15.1 / 14.6 / 17.1, bfloat16 19.6 / 17.2 / 16.3 / 15.3.
+// Streaming steps of one loop of 96 rows and more and fewer than 5120 tiles: two.  Their workgroups are few and long (12 rows to a wavefront),
+// and the chip's last round is short of them.  Time of one over that of two, 3e7, 6e7, 1.2e8, 2.5e8 elements: float32 96 rows 1.08, 1.10,
+// 1.00, - (1758 -> 1623 us at 8e7), 128 rows 1.14, 1.24, 1.04, 1.01, bfloat16 96 rows 1.28, 1.16, 1.04, 1.03 (1692 -> 1436), 128 rows 1.09,
+// 1.11, 1.02, 1.07; with s = 1 and with decay the same.  But float32 16 rows 0.96, 32 rows 0.93 to 1.06 (8e8 elements 3640 / 3881), 64 rows 0.93
+// to 1.05, 96 rows of 12200 tiles 0.99, bfloat16 32 and 64 rows 0.98, 70 rows 0.91 to 1.12; loops of 48, 24, 24 of 8e7 elements 0.94; mixing 0.93, half
+// of its bytes are sources; most launches that do not stream lose as well.
+uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_t n_tiles, bool mix_only, bool streams) {
+  for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
+    if (!h->inplace_cols[i].empty()) return 1;
+  uint32_t rows = 0;
+  for (const Loop& l : slot.loops) rows = std::max(rows, (uint32_t)l.n_rows);
+  const uint32_t most = (rows + (uint32_t)waves - 1) / (uint32_t)waves;
+  const uint32_t units = n_tiles * (uint32_t)slot.loops.size();
+  if (2 * units <= kFewTiles) return std::min(most, kFewTiles / units);
+  return streams && !mix_only && slot.loops.size() == 1 && rows >= 96 && n_tiles < kLongLaunch ? 2 : 1;
+}
+
 // A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: up to this many tiles and with
 // more rows than a workgroup has wavefronts, the direct kernel's one wavefront per row takes the launch from the tile
 // kernel, with the same sums in the same order.  A loop of four steps, us, tile / direct, by tiles: 16 rows of 5 sources 98:
@@ -733,6 +757,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (by_loops) {
     a.loops = slot.d_loops;
     a.n_loops = (uint32_t)slot.loops.size();
+    a.loop_shares = loop_shares(h, slot, loop_waves, n_tiles, mix_only, streams);
     a.col = slot.d_loop_col;
     a.w = slot.d_loop_w;
     a.row_order = slot.d_loop_rows;

@@ -99,6 +99,7 @@ struct StepArgsFor {
   const Loop* loops;
   uint32_t list_stride;
   uint32_t n_loops;      // > 0: the loop kernel's launch (see launch_tile)
+  uint32_t loop_shares;  // workgroups that share the rows of one tile of a loop (see loop_shares)
   uint32_t order;        // Order: how a launch of the row kernel walks pieces and rows
   uint32_t n_pieces;     // pieces of this launch (kOrderDieBlocks)
   uint32_t die_run;      // pieces a die walks row after row (kOrderDieBlocks)
@@ -139,6 +140,7 @@ constexpr uint64_t kMostMapped = 1ull << 28, kWidestGap = 7;  // elements; see c
 constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks; measured, see rows_stay_on_one_die
 constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
+constexpr uint32_t kLongLaunch = 5120;   // tiles; measured, see loop_shares
 constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
 constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there, whole_items, accumulate_whole_items
 constexpr uint64_t kPairElems = 13000000;   // the same, of launches that do not stream; measured, see rows_stay_on_one_die

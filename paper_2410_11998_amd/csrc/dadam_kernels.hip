@@ -28,8 +28,8 @@ namespace dadam {
   KernelFn direct_kernel_##name(int phase, bool shared, bool map);       \
   KernelFn rows_kernel_##name(int phase, bool map);                      \
   KernelFn rows_kernel_##name##_ext(int phase, bool map);                \
-  KernelFn loop_kernel_##name(int phase, bool map);                      \
-  KernelFn loop_kernel_##name##_ext(int phase, bool map);                \
+  KernelFn loop_kernel_##name(int phase, bool shared, bool map);         \
+  KernelFn loop_kernel_##name##_ext(int phase, bool shared, bool map);   \
   KernelFn tile_kernel_##name##_ext(int phase, TileShape s, bool map);   \
   KernelFn direct_kernel_##name##_ext(int phase, bool shared, bool map)
 DADAM_PART(f32_f32_nt);
@@ -287,20 +287,20 @@ bool tile_shape_supported(TileShape s) {
 static int launch_loops(int xdt, int gdt, Phase phase, TileShape shape, StepArgs a, uint32_t n_tiles, uint32_t lds_bytes,
                         void* stream) {
   KernelFn fn = nullptr;
-  const bool nt = shape.nontemporal, ext = a.ext != nullptr, map = a.map != nullptr;
-#define DADAM_PICK(name) (ext ? (nt ? loop_kernel_##name##_nt_ext(phase, map) : loop_kernel_##name##_ext(phase, map)) \
-                              : (nt ? loop_kernel_##name##_nt(phase, map) : loop_kernel_##name(phase, map)))
+  const bool nt = shape.nontemporal, ext = a.ext != nullptr, shared = a.loop_shares > 1, map = a.map != nullptr;
+#define DADAM_PICK(name) (ext ? (nt ? loop_kernel_##name##_nt_ext(phase, shared, map) : loop_kernel_##name##_ext(phase, shared, map)) \
+                              : (nt ? loop_kernel_##name##_nt(phase, shared, map) : loop_kernel_##name(phase, shared, map)))
   if (xdt == DADAM_F32 && gdt == DADAM_F32) fn = DADAM_PICK(f32_f32);
   if (xdt == DADAM_BF16 && gdt == DADAM_BF16) fn = DADAM_PICK(bf16_bf16);
   if (xdt == DADAM_BF16 && gdt == DADAM_F32) fn = DADAM_PICK(bf16_f32);
   if (xdt == DADAM_F32 && gdt == DADAM_BF16) fn = DADAM_PICK(f32_bf16);
 #undef DADAM_PICK
   const uint32_t threads = (uint32_t)(kWave * shape.waves);
-  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / threads / a.n_loops);
+  const uint32_t most = (uint32_t)(((1ull << 32) - 1) / threads / (a.n_loops * a.loop_shares));
   int e = (int)hipSuccess;
   while (n_tiles > 0 && e == (int)hipSuccess) {
     const uint32_t now = n_tiles < most ? n_tiles : most;
-    e = launch(fn, false, now * a.n_loops, threads, lds_bytes, a, stream);
+    e = launch(fn, false, now * a.n_loops * a.loop_shares, threads, lds_bytes, a, stream);
     a.work_begin += now;
     n_tiles -= now;
   }

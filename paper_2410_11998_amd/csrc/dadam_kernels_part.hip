@@ -38,7 +38,9 @@ KernelFn DADAM_JOIN(rows_kernel_, DADAM_PART_NAME)(int phase, bool map) {
   return rows_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase, map);
 }
 
-KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase, bool map) {
+// shared: several workgroups sum the sources of a tile (a streaming part then keeps the hint off the source loads)
+KernelFn DADAM_JOIN(loop_kernel_, DADAM_PART_NAME)(int phase, bool shared, bool map) {
+  if (DADAM_PART_NT && shared) return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 2 : 0, DADAM_PART_EXT>(phase, map);
   return loop_kernel_for_phase<DADAM_PART_XT, DADAM_PART_GT, DADAM_PART_NT ? 1 : 0, DADAM_PART_EXT>(phase, map);
 }
 
