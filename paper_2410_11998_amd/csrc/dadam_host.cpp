@@ -505,12 +505,14 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
 // 65 / 45 / 38 / 32, 1.5e6 elements 73 / 51 / 46 / 57 (62 tiles), 5e6 119 / 130 (204 tiles); bfloat16 96 rows 98 / 64 / 52 / 40, 5e6 125 / 98 / 130
 // (102 tiles); 96 rows in loops of 48, 24, 24, 4e5 elements 45 / 37 / 31, 1.5e6 50 / 59 (186 tiles of a loop); mixing of 96 rows, 1.5e6
 // 17.0 / 15.1 / 14.6 / 17.1, bfloat16 19.6 / 17.2 / 16.3 / 15.3.
-// Streaming steps of one loop of 96 rows and more and fewer than 5120 tiles: two.  Their workgroups are few and long (12 rows to a wavefront),
-// and the chip's last round is short of them.  Time of one over that of two, 3e7, 6e7, 1.2e8, 2.5e8 elements: float32 96 rows 1.08, 1.10,
-// 1.00, - (1758 -> 1623 us at 8e7), 128 rows 1.14, 1.24, 1.04, 1.01, bfloat16 96 rows 1.28, 1.16, 1.04, 1.03 (1692 -> 1436), 128 rows 1.09,
-// 1.11, 1.02, 1.07; with s = 1 and with decay the same.  But float32 16 rows 0.96, 32 rows 0.93 to 1.06 (8e8 elements 3640 / 3881), 64 rows 0.93
-// to 1.05, 96 rows of 12200 tiles 0.99, bfloat16 32 and 64 rows 0.98, 70 rows 0.91 to 1.12; loops of 48, 24, 24 of 8e7 elements 0.94; mixing 0.93, half
-// of its bytes are sources; most launches that do not stream lose as well.
+// Streaming steps of one loop of 96 rows and more, of fewer than 4096 tiles: two where the last round of workgroups, which are few and long (12 rows
+// to a wavefront), would be short of them.  Float32: from a round of three to a unit on.  Bfloat16, two to a unit by registers: where at most
+// half of the last round is there.  Time of one over that of two, s = 1 / 4: float32 96 rows of 976, 1831, 2441, 3255, 4069, 6100 tiles 1.08 /
+// 1.05, 1.08 / 1.03, 1.11 / 1.07, 1.07 / 1.04, 1.09 / 1.06, 1.01 / 1.00, 128 rows of 732, 916, 1373, 1831, 4578 0.96 / 0.97, 1.06 / 1.01, 1.16 / 1.08, 1.14 /
+// 1.05, 0.99 / 0.98; bfloat16 96 rows of 488, 610, 916, 1221, 1628, 2035 0.90 / 0.91, 1.10 / 1.08, 0.94 / 0.93, 1.05 / 1.03, 1.03 / 1.08, 1.00 / 1.01, 128
+// rows of 458, 687, 916, 1221, 2289, 3815 0.88 / 0.90, 1.01 / 0.99, 0.96 / 0.96, 1.12 / 1.10, 1.00 / 1.01, 1.05 / 1.05.  Fewer rows gain nothing
+// sure (float32 32 rows 0.93 to 1.06, 64 rows 0.93 to 1.05, bfloat16 70 rows 0.91 to 1.12); loops of 48, 24, 24 lose, and so does mixing, half of whose bytes
+// are sources (0.93), and most of what does not stream.
 uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_t n_tiles, bool mix_only, bool streams) {
   for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
     if (!h->inplace_cols[i].empty()) return 1;
@@ -519,7 +521,10 @@ uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_
   const uint32_t most = (rows + (uint32_t)waves - 1) / (uint32_t)waves;
   const uint32_t units = n_tiles * (uint32_t)slot.loops.size();
   if (2 * units <= kFewTiles) return std::min(most, kFewTiles / units);
-  return streams && !mix_only && slot.loops.size() == 1 && rows >= 96 && n_tiles < kLongLaunch ? 2 : 1;
+  if (!streams || mix_only || slot.loops.size() > 1 || rows < 96 || n_tiles >= kLongLaunch) return 1;
+  if (h->vec == 4) return n_tiles > 3 * kFewTiles ? 2 : 1;
+  const uint32_t last = n_tiles % (2 * kFewTiles);
+  return n_tiles > 2 * kFewTiles && last > 0 && last <= kFewTiles ? 2 : 1;
 }
 
 // A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: up to this many tiles and with

@@ -18,9 +18,10 @@ import harness as H
     ("aer", 96, 42, "f32", "f32"),              # loops of 48, 24 and 24: two, of which the short loops need one and a half
     ("complete", 64, 129, "f32", "f32"),        # one
     ("complete", 32, 2900, "f32", "f32"),       # streaming: one
-    ("complete", 96, 5119, "f32", "f32"),       # streaming, the longest launch of two, tables in device memory
-    ("complete", 96, 5120, "f32", "f32"),       # one
-    ("complete", 97, 800, "bf16", "bf16"),
+    ("complete", 96, 4095, "f32", "f32"),       # streaming, the longest launch of two, tables in device memory
+    ("complete", 96, 4096, "f32", "f32"),       # one
+    ("complete", 97, 768, "bf16", "bf16"),       # two: half of the last round
+    ("complete", 97, 769, "bf16", "bf16"),       # one
 ])
 def test_shared_rows_have_the_same_bits(kind, rows, tiles, params, grads):
     print("case", kind, rows, tiles, params, grads, flush=True)
