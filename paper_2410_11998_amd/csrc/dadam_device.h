@@ -216,9 +216,6 @@ __device__ __forceinline__ T* at(void* base, uint32_t e) {
 // outside (the consensus error counts on that).  Both need whole groups to end within the buffer (clip_of).  us, elements / groups:
 // 8 replicas of 300 odd-sized tensors, bfloat16, four steps 68.6 / 59.8, one row of 700 such tensors 32.3 / 28.1 (bfloat16 37.5 /
 // 33.8), ring of 12 x 20 tensors 26.2 / 22.0, 100 rows of seven sources x 400 tensors, bfloat16 1285 / 957.
-// Streaming kernels of large handles have the body too, though a layout of one segment has one such tile: it ends the launch, and element by element the
-// rows of a wavefront wait one after the other.  us of four steps, elements / groups, one cut tile: 96 rows of one loop, 3e7 elements 683 / 636, bfloat16
-// 663 / 500 (mixing 88 / 57), exponential graph on 96 rows 688 / 649, mixing of 96 bfloat16 pairs with the error, seven rounds, 363 / 325.
 // Streaming accesses: every global datum of a step is touched exactly once, so full-group
 // accesses may carry the non-temporal hint (NT) and leave the caches to nobody in particular.
 // Which classes of access carry the hint when a handle streams (all eight combinations measured:
@@ -472,6 +469,15 @@ struct Needs {
   static constexpr bool acc_out = PHASE == kPlain || PHASE == kLoopStart || PHASE == kFold;
   static constexpr bool moments_out = PHASE == kFold || PHASE == kAlg1;
 };
+
+// The place of a launch's n tiles that comes up when the order says b.  Streaming kernels of large handles (LAST_FIRST) begin with the last tile:
+// they load cut tiles element by element (see tile_entry), which is long, 6 or 12 rows to a wavefront one after the other, and at a layout's ragged end
+// it was the launch's tail.  us of four steps, one cut tile, last / first: 96 rows of one loop, 3e7 elements 683 / 603, bfloat16 663 / 517 (mixing of 1e8 184 / 149),
+// exponential graph on 96 rows 688 / 646, seven rounds of 96 bfloat16 pairs with the error 363 / 315.
+template <bool LAST_FIRST>
+__device__ __forceinline__ uint32_t begin_with_last(uint32_t b, uint32_t n) {
+  return !LAST_FIRST ? b : b == 0 ? n - 1 : b - 1;
+}
 
 // Which segment does work item `work` belong to, and which tile of the launch's grid is it?  Every lane of the
 // wavefront is active here.  In small launches, whose time is a chain of trips to memory, all lanes search the
@@ -988,7 +994,7 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   const uint32_t b = die_block_order(blockIdx.x, gridDim.x, a.n_xcd, a.xcd_block);
   uint64_t tile_index, lo, hi;
   float wd;
-  locate<MAP>(a, a.work_begin + b, tile_index, lo, hi, wd);
+  locate<MAP>(a, a.work_begin + begin_with_last<NT && EXT && !MAP>(b, gridDim.x), tile_index, lo, hi, wd);
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
   if constexpr (MAP) {
@@ -997,13 +1003,14 @@ __device__ __forceinline__ void tile_entry(const A& a) {
   } else {
     const uint64_t start = lane_start<VEC, UT, NT>(tile_index, lo, hi, lane);
     const Cut cut = cut_of<VEC, UT, NT>(tbase, lo, hi, lane);
-    constexpr int CUT = PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
+    // streaming launches of large handles have few cut tiles: a third body with its look-ups in the tables is not worth its size
+    constexpr int CUT = NT && EXT ? kElements : PHASE == kMixConsensus ? kGroupsZeroed : kGroups;
     // see `from`; bfloat16 rows with float32 gradients keep their wavefronts with 64 bits where nothing is folded
     constexpr bool NARROW = NT || (Needs<PHASE>::grad && (XT::bytes == 4 || GT::bytes == 2 || PHASE == kFold));
     const int clip = clip_of(a, full, hi);
     if (clip == kWhole) tile_body<XT, GT, PHASE, W, UT, kWhole, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
-    else if (clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, full, wd, b, lane, wave);
-    else if (clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
+    else if (CUT != kElements && clip == kGroups && NARROW) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, tbase, cut.e, cut.lo, cut.hi, full, wd, b, lane, wave);
+    else if (CUT != kElements && clip == kGroups) tile_body<XT, GT, PHASE, W, UT, CUT, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
     else tile_body<XT, GT, PHASE, W, UT, kElements, NT, EXT>(a, lds, 0, start, lo, hi, full, wd, b, lane, wave);
   }
 }
@@ -1222,13 +1229,14 @@ __device__ __forceinline__ void direct_entry(const A& a) {
   } else {
     const uint64_t e[1] = {lane_start<XT::vec, 1, HINT != 0>(p.index, p.lo, p.hi, lane)};
     if (active && p.any) {  // uniform over the workgroup
+      constexpr int CUT = HINT == 1 && EXT ? kElements : kGroups;  // see tile_entry
       const int clip = clip_of(a, p.full, p.hi);
       const uint64_t tbase = p.index * (kWave * XT::vec);
       const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, p.lo, p.hi, lane);
       const uint32_t c[1] = {cut.e};
       if (clip == kWhole) direct_body<XT, GT, PHASE, 1, kWhole, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
-      else if (clip == kGroups && Needs<PHASE>::grad) direct_body<XT, GT, PHASE, 1, kGroups, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.full, p.wd, lane);
-      else if (clip == kGroups) direct_body<XT, GT, PHASE, 1, kGroups, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
+      else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, tbase, c, cut.lo, cut.hi, p.full, p.wd, lane);
+      else if (CUT == kGroups && clip == kGroups) direct_body<XT, GT, PHASE, 1, CUT, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
       else direct_body<XT, GT, PHASE, 1, kElements, HINT, EXT>(a, (int)position, row, 0, e, p.lo, p.hi, p.full, p.wd, lane);
     }
   }
@@ -1429,16 +1437,17 @@ __global__ __launch_bounds__(kWave* kMaxLoopWaves) void k_loop(const StepArgs a)
   const int loop = (int)(unit / a.loop_shares), share = (int)unit - loop * (int)a.loop_shares;
   uint64_t tile_index, lo, hi;
   float wd;
-  locate(a, a.work_begin + tile, tile_index, lo, hi, wd);
+  locate(a, a.work_begin + begin_with_last<HINT != 0 && EXT>(tile, gridDim.x / units), tile_index, lo, hi, wd);
   const uint64_t tbase = tile_index * TILE;
   const bool full = tbase >= lo && tbase + TILE <= hi;
   const int waves = (int)(blockDim.x / kWave);
   const uint64_t start = lane_start<XT::vec, 1, HINT != 0>(tile_index, lo, hi, lane);
+  constexpr int CUT = HINT != 0 && EXT ? kElements : kGroups;  // see tile_entry
   const int clip = clip_of(a, full, hi);
   const Cut cut = cut_of<XT::vec, 1, HINT != 0>(tbase, lo, hi, lane);
   if (clip == kWhole) loop_body<XT, GT, PHASE, kWhole, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
-  else if (clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, kGroups, HINT, EXT>(a, lds, loop, share, tbase, cut.e, cut.lo, cut.hi, full, wd, lane, wave, waves);
-  else if (clip == kGroups) loop_body<XT, GT, PHASE, kGroups, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups && Needs<PHASE>::grad) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, share, tbase, cut.e, cut.lo, cut.hi, full, wd, lane, wave, waves);
+  else if (CUT == kGroups && clip == kGroups) loop_body<XT, GT, PHASE, CUT, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
   else loop_body<XT, GT, PHASE, kElements, HINT, EXT>(a, lds, loop, share, 0, start, lo, hi, full, wd, lane, wave, waves);
 }
 template <typename XT, typename GT, int PHASE, int HINT, bool EXT>
@@ -1523,10 +1532,11 @@ __device__ __forceinline__ void acc_entry(const A& a) {
   const PieceAt p = locate_piece<VEC, MAP>(a, t);
   const uint64_t e[1] = {lane_start<VEC, 1, NT>(p.index, p.lo, p.hi, (int)threadIdx.x)};
   if (active && p.any) {
+    constexpr int CUT = NT && EXT ? kElements : kGroups;  // see tile_entry
     const int clip = clip_of(a, p.full, p.hi);
     if constexpr (MAP) acc_body<GT, VEC, PHASE, 1, kMapped, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
     else if (clip == kWhole) acc_body<GT, VEC, PHASE, 1, kWhole, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
-    else if (clip == kGroups) acc_body<GT, VEC, PHASE, 1, kGroups, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
+    else if (CUT == kGroups && clip == kGroups) acc_body<GT, VEC, PHASE, 1, CUT, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
     else acc_body<GT, VEC, PHASE, 1, kElements, NT, EXT>(a, row, e, p.lo, p.hi, p.full);
   }
 }

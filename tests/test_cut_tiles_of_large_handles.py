@@ -1,5 +1,5 @@
-"""Streaming launches of handles with their tables in device memory, whose cut tiles load whole groups: bit for bit against handles over parts of
-the same elements, which do not stream.  Padding is NaN on input and must keep a sentinel."""
+"""Streaming launches of handles with their tables in device memory, which load cut tiles element by element and begin with the last one: bit for bit
+against handles over parts of the same elements, which do not stream.  Padding is NaN on input and must keep a sentinel."""
 
 import numpy as np
 import pytest
