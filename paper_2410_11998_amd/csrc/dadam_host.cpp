@@ -499,7 +499,8 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
 }
 
 // How many workgroups share the rows of one tile of a loop.  The order of the sums does not depend on it.  A row updated in place
-// overwrites a source that the other workgroups may still read, so there it is one.
+// overwrites a source that the other workgroups may still read, so there it is one; and one in streaming mixing, which has no kernel of
+// shares (whether a handle streams follows from d, its tiles from what the tensors cover of it, so a streaming launch may well be small).
 // Launches that leave compute units idle: as many as keep it at one workgroup a unit (sixteen wavefronts then walk 6 rows of 96 in turn
 // otherwise).  us of four steps, one / two / four / eight workgroups: 32 rows of 4e5 elements in all 28.2 / 23.5, 64 rows 42.9 / 32.6 / 27.4, 96 rows
 // 65 / 45 / 38 / 32, 1.5e6 elements 73 / 51 / 46 / 57 (62 tiles), 5e6 119 / 130 (204 tiles); bfloat16 96 rows 98 / 64 / 52 / 40, 5e6 125 / 98 / 130
@@ -514,6 +515,7 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
 // sure (float32 32 rows 0.93 to 1.06, 64 rows 0.93 to 1.05, bfloat16 70 rows 0.91 to 1.12); loops of 48, 24, 24 lose, and so does mixing, half of whose bytes
 // are sources (0.93), and most of what does not stream.
 uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_t n_tiles, bool mix_only, bool streams) {
+  if (mix_only && streams) return 1;
   for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
     if (!h->inplace_cols[i].empty()) return 1;
   uint32_t rows = 0;
@@ -521,7 +523,7 @@ uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_
   const uint32_t most = (rows + (uint32_t)waves - 1) / (uint32_t)waves;
   const uint32_t units = n_tiles * (uint32_t)slot.loops.size();
   if (2 * units <= kFewTiles) return std::min(most, kFewTiles / units);
-  if (!streams || mix_only || slot.loops.size() > 1 || rows < 96 || n_tiles >= kLongLaunch) return 1;
+  if (!streams || slot.loops.size() > 1 || rows < 96 || n_tiles >= kLongLaunch) return 1;
   if (h->vec == 4) return n_tiles > 3 * kFewTiles ? 2 : 1;
   const uint32_t last = n_tiles % (2 * kFewTiles);
   return n_tiles > 2 * kFewTiles && last > 0 && last <= kFewTiles ? 2 : 1;

@@ -18,6 +18,7 @@ static bool capturing = false;
 static std::vector<std::function<void()>> recorded;
 static const char* fail_launch = nullptr;  // name of the launcher whose next call fails
 static std::string route, how;  // how: the shape of the tile's workgroup, the order of a row launch
+static uint32_t shares = 0;  // workgroups that share the rows of a loop's tile
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -46,6 +47,8 @@ int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint3
   how = std::to_string(shape.waves) + "x" + std::to_string(shape.ut) + (shape.nontemporal ? " streaming" : "") + " block " +
         std::to_string(a.xcd_block) + (a.d == 0 ? " cut by elements" : "");
   route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
+  shares = a.n_loops > 0 ? a.loop_shares : 0;
+  if (shares > 1 && shape.nontemporal && phase == kMixOnly) return (int)hipErrorInvalidDeviceFunction;  // there is no such kernel
   double* p = a.partials;
   return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
 }
@@ -231,25 +234,26 @@ static void consensus() {
   }
 }
 
+static Rows complete(int n) {
+  Rows r;
+  std::vector<int32_t> all;
+  for (int c = 0; c < n; ++c) all.push_back(c);
+  for (int i = 0; i < n; ++i) add_row(r, all);
+  return r;
+}
+static Rows halves(int n) {  // loops of n/2, n/4, n/4 rows
+  Rows r;
+  const int from[] = {0, n / 2, n / 2 + n / 4, n};
+  for (int l = 0; l < 3; ++l) {
+    std::vector<int32_t> own;
+    for (int c = from[l]; c < from[l + 1]; ++c) own.push_back(c);
+    for (size_t i = 0; i < own.size(); ++i) add_row(r, own);
+  }
+  return r;
+}
+
 // Which launches of an All-Reduce loop, or of several, share one sum.
 static void loops() {
-  auto complete = [](int n) {
-    Rows r;
-    std::vector<int32_t> all;
-    for (int c = 0; c < n; ++c) all.push_back(c);
-    for (int i = 0; i < n; ++i) add_row(r, all);
-    return r;
-  };
-  auto halves = [](int n) {  // loops of n/2, n/4, n/4 rows
-    Rows r;
-    const int from[] = {0, n / 2, n / 2 + n / 4, n};
-    for (int l = 0; l < 3; ++l) {
-      std::vector<int32_t> own;
-      for (int c = from[l]; c < from[l + 1]; ++c) own.push_back(c);
-      for (size_t i = 0; i < own.size(); ++i) add_row(r, own);
-    }
-    return r;
-  };
   struct { const char* kind; int rows; uint64_t tiles; } cases[] = {
       {"complete", 15, 256}, {"complete", 16, 256}, {"complete", 16, 257}, {"complete", 16, 512}, {"complete", 16, 513},
       {"complete", 28, 257}, {"complete", 28, 512}, {"complete", 28, 513}, {"complete", 32, 1024}, {"complete", 32, 1025}, {"complete", 55, 1761},
@@ -270,6 +274,19 @@ static void loops() {
       ranges = differs(ranges) || differs(decay.step(F, 1, 2)) || differs(decay.step(0)) ? " but ranges differ" : "";
       say((std::string(c.kind) + std::to_string(c.rows) + " " + std::to_string(c.tiles) + (dtype == DADAM_BF16 ? " bf16" : " f32")).c_str(),
           plain.step(F) + " " + plain.mix(0) + " decay " + decay.step(F) + " " + decay.mix(0) + ranges);
+    }
+}
+
+// Handles whose size says that they stream and whose tensors cover few tiles: one tensor of 20000 elements in 2.3e7 of all rows.
+static void sparse_loops() {
+  for (int n : {32, 64, 96})
+    for (uint32_t dtype : {DADAM_F32, DADAM_BF16}) {
+      const uint64_t d = 23000000 / n / 8 * 8 + 8;
+      Sim s(n, n, {{d / 2 / 8 * 8, 20000, 0.f, 0}, {d, 0, 0.f, 0}}, complete(n), dtype);
+      s.bind();
+      auto told = [](const std::string& r) { return r + " shared by " + std::to_string(shares) + (how.find("streaming") != std::string::npos ? " streaming" : ""); };
+      const std::string step = told(s.step(DADAM_FUSE_ACCUM)), update = told(s.step(0)), mix = told(s.mix(0));
+      say((std::to_string(n) + (dtype == DADAM_BF16 ? " bf16" : " f32")).c_str(), step + ", update " + update + ", mix " + mix);
     }
 }
 
@@ -364,6 +381,7 @@ int main(int argc, char** argv) {
   if (what == "foreign_in_place") foreign_in_place();
   else if (what == "consensus") consensus();
   else if (what == "loops") loops();
+  else if (what == "sparse_loops") sparse_loops();
   else if (what == "few") few();
   else if (what == "die_order") die_order();
   else if (what == "accumulation") accumulation();

@@ -6,8 +6,65 @@ import torch
 
 from paper_2410_11998_amd import binding as B
 from paper_2410_11998_amd import workloads as WL
+from test_host_abi import _route_answers
 
 import harness as H
+
+
+def test_streaming_mixing_is_not_shared_out(tmp_path):
+    """Handles that stream by their size while their tensors cover few tiles: steps have kernels of shared rows there, mixing has none."""
+    shared = {"32": (2, 2), "64": (3, 4), "96": (3, 6)}  # 79 or 40 tiles on 256 compute units; as many as there are rows for sixteen wavefronts
+    want = {}
+    for rows, by_type in shared.items():
+        for dtype, n in zip(("f32", "bf16"), by_type):
+            step = f"loop16 shared by {n} streaming"
+            want[f"{rows} {dtype}"] = f"{step}, update {step}, mix loop16 shared by 1 streaming"
+    assert _route_answers(tmp_path, "sparse_loops") == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,dtype", [(32, "f32"), (64, "bf16"), (96, "f32"), (96, "bf16")])
+@pytest.mark.parametrize("tensors", [1, 12])
+def test_mixing_of_few_tiles_in_a_handle_that_streams(rows, dtype, tensors):
+    """20000 elements in the middle of 2.3e7 of all rows, as one tensor or as twelve short ones (which have a map), on the complete graph: every
+    row gets the mean of the sources, mixing and steps keep to the tensors."""
+    print("case", rows, dtype, tensors, flush=True)
+    dev = torch.device("cuda:0")
+    d = 23000000 // rows // 8 * 8 + 8
+    lead, each = d // 2 // 8 * 8, 20000 // tensors
+    offsets = [lead + k * (-(-each // 8) * 8) for k in range(tensors)] + [d]
+    numels = [each] * tensors + [0]
+    inside = torch.zeros(d, dtype=torch.bool, device=dev)
+    for o, n in zip(offsets, numels):
+        inside[o:o + n] = True
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows)
+    dt = H.TORCH_DT[dtype]
+    # eighths between -1 and 1
+    x = [torch.full((d,), float("nan"), dtype=dt, device=dev) for _ in range(rows)]
+    for t in x:
+        t[inside] = (torch.randint(-8, 9, (int(inside.sum()),), device=dev, generator=gen).float() / 8).to(dt)
+    out = [torch.full_like(t, 7.0) for t in x]
+    g = [torch.zeros_like(t) for t in x]
+    state = [torch.full((d,), 0.0, device=dev) for _ in range(3 * rows)]
+    h = B.dadam_init(rows, rows, d, offsets, numels, H.ABI_DT[dtype], H.ABI_DT[dtype], 1e-3, 0.9, 0.999, 1e-8, 2, device=0)
+    assert B.dadam_get_plan_info(h).streaming == 1
+    B.dadam_set_topology(h, 0, *WL.complete(rows))
+    B.dadam_bind(h, x, out, state[:rows], state[rows:2 * rows], state[2 * rows:])
+    stream = B.current_stream()
+    want = sum(t[inside].double() for t in x) / rows
+    # partial sums are at most 1: a rounding of 2^-25 for the weights together and for each term and part, and that of the result
+    bound = 2 * rows * 2.0 ** -25 + (want.abs() * 2.0 ** -8 if dtype == "bf16" else 0.0)
+    for call in (lambda: B.dadam_mix(h, 0, 0, stream), lambda: B.dadam_gossip_step(h, 0, g, 1, B.DADAM_FUSE_ACCUM, stream),
+                 lambda: B.dadam_gossip_step(h, 0, g, 1, 0, stream)):
+        for t in out:
+            t.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        for t in out:
+            assert bool(((t[inside].double() - want).abs() <= bound).all())
+            assert bool((t[~inside] == 7.0).all())
+    B.dadam_destroy(h)
 
 
 @pytest.mark.gpu
