@@ -153,14 +153,17 @@ def host_cpu():
     return model, n
 
 
-def kernel_name(info, tile_mode: bool, wl, path: str, shared: bool = False) -> str:
+def kernel_name(info, tile_mode: bool, wl, path: str, shared: bool = False, step_bytes: int = 0) -> str:
     """Name of the kernel shape a launch uses, as the profile summaries spell it (a direct kernel whose rows
-    share sources streams everything but the sources: "shared")."""
+    share sources streams everything but the sources: "shared").  step_bytes: what a step touches, by which
+    steps of up to three rows stream."""
     dt = {"f32": "TF32", "bf16": "TBF16"}
-    nt = "true" if info.streaming else "false"
-    if not tile_mode and shared and info.streaming:
+    mixes = path in ("mix", "mix_consensus")
+    streams = bool(info.streaming) or (not mixes and wl.n_rows <= 3 and step_bytes > 344 << 20)
+    nt = "true" if streams else "false"
+    if not tile_mode and shared and streams:
         nt = "shared"
-    if path in ("mix", "mix_consensus"):
+    if mixes:
         return f"k_tile<{dt[wl.param_dtype]},{dt[wl.grad_dtype]},{info.mix_waves},{info.mix_vectors},{nt}>" if tile_mode else \
                f"k_direct<{dt[wl.param_dtype]},{dt[wl.grad_dtype]},{nt}>"
     if tile_mode:
@@ -422,7 +425,10 @@ def measure(args, want_cpu_sample: bool):
 
     # counter-measured HBM bytes, only for the kernel shape that was profiled
     import numpy as np
-    kname = kernel_name(info, tile_mode, wl, args.path, shared=bool(np.bincount(csrs[0][1], minlength=C).max() > 1))
+    read = np.bincount(csrs[0][1], minlength=C)
+    psize, gsize = esize[pdt], esize[gdt]
+    step_bytes = d * ((int((read > 0).sum()) + (0 if inplace else R)) * psize + R * (gsize + (12 if wl.s > 1 else 8)))
+    kname = kernel_name(info, tile_mode, wl, args.path, bool(read.max() > 1), step_bytes)
     traffic, traffic_source = None, None
     table = measured_traffic().get((wl.name, kname))
     if table is not None and args.path == "fused" and all(p in table for p in phases):

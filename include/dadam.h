@@ -167,7 +167,10 @@ typedef struct {
   uint32_t tile_waves, tile_vectors; /* shape of the fused step's tile kernel: wavefronts per workgroup,
                                         16-byte vectors per lane and row                          */
   uint32_t mix_waves, mix_vectors;   /* the same for the mixing-only launch                       */
-  uint32_t streaming;       /* 1 if accesses carry the non-temporal hint (large working sets)   */
+  uint32_t streaming;       /* 1 if accesses carry the non-temporal hint (large working sets).  Where this is
+                               0, steps of up to three rows (not mixing or accumulation) carry it all the same
+                               if the sources that the slot's rows list, outputs that are not updated in place,
+                               gradients and state add up to more than 344 MB (2^20) */
 } dadam_plan_info;
 
 /* Create a handle.  Validates the configuration, builds the segment table from the tensor list

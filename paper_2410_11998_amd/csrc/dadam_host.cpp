@@ -29,6 +29,7 @@ struct Slot {
   std::vector<int32_t> row_ptr, col;
   std::vector<float> w;
   int32_t max_degree = 0;             // longest row
+  uint32_t n_read = 0;                // sources that some row lists
   std::vector<int32_t> order;         // rows ordered so that neighbours share sources (empty: nothing is shared)
   bool reuse = false;                 // some source is read by two or more rows
   // Loops: rows that list the same sources with the same weights.  Filled only where the loop kernel may take the
@@ -93,8 +94,7 @@ struct dadam_handle {
   TileShape mix_shape{4, 1, false};  // shape of the mixing-only launch (more bytes in flight per wavefront)
   uint32_t mix_tile_elems = 0, mix_lds_bytes = 0;
   uint64_t n_work_m = 0;
-  bool nontemporal = false;      // steps and accumulation stream
-  bool mix_nontemporal = false;  // mixing streams
+  bool nontemporal = false;  // every launch streams (steps of few rows may all the same, see few_rows_stream)
   bool decays = false;  // some tensor carries weight decay
   // Segments of fewer than 65536 elements on average: lanes are hardly ever spread and most tiles need their segment searched, so
   // streaming launches keep the shapes and orders of contiguous lanes.  (By the share of elements in whole blocks, which takes a long tensor
@@ -104,6 +104,7 @@ struct dadam_handle {
   int vec = 4;
   uint32_t tile_elems = 0, direct_elems = 0, lds_bytes = 0;
   bool tile_possible = false;
+  uint64_t n_elems = 0;  // elements of the tensors
   uint64_t n_work_t = 0, n_work_d = 0, n_work_v = 0;
   Slot slots[DADAM_MAX_SLOTS];
   bool bound = false;
@@ -187,6 +188,7 @@ void find_segments(dadam_handle* h) {
     }
     h->tensor_seg[k] = (uint32_t)(h->segs.size() - 1);
   }
+  for (const Segment& s : h->segs) h->n_elems += s.hi - s.lo;
   h->short_segments = h->segs.size() * (uint64_t)kLongSegment > h->cfg.d;
 }
 
@@ -455,6 +457,25 @@ int choose_mode(const dadam_handle* h, const Slot& slot, uint32_t flags, bool de
   return DADAM_OK;
 }
 
+// Do steps of up to three rows stream in a handle whose other launches do not (see dadam_init)?  From 344 MB (2^20) of buffers that an
+// iteration touches: the sources that rows list, outputs that are not updated in place, gradients and state.  One row with two receive
+// buffers, updated in place, has 28 bytes an element in float32 and is past the last-level cache (256 MB) from 1.29e7 elements on, where
+// ordinary accesses with lanes side by side lose.  Four steps, time of streaming accesses over ordinary ones, by MB:
+//   one row of 2 sources 320 1.03, 332 0.98, 343 0.95, 366 0.90; of 3 320 1.04, 334 1.01, 344 0.97, 360 0.94, 401 0.87 (bfloat16 324 1.00, 334 0.97, 343
+//   0.96, 362 0.90; s = 1 320 1.02, 343 0.97, 366 0.91); of 5 326 1.05, 343 1.00, 360 0.93, 412 0.87; of 3 in 64 buffers 133 1.03, 339 0.88
+//   two rows 320 1.00, 343 0.97, 366 0.93, 412 0.86 (bfloat16 326 0.97, 343 0.92, 378 0.88); three 326 0.97, 343 0.94, 412 0.84 (335 0.94, 360 0.90)
+// With an accumulation behind every step, at 343 MB, steps alone / both streaming: 0.96 / 1.00, two rows 0.97 / 1.00, three 0.94 / 0.99, and so up to the
+// handle's line, so accumulation keeps to that; mixing was not measured and does too.  (Steps of more rows would gain between 15 and 22 million elements
+// as well, but pairs in bfloat16 and loops lose there; they were not measured by bytes, nor were short segments without a map.)
+bool few_rows_stream(const dadam_handle* h, uint32_t sources) {
+  const uint32_t R = h->cfg.n_rows;
+  if (R > 3 || h->short_segments) return false;
+  uint32_t outputs = 0;
+  for (uint32_t i = 0; i < R; ++i) outputs += h->inplace_cols[i].empty() ? 1 : 0;
+  const uint64_t row = dtype_bytes(h->cfg.grad_dtype) + (h->cfg.accum_s > 1 ? 12u : 8u);
+  return h->n_elems * ((sources + outputs) * dtype_bytes(h->cfg.param_dtype) + R * row) > kStreamedBytes;
+}
+
 uint32_t loop_lds_bytes(const dadam_handle* h, int waves) { return (uint32_t)(waves * kWave * h->vec * 4); }
 
 // Tiles of one vector a lane of a launch over the whole layout.
@@ -624,7 +645,7 @@ bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, u
   const uint32_t C = h->cfg.n_cols;
   if (h->short_segments && (usual || mix_only)) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
-  if (lone_tile(h)) return (mix_only ? h->mix_shape : h->shape).waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
+  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
   return mix_only && C < 32;
 }
 
@@ -635,8 +656,8 @@ bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, u
 // 9: 0.780; bfloat16 (10 KB) 32: 0.744, 14: 0.770, 11: 0.787, 9: 0.805; s = 1 0.767 -> 0.809.  Short launches need
 // every wavefront (12000 pieces: 0.725 -> 0.670; 25000 in buckets 0.743 -> 0.713; 117000: 0.755 -> 0.779), and so do
 // the passes that load little (mixing 0.828 -> 0.625, accumulation).  Only one row was measured.
-uint32_t bounded_occupancy_lds(const dadam_handle* h, const Slot& slot, Phase phase, uint32_t n_pieces) {
-  if (h->cfg.n_rows != 1 || phase == kMixOnly || !h->nontemporal || n_pieces < kBoundedPieces) return 0;
+uint32_t bounded_occupancy_lds(const dadam_handle* h, const Slot& slot, Phase phase, bool streams, uint32_t n_pieces) {
+  if (h->cfg.n_rows != 1 || phase == kMixOnly || !streams || n_pieces < kBoundedPieces) return 0;
   if (h->lds_limit < kLdsPerUnit) return 0;  // the configuration keeps LDS for other kernels
   const uint32_t state = kWave * 4 * (uint32_t)h->vec;
   const uint32_t loads = 16 * kWave * (uint32_t)std::min(slot.max_degree, 8) + kWave * (uint32_t)h->vec * (uint32_t)dtype_bytes(h->cfg.grad_dtype) +
@@ -741,25 +762,26 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   const bool by_loops = loop_waves > 0;
   const bool few_tiles = !by_loops && tile_mode && !consensus_out && !(flags & DADAM_FORCE_TILE) && h->cfg.n_rows > 8 &&
                          n_tiles <= few_tiles_limit(h, slot) && direct_is_legal(h, slot, decays);
-  const bool streams = mix_only ? h->mix_nontemporal : h->nontemporal;
-  if (streams && !by_loops && !few_tiles && !consensus_out &&
+  if (h->nontemporal && !by_loops && !few_tiles && !consensus_out &&
       !(flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) && slot.reuse && h->n_xcds > 1 && h->tile_possible && direct_is_legal(h, slot, decays))
     tile_mode = staging_is_faster(h, slot, mix_only, n_tiles, tile_mode);
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
+  const bool streams = h->nontemporal || (!mix_only && few_rows_stream(h, slot.n_read));
   const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mix_only ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
-  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(streams && h->short_segments)) set_die_run(kDieRunPieces, &a);
+  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
   if (h->mapped && !decays) a.weight_decay = 0.f;
   if (tile_mode && cut_by_elements(h, mix_only, by_loops)) a.d = 0;
   a.partials = partials;
-  if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, (w1 - w0) * kDirectItem);
+  if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, streams, (w1 - w0) * kDirectItem);
   fill_scalars(h, mix_only ? 1 : t, &a.s);
   TileShape shape = mix_only ? h->mix_shape : h->shape;
+  shape.nontemporal = streams;
   uint32_t lds = mix_only ? h->mix_lds_bytes : h->lds_bytes;
   if (by_loops) {
     a.loops = slot.d_loops;
@@ -770,10 +792,10 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.row_order = slot.d_loop_rows;
     shape.ut = 1;
     shape.waves = loop_waves;
-    if (streams) a.xcd_block = kDieBlockLoops;
+    if (h->nontemporal) a.xcd_block = kDieBlockLoops;
     lds = loop_lds_bytes(h, shape.waves);
   } else if (tile_mode) {
-    if (mix_only && streams && shape.ut == 2) a.xcd_block = kDieBlockMix;
+    if (mix_only && h->nontemporal && shape.ut == 2) a.xcd_block = kDieBlockMix;
     a.row_ptr = slot.d_row_ptr;
     a.col = slot.d_col;
     a.w = slot.d_w;
@@ -981,48 +1003,38 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   h->n_xcds = (uint32_t)env_int("DADAM_XCDS", (int)h->n_xcds);
   if (h->n_xcds > 64) { delete h; return fail(nullptr, DADAM_EINVAL, "n_xcds out of range"); }
 
-  h->vec = vec_elems((int)cfg->param_dtype);
-  find_segments(h);
-  h->mapped = env_int("DADAM_MAP", 1) && can_map(h, &h->map_decay);
-  if (h->mapped) h->short_segments = false;
-
-  // Non-temporal accesses pay off when an iteration's working set cannot stay in the last-level cache (256 MB) anyway; small problems
-  // keep ordinary accesses so that one iteration finds the previous one's output on chip.  The line is at 22 million elements of all rows; steps
-  // and accumulation of up to three rows stream from 336 MB of sources, outputs, gradients and state on.  Time of ordinary accesses over
-  // streaming ones, one row with three sources, one handle / three in turn: float32 1.1e7 elements 0.94 / 1.01, 1.5e7 1.17 / 1.14, 2e7
-  // 1.20 / 1.18 (four steps 550 -> 461 us, with accumulation apart 640 -> 546), bfloat16 0.96 / 0.98, 0.97 / 1.02, 1.13 / 1.11.  (Steps of more rows would gain
-  // as much between 15 and 22 million elements, but pairs in bfloat16 and loops lose, and the kernels of 2e7 elements are held by
-  // tests.  Mixing of 2e7 elements: pairs of 32 rows 0.79 / 0.82.  Short segments without a map were not measured.)
-  const double px = (double)dtype_bytes(cfg->param_dtype), state = dtype_bytes(cfg->grad_dtype) + (cfg->accum_s > 1 ? 12.0 : 8.0);
-  const double touched = (double)cfg->d * ((cfg->n_cols + cfg->n_rows) * px + cfg->n_rows * state);
-  h->nontemporal = h->mix_nontemporal = env_int("DADAM_NT", (double)cfg->d * cfg->n_rows * 24.0 > 512.0 * 1024 * 1024 ? 1 : 0) != 0;
-  if (cfg->n_rows < 4 && !h->short_segments && touched > 336.0 * 1024 * 1024) h->nontemporal = true;
-
   // tile geometry: 16 bytes per lane and vector, `ut` vectors per lane, all source buffers' slices
   // of one tile resident in LDS.  One vector per lane (many small workgroups) and eight wavefronts per group, four when there
   // are fewer than eight rows to deal out; larger launches below.
+  h->vec = vec_elems((int)cfg->param_dtype);
+  TileShape shape;
+  shape.ut = 1;
+  shape.waves = cfg->n_rows >= 8 ? 8 : 4;
+  // Non-temporal accesses pay off when an iteration's working set cannot stay in the last-level
+  // cache anyway; small problems keep ordinary accesses so that one iteration finds the previous
+  // one's output on chip (steps of up to three rows go by what they touch, see few_rows_stream).
+  const double touched = (double)cfg->d * cfg->n_rows * 24.0;
+  h->nontemporal = env_int("DADAM_NT", touched > 512.0 * 1024 * 1024 ? 1 : 0) != 0;
+  shape.nontemporal = h->nontemporal;
+  shape.ut = env_int("DADAM_TILE_UT", shape.ut);
+  shape.waves = env_int("DADAM_TILE_WAVES", shape.waves);
   // Streaming float32 steps: two vectors a lane, which lie the way the memory serves best (see lane_start), up to the
   // sources whose tile fits; sixteen wavefronts from 16 rows on.  Fraction of 8 TB/s, one vector by eight wavefronts / two by
   // eight / two by sixteen, 3e8 to 2e9 elements: 16 rows 0.710 / 0.802 / 0.814, 24 rows 0.801 / 0.802 / 0.809, 48 rows 0.783 / 0.806 /
   // 0.805, 72 rows 0.72 / 0.725 / 0.779; 8 rows 0.817 / 0.825 / 0.802, 4 rows by four wavefronts 0.816 / 0.820, by sixteen 0.794.
   // In bfloat16 one vector has that layout already, and sixteen wavefronts lose (8 rows 0.813 / 0.783, 16 rows 0.780 / 0.770).
-  auto tile_shape = [&](bool streams) {
-    TileShape shape;
-    shape.ut = env_int("DADAM_TILE_UT", 1);
-    shape.waves = env_int("DADAM_TILE_WAVES", cfg->n_rows >= 8 ? 8 : 4);
-    shape.nontemporal = streams;
-    if (env_int("DADAM_TILE_UT", 0) == 0 && streams && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
-      shape.ut = 2;
-      if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
-    } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
-      // A compute unit holds one workgroup of the tile: sixteen wavefronts keep more of it busy.  us, eight / sixteen: steps of 96
-      // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
-      // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
-      shape.waves = env_int("DADAM_TILE_WAVES", 16);
-    }
-    return shape;
-  };
-  const TileShape shape = tile_shape(h->nontemporal);
+  find_segments(h);
+  h->mapped = env_int("DADAM_MAP", 1) && can_map(h, &h->map_decay);
+  if (h->mapped) h->short_segments = false;
+  if (env_int("DADAM_TILE_UT", 0) == 0 && h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_cols * 2u * kWave * 16u <= h->lds_limit) {
+    shape.ut = 2;
+    if (cfg->n_rows >= 16) shape.waves = env_int("DADAM_TILE_WAVES", 16);
+  } else if (cfg->n_cols > (uint32_t)kInlineRows && lone_tile(h) && cfg->n_rows >= 16) {
+    // A compute unit holds one workgroup of the tile: sixteen wavefronts keep more of it busy.  us, eight / sixteen: steps of 96
+    // rows with 16 sources each, 3e8 elements 9850 / 6860, 1e7 elements 430 / 295; 128 rows of 12 in bfloat16, 3e7 elements 910 / 690; mixing of
+    // 96 rows with 7 sources, 3e8 elements 1730 / 1190, with the error 1e8 elements 650 / 460.
+    shape.waves = env_int("DADAM_TILE_WAVES", 16);
+  }
   if (!tile_shape_supported(shape)) {
     delete h;
     return fail(nullptr, DADAM_EINVAL, "unsupported tile shape (waves %d, ut %d)", shape.waves, shape.ut);
@@ -1039,19 +1051,18 @@ int dadam_init(const dadam_config* cfg, dadam_handle** out) {
   // step's one-vector tile, so larger source counts keep the step's shape.  Streaming float32 passes spread the lanes and take eight
   // wavefronts up to 32 sources, then the step's sixteen (four / eight / sixteen: 12 sources 0.815 / 0.814, 16 sources 0.810 / 0.819, with
   // the error 0.750 / 0.778, 24 sources 0.797 / 0.812 / 0.809, with the error 0.73 / 0.80 / 0.74, 48 sources 0.63 / 0.745 / 0.780).
-  const TileShape mix_base = tile_shape(h->mix_nontemporal);
-  h->mix_shape = mix_base;
+  h->mix_shape = shape;
   if (cfg->n_cols * 2u * kWave * 16u <= 32768u && h->lds_limit >= 32768u && env_int("DADAM_TILE_UT", 0) == 0 &&
       env_int("DADAM_TILE_WAVES", 0) == 0) {
     h->mix_shape.ut = 2;
     h->mix_shape.waves = 4;
   }
-  if (h->mix_nontemporal && !h->short_segments && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2)
+  if (h->nontemporal && !h->short_segments && h->vec == 4 && cfg->n_rows >= 8 && cfg->n_cols <= 32 && h->mix_shape.ut == 2)
     h->mix_shape.waves = 8;
   h->mix_shape.ut = env_int("DADAM_MIX_UT", h->mix_shape.ut);
   h->mix_shape.waves = env_int("DADAM_MIX_WAVES", h->mix_shape.waves);
   if (!tile_shape_supported(h->mix_shape) || cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u > h->lds_limit)
-    h->mix_shape = mix_base;
+    h->mix_shape = shape;
   h->mix_tile_elems = (uint32_t)(kWave * h->vec * h->mix_shape.ut);
   h->mix_lds_bytes = cfg->n_cols * (uint32_t)h->mix_shape.ut * kWave * 16u;
   int rc = plan(h);
@@ -1139,6 +1150,7 @@ int dadam_set_topology(dadam_handle* h, uint32_t slot_id, const int32_t* row_ptr
   fresh.w.assign(w, w + nnz);
   fresh.reuse = reuse;
   fresh.sole_reader = sole;
+  for (uint32_t c = 0; c < C; ++c) fresh.n_read += sole[c] != -1 ? 1 : 0;
   for (uint32_t i = 0; i < R; ++i) fresh.max_degree = std::max(fresh.max_degree, row_ptr[i + 1] - row_ptr[i]);
   if (reuse) fresh.order = sharing_order(R, C, row_ptr, col_idx);
   std::vector<int32_t> loop_col, loop_rows;
@@ -1357,7 +1369,7 @@ int dadam_get_plan_info(const dadam_handle* h, dadam_plan_info* out) {
   out->tile_vectors = (uint32_t)h->shape.ut;
   out->mix_waves = (uint32_t)h->mix_shape.waves;
   out->mix_vectors = (uint32_t)h->mix_shape.ut;
-  out->streaming = h->mix_nontemporal ? 1u : 0u;
+  out->streaming = h->nontemporal ? 1u : 0u;
   return DADAM_OK;
 }
 

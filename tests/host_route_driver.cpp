@@ -19,6 +19,7 @@ static std::vector<std::function<void()>> recorded;
 static const char* fail_launch = nullptr;  // name of the launcher whose next call fails
 static std::string route, how;  // how: the shape of the tile's workgroup, the order of a row launch
 static uint32_t shares = 0;  // workgroups that share the rows of a loop's tile
+static bool streams = false; // accesses carry the non-temporal hint
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -48,18 +49,21 @@ int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint3
         std::to_string(a.xcd_block) + (a.d == 0 ? " cut by elements" : "");
   route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
   shares = a.n_loops > 0 ? a.loop_shares : 0;
+  streams = shape.nontemporal;
   if (shares > 1 && shape.nontemporal && phase == kMixOnly) return (int)hipErrorInvalidDeviceFunction;  // there is no such kernel
   double* p = a.partials;
   return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
 }
-int launch_direct(int, int, Phase, bool, bool, bool whole_items, const StepArgs& a, uint32_t, void*) {
+int launch_direct(int, int, Phase, bool nontemporal, bool, bool whole_items, const StepArgs& a, uint32_t, void*) {
+  streams = nontemporal;
   how = std::string(a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : a.order == kOrderDieGroups ? "groups" : "linear") +
         (whole_items ? ", whole items" : "") + (a.d == 0 ? " cut by elements" : "");
   route = a.order == kOrderDieBlocks ? "direct-blocks" : a.order == kOrderDieGroups ? "direct-groups" : "direct";
   if (whole_items) route += " whole";
   return enqueue("direct", [] {});
 }
-int launch_accumulate(int, Phase, bool, bool whole_items, const StepArgs& a, uint32_t, void*, int) {
+int launch_accumulate(int, Phase, bool nontemporal, bool whole_items, const StepArgs& a, uint32_t, void*, int) {
+  streams = nontemporal;
   how = (a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : std::string("linear")) + (whole_items ? ", whole items" : "");
   route = whole_items ? "whole" : "pieces";
   return enqueue("accumulate", [] {});
@@ -290,6 +294,46 @@ static void sparse_loops() {
     }
 }
 
+// Steps of few rows on both sides of 344 MB of what they touch.
+static void few_rows() {
+  struct { const char* name; uint32_t rows, cols, read, dtype, bytes; bool in_place; uint64_t outside; } cases[] = {
+      {"share of 3", 1, 3, 3, DADAM_F32, 28, true, 0},          // sources (the first is the output), gradient, two moments, accumulator
+      {"share of 3, apart", 1, 3, 3, DADAM_F32, 32, false, 0},
+      {"share of 3, one neighbour", 1, 3, 2, DADAM_F32, 24, true, 0},
+      {"share of 64, 3 read", 1, 64, 3, DADAM_F32, 28, true, 0},
+      {"share of 3, bf16", 1, 3, 3, DADAM_BF16, 20, true, 0},
+      {"2 rows", 2, 2, 2, DADAM_F32, 48, false, 0},
+      {"2 rows in place", 2, 2, 2, DADAM_F32, 40, true, 0},
+      {"3 rows, bf16", 3, 3, 3, DADAM_BF16, 54, false, 0},
+      {"share of 3, a part of d", 1, 3, 3, DADAM_F32, 28, true, 3000000},
+      {"4 rows", 4, 4, 3, DADAM_F32, 92, false, 0}};
+  for (const auto& c : cases) {
+    std::string answers;
+    for (uint64_t more : {0, 1}) {
+      const uint64_t n = (344ull << 20) / c.bytes + more;
+      Rows r;
+      for (uint32_t i = 0; i < c.rows; ++i) {
+        std::vector<int32_t> cols;
+        for (uint32_t k = 0; k < c.read; ++k) cols.push_back((int32_t)((i + k) % c.cols));
+        add_row(r, cols);
+      }
+      Sim s(c.rows, c.cols, {{0, n, 0.f, 0}, {n + c.outside, 0, 0.f, 0}}, r, c.dtype);
+      if (c.in_place)
+        for (uint32_t i = 0; i < c.rows; ++i) s.xd[i] = const_cast<void*>(s.xs[i]);
+      s.bind();
+      auto told = [&answers](const std::string& route) { answers += route.substr(0, 5) == "error" ? " error" : streams ? " yes" : " no"; };
+      told(s.step(DADAM_FUSE_ACCUM));
+      told(s.step(0, 0, 1));
+      told(s.mix(0));
+      told(dadam_accumulate(s.h, s.g.data(), 1, nullptr) == DADAM_OK ? "" : "error");
+      dadam_plan_info info;
+      dadam_get_plan_info(s.h, &info);
+      answers += " plan " + std::to_string(info.streaming) + (more ? "" : ",");
+    }
+    say(c.name, answers.substr(1));
+  }
+}
+
 // How many tiles a launch of rows that share sources may have and still go row by row.
 static void few() {
   for (uint32_t dtype : {DADAM_F32, DADAM_BF16})
@@ -382,6 +426,7 @@ int main(int argc, char** argv) {
   else if (what == "consensus") consensus();
   else if (what == "loops") loops();
   else if (what == "sparse_loops") sparse_loops();
+  else if (what == "few_rows") few_rows();
   else if (what == "few") few();
   else if (what == "die_order") die_order();
   else if (what == "accumulation") accumulation();

@@ -1,5 +1,5 @@
-"""Steps and accumulation of up to three rows around the size from which they stream (336 MB of sources, outputs, gradients and state), bit
-for bit against handles over parts of the same elements, which are too small to."""
+"""Steps of up to three rows around the size from which they stream (344 MB of what they touch): which launches do, without a GPU, and
+on the GPU bit for bit against handles over parts of the same elements, which are too small to."""
 
 import pytest
 import torch
@@ -7,7 +7,34 @@ import torch
 from paper_2410_11998_amd import binding as B
 from paper_2410_11998_amd import workloads as WL
 
+from test_host_abi import _route_answers
+
 import harness as H
+
+
+def test_steps_of_few_rows_stream_by_what_they_touch(tmp_path):
+    """Just below and just above: fused step, update of a range, mixing, accumulation, and what the plan says of the handle.  Sources that no
+    row lists, outputs that are sources and elements outside the tensors do not count; the library's answer at 2^20 * 344 bytes exactly."""
+    got = _route_answers(tmp_path, "few_rows")
+    below, above = "no no no no plan 0", "yes yes no no plan 0"
+    assert got.pop("4 rows") == f"{below}, {below}"
+    assert len(got) == 9 and set(got.values()) == {f"{below}, {above}"}, got
+
+
+def test_bench_names_the_kernel_of_steps_that_stream_by_what_they_touch():
+    import importlib.util
+    import os
+    spec = importlib.util.spec_from_file_location("bench_module", os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    wl = WL.workload(3)
+    for d, streaming, fused in ((12_000_000, 0, "false"), (15_000_000, 0, "true"), (23_000_000, 1, "true")):
+        h = B.dadam_init(1, 3, d, [0], [d], B.DADAM_F32, B.DADAM_F32, accum_s=2, device=B.DADAM_DEVICE_NONE)
+        info = B.dadam_get_plan_info(h)
+        B.dadam_destroy(h)
+        assert info.streaming == streaming
+        assert bench.kernel_name(info, False, wl, "fused", step_bytes=28 * d) == f"k_direct<TF32,TF32,{fused}>"
+        assert bench.kernel_name(info, False, wl, "mix", step_bytes=28 * d) == f"k_direct<TF32,TF32,{'true' if streaming else 'false'}>"
 
 
 @pytest.mark.gpu
@@ -18,7 +45,8 @@ def test_steps_around_the_line(rows, params, grads, side):
     dev = torch.device("cuda:0")
     cols = 3 if rows == 1 else rows
     size = {"f32": 4, "bf16": 2}
-    d = (336 << 20) // ((cols + rows) * size[params] + rows * (size[grads] + 12)) + side
+    outputs = 0 if rows == 1 else rows                     # the one row is updated in place
+    d = (344 << 20) // ((cols + outputs) * size[params] + rows * (size[grads] + 12)) + side
     hp = H.HyperF32(s=2)
     csr = WL.node_share_ring() if rows == 1 else WL.ring(rows)
     gen = torch.Generator(device=dev)
