@@ -768,7 +768,9 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (few_tiles) tile_mode = false;
   if (by_loops) tile_mode = true;
   const bool streams = h->nontemporal || (!mix_only && few_rows_stream(h, slot.n_read));
-  const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mix_only ? kGridMix : kGridTile;
+  // streaming float32 steps take two vectors a lane (see dadam_init): in a handle whose other launches do not stream, the mixing tile has them
+  const bool mixing_tile = mix_only || (streams && !h->nontemporal && h->vec == 4 && h->mix_shape.ut == 2);
+  const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mixing_tile ? kGridMix : kGridTile;
   work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
@@ -780,9 +782,9 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, streams, (w1 - w0) * kDirectItem);
   fill_scalars(h, mix_only ? 1 : t, &a.s);
-  TileShape shape = mix_only ? h->mix_shape : h->shape;
+  TileShape shape = mixing_tile ? h->mix_shape : h->shape;
   shape.nontemporal = streams;
-  uint32_t lds = mix_only ? h->mix_lds_bytes : h->lds_bytes;
+  uint32_t lds = mixing_tile ? h->mix_lds_bytes : h->lds_bytes;
   if (by_loops) {
     a.loops = slot.d_loops;
     a.n_loops = (uint32_t)slot.loops.size();
