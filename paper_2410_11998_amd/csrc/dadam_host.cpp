@@ -523,31 +523,34 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
 // overwrites a source that the other workgroups may still read, so there it is one; and one in streaming mixing, which has no kernel of
 // shares (whether a handle streams follows from d, its tiles from what the tensors cover of it, so a streaming launch may well be small).
 // Launches that leave compute units idle: as many as keep it at one workgroup a unit (sixteen wavefronts then walk 6 rows of 96 in turn
-// otherwise).  us of four steps, one / two / four / eight workgroups: 32 rows of 4e5 elements in all 28.2 / 23.5, 64 rows 42.9 / 32.6 / 27.4, 96 rows
-// 65 / 45 / 38 / 32, 1.5e6 elements 73 / 51 / 46 / 57 (62 tiles), 5e6 119 / 130 (204 tiles); bfloat16 96 rows 98 / 64 / 52 / 40, 5e6 125 / 98 / 130
-// (102 tiles); 96 rows in loops of 48, 24, 24, 4e5 elements 45 / 37 / 31, 1.5e6 50 / 59 (186 tiles of a loop); mixing of 96 rows, 1.5e6
-// 17.0 / 15.1 / 14.6 / 17.1, bfloat16 19.6 / 17.2 / 16.3 / 15.3.
-// Streaming steps of one loop of 96 rows and more, of fewer than 4096 tiles: two where the last round of workgroups, which are few and long (12 rows
-// to a wavefront), would be short of them.  Float32: from a round of three to a unit on.  Bfloat16, two to a unit by registers: where at most
-// half of the last round is there.  Time of one over that of two, s = 1 / 4: float32 96 rows of 976, 1831, 2441, 3255, 4069, 6100 tiles 1.08 /
-// 1.05, 1.08 / 1.03, 1.11 / 1.07, 1.07 / 1.04, 1.09 / 1.06, 1.01 / 1.00, 128 rows of 732, 916, 1373, 1831, 4578 0.96 / 0.97, 1.06 / 1.01, 1.16 / 1.08, 1.14 /
-// 1.05, 0.99 / 0.98; bfloat16 96 rows of 488, 610, 916, 1221, 1628, 2035 0.90 / 0.91, 1.10 / 1.08, 0.94 / 0.93, 1.05 / 1.03, 1.03 / 1.08, 1.00 / 1.01, 128
-// rows of 458, 687, 916, 1221, 2289, 3815 0.88 / 0.90, 1.01 / 0.99, 0.96 / 0.96, 1.12 / 1.10, 1.00 / 1.01, 1.05 / 1.05.  Fewer rows gain nothing
-// sure (float32 32 rows 0.93 to 1.06, 64 rows 0.93 to 1.05, bfloat16 70 rows 0.91 to 1.12); loops of 48, 24, 24 lose, and so does mixing, half of whose bytes
-// are sources (0.93), and most of what does not stream.
-uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_t n_tiles, bool mix_only, bool streams) {
-  if (mix_only && streams) return 1;
+// otherwise).  us of two steps from a graph, one / two / four / as many as this gives, 16 tiles: 32 rows 16.4 / 13.0 / 13.1 / 13.0, 64 rows 25.4 / 19.0 / 15.5 /
+// 15.4, 96 rows 39.3 / 27.5 / 22.3 / 18.6 (bfloat16 58.8 / 38.0 / 31.2 / 25.0), in loops of 48, 24, 24 24.1 / 19.8 / 16.1 / 16.0; 128 tiles, two or none fit: 32 rows
+// 18.3 / 15.4, 96 rows 60 / 45 (82 / 62), loops 49.2 / 54.6.  17 rows, one of them in the second workgroup, 0.86 to 0.95 of the time of one.
+// Mixing, half of whose bytes are sources, gains from 32 rows on, and only where the tiles divide among the dies: then the workgroups of a tile run on one
+// and find the sources in its L2.  Time of two over that of one, 32 / 64 / 96 rows: 24 tiles 0.96 / 0.95 / 0.89, 64 tiles 0.98 / 0.97 (56 rows), but 4 tiles 1.16 / 1.17 (56
+// rows), 31 tiles 1.07 / 1.10 / 1.15, 42 tiles 1.10 / 1.10 / 1.19, 85 tiles 1.11 / 1.13 / 1.19; 17 to 20 rows of 24 to 128 tiles 0.98 to 1.02.
+// Streaming steps of one loop of 96 rows and more, whose workgroups are few and long (12 rows to a wavefront): two where the last round of workgroups
+// would be short of them, at most a quarter of one (three to a compute unit in float32, two in bfloat16, by registers).  In the first two rounds a tile
+// that the layout's end cuts, which takes longer than others, counts too (see begin_with_last): there up to half a round.  Time of two over that of one, whole tiles /
+// one cut, 96 to 160 rows: float32 769 to 960 tiles 0.92 to 1.00 / 0.85 to 0.93, 1024 to 1100 1.00 / 0.92 to 0.95, 1200 to 1536 0.99 to 1.07 / 1.00 to 1.04, 1540 to 1728 0.96 to
+// 1.00 / 0.97 to 1.01, 1900 1.00 / 0.98, 2048 and more 0.99 to 1.10 / 0.99 to 1.03; bfloat16 513 to 640 0.92 to 0.95 / 0.76 to 0.83, 700 to 768 1.01 to 1.07 / 0.85 to 0.95, 800 to 1000
+// 1.03 to 1.07 / 0.96 to 1.04, 1025 to 1152 0.94 to 0.99 / 0.94 to 0.99, 1200 to 1400 1.00 to 1.04 / 0.98 to 1.04, 1537 to 1664 0.97 to 1.01 / 0.97 to 1.01, 1700 and more 0.98 to 1.05.
+// s = 1, decay, accumulation apart and mixed types the same or more (0.86 to 0.98 at 560, 860, 1100 tiles).  Fewer rows gain nothing sure (float32 32 rows
+// 0.93 to 1.06, 64 rows 0.93 to 1.05, bfloat16 70 rows 0.91 to 1.12); loops of 48, 24, 24 lose, and so does most of what does not stream.
+// With a map 96 and 128 rows of float32 by two over one 0.88 to 0.97 at 800 to 1100 tiles, 0.96 at 1300, as where a tile is cut, bfloat16 0.88 to 0.94 at 560, 0.96 to 1.02 at 640
+// to 768, 0.94 to 0.97 at 1100, as where none is.  cut: some tile of the launch is not whole, or it has a map in float32.
+uint32_t loop_shares(const dadam_handle* h, const Slot& slot, int waves, uint32_t n_tiles, bool cut, bool mix_only) {
+  if (mix_only && h->nontemporal) return 1;
   for (uint32_t i = 0; i < h->cfg.n_rows; ++i)
     if (!h->inplace_cols[i].empty()) return 1;
   uint32_t rows = 0;
   for (const Loop& l : slot.loops) rows = std::max(rows, (uint32_t)l.n_rows);
   const uint32_t most = (rows + (uint32_t)waves - 1) / (uint32_t)waves;
   const uint32_t units = n_tiles * (uint32_t)slot.loops.size();
-  if (2 * units <= kFewTiles) return std::min(most, kFewTiles / units);
-  if (!streams || slot.loops.size() > 1 || rows < 96 || n_tiles >= kLongLaunch) return 1;
-  if (h->vec == 4) return n_tiles > 3 * kFewTiles ? 2 : 1;
-  const uint32_t last = n_tiles % (2 * kFewTiles);
-  return n_tiles > 2 * kFewTiles && last > 0 && last <= kFewTiles ? 2 : 1;
+  if (2 * units <= kFewTiles) return mix_only && (rows < 32 || n_tiles % h->n_xcds != 0) ? 1 : std::min(most, kFewTiles / units);
+  if (!h->nontemporal || slot.loops.size() > 1 || rows < 96 || n_tiles >= kLongLaunch) return 1;
+  const uint32_t round = kFewTiles * (h->vec == 4 ? 3u : 2u), last = n_tiles % round;
+  return n_tiles > round && last > 0 && last <= (cut && n_tiles < 2 * round ? round / 2 : round / 4) ? 2 : 1;
 }
 
 // A launch of few tiles leaves compute units idle, and each workgroup walks its rows in turn: up to this many tiles and with
@@ -788,7 +791,8 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   if (by_loops) {
     a.loops = slot.d_loops;
     a.n_loops = (uint32_t)slot.loops.size();
-    a.loop_shares = loop_shares(h, slot, loop_waves, n_tiles, mix_only, streams);
+    const uint64_t T = vector_elems(h);
+    a.loop_shares = loop_shares(h, slot, loop_waves, n_tiles, a.n_seg > 1 || (h->mapped ? h->vec == 4 : lo % T != 0 || hi % T != 0), mix_only);
     a.col = slot.d_loop_col;
     a.w = slot.d_loop_w;
     a.row_order = slot.d_loop_rows;
@@ -809,7 +813,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.list_stride = (uint32_t)slot.max_degree;
     a.order_group = (h->cfg.n_rows + h->n_xcds - 1) / h->n_xcds;
   }
-  const uint64_t wavefronts = (uint64_t)(w1 - w0) * (tile_mode ? shape.waves * (by_loops ? slot.loops.size() : 1) : kDirectItem * (uint64_t)h->cfg.n_rows);
+  const uint64_t wavefronts = (uint64_t)(w1 - w0) * (tile_mode ? shape.waves * (by_loops ? slot.loops.size() * a.loop_shares : 1) : kDirectItem * (uint64_t)h->cfg.n_rows);
   a.wide_search = wavefronts <= kWideSearchWaves ? 1u : 0u;
   int e = tile_mode
               ? launch_tile((int)h->cfg.param_dtype, (int)h->cfg.grad_dtype, phase, shape, a, w1 - w0, lds, stream)

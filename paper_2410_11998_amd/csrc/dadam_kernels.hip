@@ -283,7 +283,7 @@ bool tile_shape_supported(TileShape s) {
   return (s.waves == 4 && s.ut == 2) || ((s.waves == 4 || s.waves == 8) && s.ut == 1);
 }
 
-// Loop kernel: one workgroup per tile and loop, in several launches where a grid would reach 2^32 threads.
+// Loop kernel: a.loop_shares workgroups per tile and loop, in several launches where a grid would reach 2^32 threads.
 static int launch_loops(int xdt, int gdt, Phase phase, TileShape shape, StepArgs a, uint32_t n_tiles, uint32_t lds_bytes,
                         void* stream) {
   KernelFn fn = nullptr;

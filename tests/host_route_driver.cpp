@@ -294,6 +294,38 @@ static void sparse_loops() {
     }
 }
 
+// How many workgroups take the rows of a loop's tile: fused step, update of the first tensor alone, mixing, and a step and mixing of rows updated in place.
+static void loop_shares() {
+  struct { const char* kind; int rows; uint64_t tiles; uint32_t dtype; bool cut; } cases[] = {
+      {"complete", 16, 128, DADAM_F32, true}, {"complete", 17, 128, DADAM_F32, true}, {"complete", 17, 129, DADAM_F32, true}, {"complete", 32, 24, DADAM_F32, true},
+      {"complete", 31, 24, DADAM_F32, true}, {"complete", 33, 85, DADAM_F32, true}, {"complete", 33, 86, DADAM_F32, true}, {"complete", 64, 64, DADAM_BF16, true},
+      {"complete", 64, 129, DADAM_F32, true}, {"complete", 96, 42, DADAM_F32, true}, {"complete", 96, 40, DADAM_BF16, true}, {"complete", 100, 36, DADAM_BF16, true},
+      {"halves", 96, 42, DADAM_F32, true}, {"halves", 96, 16, DADAM_F32, true}, {"halves", 96, 43, DADAM_F32, true},
+      {"complete", 32, 2900, DADAM_F32, true}, {"complete", 95, 1100, DADAM_F32, true}, {"halves", 128, 900, DADAM_F32, true},
+      {"complete", 128, 768, DADAM_F32, true}, {"complete", 128, 769, DADAM_F32, false}, {"complete", 128, 960, DADAM_F32, false}, {"complete", 128, 961, DADAM_F32, false},
+      {"complete", 128, 961, DADAM_F32, true}, {"complete", 128, 1152, DADAM_F32, true}, {"complete", 128, 1153, DADAM_F32, true}, {"complete", 96, 1536, DADAM_F32, true},
+      {"complete", 96, 1537, DADAM_F32, true}, {"complete", 96, 1728, DADAM_F32, true}, {"complete", 96, 1729, DADAM_F32, true}, {"complete", 96, 2305, DADAM_F32, true},
+      {"complete", 97, 512, DADAM_BF16, true}, {"complete", 97, 513, DADAM_BF16, false}, {"complete", 97, 640, DADAM_BF16, false}, {"complete", 97, 641, DADAM_BF16, false},
+      {"complete", 97, 768, DADAM_BF16, true}, {"complete", 97, 769, DADAM_BF16, true}, {"complete", 97, 1024, DADAM_BF16, true}, {"complete", 97, 1152, DADAM_BF16, true},
+      {"complete", 97, 1153, DADAM_BF16, true}, {"complete", 97, 1664, DADAM_BF16, false}, {"complete", 97, 2049, DADAM_BF16, false}};
+  for (const auto& c : cases) {
+    const uint64_t T = c.dtype == DADAM_BF16 ? 512 : 256, d = c.tiles * T - (c.cut ? 6 : 0), half = d / 2 / T * T;
+    const std::vector<dadam_tensor_desc> ts = {{0, half, 0.f, 0}, {half, d - half, 0.f, 0}};
+    std::string answers;
+    for (bool in_place : {false, true}) {
+      Sim s(c.rows, c.rows, ts, !strcmp(c.kind, "complete") ? complete(c.rows) : halves(c.rows), c.dtype);
+      if (in_place) s.xd[c.rows - 1] = const_cast<void*>(s.xs[c.rows - 1]);
+      s.bind();
+      if (in_place) answers += " |";
+      auto told = [&answers](const std::string& r) { answers += " " + (r.substr(0, 4) == "loop" ? std::to_string(shares) : r); };
+      told(s.step(DADAM_FUSE_ACCUM));
+      if (!in_place) told(s.step(0, 0, 1));
+      told(s.mix(0));
+    }
+    say((std::string(c.kind) + std::to_string(c.rows) + " " + std::to_string(c.tiles) + (c.dtype == DADAM_BF16 ? " bf16" : " f32") + (c.cut ? "" : " whole")).c_str(), answers.substr(1));
+  }
+}
+
 // Steps of few rows on both sides of 344 MB of what they touch.
 static void few_rows() {
   struct { const char* name; uint32_t rows, cols, read, dtype, bytes; bool in_place; uint64_t outside; } cases[] = {
@@ -427,6 +459,7 @@ int main(int argc, char** argv) {
   else if (what == "loops") loops();
   else if (what == "sparse_loops") sparse_loops();
   else if (what == "few_rows") few_rows();
+  else if (what == "loop_shares") loop_shares();
   else if (what == "few") few();
   else if (what == "die_order") die_order();
   else if (what == "accumulation") accumulation();
