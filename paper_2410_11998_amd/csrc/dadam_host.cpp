@@ -565,6 +565,13 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
   return slot.max_degree > 24 ? kFewTiles / 2 : slot.max_degree > 12 || h->vec == 8 ? kFewTiles * 3 / 4 : kFewTiles;
 }
 
+// From how many tiles on a launch is large for the rules below.  Launches that stream have that few tiles only with many rows (or by ranges), and one wavefront to
+// a piece and row in no order, as small launches go, serves spread lanes badly.  Time by the rules for large launches over that by those for small
+// ones, 640 to 1000 tiles of 44 to 160 rows: mixing in pairs and of three sources 0.59 to 0.88, of seven 0.45 to 0.72 (81 to 128 rows), steps of two 0.78 to 0.99, of three
+// 0.74 to 0.98, of seven 0.62 to 0.89, the others the same kernel; 560 tiles 0.68 to 1.02.  With a map, which has fewer tiles than its segments have, the
+// same: 128 rows of seven sources, tensors of 2000 elements, 1000 tiles, two steps 624 / 412 us (by segments 529), mixing 149 / 69 (88).
+bool many_tiles(const dadam_handle* h, uint32_t n_tiles) { return n_tiles >= (h->nontemporal ? kManyStreamed : kManyTiles); }
+
 // Direct launches of rows that share sources: does every row of a piece run on one die (die blocks), or does each die have a
 // group of the rows (die groups)?  Small launches, us, groups / blocks: 64 rows of two sources 244 tiles 87 / 83; 96 rows
 // of 7 sources 81 tiles 74 / 53, 325 tiles 215 / 186.  Large ones: mixing is far slower in blocks (0.75 to 0.9 of the rate).
@@ -579,7 +586,7 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
 //   128 rows   1.00  1.03   0.98  0.98         128 rows   0.95  1.04   1.02  1.01     (3e8: 1.08)
 //   160 rows   0.98  0.99   1.04  0.99         160 rows   0.88  0.99   0.98  0.98
 // That was with all rows of a piece one after the other.  Since large launches walk runs of 256 pieces a die row after row,
-// blocks are ahead of groups in every streaming launch of at least 1024 tiles: a die has the arrays of few rows in use at a time
+// blocks are ahead of groups in every streaming launch of at least 1024 tiles (640, see many_tiles): a die has the arrays of few rows in use at a time
 // instead of those of all, and rows that do not divide among the dies leave none waiting.  Fraction of 8 TB/s, groups / piece by piece / runs of 64 / 256 / 512, two rows to a source: 64 rows of 26 million elements
 // 0.83 / 0.78 / 0.83 / 0.84 / 0.84, 18 rows 0.67 / - / 0.81 / 0.80 / 0.81, 32 rows 0.82 / 0.82 / 0.83 / 0.83 / 0.84, 40 rows 0.79 / - / 0.79 / 0.82 /
 // 0.82, bfloat16 18 rows 0.67 / - / 0.78 / 0.80 / 0.80; rings of 48 in bfloat16 0.79 / - / 0.80 / 0.80 / 0.80, of 64 0.80 / 0.72 / 0.80 /
@@ -590,12 +597,11 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
 // groups / runs, float32 of 4e7, 1.2e8, 4e8 elements of all rows: 32 rows 372 / 366, 1104 / 1081, 3620 / 3586, 33 rows 415 / 370, 1240 / 1086, 4111 / 3583,
 // 36 rows 390 / 371, 1152 / 1084, 3849 / 3597, 48 rows 380 / 371, 1101 / 1082, 3642 / 3606, 63 rows 375 / 370, 1114 / 1078, 3666 / 3577, 72 rows 385 / 372,
 // 1115 / 1086, 3773 / 3605, 80 rows 381 / 371, 1103 / 1085, 3693 / 3596 (bfloat16 33 rows 341 / 305, 1004 / 884, 3336 / 2911, 48 rows 308 / 303, 912 / 881, 2978 /
-// 2947, 160 rows of 1.2e8, 4e8 931 / 882, 3043 / 2918).  Streaming launches of fewer tiles go piece by piece and would be faster by groups from 80
-// rows on (bfloat16, 4e7 elements: 96 rows 375 / 318, 128 rows 330 / 321).
+// 2947, 160 rows of 1.2e8, 4e8 931 / 882, 3043 / 2918).  Launches of fewer tiles go piece by piece.
 // Launches that do not stream, us, groups / runs, 1.1e7 and 1.6e7 elements: float32 32 rows 106 / 112, 170 / 163, 33 rows 120 / 107, 182 / 159, 40 rows 107 /
 // 107, 171 / 164, 48 rows 108 / 109, 168 / 155; bfloat16 of 1.6e7 32 rows 121 / 125, 40 rows 132 / 141, 48 rows 124 / 132, 56 rows 124 / 129, 33 rows 140 / 126.
 bool rows_stay_on_one_die(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles) {
-  if (n_tiles < kManyTiles) return true;
+  if (!many_tiles(h, n_tiles)) return true;
   const uint32_t R = h->cfg.n_rows;
   if (mix_only) return false;
   if (!h->nontemporal) {
@@ -644,7 +650,7 @@ bool accumulate_whole_items(const dadam_handle* h, uint64_t elems) {
 // 1577); mixing in pairs 24 rows 898 / 1673, 32 rows 910 / 1606, 48 rows 1088 / 1902, 64 rows 1068 / 1891 (bfloat16 545 / 1801, 514 / 1797, 655 / 2123, 717 / 2120), 96 and
 // 160 rows 1712 / 2405, 1791 / 2808 (1321 / 2578, 1555 / 2957), with three sources 504 / 791, 468 / 812 (398 / 881, 409 / 884).
 bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, uint32_t n_tiles, bool usual) {
-  if (n_tiles < kManyTiles) return usual;
+  if (!many_tiles(h, n_tiles)) return usual;
   const uint32_t C = h->cfg.n_cols;
   if (h->short_segments && (usual || mix_only)) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
@@ -778,7 +784,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   StepArgs a;
   fill_args(h, mix_only ? nullptr : grads, &a);
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
-  if (a.order == kOrderDieBlocks && n_tiles >= kManyTiles && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
+  if (a.order == kOrderDieBlocks && many_tiles(h, n_tiles) && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
   set_range(h, grid, w0, lo, hi, &a);
   if (h->mapped && !decays) a.weight_decay = 0.f;
   if (tile_mode && cut_by_elements(h, mix_only, by_loops)) a.d = 0;

@@ -142,7 +142,7 @@ constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks;
 constexpr uint32_t kDieBlockMix = 256, kDieBlockLoops = 2;  // streaming launches; measured, see k_tile, k_loop
 constexpr uint32_t kFewTiles = 256;      // compute units of the chip; measured, see few_tiles_limit, loop_kernel_waves
 constexpr uint32_t kLongLaunch = 2048;   // tiles; measured, see loop_shares
-constexpr uint32_t kManyTiles = 1024;    // measured, see rows_stay_on_one_die
+constexpr uint32_t kManyTiles = 1024, kManyStreamed = 640;  // measured, see rows_stay_on_one_die, many_tiles
 constexpr uint64_t kManyElems = 100000000;  // elements of all rows of a launch; measured, see there, whole_items, accumulate_whole_items
 constexpr uint64_t kPairElems = 13000000;   // the same, of launches that do not stream; measured, see rows_stay_on_one_die
 constexpr uint32_t kWideSearchWaves = 16384;  // up to two rounds of wavefronts on the chip; see locate
