@@ -255,10 +255,11 @@ int plan(dadam_handle* h) {
 
 // Work-item range [w0, w1) of the tiles that intersect elements [lo, hi), which start in segment
 // s0 and end in segment s1.
-void work_range(const dadam_handle* h, Grid grid, uint32_t s0, uint32_t s1, uint64_t lo,
+// by_map: over the dense grid of a layout with a map.
+void work_range(const dadam_handle* h, bool by_map, Grid grid, uint32_t s0, uint32_t s1, uint64_t lo,
                 uint64_t hi, uint32_t* w0, uint32_t* w1) {
   const uint64_t T = grid == kGridTile ? h->tile_elems : grid == kGridDirect ? h->direct_elems : grid == kGridMix ? h->mix_tile_elems : vector_elems(h);
-  if (h->mapped) {
+  if (by_map) {
     *w0 = (uint32_t)(lo / T);
     *w1 = (uint32_t)((hi - 1) / T) + 1;
     return;
@@ -322,7 +323,7 @@ int check_grads(dadam_handle* h, const void* const* grads) {
   return DADAM_OK;
 }
 
-void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
+void fill_args(const dadam_handle* h, bool by_map, const void* const* grads, StepArgs* a) {
   memset(a, 0, sizeof(*a));
   const uint32_t R = h->cfg.n_rows, C = h->cfg.n_cols;
   if (h->d_tables) {
@@ -339,8 +340,8 @@ void fill_args(const dadam_handle* h, const void* const* grads, StepArgs* a) {
   for (uint32_t i = 0; i < R; ++i) a->grad[i] = grads ? grads[i] : nullptr;
   a->seg = h->d_segs;
   a->seg_work = h->d_seg_work;
-  a->map = h->d_map;
-  a->n_seg = h->mapped ? 1u : (uint32_t)h->segs.size();
+  a->map = by_map ? h->d_map : nullptr;
+  a->n_seg = by_map ? 1u : (uint32_t)h->segs.size();
   a->n_rows = R;
   a->n_cols = C;
   a->n_xcd = h->n_xcds;
@@ -413,13 +414,14 @@ void set_die_run(uint32_t run, StepArgs* a) { a->die_run = a->xcd_block = run; }
 // Do direct launches of this slot walk its rows in the sharing order?
 bool ordered_rows(const dadam_handle* h, const Slot& slot) { return !slot.order.empty() && h->n_xcds > 1; }
 
-void set_range(const dadam_handle* h, Grid grid, uint32_t work_begin, uint64_t lo, uint64_t hi, StepArgs* a) {
+// decays: the launch applies weight decay.
+void set_range(const dadam_handle* h, bool by_map, bool decays, Grid grid, uint32_t work_begin, uint64_t lo, uint64_t hi, StepArgs* a) {
   a->grid = grid;
   a->work_begin = work_begin;
   a->clip_lo = lo;
   a->clip_hi = hi;
-  a->first_tile = h->mapped ? 0 : h->segs.front().first_tile[grid];
-  a->weight_decay = h->mapped ? h->map_decay : h->segs.front().weight_decay;
+  a->first_tile = by_map ? 0 : h->segs.front().first_tile[grid];
+  a->weight_decay = !by_map ? h->segs.front().weight_decay : decays ? h->map_decay : 0.f;
 }
 
 // Does a compute unit hold one workgroup of the tile, even with one vector a lane?
@@ -570,6 +572,7 @@ uint32_t few_tiles_limit(const dadam_handle* h, const Slot& slot) {
 // ones, 640 to 1000 tiles of 44 to 160 rows: mixing in pairs and of three sources 0.59 to 0.88, of seven 0.45 to 0.72 (81 to 128 rows), steps of two 0.78 to 0.99, of three
 // 0.74 to 0.98, of seven 0.62 to 0.89, the others the same kernel; 560 tiles 0.68 to 1.02.  With a map, which has fewer tiles than its segments have, the
 // same: 128 rows of seven sources, tensors of 2000 elements, 1000 tiles, two steps 624 / 412 us (by segments 529), mixing 149 / 69 (88).
+// Without a map segments of 1100 elements 0.52 to 0.94, but steps of seven float32 sources 1.02, which keep to the old line (see staging_is_faster).
 bool many_tiles(const dadam_handle* h, uint32_t n_tiles) { return n_tiles >= (h->nontemporal ? kManyStreamed : kManyTiles); }
 
 // Direct launches of rows that share sources: does every row of a piece run on one die (die blocks), or does each die have a
@@ -654,8 +657,37 @@ bool staging_is_faster(const dadam_handle* h, const Slot& slot, bool mix_only, u
   const uint32_t C = h->cfg.n_cols;
   if (h->short_segments && (usual || mix_only)) return true;
   if (usual) return mix_only || slot.max_degree > 3 || C < 32;
-  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (h->vec == 4 || !h->short_segments);
+  if (lone_tile(h)) return h->shape.waves == 16 && slot.max_degree >= (h->vec == 8 ? 6 : mix_only ? 4 : 5) && (!h->short_segments || (h->vec == 4 && n_tiles >= kManyTiles));
   return mix_only && C < 32;
+}
+
+// Launches over a layout with a map that go by its segments all the same, because these are long: what a map saves is cut tiles and the search for a
+// segment, and where the tile and loop kernels are bound by more than that, its byte for every four elements and its tests at every store, and lanes
+// that it lets spread over segments (bfloat16 mixing by the tile has them side by side where segments end), cost more.  The sums are the same.  From which
+// average length on, by time by segments over time by the map, 3e8 elements of all rows in tensors of 1500, 3000, 6000, 12000, 24000 (30000 of the tile) elements:
+//   loops in float32   32 rows steps 1.13 1.10 1.07 1.03 0.97, mixing 1.06 1.03 1.05 1.00 0.96   64 rows 1.16 1.11 1.09 1.08 1.00, 1.10 1.07 1.08 1.04 0.95 (in loops of 32, 16, 16
+//     1.13 1.11 1.06 1.02 0.97, 1.05 0.96 0.95 0.98 0.95)
+//     72 rows 1.07 1.01 0.98 0.94 0.89, 1.01 0.98 0.93 0.97 0.90   96 rows 1.07 1.03 1.00 0.96 0.91, 1.01 0.96 0.93 0.91 0.89 (in loops of 48, 24, 24 1.09 1.02 1.00 0.95
+//     0.92, 1.02 0.93 0.90 0.88 0.89)   128 rows 1.11 1.05 1.02 1.00 0.95, 1.09 1.05 1.03 0.98 0.96
+//   loops in bfloat16  72 to 128 rows steps 1.5 to 1.12, mixing 1.33 1.11 1.01 0.95 0.92, 96 rows 1.39 1.16 1.04 1.00 0.96
+//   mixing by the tile in bfloat16, three sources  18 rows 1.35 1.19 1.11 1.07 1.08   24 rows 1.13 1.00 0.94 0.93 0.90   32 rows 1.04 0.93 0.92 0.92 0.91   48 rows 1.04 0.92
+//     0.89 0.88 0.86   64 rows 1.08 1.00 0.89 0.90 0.90 (1e8 elements 24 rows 1.19 1.08 1.03 1.02 1.00, 48 rows 1.14 1.03 0.99 0.96 0.96, 56 rows 1.21 1.07 1.03 0.98 0.98; 3e7
+//     1.17 and less to 0.98; 81 rows and more 1.4 to 1.07)
+//   steps by the tile in float32, seven sources  72 rows 1.24 to 1.11   96 rows - 1.02 0.97 0.95 1.00   128 rows - 1.03 0.98 0.96 0.99   160 rows - 1.03 1.00 0.98 1.00
+// 24000, 40000 elements, less in all: loops in float32 32 rows of 9.6e7 steps 0.98 0.96, mixing 0.96 0.94, 64 rows of 1.9e8 0.99 0.97, 0.95 0.94, bfloat16 mixing 0.97 0.97; from 1.9e7 to
+// 6e7 1.00 to 1.3.  What else has a map loses nothing by it or 1 to 3 % at most (of 1.2e8 elements and less, segments of 12000 and more).
+// n_loops: of a launch of the loop kernel, otherwise 0.
+bool segments_are_faster(const dadam_handle* h, bool tile_mode, size_t n_loops, bool mix_only, uint64_t elems) {
+  if (!h->nontemporal || !tile_mode || elems < kSegmentElems) return false;
+  const uint32_t R = h->cfg.n_rows, C = h->cfg.n_cols;
+  const bool most = elems >= 2 * kManyElems, tables = R > (uint32_t)kInlineRows || C > (uint32_t)kInlineRows;  // (in device memory)
+  uint64_t from = 0;  // 0: never
+  if (n_loops > 0 && h->vec == 8 && mix_only) from = most ? 8192 : tables ? 0 : 20480;
+  if (n_loops > 0 && h->vec == 4 && !tables) from = !most ? 20480 : mix_only && n_loops > 1 ? 2560 : 16384;
+  if (n_loops > 0 && h->vec == 4 && tables && most) from = !mix_only ? 6144 : R < 112 ? 2048 : 8192;
+  if (n_loops == 0 && h->vec == 8 && mix_only && !tables && C >= 24) from = !most ? 12288 : C < 32 ? 4096 : 2560;
+  if (n_loops == 0 && h->vec == 4 && !mix_only && tables && lone_tile(h) && most) from = 5120;
+  return from != 0 && h->n_elems >= from * h->segs.size();
 }
 
 // LDS a workgroup of a large one-row step reserves without using it, to bound how many wavefronts a compute unit
@@ -765,7 +797,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     return DADAM_OK;
   }
   uint32_t w0 = 0, w1 = 0;
-  work_range(h, kGridVector, s0, s1, lo, hi, &w0, &w1);
+  work_range(h, h->mapped, kGridVector, s0, s1, lo, hi, &w0, &w1);
   const uint32_t n_tiles = w1 - w0;
   const int loop_waves = consensus_out || (flags & (DADAM_FORCE_TILE | DADAM_FORCE_DIRECT)) ? 0 : loop_kernel_waves(h, slot, mix_only);
   const bool by_loops = loop_waves > 0;
@@ -780,13 +812,13 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
   // streaming float32 steps take two vectors a lane (see dadam_init): in a handle whose other launches do not stream, the mixing tile has them
   const bool mixing_tile = mix_only || (streams && !h->nontemporal && h->vec == 4 && h->mix_shape.ut == 2);
   const Grid grid = !tile_mode ? kGridDirect : by_loops ? kGridVector : mixing_tile ? kGridMix : kGridTile;
-  work_range(h, grid, s0, s1, lo, hi, &w0, &w1);
+  const bool by_map = h->mapped && !segments_are_faster(h, tile_mode, by_loops ? slot.loops.size() : 0, mix_only, (uint64_t)n_tiles * vector_elems(h) * h->cfg.n_rows);
+  work_range(h, by_map, grid, s0, s1, lo, hi, &w0, &w1);
   StepArgs a;
-  fill_args(h, mix_only ? nullptr : grads, &a);
+  fill_args(h, by_map, mix_only ? nullptr : grads, &a);
   if (!tile_mode && ordered_rows(h, slot)) a.order = rows_stay_on_one_die(h, slot, mix_only, n_tiles) ? kOrderDieBlocks : kOrderDieGroups;
   if (a.order == kOrderDieBlocks && many_tiles(h, n_tiles) && !(h->nontemporal && h->short_segments)) set_die_run(kDieRunPieces, &a);
-  set_range(h, grid, w0, lo, hi, &a);
-  if (h->mapped && !decays) a.weight_decay = 0.f;
+  set_range(h, by_map, decays, grid, w0, lo, hi, &a);
   if (tile_mode && cut_by_elements(h, mix_only, by_loops)) a.d = 0;
   a.partials = partials;
   if (!tile_mode) a.reserve_lds = bounded_occupancy_lds(h, slot, phase, streams, (w1 - w0) * kDirectItem);
@@ -798,7 +830,7 @@ int step_impl(dadam_handle* h, uint32_t slot_id, const void* const* grads, uint6
     a.loops = slot.d_loops;
     a.n_loops = (uint32_t)slot.loops.size();
     const uint64_t T = vector_elems(h);
-    a.loop_shares = loop_shares(h, slot, loop_waves, n_tiles, a.n_seg > 1 || (h->mapped ? h->vec == 4 : lo % T != 0 || hi % T != 0), mix_only);
+    a.loop_shares = loop_shares(h, slot, loop_waves, n_tiles, a.n_seg > 1 || (by_map ? h->vec == 4 : lo % T != 0 || hi % T != 0), mix_only);
     a.col = slot.d_loop_col;
     a.w = slot.d_loop_w;
     a.row_order = slot.d_loop_rows;
@@ -1332,10 +1364,10 @@ int dadam_accumulate(dadam_handle* h, const void* const* grads, uint64_t t, void
   if (rc) return rc;
   if (h->segs.empty()) return DADAM_OK;
   StepArgs a;
-  fill_args(h, grads, &a);
+  fill_args(h, h->mapped, grads, &a);
   uint32_t w0 = 0, w1 = 0;
-  work_range(h, kGridDirect, 0, (uint32_t)h->segs.size() - 1, h->segs.front().lo, h->segs.back().hi, &w0, &w1);
-  set_range(h, kGridDirect, w0, h->segs.front().lo, h->segs.back().hi, &a);
+  work_range(h, h->mapped, kGridDirect, 0, (uint32_t)h->segs.size() - 1, h->segs.front().lo, h->segs.back().hi, &w0, &w1);
+  set_range(h, h->mapped, false, kGridDirect, w0, h->segs.front().lo, h->segs.back().hi, &a);
   a.wide_search = (uint64_t)(w1 - w0) * kDirectItem * h->cfg.n_rows <= kWideSearchWaves ? 1u : 0u;
   fill_scalars(h, t, &a.s);
   DeviceGuard guard(h->cfg.device);

@@ -136,6 +136,7 @@ static_assert(sizeof(StepArgs) <= 4096, "the argument block of a launch holds 4 
 
 constexpr uint32_t kDieBlockTiles = 32;  // measured, see k_tile
 constexpr uint32_t kLongSegment = 65536;  // elements of two blocks of spread lanes; measured, see dadam_handle::short_segments
+constexpr uint64_t kSegmentElems = 80000000;  // elements of all rows of a launch; measured, see segments_are_faster
 constexpr uint64_t kMostMapped = 1ull << 28, kWidestGap = 7;  // elements; see can_map
 constexpr uint64_t kStreamedBytes = 344ull << 20;  // measured, see few_rows_stream
 constexpr uint32_t kDieRunPieces = 256;  // large direct launches in die blocks; measured, see rows_stay_on_one_die

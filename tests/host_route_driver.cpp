@@ -20,6 +20,8 @@ static const char* fail_launch = nullptr;  // name of the launcher whose next ca
 static std::string route, how;  // how: the shape of the tile's workgroup, the order of a row launch
 static uint32_t shares = 0;  // workgroups that share the rows of a loop's tile
 static bool streams = false; // accesses carry the non-temporal hint
+static std::string walk;     // by the map or by how many segments
+static void note_walk(const dadam::StepArgs& a) { walk = a.map ? a.n_seg == 1 ? "map" : "map and segments" : std::to_string(a.n_seg) + " segments"; }
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -50,12 +52,14 @@ int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint3
   route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
   shares = a.n_loops > 0 ? a.loop_shares : 0;
   streams = shape.nontemporal;
+  note_walk(a);
   if (shares > 1 && shape.nontemporal && phase == kMixOnly) return (int)hipErrorInvalidDeviceFunction;  // there is no such kernel
   double* p = a.partials;
   return enqueue("tile", [=] { if (phase == kMixConsensus) p[7] += 3.0; });  // the modelled error of any pass is 3
 }
 int launch_direct(int, int, Phase, bool nontemporal, bool, bool whole_items, const StepArgs& a, uint32_t, void*) {
   streams = nontemporal;
+  note_walk(a);
   how = std::string(a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : a.order == kOrderDieGroups ? "groups" : "linear") +
         (whole_items ? ", whole items" : "") + (a.d == 0 ? " cut by elements" : "");
   route = a.order == kOrderDieBlocks ? "direct-blocks" : a.order == kOrderDieGroups ? "direct-groups" : "direct";
@@ -64,6 +68,7 @@ int launch_direct(int, int, Phase, bool nontemporal, bool, bool whole_items, con
 }
 int launch_accumulate(int, Phase, bool nontemporal, bool whole_items, const StepArgs& a, uint32_t, void*, int) {
   streams = nontemporal;
+  note_walk(a);
   how = (a.order == kOrderDieBlocks ? "blocks, runs of " + std::to_string(a.die_run) : std::string("linear")) + (whole_items ? ", whole items" : "");
   route = whole_items ? "whole" : "pieces";
   return enqueue("accumulate", [] {});
@@ -326,6 +331,79 @@ static void loop_shares() {
   }
 }
 
+// Layouts of tensors with gaps of a few elements between them: what goes by the map, what by the segments, and which of it by whole items.
+static void maps() {
+  struct { const char* kind; int rows, degree; uint32_t dtype; uint64_t each, total, gap; } cases[] = {
+      {"share", 1, 3, DADAM_F32, 1100, 30000, 4}, {"share", 1, 3, DADAM_BF16, 1100, 30000, 4}, {"ring", 8, 3, DADAM_BF16, 1100, 2400000, 4},
+      {"ring", 8, 3, DADAM_F32, 1100, 2400000, 8}, {"ring", 8, 3, DADAM_F32, 70000, 2400000, 4},
+      {"ring", 40, 2, DADAM_F32, 1100, 120000000, 4}, {"ring", 40, 2, DADAM_F32, 1100, 120000000, 12}, {"ring", 48, 2, DADAM_BF16, 1100, 120000000, 4}, {"ring", 100, 2, DADAM_F32, 1100, 120000000, 4},
+      {"complete", 32, 32, DADAM_F32, 16380, 205000000, 4}, {"complete", 32, 32, DADAM_F32, 16388, 205000000, 4}, {"complete", 32, 32, DADAM_F32, 16388, 190000000, 4},
+      {"complete", 32, 32, DADAM_F32, 20484, 81000000, 4}, {"complete", 32, 32, DADAM_F32, 20476, 81000000, 4}, {"complete", 32, 32, DADAM_F32, 20484, 79000000, 4},
+      {"complete", 64, 64, DADAM_BF16, 20484, 81000000, 4}, {"halves", 64, 0, DADAM_F32, 2564, 205000000, 4}, {"halves", 64, 0, DADAM_F32, 2556, 205000000, 4},
+      {"complete", 96, 96, DADAM_F32, 2052, 205000000, 4}, {"complete", 96, 96, DADAM_F32, 2044, 205000000, 4}, {"complete", 96, 96, DADAM_F32, 6148, 205000000, 4},
+      {"complete", 128, 128, DADAM_F32, 6148, 205000000, 4}, {"complete", 96, 96, DADAM_BF16, 8200, 205000000, 4}, {"complete", 96, 96, DADAM_BF16, 8184, 205000000, 4},
+      {"ring", 18, 3, DADAM_BF16, 20004, 205000000, 4}, {"ring", 24, 3, DADAM_BF16, 4100, 205000000, 4}, {"ring", 24, 3, DADAM_BF16, 4092, 205000000, 4},
+      {"ring", 32, 3, DADAM_BF16, 2564, 205000000, 4}, {"ring", 32, 3, DADAM_BF16, 2556, 205000000, 4}, {"ring", 48, 3, DADAM_BF16, 12292, 101000000, 4},
+      {"ring", 48, 3, DADAM_BF16, 12284, 101000000, 4}, {"ring", 48, 3, DADAM_BF16, 20004, 99000000, 4}, {"ring", 72, 3, DADAM_BF16, 20004, 205000000, 4},
+      {"ring", 32, 3, DADAM_F32, 20004, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5124, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5116, 205000000, 4},
+      {"ring", 72, 7, DADAM_F32, 5124, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5124, 190000000, 4}};
+  for (const auto& c : cases) {
+    Rows r;
+    if (c.degree == 0) r = halves(c.rows);
+    for (int i = 0; i < c.rows && c.degree > 0; ++i) {
+      std::vector<int32_t> cols;
+      for (int k = 0; k < c.degree; ++k) cols.push_back(c.rows == 1 ? k : (i + k) % c.rows);
+      add_row(r, cols);
+    }
+    std::vector<dadam_tensor_desc> ts;
+    for (uint64_t at = 0; at < c.total / c.rows; at += c.each + c.gap) ts.push_back({at, c.each, 0.f, 0});
+    ts.push_back({ts.back().offset_elems + c.each + c.gap, 0, 0.f, 0});  // d is a multiple of four
+    Sim s(c.rows, c.rows == 1 ? 3 : c.rows, ts, r, c.dtype);
+    s.bind();
+    const std::string n = std::to_string(ts.size() - 1) + " segments";
+    std::string answers;
+    auto told = [&](const std::string& what) {
+      answers += (answers.empty() ? "" : ", ") + (what.substr(0, 5) == "error" ? what : walk == n ? "segments" : walk) + (what.find("whole") != std::string::npos ? " whole" : "");
+    };
+    told(s.step(DADAM_FUSE_ACCUM));
+    told(s.mix(0));
+    double out = 0.0;
+    if (c.rows > 1) told(dadam_mix_consensus(s.h, 0, 0, &out, nullptr) == DADAM_OK ? route : "error");
+    told(dadam_accumulate(s.h, s.g.data(), 1, nullptr) == DADAM_OK ? route : "error");
+    say((std::string(c.kind) + std::to_string(c.rows) + " of " + std::to_string(c.degree) + (c.dtype == DADAM_BF16 ? " bf16 " : " f32 ") + std::to_string(c.each) + "+" + std::to_string(c.gap) +
+         " " + std::to_string(c.total / 1000000) + "e6").c_str(), answers);
+  }
+}
+
+// The same of given layouts: lines of a name, rows, sources, whether bfloat16, d, and of every tensor its offset, elements and decay.
+static void map_of() {
+  char name[64];
+  unsigned rows, cols, wide, n;
+  unsigned long long d;
+  while (scanf("%63s %u %u %u %llu %u", name, &rows, &cols, &wide, &d, &n) == 6) {
+    std::vector<dadam_tensor_desc> ts;
+    for (unsigned k = 0; k < n; ++k) {
+      unsigned long long offset, numel;
+      float decay;
+      if (scanf("%llu %llu %f", &offset, &numel, &decay) != 3) exit(1);
+      ts.push_back({offset, numel, decay, 0});
+    }
+    ts.push_back({d, 0, 0.f, 0});
+    Rows r;
+    for (unsigned i = 0; i < rows; ++i) {
+      std::vector<int32_t> of;
+      for (unsigned k = 0; k < (cols < 3 ? cols : 3u); ++k) of.push_back((int32_t)((i + k) % cols));
+      add_row(r, of);
+    }
+    Sim s(rows, cols, ts, r, wide ? DADAM_BF16 : DADAM_F32);
+    s.bind();
+    std::string answers = s.step(DADAM_FUSE_ACCUM).substr(0, 5) == "error" ? "error" : walk;
+    if (dadam_accumulate(s.h, s.g.data(), 1, nullptr) == DADAM_OK) answers += ", " + walk;
+    if (s.mix(0).substr(0, 5) != "error") answers += ", " + walk;
+    say(name, answers);
+  }
+}
+
 // Steps of few rows on both sides of 344 MB of what they touch.
 static void few_rows() {
   struct { const char* name; uint32_t rows, cols, read, dtype, bytes; bool in_place; uint64_t outside; } cases[] = {
@@ -460,6 +538,8 @@ int main(int argc, char** argv) {
   else if (what == "sparse_loops") sparse_loops();
   else if (what == "few_rows") few_rows();
   else if (what == "loop_shares") loop_shares();
+  else if (what == "maps") maps();
+  else if (what == "map_of") map_of();
   else if (what == "few") few();
   else if (what == "die_order") die_order();
   else if (what == "accumulation") accumulation();

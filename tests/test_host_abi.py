@@ -552,7 +552,7 @@ def test_host_code_under_address_and_ub_sanitizers(tmp_path):
     assert "ERROR" not in r.stderr and "runtime error" not in r.stderr, r.stderr[-3000:]
 
 
-def _route_answers(tmp_path, question):
+def _route_answers(tmp_path, question, asked=None):
     """What tests/host_route_driver.cpp (the host code on a modelled runtime, under ASan + UBSan) answers."""
     import subprocess
     clang = "/opt/rocm/lib/llvm/bin/clang++"
@@ -565,7 +565,7 @@ def _route_answers(tmp_path, question):
            os.path.join(ROOT, "paper_2410_11998_amd", "csrc", "dadam_host.cpp"), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
-    r = subprocess.run([exe, question], capture_output=True, text=True, timeout=600)
+    r = subprocess.run([exe, question], capture_output=True, text=True, timeout=600, input=asked)
     assert r.returncode == 0 and "ERROR" not in r.stderr, (r.stdout[-500:], r.stderr[-3000:])
     return dict(line.split(": ", 1) for line in r.stdout.strip().splitlines())
 
