@@ -344,7 +344,7 @@ static void maps() {
       {"complete", 128, 128, DADAM_F32, 6148, 205000000, 4}, {"complete", 96, 96, DADAM_BF16, 8200, 205000000, 4}, {"complete", 96, 96, DADAM_BF16, 8184, 205000000, 4},
       {"ring", 18, 3, DADAM_BF16, 20004, 205000000, 4}, {"ring", 24, 3, DADAM_BF16, 4100, 205000000, 4}, {"ring", 24, 3, DADAM_BF16, 4092, 205000000, 4},
       {"ring", 32, 3, DADAM_BF16, 2564, 205000000, 4}, {"ring", 32, 3, DADAM_BF16, 2556, 205000000, 4}, {"ring", 48, 3, DADAM_BF16, 12292, 101000000, 4},
-      {"ring", 48, 3, DADAM_BF16, 12284, 101000000, 4}, {"ring", 48, 3, DADAM_BF16, 20004, 99000000, 4}, {"ring", 72, 3, DADAM_BF16, 20004, 205000000, 4},
+      {"ring", 48, 3, DADAM_BF16, 12284, 101000000, 4}, {"ring", 48, 3, DADAM_BF16, 20004, 79000000, 4}, {"ring", 72, 3, DADAM_BF16, 20004, 205000000, 4},
       {"ring", 32, 3, DADAM_F32, 20004, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5124, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5116, 205000000, 4},
       {"ring", 72, 7, DADAM_F32, 5124, 205000000, 4}, {"ring", 96, 7, DADAM_F32, 5124, 190000000, 4}};
   for (const auto& c : cases) {

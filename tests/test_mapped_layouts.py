@@ -101,7 +101,7 @@ def test_which_launches_go_by_the_map(tmp_path):
         "complete96 of 96 bf16 8184+4 205e6": (m, m, m, m), "ring18 of 3 bf16 20004+4 205e6": (m, m, m, m),
         "ring24 of 3 bf16 4100+4 205e6": (m, s, s, m), "ring24 of 3 bf16 4092+4 205e6": (m, m, m, m), "ring32 of 3 bf16 2564+4 205e6": (m, s, s, m),
         "ring32 of 3 bf16 2556+4 205e6": (m, m, m, m), "ring48 of 3 bf16 12292+4 101e6": (m, s, s, m), "ring48 of 3 bf16 12284+4 101e6": (m, m, m, m),
-        "ring48 of 3 bf16 20004+4 99e6": (m, m, m, m), "ring72 of 3 bf16 20004+4 205e6": (m, m, m, m), "ring32 of 3 f32 20004+4 205e6": (m, m, m, m),
+        "ring48 of 3 bf16 20004+4 79e6": (m, m, m, m), "ring72 of 3 bf16 20004+4 205e6": (m, m, m, m), "ring32 of 3 f32 20004+4 205e6": (m, m, m, m),
         "ring96 of 7 f32 5124+4 205e6": (s, m, m, m), "ring96 of 7 f32 5116+4 205e6": (m, m, m, m), "ring72 of 7 f32 5124+4 205e6": (m, m, m, m),
         "ring96 of 7 f32 5124+4 190e6": (m, m, m, m),
     }
