@@ -474,9 +474,15 @@ def test_arena_finds_stretches_in_different_thirds_by_timing():
         H.record("arena_calibration", dict(first_gib=first_gib, stretches=[[t, lo >> 30, hi >> 30] for t, lo, hi in ar.stretches],
                                            regions=[[lo >> 30, hi >> 30] for lo, hi in ar.regions_used], policy=ar.policy))
         if ar.report.note != 0:
-            # what the probe sees is a property of the machine and of what else holds its memory; the placement
-            # it falls back to is still checked by every test that carves its buffers from an arena
-            pytest.skip("the timing probe found nothing usable on this device: " + ar.describe())
+            # what the probe sees is a property of the machine and of what else holds its memory: the buffers then lie as the rule has them
+            placed, regions, advice = B.dadam_place_offsets(sizes, ar.span_bytes, total)
+            assert ar.offsets == list(placed) and ar.advice == advice and [tuple(r) for r in regions] == ar.regions_used, ar.describe()
+            assert ar.policy.startswith("two regions across" if advice == B.DADAM_PLACE_TWO_REGIONS else "equal distances")
+            del ar, first
+            import gc
+            gc.collect()
+            torch.cuda.empty_cache()
+            continue
         assert len(ar.stretches) >= 2 and len({t for t, _lo, _hi in ar.stretches}) >= 2
         assert ar.policy.startswith("two regions found by timing") and ar.advice == B.DADAM_PLACE_TWO_REGIONS
         (lo0, hi0), (lo1, hi1) = ar.regions_used

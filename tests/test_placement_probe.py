@@ -1,5 +1,7 @@
-"""The placement probe's own pass on the real memory."""
+"""The placement probe's own pass on the real memory.  Whether that memory shows its thirds is a property of the machine and of what else has
+been in it (on some the rates of such passes lie anywhere between), so the tests time the pass themselves and ask of the library what it can know."""
 
+import ctypes as C
 import gc
 
 import numpy as np
@@ -46,10 +48,44 @@ def test_the_probe_copies_inside_the_chunks_it_names_and_nowhere_else():
             assert low[k] in sources, (k, low[k])
 
 
+def clear_thirds(arena, span):
+    """Do passes of the probe, three times as many of them, tell chunks of the arena apart without a doubt?  Of the rates with the first chunk all but a few (chunks
+    across a boundary) lie within 3 % of the fastest or 7 % and more below it, some on either side, and the library's search finds thirds in them."""
+    launch = B.lib._ZN5dadam12launch_probeEPKPKvPKPvmjS4_
+    launch.restype, launch.argtypes = C.c_int, [C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_void_p]
+    buf, e0, e1 = 64 << 20, torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    with_first = {}
+
+    def rate(a, b):
+        at = [o + k * buf for half in (0, 8) for o in (a, b) for k in range(half, half + 8)]
+        assert all(0 <= o and o + buf <= span for o in at)
+        src, dst = ((C.c_void_p * 16)(*[arena + o for o in at[k:k + 16]]) for k in (0, 16))
+        ms = []
+        for _ in range(3):
+            for k in range(8):
+                if k == 2:
+                    e0.record(torch.cuda.default_stream())
+                assert launch(src, dst, buf // 4, 8, None) == 0
+            e1.record(torch.cuda.default_stream())
+            e1.synchronize()
+            ms.append(e0.elapsed_time(e1) / 6)
+        r = 32 * buf / (sorted(ms)[1] * 1e-3) / 8e12
+        if a == 0:
+            with_first[b] = r
+        return r
+
+    found = B.dadam_find_stretches(span, rate)
+    best = max(with_first.values())
+    between = [r for r in with_first.values() if 0.93 * best < r < 0.97 * best]
+    slow = [r for r in with_first.values() if r <= 0.93 * best]
+    print("rates", f"{min(with_first.values()):.3f} to {best:.3f}, {len(between)} between, {len(slow)} slow", found, flush=True)
+    return best >= 0.78 and len(between) <= 3 and 0 < len(slow) < len(with_first) - len(between) and len({t for t, _, _ in found}) >= 2
+
+
 @pytest.mark.gpu
 def test_the_probe_sees_a_picture_of_a_free_devices_memory():
-    """On a device whose memory is free the pass tells chunks of one third from chunks of two: the first look gives
-    stretches, whether or not the buffers then find room, and nothing is timed twice."""
+    """Where the pass tells chunks of one third from chunks of two without a doubt the first look gives stretches, whether or not the buffers then
+    find room, and nothing is timed twice.  Where it does not, the library may say so after a second look, and then places by the rule."""
     free, total = torch.cuda.mem_get_info(DEV)
     if free < (250 << 30):
         pytest.skip("needs a device with 250 GiB free")
@@ -57,9 +93,21 @@ def test_the_probe_sees_a_picture_of_a_free_devices_memory():
     arena = torch.empty((free - (12 << 30)) // unit * unit + unit, dtype=torch.uint8, device=DEV)
     shift = -arena.data_ptr() % unit
     span = (arena.numel() - unit) // unit * unit
-    _, rep = B.dadam_place_by_timing(arena.data_ptr() + shift, span, 0, [48 << 20] * 64, total)
+    clear = clear_thirds(arena.data_ptr() + shift, span)
+    sizes = [48 << 20] * 64
+    offsets, rep = B.dadam_place_by_timing(arena.data_ptr() + shift, span, 0, sizes, total)
     found = [(s.third, s.lo >> 30, s.hi >> 30) for s in rep.stretches[:rep.n_stretches]]
     print("case", found, rep.note, rep.probe_launches, rep.rate_across, list(rep.rate_inside), flush=True)
     chunks = (span - B.PROBE_CHUNK_BYTES) // B.PROBE_STEP_BYTES + 1
-    assert rep.note != B.DADAM_NOTE_NO_PICTURE and len({t for t, _, _ in found}) >= 2
-    assert rep.probe_launches <= 8 * (2 * (chunks - 1) + 3)
+    assert rep.note != B.DADAM_NOTE_NO_PROBE
+    if clear:
+        assert rep.note != B.DADAM_NOTE_NO_PICTURE and len({t for t, _, _ in found}) >= 2
+    if rep.note != B.DADAM_NOTE_NO_PICTURE:
+        assert rep.probe_launches <= 8 * ((2 if clear else 4) * (chunks - 1) + 3)
+    else:
+        assert not found and rep.probe_launches <= 8 * 4 * (chunks - 1)
+        placed, _, advice = B.dadam_place_offsets(sizes, span, total)
+        assert list(offsets) == list(placed) and rep.advice == advice and rep.rate_across == 0
+        assert rep.policy == (B.DADAM_POLICY_RULE_REGIONS if advice == B.DADAM_PLACE_TWO_REGIONS else B.DADAM_POLICY_EQUAL_DISTANCES)
+    taken = sorted(zip(offsets, sizes))
+    assert taken[0][0] >= 0 and all(a + n <= b for (a, n), (b, _) in zip(taken, taken[1:])) and sum(taken[-1]) <= span
