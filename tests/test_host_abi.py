@@ -451,13 +451,15 @@ def test_kernels_use_no_scratch_memory_and_load_neighbour_lists_with_all_lanes(t
     import subprocess as sp
     names = sorted(hints)
     plain_names = sp.run(["c++filt"], input="\n".join(names), capture_output=True, text=True).stdout.split("\n")
-    streaming, other, seen = 0, 0, set()
+    streaming, other, mapped, seen = 0, 0, 0, set()
     for mangled, plain in zip(names, plain_names):
         st_nt, st_plain, ld_nt, ld_plain = hints[mangled]
-        m = re.search(r"\b(k_tile|k_direct|k_acc|k_rows|k_mix_rows|k_acc_rows|k_loop|k_tile_few|k_direct_few|k_acc_few)<(.*)>\(", plain)
+        # (_map: layouts with a map, the same kernels otherwise; k_rows and k_acc_rows have none)
+        m = re.search(r"\b(k_tile|k_direct|k_acc|k_rows|k_mix_rows|k_acc_rows|k_loop|k_tile_few|k_direct_few|k_acc_few)(?:_map)?<(.*)>\(", plain)
         if not m:
             continue
         seen.add(m.group(1))
+        mapped += "_map<" in plain
         targs = [x.strip() for x in m.group(2).split(",")]
         few = m.group(1).endswith("_few")                                  # kernels on the short argument block never stream
         nt, ext = not few and targs[-2] in ("true", "1", "2"), not few and targs[-1] == "true"     # <..., hints, tables in device memory>
@@ -469,12 +471,13 @@ def test_kernels_use_no_scratch_memory_and_load_neighbour_lists_with_all_lanes(t
             streaming += 1
             assert st_plain == 0 and st_nt > 0, f"{plain}: {st_plain} vector stores without the hint"
             # (the loop kernel has two bodies of row inputs, each with its look-ups in the tables)
-            assert ld_plain <= ((80 if m.group(1) == "k_loop" else 60) if ext else 8) and ld_nt >= (1 if ext else 4) * ld_plain, \
+            # (with a map there is one body, in which look-ups in the tables are as many as loads, or one or two more)
+            assert ld_plain <= ((80 if m.group(1) == "k_loop" else 60) if ext else 8) and ld_nt + (2 if "_map<" in plain else 0) >= (1 if ext else 4) * ld_plain, \
                 f"{plain}: {ld_plain} vector loads without the hint, {ld_nt} with"
         else:
             other += 1
             assert st_nt == 0 and ld_nt == 0, f"{plain}: hints in a kernel built without them"
-    assert streaming > 150 and other > 150, (streaming, other)
+    assert streaming > 150 and other > 150 and mapped > 900, (streaming, other, mapped)
     assert len(seen) == 10, seen
 
     # the kernels in which neighbour lists are handed out with readlane from what the lanes loaded: direct, whole items, loops

@@ -80,3 +80,17 @@ def test_registers_and_scratch_of_the_kernels(tmp_path):
     assert len(held) > 250
     over = {n: (found[n][0], most) for n, most in held.items() if found[n][0] > most}
     assert not over, over
+
+
+def test_kernels_of_layouts_with_a_map_hold_as_many_wavefronts(tmp_path):
+    """Each stands for an ordinary kernel, whose registers are held above or were measured: 512 a lane, given out by eight, for at most eight wavefronts."""
+    if not os.path.exists(f"{LLVM}/llvm-readelf") or shutil.which("c++filt") is None:
+        pytest.skip("no llvm-readelf or c++filt")
+    found = kernels(tmp_path)
+    waves = lambda name: min(8, 512 // (-(-found[name][0] // 8) * 8))
+    mapped = [n for n in found if "_map<" in n]
+    assert len(mapped) > 900 and {n.split("<")[0] for n in mapped} == {
+        "k_tile_map", "k_tile_few_map", "k_direct_map", "k_direct_few_map", "k_loop_map", "k_mix_rows_map", "k_acc_map", "k_acc_few_map"}
+    fewer = {n for n in mapped if waves(n) < waves(n.replace("_map<", "<"))}
+    # mixing with the error of more than 64 bfloat16 rows over at most 16 sources: seven
+    assert fewer <= {f"k_tile_map<TBF16, {g}, 6, 4, 2, true, true>" for g in ("TF32", "TBF16")}, fewer
