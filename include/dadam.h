@@ -33,10 +33,11 @@
  *     handle is available from dadam_last_error().
  *   - "host" / "device" says where a pointer must point.  Large buffers (parameters, gradients,
  *     moments, accumulator) are DEVICE memory owned by the caller; the library never allocates,
- *     frees or copies them and never synchronises a stream.  The library owns only small metadata
- *     (segment table, CSR slots) on host and device.  (One set-up call is the exception and says so:
- *     dadam_place_by_timing overwrites the empty arena it is given and returns when its measurements
- *     are done.)
+ *     frees or copies them and never synchronises a stream.  The library owns only metadata on host and
+ *     device: the segment table, the CSR slots and, for layouts of many short tensors with at most seven
+ *     elements between two of them, a byte of device memory for every four elements of one buffer, up
+ *     to 64 MB (d of 2^28).  (One set-up call is the exception and says so: dadam_place_by_timing
+ *     overwrites the empty arena it is given and returns when its measurements are done.)
  *   - Launching entry points enqueue work on the given HIP stream (a hipStream_t passed as
  *     void*; NULL = the default stream) and return at once.  The caller keeps every buffer alive
  *     and unmodified until that work has finished.
@@ -98,8 +99,8 @@ typedef struct dadam_handle dadam_handle; /* opaque, owned by the library */
 
 /* One tensor of the packed layout: elements [offset_elems, offset_elems + numel) of every
  * per-replica buffer.  Tensors must be listed in increasing offset order and must not overlap;
- * elements between tensors (padding) are never written, and what they hold is never used (a 16-byte load at the edge of
- * a tensor may take up to three of them along).  weight_decay >= 0 is the decoupled
+ * elements between tensors (padding) are never written, and what they hold is never used (loads may take them along: up to
+ * three at the edge of a tensor, all that lie between tensors at most seven apart).  weight_decay >= 0 is the decoupled
  * weight decay of this tensor (0 = plain Adam; e.g. 3e-5 on all but the normalisation parameters in
  * the paper's ResNet-50 recipe).  flags is reserved and must be 0. */
 typedef struct {
@@ -155,15 +156,17 @@ typedef struct {
   uint32_t n_segments;      /* maximal runs of contiguous tensors                               */
   uint32_t tile_elems;      /* elements of one tile in tile mode                                */
   uint32_t direct_elems;    /* elements of one work item in direct mode                         */
-  uint64_t n_tiles_tile;    /* work items (workgroups) of a full step in tile mode              */
-  uint64_t n_tiles_direct;  /* tiles per row in direct mode (work items = this * n_rows)        */
+  uint64_t n_tiles_tile;    /* work items (workgroups) of a full step in tile mode that goes by segments: a tile
+                               that several of them touch counts for each.  Layouts of short segments side by
+                               side mostly go by one grid over the vector, with each tile once */
+  uint64_t n_tiles_direct;  /* the same per row in direct mode (work items = this * n_rows)     */
   uint32_t lds_bytes_tile;  /* LDS per workgroup in tile mode                                   */
   uint32_t tile_mode_possible; /* 1 if the source tile fits in LDS                              */
   uint32_t lds_limit_bytes; /* LDS per workgroup the plan was made for                          */
   uint32_t n_xcds;          /* dies the tile order is laid out for                              */
   uint32_t mix_tile_elems;  /* elements of one tile of the mixing-only launch (tile mode)       */
   uint32_t lds_bytes_mix;   /* LDS per workgroup of the mixing-only launch                      */
-  uint64_t n_tiles_mix;     /* work items of a mixing-only launch in tile mode                  */
+  uint64_t n_tiles_mix;     /* the same of a mixing-only launch in tile mode                    */
   uint32_t tile_waves, tile_vectors; /* shape of the fused step's tile kernel: wavefronts per workgroup,
                                         16-byte vectors per lane and row                          */
   uint32_t mix_waves, mix_vectors;   /* the same for the mixing-only launch                       */

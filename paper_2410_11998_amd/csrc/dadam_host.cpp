@@ -193,10 +193,9 @@ void find_segments(dadam_handle* h) {
 }
 
 // Does the layout get a map?  Segments of 65536 elements on average or fewer, a gap of at most 7 elements between two (what packing to
-// multiples of 8 leaves), one value of decay beside 0, four elements never with and without it, d a multiple of 4 (the last group of a
-// buffer is whole), and at most 2^28 elements (64 MB of map).  Such layouts then count as one segment everywhere.  What it gives stands at
-// MapTile.  Where segments are long, a byte for every four elements costs a step of one row 1 % and there are few cut tiles to save; wider gaps
-// keep the walk by segments, whose routes tests/golden/large_routes.txt holds (segments of 1100 elements 8 apart).
+// multiples of 8 leaves; wider gaps, whose padding a dense grid loads too, were not measured and keep the walk by segments), one value of decay beside 0,
+// four elements never with and without it, d a multiple of 4 (the last group of a buffer is whole), and at most 2^28 elements (64 MB of map).  Such layouts
+// then count as one segment, but in launches that are faster by segments (segments_are_faster).  What a map gives stands at MapTile.
 bool can_map(const dadam_handle* h, float* decay) {
   if (!h->short_segments || h->segs.size() < 2 || h->cfg.d % 4 != 0 || h->cfg.d > kMostMapped) return false;
   *decay = 0.f;
