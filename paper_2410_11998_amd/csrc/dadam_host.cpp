@@ -526,7 +526,8 @@ int loop_kernel_waves(const dadam_handle* h, const Slot& slot, bool mix_only) {
 // Launches that leave compute units idle: as many as keep it at one workgroup a unit (sixteen wavefronts then walk 6 rows of 96 in turn
 // otherwise).  us of two steps from a graph, one / two / four / as many as this gives, 16 tiles: 32 rows 16.4 / 13.0 / 13.1 / 13.0, 64 rows 25.4 / 19.0 / 15.5 /
 // 15.4, 96 rows 39.3 / 27.5 / 22.3 / 18.6 (bfloat16 58.8 / 38.0 / 31.2 / 25.0), in loops of 48, 24, 24 24.1 / 19.8 / 16.1 / 16.0; 128 tiles, two or none fit: 32 rows
-// 18.3 / 15.4, 96 rows 60 / 45 (82 / 62), loops 49.2 / 54.6.  17 rows, one of them in the second workgroup, 0.86 to 0.95 of the time of one.
+// 18.3 / 15.4, 96 rows 60 / 45 (82 / 62), loops 49.2 / 54.6.  17 rows, one of them in the second workgroup, 0.86 to 0.95 of the time of one.  Of unequal loops
+// the longest decides, and the others have workgroups that sum and own no row: of 48, 24, 24 by three 16.0, by the two that the shorter ones fill 19.8.
 // Mixing, half of whose bytes are sources, gains from 32 rows on, and only where the tiles divide among the dies: then the workgroups of a tile run on one
 // and find the sources in its L2.  Time of two over that of one, 32 / 64 / 96 rows: 24 tiles 0.96 / 0.95 / 0.89, 64 tiles 0.98 / 0.97 (56 rows), but 4 tiles 1.16 / 1.17 (56
 // rows), 31 tiles 1.07 / 1.10 / 1.15, 42 tiles 1.10 / 1.10 / 1.19, 85 tiles 1.11 / 1.13 / 1.19; 17 to 20 rows of 24 to 128 tiles 0.98 to 1.02.

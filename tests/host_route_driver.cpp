@@ -20,6 +20,7 @@ static const char* fail_launch = nullptr;  // name of the launcher whose next ca
 static std::string route, how;  // how: the shape of the tile's workgroup, the order of a row launch
 static uint32_t shares = 0;  // workgroups that share the rows of a loop's tile
 static bool streams = false; // accesses carry the non-temporal hint
+static bool wide_search = false;  // all lanes search the segments
 static std::string walk;     // by the map or by how many segments
 static void note_walk(const dadam::StepArgs& a) { walk = a.map ? a.n_seg == 1 ? "map" : "map and segments" : std::to_string(a.n_seg) + " segments"; }
 extern "C" {
@@ -52,6 +53,7 @@ int launch_tile(int, int, Phase phase, TileShape shape, const StepArgs& a, uint3
   route = a.n_loops > 0 ? "loop" + std::to_string(shape.waves) : "tile";
   shares = a.n_loops > 0 ? a.loop_shares : 0;
   streams = shape.nontemporal;
+  wide_search = a.wide_search != 0;
   note_walk(a);
   if (shares > 1 && shape.nontemporal && phase == kMixOnly) return (int)hipErrorInvalidDeviceFunction;  // there is no such kernel
   double* p = a.partials;
@@ -328,6 +330,13 @@ static void loop_shares() {
       told(s.mix(0));
     }
     say((std::string(c.kind) + std::to_string(c.rows) + " " + std::to_string(c.tiles) + (c.dtype == DADAM_BF16 ? " bf16" : " f32") + (c.cut ? "" : " whole")).c_str(), answers.substr(1));
+  }
+  for (uint64_t tiles : {1030, 1300}) {  // of two segments: 8 wavefronts to a workgroup, two and one of them to a tile
+    const uint64_t half = tiles * 256;
+    Sim s(97, 97, {{0, half - 8, 0.f, 0}, {half, half - 8, 0.f, 0}}, complete(97), DADAM_BF16);
+    s.bind();
+    s.step(DADAM_FUSE_ACCUM);
+    say(("wide search, " + std::to_string(tiles)).c_str(), std::to_string(shares) + (wide_search ? " yes" : " no"));
   }
 }
 

@@ -45,6 +45,7 @@ CASES = [
     (1, "share", 5, "bf16", "f32", True),
     (8, "ring", 300, "bf16", "f32", True),           # tile kernel
     (5, "ring", 300, "f32", "bf16", False),
+    (2, "ring", 8400, "f32", "f32", True),           # streams in steps alone, by the mixing tile's shape
     (16, "exp", 900, "bf16", "bf16", True),
     (20, "exp", 3, "f32", "f32", True),              # few tiles: row by row
     (32, "complete", 700, "f32", "f32", True),       # loops
